@@ -581,7 +581,10 @@ void fupr_graph_destroy(fupr_graph* g);
  *   patch_tile, pipe_tile, stream_tile = <index>
  *                                                 force a tile of that kernel family (where it fits)
  *   conv_tile = <tile name>                       force a tile of the general kernel
- *   conv_patch, conv1x1_stream, conv1x1_pipe, conv1x1_fuse = 0
+ *   window_tile = <index>x<f>x<r>                 force a tile of the kernel with weights straight into
+ *                                                 registers, f waves along the filters, r along the
+ *                                                 reduction (powers of two)
+ *   conv_patch, conv1x1_stream, conv1x1_pipe, conv1x1_fuse, conv_window = 0
  *                                                 leave that kernel family out
  *   pipe_order = 0 | 1                            tiles of the pipelined 1 x 1 kernel as one contiguous
  *                                                 range per workgroup | consecutive tiles per XCD

@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfupr.so")
 MEASURE_DIR = os.path.join(HERE, "measure")
 MEASURE_LIB = os.path.join(MEASURE_DIR, "libfupr_measure.so")
-SOURCES = ["host_passes.cpp", "tuning.cpp", "kernels.hip", "conv_tiled.hip", "conv_patch.hip",
+SOURCES = ["host_passes.cpp", "tuning.cpp", "kernels.hip", "conv_tiled.hip", "conv_patch.hip", "conv_window.hip",
            "stem_pool.hip", "conv1x1.hip", "conv1x1_pipe.hip", "resident.hip", "model.cpp",
            "static_workspace.hip"]
 HEADERS = [os.path.join(ROOT, "include", "fupr.h")] + [

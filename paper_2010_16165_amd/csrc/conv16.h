@@ -18,6 +18,7 @@ struct Conv16Params {
   int Kp, FT, cpt, nchunk, nsteps;
   int rH, rW, rcs, rss, roff;
   int relu;
+  int plan_N;                  // images of the batch this launch is a part of; 0: it is all of it
   uint32_t x_bytes, w_bytes;   // extents of x and w, for range-checked buffer loads
   // A block's last convolution after its output filters were pruned (Alg. 1):
   // filter j adds into channel keep[j] of y, which already holds the shortcut,
@@ -64,5 +65,12 @@ fupr_status launch_conv1x1_fused_pair(const Conv16Params& first, const Conv16Par
 bool conv1x1_pipe_applies(const Conv16Params& geometry);
 const char* conv1x1_pipe_name(const Conv16Params& geometry);
 fupr_status launch_conv1x1_pipe(const Conv16Params& p, int N, bool bf16, void* stream);
+
+// conv_window.hip: any window of at most 25 taps, one or two input tensors, with the tile's
+// pixels in LDS and the weights straight from L2 into registers.  Geometry fields decide whether
+// it takes a layer; launch_conv_window returns false, and launches nothing, when it does not.
+bool conv_window_applies(const Conv16Params& geometry, int N);
+const char* conv_window_name(const Conv16Params& geometry, int N);
+bool launch_conv_window(const Conv16Params& p, int N, bool bf16, void* stream, fupr_status* status);
 
 }  // namespace fupr

@@ -1,0 +1,761 @@
+// 16-bit convolutions with the input of a workgroup's pixels in LDS and the weights
+// streamed straight from L2 into registers (Sec. III, Sec. IV-B-1: operator
+// k x c x r x s with its fused epilogue).
+//
+// What it is for: layers that a pipeline of LDS stages does not fill - one image or a few, deep
+// layers of any batch, strided windows.  There a chain of dependent stages (load, barrier,
+// multiply) leaves the matrix pipe idle most of the time (512 -> 359 channels, 3 x 3 on a 7 x 7
+// image: 13.9 us, of which 16 dependent stages of 2250 clocks each).  Here a tile has no stages:
+//
+//   * The tile's whole input, all channels, goes to LDS once.  Input pixels of a window are
+//     taken as one row of pixels, first to last, rows and images one behind the other: the patch
+//     is one contiguous run of memory and a tap a constant distance in it.  What the run holds
+//     beyond the image border is not used: each lane knows which taps of its pixel lie inside
+//     (one bit each), and reads zeros (patch pixel 0) for the others.
+//   * Weights are not shared between the waves of a workgroup: waves lie side by side along the
+//     filters (WF) or take every WK-th step of the reduction, each over all pixels of the tile.
+//     So no weight is read twice in a workgroup, none goes through LDS, and no barrier stands in
+//     the loop: a wave loads fragments in MFMA layout D steps ahead and multiplies.
+//     (Loading the pixels like that as well reads at 9.5 TB/s where a pixel's bytes are a multiple
+//     of 512, since neighbouring lanes then hit one bank of the L1, against 27 TB/s for runs of
+//     64 bytes or more: that version took 33 us where this one takes 14.3, 256 -> 180 at 14 x 14 x 64.)
+//   * The waves' partial sums meet in LDS at the end, in the order of the waves; the tiles are
+//     shared out between the waves for the epilogue (shortcut, ReLU, one rounding, 16 bytes per lane).
+//   * Workgroups are numbered so that those of one XCD share what is larger, the filters of a
+//     group or the pixels of a region, in that XCD's L2.
+//
+// Measured, before -> now (us per launch in a replayed graph): 3 x 3, 512 -> 359 at 7 x 7, one
+// image 13.9 -> 5.2; 64 -> 45 at 56 x 56, one image 6.4 -> 3.9; stride 2, 229 -> 117 at 25 x 25 x 9
+// 22.2 -> 5.7; 256 -> 180 at 14 x 14 x 20 12.5 -> 7.8, x 64 19.1 -> 14.3; 163 -> 183 at 14 x 14 x 256
+// 41 -> 29; fc, 2048 -> 1000 on 64 pixels 12.3 -> 4.6.  A kernel that does nothing takes 1.7.
+// What bounds it: below some ten images latency (arguments, patch, first weights, one store);
+// then the weights, which every tile reads anew (45 bytes per clock and compute unit), and the
+// vector instructions that work out pixel addresses, beside the matrix pipe.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+
+#include "conv16.h"
+#include "device_utils.h"
+#include "fupr.h"
+#include "layout.h"
+#include "tuning.h"
+
+namespace fupr {
+namespace {
+
+constexpr uint32_t kOutside = 0x80000000u;   // beyond every tensor this kernel accepts
+constexpr int kMaxTaps = 25;                 // taps whose validity fits one register
+constexpr size_t kLdsLimit = 160 * 1024;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef short short2_t __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef void __attribute__((address_space(3)))* LdsPtr;
+
+enum { kOneTap = 0, kWindow = 1, kCat = 2 };
+
+struct WindowParams {
+  const uint16_t* x;
+  const uint16_t* x2;    // kCat: the channels from step split_steps on
+  const uint16_t* w;
+  const float* bias;
+  const uint16_t* res;
+  uint16_t* y;
+  uint32_t x_bytes, x2_bytes, w_bytes, res_bytes, y_bytes;
+  int H, W, pix;         // input extent; bytes per pixel
+  int pixels;            // N * H * W
+  int P, Q, PQ, M, ycs;
+  int R, S, stride, pad;
+  int Kp, cpt, nsteps;
+  int split_steps, H2, W2, pix2, stride2;
+  int rH, rW, rcs, rss, roff, relu;
+  int mgroups, fgroups, total, per_xcd, filter_major;
+  int WF, WK;            // waves along the filters, along the reduction (powers of two)
+  int log2_WF;
+  int slots, slots2;     // 16-byte LDS slots per pixel (kCat: of the first, of the second tensor)
+  int live, live2;       // of these, slots that hold channels of the tensor
+  int res_linear;        // the shortcut's pixels are the output's
+  int table_at, table_bytes, pixels_at, patch2_at;   // LDS byte offsets (the patch starts at 0)
+  FastDiv divPQ, divQ, divC, divS, divSlots, divSlots2;
+  FastDiv divG;          // by mgroups or fgroups, whichever runs fastest
+};
+
+__device__ __forceinline__ uint32_t clamp_below(uint32_t v, uint32_t floor2) {
+  const short2_t a = __builtin_bit_cast(short2_t, v), f = __builtin_bit_cast(short2_t, floor2);
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(a, f));
+}
+
+__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
+}
+
+// lane i moves the 16 bytes at offset off of the buffer to the i-th slot after
+// lds_base; an offset outside the buffer writes zeros
+__device__ __forceinline__ void load_to_lds(const i32x4& rsrc, uint32_t off, uint32_t lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, 0 offen lds"
+      :
+      : "s"(lds_base), "v"(off), "s"(rsrc)
+      : "memory", "m0");
+}
+
+__device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  i32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00020000;
+  return r;
+}
+
+// A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
+// wave; G: steps whose pixels are read from LDS together.
+template <bool BF, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES>
+__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams p) {
+  touch_arguments<sizeof(WindowParams)>();
+  extern __shared__ uint4 lds4[];
+  char* lds = reinterpret_cast<char*>(lds4);
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(LdsPtr)lds;
+  constexpr int TT = MT * NT, BM = MT * 16;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int waves = p.WF * p.WK;
+  const int wk = wave >> p.log2_WF, wf = wave & (p.WF - 1);
+
+  const int l = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+  if (l >= p.total) return;
+  const int slow = div_by(l, p.divG);
+  const int fast = l - slow * (p.filter_major ? p.mgroups : p.fgroups);
+  const int mg = p.filter_major ? fast : slow, fg = p.filter_major ? slow : fast;
+  const int m0 = mg * BM;
+  const int f0 = (fg * p.WF + wf) * (NT * 16);
+
+  const __amdgpu_buffer_rsrc_t wr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.w), 0, p.w_bytes, 0x00020000);
+  uint32_t a_off[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) a_off[t] = (uint32_t)(g * p.Kp + min(f0 + t * 16, p.Kp - 16) + li) * 16u;
+  const uint32_t a_step = (uint32_t)p.Kp * 64u;
+  uint4 a[D][NT];
+  auto load_weights = [&](int step, uint4* av) {
+    // (steps past the end read the last step's weights; their pixels are zeros)
+    const uint32_t so = (uint32_t)min(step, p.nsteps - 1) * a_step;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) av[t] = load16(wr, a_off[t], so);
+  };
+
+  // ---- the pixels' input into LDS ----
+  // Patch pixel 0 is zeros.  kWindow: pixel 1 + i is input pixel first + i of the batch taken
+  // as one row of pixels, so that a tap is a constant distance; else it is the input pixel of
+  // output pixel m0 + i.
+  auto split_pixel = [&](int m, int* n, int* pp, int* qq) {
+    *n = div_by(m, p.divPQ);
+    const int rem = m - *n * p.PQ;
+    *pp = div_by(rem, p.divQ);
+    *qq = rem - *pp * p.Q;
+  };
+  int first = m0, patch_pixels = 1 + BM;
+  if constexpr (MODE == kWindow) {
+    auto window_origin = [&](int m) {
+      int n, pp, qq;
+      split_pixel(m, &n, &pp, &qq);
+      return (n * p.H + pp * p.stride - p.pad) * p.W + qq * p.stride - p.pad;
+    };
+    first = window_origin(m0);
+    const int last = window_origin(min(m0 + BM, p.M) - 1) + (p.R - 1) * p.W + p.S - 1;
+    patch_pixels = 1 + last - first + 1;
+  }
+  const int stride64 = waves * 64;
+  // pixels that follow each other in memory: slot after slot, stepping
+  auto fill_run = [&](const i32x4& rsrc, int slots, const FastDiv& by, int live, int pix, int limit, int at) {
+    const int step_pix = div_by(stride64, by), step_c = stride64 - step_pix * slots;   // (scalar)
+    int slot = wave * 64 + lane;
+    int pixel = div_by(slot, by), c = slot - pixel * slots;
+    pixel += first - 1;                       // input pixel
+    const int zero = first - 1;
+    uint32_t off = (uint32_t)pixel * (uint32_t)pix + (uint32_t)c * 16u;
+    const uint32_t step_off = (uint32_t)(step_pix * pix + step_c * 16), wrap_off = (uint32_t)(pix - slots * 16);
+    const int count = patch_pixels * slots;
+    for (int base = wave * 64; base < count; base += stride64) {
+      const bool ok = c < live && pixel != zero && (unsigned)pixel < (unsigned)limit;
+      load_to_lds(rsrc, ok ? off : kOutside, lds_base + at + base * 16);
+      c += step_c;
+      pixel += step_pix;
+      off += step_off;
+      const bool wrap = c >= slots;
+      c -= wrap ? slots : 0;
+      pixel += wrap ? 1 : 0;
+      off += wrap ? wrap_off : 0u;
+    }
+  };
+  // a pixel of every stride-th column and row
+  auto fill_strided = [&](const i32x4& rsrc, int slots, const FastDiv& by, int live, int pix, int stride, int H, int W,
+                          int at) {
+    const int count = patch_pixels * slots;
+    for (int base = wave * 64; base < count; base += stride64) {
+      const int slot = base + lane;
+      const int pixel = div_by(slot, by), c = slot - pixel * slots, m = m0 + pixel - 1;
+      int n, pp, qq;
+      split_pixel(m, &n, &pp, &qq);
+      const bool ok = c < live && pixel > 0 && m < p.M;
+      const uint32_t in = (uint32_t)((n * H + pp * stride) * W + qq * stride);
+      load_to_lds(rsrc, ok ? in * (uint32_t)pix + (uint32_t)c * 16u : kOutside, lds_base + at + base * 16);
+    }
+  };
+  const i32x4 xr = make_rsrc(p.x, p.x_bytes);
+  if (MODE == kOneTap && p.stride != 1)
+    fill_strided(xr, p.slots, p.divSlots, p.live, p.pix, p.stride, p.H, p.W, 0);
+  else
+    fill_run(xr, p.slots, p.divSlots, p.live, p.pix, p.pixels, 0);
+  if constexpr (MODE == kCat) {
+    const i32x4 x2r = make_rsrc(p.x2, p.x2_bytes);
+    fill_strided(x2r, p.slots2, p.divSlots2, p.live2, p.pix2, p.stride2, p.H2, p.W2, p.patch2_at);
+  }
+
+  // the first weights travel with the pixels
+  int next = wk;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    load_weights(next, a[d]);
+    next += p.WK;
+  }
+
+  // per chunk of 8 channels: its LDS distance from the window origin, and its tap
+  u32x2* table = reinterpret_cast<u32x2*>(lds + p.table_at);
+  if constexpr (MODE == kWindow) {
+    const int entries = p.table_bytes / 8;
+    for (int j = tid; j < entries; j += waves * 64) {
+      const int tap = div_by(j, p.divC), cc = j - tap * p.cpt;
+      const int r = div_by(tap, p.divS), s = tap - r * p.S;
+      const bool ok = tap < p.R * p.S;
+      u32x2 e;
+      e[0] = ok ? (uint32_t)(((r * p.W + s) * p.slots + cc) * 16) : 0u;
+      e[1] = ok ? (uint32_t)tap : 31u;
+      table[j] = e;
+    }
+  }
+
+  // per pixel of the tile: LDS address of the window origin, and which taps lie inside the image
+  u32x2* pixel_table = reinterpret_cast<u32x2*>(lds + p.pixels_at);
+  if constexpr (MODE == kWindow) {
+    for (int i = tid; i < BM; i += stride64) {
+      const int m = m0 + i;
+      int n, pp, qq;
+      split_pixel(min(m, p.M - 1), &n, &pp, &qq);
+      const int ih = pp * p.stride - p.pad, iw = qq * p.stride - p.pad;
+      const int lo = max(0, -iw), hi = min(p.S, p.W - iw);   // columns lo .. hi - 1 of the window
+      const uint32_t cols = hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+      uint32_t taps = 0;
+      for (int r = 0; r < p.R; ++r)
+        taps |= (uint32_t)(ih + r) < (uint32_t)p.H ? cols << (r * p.S) : 0u;
+      u32x2 e;
+      e[0] = (uint32_t)((1 + (n * p.H + ih) * p.W + iw - first) * p.slots * 16);
+      e[1] = m < p.M ? taps : 0u;
+      pixel_table[i] = e;
+    }
+  }
+
+  // the first wave of a column starts from the bias, the others from zero
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+    if (wk == 0) b4 = *reinterpret_cast<const f32x4*>(p.bias + min(f0 + t * 16, p.Kp - 16) + g * 4);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt][t] = b4;
+  }
+
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  uint32_t origin[MT], origin2[MT], inside[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int i = mt * 16 + li;
+    origin2[mt] = inside[mt] = 0;
+    if constexpr (MODE == kWindow) {
+      const u32x2 e = pixel_table[i];
+      origin[mt] = e[0];
+      inside[mt] = e[1];
+    } else {
+      origin[mt] = (uint32_t)((1 + i) * p.slots * 16 + g * 16);
+      if constexpr (MODE == kCat) origin2[mt] = (uint32_t)(p.patch2_at + (1 + i) * p.slots2 * 16 + g * 16);
+    }
+  }
+
+  // Steps are taken in groups of G: the pixels of a group, and the table entries of the group
+  // after it, are read from LDS while the group before is multiplied.
+  uint4 b[2][G][MT];
+  u32x2 entry[G];
+  auto look_up = [&](int step) {
+    if constexpr (MODE == kWindow) {
+#pragma unroll
+      for (int i = 0; i < G; ++i) entry[i] = table[(step + i * p.WK) * 4 + g];
+    }
+  };
+  auto read_pixels = [&](int step, uint4 (*bv)[MT]) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      if constexpr (MODE == kWindow) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          // a tap outside the image reads patch pixel 0, which lies at LDS address 0
+          const uint32_t in = (uint32_t)__builtin_amdgcn_sbfe((int)inside[mt], entry[i][1], 1);
+          bv[i][mt] = *reinterpret_cast<const uint4*>(lds + ((origin[mt] + entry[i][0]) & in));
+        }
+      } else {
+        const int st = step + i * p.WK;
+        const bool second = MODE == kCat && st >= p.split_steps;
+        const uint32_t off = (uint32_t)(second ? st - p.split_steps : st) * 64u;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const uint32_t at = st < p.nsteps ? (second ? origin2[mt] : origin[mt]) + off : 0u;
+          bv[i][mt] = *reinterpret_cast<const uint4*>(lds + at);
+        }
+      }
+    }
+  };
+
+  int left = (p.nsteps - wk + p.WK - 1) / p.WK;   // this wave's steps
+  int step = wk;
+  look_up(step);
+  read_pixels(step, b[0]);
+  look_up(step + G * p.WK);
+  static_assert(D % (2 * G) == 0, "the pixel buffers alternate");
+  auto group = [&](int gi, bool more) {
+    step += G * p.WK;
+    read_pixels(step, b[(gi + 1) & 1]);
+    look_up(step + G * p.WK);
+    // (left alone, the scheduler sinks every read to just before its use)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int d = gi * G + i;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[mt][t] = mfma_16x16x32<BF>(a[d][t], b[gi & 1][i][mt], acc[mt][t]);
+      if (more) {
+        load_weights(next, a[d]);
+        next += p.WK;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (; left > D; left -= D) {
+#pragma unroll
+    for (int gi = 0; gi < D / G; ++gi) group(gi, true);
+  }
+  // the last round loads nothing and ends at the last group that holds a step
+#pragma unroll
+  for (int gi = 0; gi < D / G; ++gi)
+    if (gi * G < left) group(gi, false);
+
+  // ---- epilogue: shortcut, ReLU, one rounding ----
+  const __amdgpu_buffer_rsrc_t rr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.res), 0, p.res_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
+  const uint32_t floor2 = p.relu ? 0u : 0x80008000u;
+  auto res_at = [&](int m) {     // byte offset of output pixel m's shortcut pixel
+    if (p.res_linear) return (uint32_t)(m * p.rcs) * 2u;
+    int n, pp, qq;
+    split_pixel(m, &n, &pp, &qq);
+    return (uint32_t)(((n * p.rH + pp * p.rss) * p.rW + qq * p.rss) * p.rcs) * 2u;
+  };
+
+  // The waves of a column share its pairs of filter tiles: wave e % WK finishes pair e, the
+  // others hand it their sums through LDS (over the patch, which nobody reads any more).
+  constexpr int NP = (NT + 1) / 2;               // pairs of filter tiles; an odd last tile is alone
+  f32x4* part = reinterpret_cast<f32x4*>(lds);   // [giver][column][tile][lane]
+  if (p.WK > 1) {
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int giver = (wk - (mt * NP + t / 2)) & (p.WK - 1);   // 0: the owner
+        if (giver > 0) part[(((giver - 1) * p.WF + wf) * TT + mt * NT + t) * 64 + lane] = acc[mt][t];
+      }
+    __syncthreads();
+  }
+  if (f0 >= p.Kp) return;
+  auto finish = [&](const f32x4& av, uint32_t r0, uint32_t r1) {
+    float v[4] = {av[0], av[1], av[2], av[3]};
+    if (p.res) {
+      v[0] += to_float<BF>((uint16_t)(r0 & 0xffffu));
+      v[1] += to_float<BF>((uint16_t)(r0 >> 16));
+      v[2] += to_float<BF>((uint16_t)(r1 & 0xffffu));
+      v[3] += to_float<BF>((uint16_t)(r1 >> 16));
+    }
+    u32x2 o;
+    o[0] = clamp_below(pack2<BF>(v[0], v[1]), floor2);
+    o[1] = clamp_below(pack2<BF>(v[2], v[3]), floor2);
+    return o;
+  };
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int m = m0 + mt * 16 + li;
+    const uint32_t yo = m < p.M ? (uint32_t)(m * p.ycs) * 2u : kOutside;
+#pragma unroll
+    for (int pr = 0; pr < NP; ++pr) {
+      if (((mt * NP + pr) & (p.WK - 1)) != wk) continue;
+      const int t = 2 * pr;
+      const bool pair = t + 1 < NT;
+      // after the exchange between 16-lane rows lane (pixel, g) holds channels
+      // (g >> 1) * 8 .. + 7 of tile t + (g & 1): 16-byte accesses; a lone tile keeps 8 bytes
+      const int k0 = f0 + t * 16 + (pair ? (g & 1) * 16 + (g >> 1) * 8 : g * 4);
+      u32x4 r4 = {0u, 0u, 0u, 0u};
+      if (p.res) {
+        const int kk = k0 - p.roff;
+        const uint32_t ro = m < p.M && kk >= 0 && kk < p.rcs ? res_at(m) + (uint32_t)kk * 2u : kOutside;
+        if (pair) {
+          r4 = __builtin_amdgcn_raw_buffer_load_b128(rr, ro, 0, 0);
+        } else {
+          const u32x2 r2 = __builtin_amdgcn_raw_buffer_load_b64(rr, ro, 0, 0);
+          r4[0] = r2[0];
+          r4[1] = r2[1];
+        }
+      }
+      // in the order of the waves, whichever of them adds up: the sum does not depend on the tile
+      f32x4 s0 = acc[mt][t], s1 = acc[mt][pair ? t + 1 : t];
+      if (p.WK > 1) {
+        const f32x4 own0 = s0, own1 = s1;
+        s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < p.WK; ++k) {
+          const int from = ((k - wk) & (p.WK - 1)) - 1;          // -1: this wave itself
+          const f32x4* src = part + ((max(from, 0) * p.WF + wf) * TT + mt * NT + t) * 64 + lane;
+          const f32x4 u0 = src[0], u1 = src[pair ? 64 : 0];
+          s0 += from < 0 ? own0 : u0;
+          s1 += from < 0 ? own1 : u1;
+        }
+      }
+      const uint32_t off = k0 < p.ycs ? yo + (uint32_t)k0 * 2u : kOutside;
+      if (pair) {
+        uint32_t ra0 = 0, ra1 = 0, rb0 = 0, rb1 = 0;
+        if (p.res) {
+          const auto q0 = __builtin_amdgcn_permlane16_swap(r4[0], r4[2], false, false);
+          const auto q1 = __builtin_amdgcn_permlane16_swap(r4[1], r4[3], false, false);
+          ra0 = q0[0]; ra1 = q1[0];   // tile t
+          rb0 = q0[1]; rb1 = q1[1];   // tile t + 1
+        }
+        const u32x2 oa = finish(s0, ra0, ra1);
+        const u32x2 ob = finish(s1, rb0, rb1);
+        const auto w0 = __builtin_amdgcn_permlane16_swap(oa[0], ob[0], false, false);
+        const auto w1 = __builtin_amdgcn_permlane16_swap(oa[1], ob[1], false, false);
+        const u32x4 o4 = {w0[0], w1[0], w0[1], w1[1]};
+        __builtin_amdgcn_raw_buffer_store_b128(o4, yr, off, 0, 0);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b64(finish(s0, r4[0], r4[1]), yr, off, 0, 0);
+      }
+    }
+  }
+}
+
+// D: steps of weights in flight; G: steps per group of pixel reads; vgprs: as compiled.
+struct WindowTile {
+  int MT, NT, D, G, threads, min_waves, vgprs;
+  const char *three, *one_tap, *other;
+};
+#define FUPR_NAMES(t) "conv3x3p_w" t, "conv1x1p_w" t, "conv16t_w" t
+constexpr WindowTile kTiles[] = {
+    {1, 1, 8, 4, 1024, 4, 85, FUPR_NAMES("16x16")},  {1, 3, 4, 2, 1024, 4, 92, FUPR_NAMES("16x48")},
+    {2, 1, 8, 2, 1024, 4, 87, FUPR_NAMES("32x16")},  {2, 2, 4, 2, 1024, 4, 96, FUPR_NAMES("32x32")},
+    {2, 3, 4, 2, 512, 2, 122, FUPR_NAMES("32x48")},  {4, 1, 6, 1, 512, 2, 89, FUPR_NAMES("64x16")},
+    {4, 2, 4, 1, 512, 2, 114, FUPR_NAMES("64x32")},  {4, 3, 4, 1, 512, 2, 148, FUPR_NAMES("64x48")},
+    {4, 4, 4, 1, 512, 2, 180, FUPR_NAMES("64x64")},  {7, 2, 4, 1, 512, 2, 168, FUPR_NAMES("112x32")},
+    {7, 3, 4, 1, 512, 2, 214, FUPR_NAMES("112x48")}, {7, 4, 2, 1, 512, 2, 227, FUPR_NAMES("112x64")},
+};
+#undef FUPR_NAMES
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+struct WindowPlan {
+  WindowParams p;
+  int tile, mode, patch_slots;
+  size_t lds;
+};
+
+int window_rows(const Conv16Params& c) { return c.nchunk / (c.cpt * c.S); }
+
+bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowPlan* out) {
+  const WindowTile& T = kTiles[tile];
+  const int waves = WF * WK, R = window_rows(c);
+  if (waves * 64 > T.threads) return false;
+  WindowParams p{};
+  const int mode = c.x2 ? kCat : (R == 1 && c.S == 1 && c.pad == 0 ? kOneTap : kWindow);
+  p.x = c.x; p.x2 = c.x2; p.w = c.w; p.bias = c.bias; p.res = c.res; p.y = c.y;
+  const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * 2, y_bytes = (uint64_t)c.M * c.ycs * 2;
+  const uint64_t x2_bytes = c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 * 2 : 0;
+  const uint64_t res_bytes = c.res ? (uint64_t)N * c.rH * c.rW * c.rcs * 2 : 0;
+  if (x_bytes >= kOutside || y_bytes >= kOutside || x2_bytes >= kOutside || res_bytes >= kOutside) return false;
+  p.x_bytes = (uint32_t)x_bytes; p.x2_bytes = (uint32_t)x2_bytes; p.res_bytes = (uint32_t)res_bytes;
+  p.y_bytes = (uint32_t)y_bytes; p.w_bytes = c.w_bytes;
+  p.H = c.H; p.W = c.W; p.pix = c.xcs * 2; p.pixels = N * c.H * c.W;
+  p.P = c.P; p.Q = c.Q; p.PQ = c.PQ; p.M = c.M; p.ycs = c.ycs;
+  p.R = R; p.S = c.S; p.stride = c.stride; p.pad = c.pad;
+  p.Kp = c.Kp; p.cpt = c.cpt; p.nsteps = c.nsteps;
+  p.H2 = c.H2; p.W2 = c.W2; p.pix2 = c.xcs2 * 2; p.stride2 = c.stride2;
+  p.rH = c.rH; p.rW = c.rW; p.rcs = c.rcs; p.rss = c.rss; p.roff = c.roff; p.relu = c.relu;
+  p.WF = WF; p.WK = WK;
+  while ((1 << p.log2_WF) < WF) ++p.log2_WF;
+  if ((WF & (WF - 1)) || (WK & (WK - 1))) return false;
+  const int BM = T.MT * 16, NF = WF * T.NT * 16;
+  p.mgroups = (c.M + BM - 1) / BM;
+  p.fgroups = (c.Kp + NF - 1) / NF;
+  const int64_t total = (int64_t)p.mgroups * p.fgroups;
+  if (total >= (int64_t(1) << 28)) return false;
+  p.total = (int)total;
+  p.per_xcd = (p.total + 7) / 8;
+  p.filter_major = (uint64_t)c.w_bytes > x_bytes + x2_bytes;
+  // LDS slots per pixel: 16 lanes read 16 bytes each of neighbouring output pixels, which is
+  // free of bank conflicts at odd multiples of 32 bytes
+  auto pad_slots = [&](int chunks) {
+    int s = chunks;
+    if (c.stride == 2 && mode == kWindow) return s | 1;
+    while (s % 4 != 2) ++s;
+    return s;
+  };
+  int pixels = 1 + BM;
+  if (mode == kWindow) {
+    // the largest distance between the window origins of a tile's first and last pixel
+    const int rows = (BM - 1 + c.Q - 1) / c.Q;               // row ends crossed, at most
+    const int images = (BM - 1 + c.PQ - 1) / c.PQ;           // image ends crossed, at most
+    const int64_t span = (int64_t)(BM - 1) * c.stride + (int64_t)rows * (c.stride * c.W - c.stride * (c.Q - 1)) +
+                         (int64_t)images * (std::max(0, c.H - c.stride * (c.P - 1)) * c.W);
+    pixels = (int)std::min<int64_t>(1 + span + (R - 1) * c.W + c.S, 1 << 20);
+    p.table_bytes = (int)(p.nsteps + (T.D + 2 * T.G + 2) * WK) * 32;
+  }
+  p.live = c.x2 ? std::min(c.split, c.xcs / 8) : c.cpt;
+  p.slots = pad_slots(c.x2 ? c.split : round_up(c.cpt, mode == kOneTap ? 4 : 1));
+  if (c.x2) {
+    p.split_steps = c.split / 4;
+    p.live2 = c.cpt - c.split;
+    p.slots2 = pad_slots(round_up(p.live2, 4));
+  }
+  p.res_linear = c.rss == 1 && c.rH == c.P && c.rW == c.Q;
+  size_t end = round_up_sz((size_t)pixels * p.slots * 16, 1024);
+  if (c.x2) {
+    p.patch2_at = (int)end;
+    end += round_up_sz((size_t)pixels * p.slots2 * 16, 1024);
+  }
+  p.table_at = (int)end;
+  p.pixels_at = p.table_at + p.table_bytes;
+  if (mode == kWindow) end = (size_t)p.pixels_at + (size_t)BM * 8;
+  out->patch_slots = pixels * (p.slots + p.slots2);
+  const size_t reduce = (size_t)(WK - 1) * WF * T.MT * T.NT * 1024;
+  out->lds = std::max(end, reduce);
+  if (out->lds > kLdsLimit) return false;
+  p.divPQ = fast_div(p.PQ); p.divQ = fast_div(p.Q); p.divC = fast_div(p.cpt); p.divS = fast_div(p.S);
+  p.divSlots = fast_div(p.slots); p.divSlots2 = fast_div(std::max(p.slots2, 1));
+  p.divG = fast_div(p.filter_major ? p.mgroups : p.fgroups);
+  out->p = p;
+  out->tile = tile;
+  out->mode = mode;
+  return true;
+}
+
+template <bool BF, int MODE, int TILE>
+fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
+  constexpr WindowTile T = kTiles[TILE];
+  auto kernel = conv_window_kernel<BF, MODE, T.MT, T.NT, T.D, T.G, T.threads, T.min_waves>;
+  if (plan.lds > 64 * 1024) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+    if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
+  }
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.p.per_xcd * 8)), dim3(plan.p.WF * plan.p.WK * 64), plan.lds, st,
+                     plan.p);
+  return launch_status("conv_window_kernel");
+}
+
+template <bool BF, int MODE>
+fupr_status dispatch(const WindowPlan& plan, hipStream_t st) {
+  switch (plan.tile) {
+#define FUPR_TILE(i) case i: return launch_as<BF, MODE, i>(plan, st);
+    FUPR_TILE(0) FUPR_TILE(1) FUPR_TILE(2) FUPR_TILE(3) FUPR_TILE(4) FUPR_TILE(5)
+    FUPR_TILE(6) FUPR_TILE(7) FUPR_TILE(8) FUPR_TILE(9) FUPR_TILE(10) FUPR_TILE(11)
+#undef FUPR_TILE
+  }
+  return FUPR_ERR_LIMIT;
+}
+
+int num_compute_units() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
+      (void)hipGetLastError();
+      return 256;
+    }
+    return n;
+  }();
+  return cus;
+}
+
+// Estimated clocks of a plan.  The constants are a fit over 420 layer shapes (1 - 256 images of the
+// ImageNet networks' layers, and arbitrary ones) x every tile and wave arrangement, 12 800 launches:
+// the plan with the least estimate is 2.6 % slower than the best one in the mean, 27 % at worst.
+double estimate(const Conv16Params& c, const WindowPlan& plan) {
+  const WindowParams& p = plan.p;
+  const WindowTile& T = kTiles[plan.tile];
+  const int waves = p.WF * p.WK, cus = num_compute_units();
+  const int per_cu = (p.total + cus - 1) / cus;                    // workgroups of the busiest unit
+  const int fit = std::max(1, std::min({(int)(kLdsLimit / plan.lds), 32 / waves, 512 / T.vgprs * 4 / waves}));
+  const int rounds = (per_cu + std::min(per_cu, fit) - 1) / std::min(per_cu, fit);
+  const double steps = round_up((p.nsteps + p.WK - 1) / p.WK, T.G);
+  const double tiles = T.MT * T.NT, slots = plan.patch_slots, out = tiles * 256.0 * p.WF * (c.res ? 2 : 1);
+  // what a workgroup takes of its compute unit: the matrix pipe and the vector instructions beside
+  // it, what it reads (45 bytes per clock), LDS
+  const double mfma = waves * steps * tiles * 4.0 + 0.376 * waves * steps * (40.35 * T.MT + 26.78) / 4.0;
+  const double reads = (slots * 16.0 * p.live / p.slots + (double)p.nsteps * p.WF * T.NT * 1024.0) / 45.1;
+  const double lds = waves * steps * T.MT * 11.55 + slots * 0.25;
+  const double work = std::max({mfma, reads, lds}) + out * 0.0185;
+  // and how long it takes when it has the unit to itself
+  const double alone = 3356.0 + 82.0 * waves + out / waves * 0.67 + slots / (waves * 64.0) * 45.3 +
+                       steps * (34.1 / T.G + tiles * 16.0) +
+                       (p.WK > 1 ? 455.0 + (p.WK - 1) * tiles * 460.0 / p.WK : 0.0) +
+                       tiles * (c.res ? 87.0 : 58.0) / p.WK;
+  return 2893.0 + std::max(rounds * alone, per_cu * work + 0.62 * alone);
+}
+
+// The plan with the least estimate among those that fit; only those that cut the reduction into
+// WK parts if WK > 0.
+bool pick_window(const Conv16Params& c, int N, int only_WK, WindowPlan* best) {
+  // The tuning switch window_tile=<index>x<waves along the filters>x<waves along the reduction>
+  // forces a tile.
+  char text[32];
+  if (tuning_text("window_tile", text, sizeof(text))) {
+    int tile = -1, wf = 1, wk = 4;
+    if (std::sscanf(text, "%dx%dx%d", &tile, &wf, &wk) != 3 || tile < 0 || tile >= kNumTiles) return false;
+    if (wf < 1 || wk < 1 || wf * wk > 16) return false;
+    return plan_window(c, N, tile, wf, wk, best);
+  }
+  // A 1 x 1 reduction of at most four steps is not cut: all of its weights are in flight at once
+  // anyway, and its sums are those of a pair of 1 x 1 convolutions in one launch (conv1x1.hip).
+  const bool whole = c.nchunk == c.cpt && c.nsteps <= 4;
+  double least = 0.0;
+  bool any = false;
+  for (int tile = 0; tile < kNumTiles; ++tile)
+    for (int wf = 1; wf <= 8; wf *= 2) {
+      if (wf > 1 && (wf / 2) * kTiles[tile].NT * 16 >= c.Kp) break;   // half of the waves would be idle
+      for (int waves = whole ? wf : 4; waves <= (whole ? wf : 8); waves *= 2) {
+        WindowPlan plan;
+        if (waves < wf || (only_WK > 0 && waves / wf != only_WK)) continue;
+        if (!plan_window(c, N, tile, wf, waves / wf, &plan)) continue;
+        const double cost = estimate(c, plan);
+        if (!any || cost < least) {
+          *best = plan;
+          least = cost;
+          any = true;
+        }
+      }
+    }
+  return any;
+}
+
+// How the reduction is cut decides the order of the sums, so it is chosen for the batch the caller
+// runs (plan_N), the tile for the images of this launch: sub-batches of one batch give its bits.
+bool pick_for_batch(const Conv16Params& c, int N, WindowPlan* plan) {
+  if (c.plan_N <= 0 || c.plan_N == N) return pick_window(c, N, 0, plan);
+  Conv16Params whole = c;
+  whole.M = (int)((int64_t)c.plan_N * c.PQ);
+  return pick_window(whole, c.plan_N, 0, plan) && pick_window(c, N, plan->p.WK, plan);
+}
+
+// The choice is a function of sizes alone; each thread remembers its answers for the sizes it
+// launched last (about 100 plans are weighed for one, several microseconds of host time).
+struct Sizes {
+  int N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two;
+  bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
+};
+struct Remembered {
+  Sizes sizes;
+  int8_t tile, WF, WK;   // WF = 0: no entry; tile = -1: no plan fits
+};
+
+bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
+  if (tuning_any()) return pick_for_batch(c, N, plan);
+  constexpr int kEntries = 256;
+  thread_local Remembered table[kEntries];
+  const Sizes z = {N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp, c.cpt,
+                   c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0};
+  uint32_t h = 2166136261u;
+  for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
+    h = (h ^ (uint32_t)reinterpret_cast<const int*>(&z)[i]) * 16777619u;
+  Remembered& r = table[(h ^ (h >> 15)) % kEntries];
+  if (r.WF == 0 || !(r.sizes == z)) {
+    const bool ok = pick_for_batch(c, N, plan);
+    r.sizes = z;
+    r.tile = ok ? (int8_t)plan->tile : (int8_t)-1;
+    r.WF = ok ? (int8_t)plan->p.WF : (int8_t)1;
+    r.WK = ok ? (int8_t)plan->p.WK : (int8_t)1;
+    return ok;
+  }
+  return r.tile >= 0 && plan_window(c, N, r.tile, r.WF, r.WK, plan);
+}
+
+// Sizes for which this kernel is the faster one.  (The switches that choose among the other
+// kernels' tiles ask for those kernels.)
+bool wanted(const Conv16Params& c, int N) {
+  if (c.keep || tuning_off("conv_window")) return false;
+  const int R = window_rows(c);
+  if (R * c.S > kMaxTaps || (c.x2 && c.split % 8 != 0)) return false;
+  if (c.res && c.roff % 8 != 0) return false;   // 16-byte shortcut loads
+  if (tuning_any()) {
+    char text[64];
+    for (const char* other : {"patch_tile", "pipe_tile", "pipe_order", "stream_tile", "stream_blocks", "conv_tile"})
+      if (tuning_text(other, text, sizeof(text))) return false;
+    if (tuning_text("window_tile", text, sizeof(text))) return true;
+  }
+  const double M = (double)(c.plan_N > 0 ? c.plan_N : N) * c.PQ;
+  if (R == 1 && c.S == 1) {
+    // Layers that are bound by the bytes of their tensors stay with the 1 x 1 kernels that keep
+    // loads in flight across tiles (32 -> 256 channels with a shortcut at 56 x 56 x 26, 89 MB: 19.3
+    // against 26.7 us; 1024 -> 204 at 14 x 14 x 87, 42 MB: 19.5 against 23.0 us); below they spend
+    // most of their time starting up (32 -> 256 at 56 x 56 x 10, 34 MB: 10.6 against 8.6 us).
+    const double bytes = 2.0 * M * (c.cpt * 8.0 + c.ycs * (c.res ? 2.0 : 1.0));
+    return bytes <= 36e6;
+  }
+  // Thin reductions over very many pixels: the patch kernel keeps its weights in LDS from tile
+  // to tile (51 -> 30 channels at 56 x 56 x 149: 32.2 against 35.6 us; x 64: 21 against 20 us).
+  return !(R == 3 && c.S == 3 && c.stride == 1 && c.cpt <= 8 && M > (1 << 18));
+}
+
+// What the launch list calls it: the family of kernels the layer belongs to, and the tile.
+const char* name_of(const Conv16Params& c, int tile) {
+  const int R = window_rows(c);
+  if (R == 1 && c.S == 1) return kTiles[tile].one_tap;
+  return R == 3 && c.S == 3 && c.stride == 1 && c.cpt >= 2 ? kTiles[tile].three : kTiles[tile].other;
+}
+
+}  // namespace
+
+bool conv_window_applies(const Conv16Params& c, int N) {
+  WindowPlan plan;
+  return wanted(c, N) && plan_for(c, N, &plan);
+}
+
+const char* conv_window_name(const Conv16Params& c, int N) {
+  WindowPlan plan;
+  return plan_for(c, N, &plan) ? name_of(c, plan.tile) : "conv16t_w";
+}
+
+bool launch_conv_window(const Conv16Params& c, int N, bool bf16, void* stream, fupr_status* status) {
+  WindowPlan plan;
+  if (!wanted(c, N) || !plan_for(c, N, &plan)) return false;
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  if (plan.mode == kCat) *status = bf16 ? dispatch<true, kCat>(plan, st) : dispatch<false, kCat>(plan, st);
+  else if (plan.mode == kOneTap) *status = bf16 ? dispatch<true, kOneTap>(plan, st) : dispatch<false, kOneTap>(plan, st);
+  else *status = bf16 ? dispatch<true, kWindow>(plan, st) : dispatch<false, kWindow>(plan, st);
+  return true;
+}
+
+}  // namespace fupr

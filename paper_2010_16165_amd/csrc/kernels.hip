@@ -242,6 +242,8 @@ Conv16Params geometry16(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, i
   p.M = (int)((int64_t)N * p.PQ);
   p.S = s.S; p.stride = s.stride; p.pad = s.pad;
   p.Kp = L.Kp; p.FT = L.Kp / 16; p.cpt = L.Cp / 8; p.nchunk = L.nchunk; p.nsteps = L.nchunk_pad / 4;
+  p.xcs = L.Cp; p.ycs = min_c_stride(s.K, dt);
+  p.w_bytes = (uint32_t)((size_t)L.nchunk_pad * L.Kp * 16);
   return p;
 }
 
@@ -263,6 +265,7 @@ Conv16Params params16(const ConvArgs& a) {
   p.Kp = L.Kp; p.FT = L.Kp / 16; p.cpt = L.Cp / 8; p.nchunk = L.nchunk; p.nsteps = L.nchunk_pad / 4;
   p.rH = a.rH; p.rW = a.rW; p.rcs = a.rcs; p.rss = a.rss; p.roff = a.roff;
   p.relu = a.relu;
+  p.plan_N = a.plan_N;
   p.x_bytes = (uint32_t)((int64_t)a.N * a.H * a.W * a.xcs * 2);
   p.w_bytes = (uint32_t)((size_t)L.nchunk_pad * L.Kp * 16);
   p.keep = a.keep; p.keep_n = a.K; p.yC = a.yC;
@@ -289,11 +292,17 @@ bool prefer_pipe(const Conv16Params& g) {
 }  // namespace
 
 const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
-                             bool indexed, bool two_inputs) {
+                             bool indexed, bool add, int first_c) {
   if (dt == FUPR_F32) return "conv32_direct";
   Conv16Params g = geometry16(s, dt, N, H, W);
-  if (two_inputs) {   // a marker that is never dereferenced stands for the second tensor
-    g.x2 = reinterpret_cast<const uint16_t*>(uintptr_t(16));
+  // markers that are never dereferenced stand for the shortcut and the second tensor
+  const uint16_t* const marker = reinterpret_cast<const uint16_t*>(uintptr_t(16));
+  if (add && !indexed) g.res = marker;
+  if (first_c > 0) {
+    g.x2 = marker;
+    g.split = round_up(first_c, FUPR_CAT_ALIGN) / 8;
+    g.xcs = min_c_stride(first_c, dt);
+    if (conv_window_applies(g, N)) return conv_window_name(g, N);
     if (prefer_pipe(g)) return conv1x1_pipe_name(g);
     if (conv1x1_stream_applies(g)) return conv1x1_stream_name(g);
     return conv1x1_pipe_applies(g) ? conv1x1_pipe_name(g) : "none";
@@ -301,6 +310,7 @@ const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int
   // the indexed epilogue needs LDS of its own, which can change the tile: a marker
   // that is never dereferenced stands for the index list
   if (indexed) g.keep = reinterpret_cast<const int32_t*>(uintptr_t(16));
+  if (conv_window_applies(g, N)) return conv_window_name(g, N);
   if (s.R == 3 && conv_patch_applies(g, N)) return conv_patch_name(g, N);
   if (indexed) return conv16_tiled_name(g.FT, g.nsteps, g.M);
   if (s.R == 1 && prefer_pipe(g)) return conv1x1_pipe_name(g);
@@ -333,6 +343,8 @@ fupr_status launch_conv(const ConvArgs& a, void* stream) {
     return launch_status(__func__);
   }
   const Conv16Params p = params16(a);
+  fupr_status status;
+  if (launch_conv_window(p, a.N, a.dt == FUPR_BF16, stream, &status)) return status;
   if (a.x2) {   // two input tensors: the two 1 x 1 kernels read them
     if (prefer_pipe(p)) return launch_conv1x1_pipe(p, a.N, a.dt == FUPR_BF16, stream);
     if (conv1x1_stream_applies(p)) return launch_conv1x1_stream(p, a.N, a.dt == FUPR_BF16, stream);
@@ -483,6 +495,17 @@ extern "C" fupr_status fupr_conv_cat_fused(const fupr_conv_shape* shape, const f
   const fupr_status st =
       check_conv_cat(shape, x1, x2, x2_spatial_stride, packed, res, epilogue_flags, y, &a);
   return st != FUPR_OK ? st : launch_conv(a, stream);
+}
+
+fupr_status fupr::conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
+                                  int32_t x2_stride, const void* packed, const fupr_residual* res,
+                                  uint32_t flags, const fupr_tensor* y, int plan_N, void* stream) {
+  ConvArgs a;
+  const fupr_status st = x2 ? check_conv_cat(shape, x, x2, x2_stride, packed, res, flags, y, &a)
+                            : check_conv(shape, x, packed, res, flags, y, &a);
+  if (st != FUPR_OK) return st;
+  a.plan_N = plan_N;
+  return launch_conv(a, stream);
 }
 
 extern "C" fupr_status fupr_conv_scatter_fused(const fupr_conv_shape* shape, const fupr_tensor* x,

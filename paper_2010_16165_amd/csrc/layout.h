@@ -67,12 +67,18 @@ struct ConvArgs {
   // second input of a convolution over two concatenated tensors; x2 = nullptr otherwise
   const void* x2;
   int H2, W2, xcs2, stride2;
+  int plan_N;            // images of the whole batch when the launch is a part of one, else 0
   int split_c;           // input channels taken from x (a multiple of 32); the others come from x2
 };
 fupr_status launch_conv(const ConvArgs& a, void* stream);
-// indexed: the convolution adds into listed channels of a wider tensor (ConvArgs::keep)
+// indexed: the convolution adds into listed channels of a wider tensor (ConvArgs::keep); add: it
+// has a shortcut; first_c > 0: it reads two tensors, the first of that many channels
 const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
-                             bool indexed = false, bool two_inputs = false);
+                             bool indexed = false, bool add = false, int first_c = 0);
+// fupr_conv_fused / fupr_conv_cat_fused (x2 != nullptr) on a part of a batch of plan_N images.
+fupr_status conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
+                            int32_t x2_stride, const void* packed, const fupr_residual* res,
+                            uint32_t flags, const fupr_tensor* y, int plan_N, void* stream);
 // fupr_conv_cat_fused followed by a 1 x 1 convolution of its output, in one launch
 // (what fupr_conv_conv1x1_fused is to fupr_conv_fused); for the model executor.
 fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x1,

@@ -997,13 +997,11 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
           r.spatial_stride = op.res_spatial_stride;
           r.c_offset = op.res_c_offset;
         }
-        if (op.epilogue & FUPR_FUSE_CAT) {
-          const fupr_tensor x2 = view(op.in2, n0, count);
-          st = fupr_conv_cat_fused(&op.conv, &x, &x2, op.in2_spatial_stride, op.packed,
-                                   add ? &r : nullptr, op.epilogue & ~uint32_t(FUPR_FUSE_CAT), &y, on);
-        } else {
-          st = fupr_conv_fused(&op.conv, &x, op.packed, add ? &r : nullptr, op.epilogue, &y, on);
-        }
+        const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
+        fupr_tensor x2;
+        if (cat) x2 = view(op.in2, n0, count);
+        st = conv_fused_part(&op.conv, &x, cat ? &x2 : nullptr, op.in2_spatial_stride, op.packed,
+                             add ? &r : nullptr, op.epilogue & ~uint32_t(FUPR_FUSE_CAT), &y, N, on);
       } else if (op.kind == FUPR_OP_MAXPOOL) {
         st = fupr_maxpool(&x, op.conv.R, op.conv.stride, op.conv.pad, &y, on);
       } else {
@@ -1106,8 +1104,8 @@ extern "C" fupr_status fupr_model_op_stats(const fupr_model* m, int32_t batch, i
     if (scatter)   // conv.K channels of the updated tensor read and written, and the index list
       s.bytes = in_b + 2.0 * es * (double)s.M * d.conv.K + es * crs * d.conv.K + 8.0 * d.conv.K;
     if (scatter) s.K = d.conv.K;
-    s.kernel = conv_kernel_name(d.conv, m->dt, batch, ti.H, ti.W, scatter,
-                                (d.epilogue & FUPR_FUSE_CAT) != 0);
+    s.kernel = conv_kernel_name(d.conv, m->dt, batch, ti.H, ti.W, scatter, d.res >= 0,
+                                (d.epilogue & FUPR_FUSE_CAT) ? ti.C : 0);
   } else {
     s.R = s.S = d.kind == FUPR_OP_MAXPOOL ? d.conv.R : ti.H;
     s.stride = d.kind == FUPR_OP_MAXPOOL ? d.conv.stride : 1;

@@ -3,6 +3,7 @@
 // the table is first used, and changes afterwards only through fupr_tuning_set.
 #include "tuning.h"
 
+#include <atomic>
 #include <cctype>
 #include <cstdlib>
 #include <cstring>
@@ -28,6 +29,8 @@ Switch g_switches[] = {
     {"stream_tile", false, {0}},     // index of the streaming 1 x 1 kernel's tile
     {"stream_blocks", false, {0}},   // workgroups per compute unit that kernel is compiled for (1, 2)
     {"conv_tile", false, {0}},       // name of the general kernel's tile
+    {"window_tile", false, {0}},     // <index>x<waves on filters>x<waves on the reduction>
+    {"conv_window", false, {0}},     // 0: layers skip the kernel with weights straight into registers
     {"conv_patch", false, {0}},      // 0: 3 x 3 layers skip the patch kernel
     {"conv1x1_stream", false, {0}},  // 0: 1 x 1 layers skip the streaming kernel
     {"conv1x1_pipe", false, {0}},    // 0: 1 x 1 layers skip the pipelined kernel
@@ -40,6 +43,7 @@ Switch g_switches[] = {
 
 std::mutex g_mutex;
 std::once_flag g_env_once;
+std::atomic<int> g_with_value{0};   // switches that have a value: launchers look at this first
 
 void read_environment() {
   for (Switch& s : g_switches) {
@@ -51,6 +55,7 @@ void read_environment() {
     if (e && *e && std::strlen(e) < kValueBytes) {
       std::strcpy(s.value, e);
       s.set = true;
+      g_with_value.fetch_add(1);
     }
   }
 }
@@ -64,7 +69,13 @@ Switch* find(const char* name) {
 
 }  // namespace
 
+bool tuning_any() {
+  std::call_once(g_env_once, read_environment);
+  return g_with_value.load(std::memory_order_acquire) != 0;
+}
+
 bool tuning_text(const char* name, char* out, size_t n) {
+  if (!tuning_any()) return false;
   Switch* s = find(name);
   if (!s || n == 0) return false;
   std::lock_guard<std::mutex> lock(g_mutex);
@@ -92,7 +103,9 @@ extern "C" fupr_status fupr_tuning_set(const char* name, const char* value) {
   if (!s) return FUPR_ERR_ARG;
   if (value && std::strlen(value) >= fupr::kValueBytes) return FUPR_ERR_ARG;
   std::lock_guard<std::mutex> lock(fupr::g_mutex);
-  s->set = value && *value;
-  if (s->set) std::strcpy(s->value, value);
+  const bool set = value && *value;
+  if (set) std::strcpy(s->value, value);
+  fupr::g_with_value.fetch_add((set ? 1 : 0) - (s->set ? 1 : 0));
+  s->set = set;
   return FUPR_OK;
 }

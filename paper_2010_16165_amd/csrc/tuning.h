@@ -7,6 +7,8 @@
 
 namespace fupr {
 
+// True when any switch has a value; the three calls below cost nothing while none has.
+bool tuning_any();
 // The switch's value parsed as an integer; `unset` when it has no value.
 int tuning_int(const char* name, int unset);
 // The switch's value copied into out (n bytes, always terminated); false when unset.

@@ -307,6 +307,45 @@ def test_every_general_tile_forced(fx, tile):
             B.fupr_tuning_set(family, None)
 
 
+# The kernel with the tile's pixels in LDS and the weights straight into registers: every tile,
+# with its waves along the filters, along the reduction, and both, on shapes that end inside a
+# tile of pixels, of filters and of channels, cross rows and images inside a tile, and leave waves
+# without a step or without a filter.
+WINDOW_TILES = ["16x16", "16x48", "32x16", "32x32", "32x48", "64x16", "64x32", "64x48", "64x64",
+                "112x32", "112x48", "112x64"]
+FORCED_WINDOW = [
+    ("window 3x3 C45 K72 +id 28x28 x2", 2, 45, 28, 28, 72, 3, 1, 1, "identity", True),
+    ("window 3x3 C40 K100 s2 27x31 x2 norelu", 2, 40, 27, 31, 100, 3, 2, 1, None, False),
+    ("window 3x3 C3 K16 optA 5x7 x3", 3, 3, 5, 7, 16, 3, 1, 1, "optionA", True),
+    ("window 5x5 C12 K33 s2 21x21 x2", 2, 12, 21, 21, 33, 5, 2, 2, None, True),
+    ("window 1x1 C72 K200 +id 9x11 x3", 3, 72, 9, 11, 200, 1, 1, 0, "identity", True),
+    ("window 1x1 C64 K130 s2 15x13 x2", 2, 64, 15, 13, 130, 1, 2, 0, None, True),
+    ("window 1x1 C136 K39 on 1x1 x3", 3, 136, 1, 1, 39, 1, 1, 0, None, False),
+]
+
+
+@pytest.mark.parametrize("waves", ["1x4", "2x2", "4x1", "1x8"])
+@pytest.mark.parametrize("tile", range(len(WINDOW_TILES)), ids=WINDOW_TILES)
+def test_every_window_tile_forced(fx, tile, waves):
+    B, network, torch = fx
+    B.fupr_tuning_set("window_tile", f"{tile}x{waves}")
+    ran = 0
+    try:
+        for case in FORCED_WINDOW:
+            if not kernel_of(B, "bf16", case).endswith("_w" + WINDOW_TILES[tile]):
+                print(f"  {case[0]}: tile does not fit", flush=True)
+                continue
+            ran += 1
+            for dtype in ("bf16", "f16"):
+                conv_site(fx, case, dtype)
+    finally:
+        B.fupr_tuning_set("window_tile", None)
+    # the partial sums of all but one wave of the reduction, 4 bytes each, must fit in LDS
+    mt, nt = (int(v) // 16 for v in WINDOW_TILES[tile].split("x"))
+    wf, wk = (int(v) for v in waves.split("x"))
+    assert ran >= 5 if (wk - 1) * wf * mt * nt <= 160 else ran == 0
+
+
 @pytest.mark.parametrize("tile", [4, 5, 12], ids=["128x32", "64x64", "64x32"])
 def test_small_tiles_with_several_units_in_flight(fx, tile):
     """The small tiles of the 3 x 3 kernel load up to three units ahead through a ring
