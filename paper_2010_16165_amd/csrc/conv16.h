@@ -1,4 +1,4 @@
-// Internal: arguments of the 16-bit implicit-GEMM convolution kernels.
+// Internal: arguments of the implicit-GEMM convolution kernels (16-bit types, but for one of them).
 #pragma once
 #include <cstdint>
 
@@ -7,6 +7,9 @@
 namespace fupr {
 
 struct Conv16Params {
+  // FUPR_F32 for conv_window.hip only: x, w, res and y then point to floats, strides count floats,
+  // a chunk is 4 channels and w is [R * S * Cp][Kp].
+  fupr_dtype dt;
   const uint16_t* x;
   const uint16_t* w;     // [nchunk_pad][Kp][8]
   const float* bias;     // [Kp]
@@ -68,9 +71,9 @@ fupr_status launch_conv1x1_pipe(const Conv16Params& p, int N, bool bf16, void* s
 
 // conv_window.hip: any window of at most 25 taps, one or two input tensors, with the tile's
 // pixels in LDS and the weights straight from L2 into registers.  Geometry fields decide whether
-// it takes a layer; launch_conv_window returns false, and launches nothing, when it does not.
+// it takes a layer (single precision included); launch_conv_window returns false, and launches nothing, when it does not.
 bool conv_window_applies(const Conv16Params& geometry, int N);
 const char* conv_window_name(const Conv16Params& geometry, int N);
-bool launch_conv_window(const Conv16Params& p, int N, bool bf16, void* stream, fupr_status* status);
+bool launch_conv_window(const Conv16Params& p, int N, void* stream, fupr_status* status);
 
 }  // namespace fupr

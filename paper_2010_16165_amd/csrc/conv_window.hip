@@ -1,4 +1,4 @@
-// 16-bit convolutions with the input of a workgroup's pixels in LDS and the weights
+// Convolutions with the input of a workgroup's pixels in LDS and the weights
 // streamed straight from L2 into registers (Sec. III, Sec. IV-B-1: operator
 // k x c x r x s with its fused epilogue).
 //
@@ -28,6 +28,10 @@
 // image 13.9 -> 5.2; 64 -> 45 at 56 x 56, one image 6.4 -> 3.9; stride 2, 229 -> 117 at 25 x 25 x 9
 // 22.2 -> 5.7; 256 -> 180 at 14 x 14 x 20 12.5 -> 7.8, x 64 19.1 -> 14.3; 163 -> 183 at 14 x 14 x 256
 // 41 -> 29; fc, 2048 -> 1000 on 64 pixels 12.3 -> 4.6.  A kernel that does nothing takes 1.7.
+// Single precision runs through the same code on the 16 x 16 x 4 MFMA: a chunk is then 4 channels
+// (16 bytes as well), a step 16 channels in four MFMAs, each of which takes one channel of every
+// lane's chunk.  A CIFAR-size network of 21 layers on 32 images: 410 us (one thread per pixel and
+// four filters, vector FMAs) -> 115.
 // What bounds it: below some ten images latency (arguments, patch, first weights, one store);
 // then the weights, which every tile reads anew (45 bytes per clock and compute unit), and the
 // vector instructions that work out pixel addresses, beside the matrix pipe.
@@ -118,9 +122,11 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 
 // A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
 // wave; G: steps whose pixels are read from LDS together.
-template <bool BF, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES>
+template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES>
 __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams p) {
   touch_arguments<sizeof(WindowParams)>();
+  constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
+  constexpr uint32_t ES = F32 ? 4 : 2;       // bytes per element
   extern __shared__ uint4 lds4[];
   char* lds = reinterpret_cast<char*>(lds4);
   const uint32_t lds_base = (uint32_t)(uintptr_t)(LdsPtr)lds;
@@ -142,14 +148,28 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.w), 0, p.w_bytes, 0x00020000);
   uint32_t a_off[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) a_off[t] = (uint32_t)(g * p.Kp + min(f0 + t * 16, p.Kp - 16) + li) * 16u;
+  for (int t = 0; t < NT; ++t)
+    a_off[t] = F32 ? (uint32_t)(g * 4 * p.Kp + min(f0 + t * 16 + li, p.Kp - 1)) * 4u
+                   : (uint32_t)(g * p.Kp + min(f0 + t * 16, p.Kp - 16) + li) * 16u;
   const uint32_t a_step = (uint32_t)p.Kp * 64u;
   uint4 a[D][NT];
   auto load_weights = [&](int step, uint4* av) {
     // (steps past the end read the last step's weights; their pixels are zeros)
     const uint32_t so = (uint32_t)min(step, p.nsteps - 1) * a_step;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) av[t] = load16(wr, a_off[t], so);
+    for (int t = 0; t < NT; ++t) {
+      if constexpr (F32) {
+        // four channels of the lane's chunk and filter; the last step may end inside itself,
+        // and what lies beyond the weights reads as zero
+        const uint32_t at = a_off[t] + so, row = (uint32_t)p.Kp * 4u;
+        av[t].x = __builtin_amdgcn_raw_buffer_load_b32(wr, at, 0, 0);
+        av[t].y = __builtin_amdgcn_raw_buffer_load_b32(wr, at + row, 0, 0);
+        av[t].z = __builtin_amdgcn_raw_buffer_load_b32(wr, at + 2 * row, 0, 0);
+        av[t].w = __builtin_amdgcn_raw_buffer_load_b32(wr, at + 3 * row, 0, 0);
+      } else {
+        av[t] = load16(wr, a_off[t], so);
+      }
+    }
   };
 
   // ---- the pixels' input into LDS ----
@@ -268,7 +288,7 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
-    if (wk == 0) b4 = *reinterpret_cast<const f32x4*>(p.bias + min(f0 + t * 16, p.Kp - 16) + g * 4);
+    if (wk == 0) b4 = *reinterpret_cast<const f32x4*>(p.bias + min(f0 + t * 16 + g * 4, p.Kp - 4));
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt][t] = b4;
   }
@@ -343,7 +363,18 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-          acc[mt][t] = mfma_16x16x32<BF>(a[d][t], b[gi & 1][i][mt], acc[mt][t]);
+          {
+          if constexpr (F32) {
+            // MFMA k takes channel k of every lane's chunk of four
+            const uint4 &av = a[d][t], &bv = b[gi & 1][i][mt];
+            acc[mt][t] = mfma_16x16x4(av.x, bv.x, acc[mt][t]);
+            acc[mt][t] = mfma_16x16x4(av.y, bv.y, acc[mt][t]);
+            acc[mt][t] = mfma_16x16x4(av.z, bv.z, acc[mt][t]);
+            acc[mt][t] = mfma_16x16x4(av.w, bv.w, acc[mt][t]);
+          } else {
+            acc[mt][t] = mfma_16x16x32<BF>(a[d][t], b[gi & 1][i][mt], acc[mt][t]);
+          }
+        }
       if (more) {
         load_weights(next, a[d]);
         next += p.WK;
@@ -366,10 +397,10 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
   const uint32_t floor2 = p.relu ? 0u : 0x80008000u;
   auto res_at = [&](int m) {     // byte offset of output pixel m's shortcut pixel
-    if (p.res_linear) return (uint32_t)(m * p.rcs) * 2u;
+    if (p.res_linear) return (uint32_t)(m * p.rcs) * ES;
     int n, pp, qq;
     split_pixel(m, &n, &pp, &qq);
-    return (uint32_t)(((n * p.rH + pp * p.rss) * p.rW + qq * p.rss) * p.rcs) * 2u;
+    return (uint32_t)(((n * p.rH + pp * p.rss) * p.rW + qq * p.rss) * p.rcs) * ES;
   };
 
   // The waves of a column share its pairs of filter tiles: wave e % WK finishes pair e, the
@@ -404,11 +435,39 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int m = m0 + mt * 16 + li;
-    const uint32_t yo = m < p.M ? (uint32_t)(m * p.ycs) * 2u : kOutside;
+    const uint32_t yo = m < p.M ? (uint32_t)(m * p.ycs) * ES : kOutside;
 #pragma unroll
     for (int pr = 0; pr < NP; ++pr) {
       if (((mt * NP + pr) & (p.WK - 1)) != wk) continue;
       const int t = 2 * pr;
+      if constexpr (F32) {
+        // single precision: a lane's four channels of a tile are 16 bytes
+#pragma unroll
+        for (int u = t; u < (t + 2 < NT ? t + 2 : NT); ++u) {
+          const int k0 = f0 + u * 16 + g * 4, kk = k0 - p.roff;
+          f32x4 r4 = {0.f, 0.f, 0.f, 0.f};
+          if (p.res)
+            r4 = __builtin_bit_cast(
+                f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                           rr, m < p.M && kk >= 0 && kk < p.rcs ? res_at(m) + (uint32_t)kk * 4u : kOutside, 0, 0));
+          f32x4 v = acc[mt][u];
+          if (p.WK > 1) {
+            v = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < p.WK; ++k) {
+              const int from = ((k - wk) & (p.WK - 1)) - 1;
+              const f32x4 q = part[((max(from, 0) * p.WF + wf) * TT + mt * NT + u) * 64 + lane];
+              v += from < 0 ? acc[mt][u] : q;
+            }
+          }
+          v += r4;
+          if (p.relu)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), yr,
+                                                 k0 < p.ycs ? yo + (uint32_t)k0 * 4u : kOutside, 0, 0);
+        }
+        continue;
+      }
       const bool pair = t + 1 < NT;
       // after the exchange between 16-lane rows lane (pixel, g) holds channels
       // (g >> 1) * 8 .. + 7 of tile t + (g & 1): 16-byte accesses; a lone tile keeps 8 bytes
@@ -463,9 +522,9 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
 // D: steps of weights in flight; G: steps per group of pixel reads; vgprs: as compiled.
 struct WindowTile {
   int MT, NT, D, G, threads, min_waves, vgprs;
-  const char *three, *one_tap, *other;
+  const char *three, *one_tap, *other, *single;
 };
-#define FUPR_NAMES(t) "conv3x3p_w" t, "conv1x1p_w" t, "conv16t_w" t
+#define FUPR_NAMES(t) "conv3x3p_w" t, "conv1x1p_w" t, "conv16t_w" t, "conv32_w" t
 constexpr WindowTile kTiles[] = {
     {1, 1, 8, 4, 1024, 4, 85, FUPR_NAMES("16x16")},  {1, 3, 4, 2, 1024, 4, 92, FUPR_NAMES("16x48")},
     {2, 1, 8, 2, 1024, 4, 87, FUPR_NAMES("32x16")},  {2, 2, 4, 2, 1024, 4, 96, FUPR_NAMES("32x32")},
@@ -492,17 +551,19 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   WindowParams p{};
   const int mode = c.x2 ? kCat : (R == 1 && c.S == 1 && c.pad == 0 ? kOneTap : kWindow);
   p.x = c.x; p.x2 = c.x2; p.w = c.w; p.bias = c.bias; p.res = c.res; p.y = c.y;
-  const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * 2, y_bytes = (uint64_t)c.M * c.ycs * 2;
-  const uint64_t x2_bytes = c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 * 2 : 0;
-  const uint64_t res_bytes = c.res ? (uint64_t)N * c.rH * c.rW * c.rcs * 2 : 0;
+  const int es = c.dt == FUPR_F32 ? 4 : 2;
+  if (es == 4 && (T.MT * T.NT > 8 || T.NT == 3)) return false;   // (not compiled for single precision)
+  const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * es, y_bytes = (uint64_t)c.M * c.ycs * es;
+  const uint64_t x2_bytes = c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 * es : 0;
+  const uint64_t res_bytes = c.res ? (uint64_t)N * c.rH * c.rW * c.rcs * es : 0;
   if (x_bytes >= kOutside || y_bytes >= kOutside || x2_bytes >= kOutside || res_bytes >= kOutside) return false;
   p.x_bytes = (uint32_t)x_bytes; p.x2_bytes = (uint32_t)x2_bytes; p.res_bytes = (uint32_t)res_bytes;
   p.y_bytes = (uint32_t)y_bytes; p.w_bytes = c.w_bytes;
-  p.H = c.H; p.W = c.W; p.pix = c.xcs * 2; p.pixels = N * c.H * c.W;
+  p.H = c.H; p.W = c.W; p.pix = c.xcs * es; p.pixels = N * c.H * c.W;
   p.P = c.P; p.Q = c.Q; p.PQ = c.PQ; p.M = c.M; p.ycs = c.ycs;
   p.R = R; p.S = c.S; p.stride = c.stride; p.pad = c.pad;
   p.Kp = c.Kp; p.cpt = c.cpt; p.nsteps = c.nsteps;
-  p.H2 = c.H2; p.W2 = c.W2; p.pix2 = c.xcs2 * 2; p.stride2 = c.stride2;
+  p.H2 = c.H2; p.W2 = c.W2; p.pix2 = c.xcs2 * es; p.stride2 = c.stride2;
   p.rH = c.rH; p.rW = c.rW; p.rcs = c.rcs; p.rss = c.rss; p.roff = c.roff; p.relu = c.relu;
   p.WF = WF; p.WK = WK;
   while ((1 << p.log2_WF) < WF) ++p.log2_WF;
@@ -562,10 +623,13 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   return true;
 }
 
-template <bool BF, int MODE, int TILE>
+template <int EL, int MODE, int TILE>
 fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
   constexpr WindowTile T = kTiles[TILE];
-  auto kernel = conv_window_kernel<BF, MODE, T.MT, T.NT, T.D, T.G, T.threads, T.min_waves>;
+  if constexpr (EL == FUPR_F32 && (T.MT * T.NT > 8 || T.NT == 3)) {
+    return FUPR_ERR_LIMIT;
+  } else {
+  auto kernel = conv_window_kernel<EL, MODE, T.MT, T.NT, T.D, T.G, T.threads, T.min_waves>;
   if (plan.lds > 64 * 1024) {
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
@@ -574,12 +638,13 @@ fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
   hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.p.per_xcd * 8)), dim3(plan.p.WF * plan.p.WK * 64), plan.lds, st,
                      plan.p);
   return launch_status("conv_window_kernel");
+  }
 }
 
-template <bool BF, int MODE>
+template <int EL, int MODE>
 fupr_status dispatch(const WindowPlan& plan, hipStream_t st) {
   switch (plan.tile) {
-#define FUPR_TILE(i) case i: return launch_as<BF, MODE, i>(plan, st);
+#define FUPR_TILE(i) case i: return launch_as<EL, MODE, i>(plan, st);
     FUPR_TILE(0) FUPR_TILE(1) FUPR_TILE(2) FUPR_TILE(3) FUPR_TILE(4) FUPR_TILE(5)
     FUPR_TILE(6) FUPR_TILE(7) FUPR_TILE(8) FUPR_TILE(9) FUPR_TILE(10) FUPR_TILE(11)
 #undef FUPR_TILE
@@ -611,16 +676,17 @@ double estimate(const Conv16Params& c, const WindowPlan& plan) {
   const int fit = std::max(1, std::min({(int)(kLdsLimit / plan.lds), 32 / waves, 512 / T.vgprs * 4 / waves}));
   const int rounds = (per_cu + std::min(per_cu, fit) - 1) / std::min(per_cu, fit);
   const double steps = round_up((p.nsteps + p.WK - 1) / p.WK, T.G);
+  const double clocks = c.dt == FUPR_F32 ? 128.0 : 16.0;           // of the matrix pipe per tile and step
   const double tiles = T.MT * T.NT, slots = plan.patch_slots, out = tiles * 256.0 * p.WF * (c.res ? 2 : 1);
   // what a workgroup takes of its compute unit: the matrix pipe and the vector instructions beside
   // it, what it reads (45 bytes per clock), LDS
-  const double mfma = waves * steps * tiles * 4.0 + 0.376 * waves * steps * (40.35 * T.MT + 26.78) / 4.0;
+  const double mfma = waves * steps * tiles * clocks / 4.0 + 0.376 * waves * steps * (40.35 * T.MT + 26.78) / 4.0;
   const double reads = (slots * 16.0 * p.live / p.slots + (double)p.nsteps * p.WF * T.NT * 1024.0) / 45.1;
   const double lds = waves * steps * T.MT * 11.55 + slots * 0.25;
   const double work = std::max({mfma, reads, lds}) + out * 0.0185;
   // and how long it takes when it has the unit to itself
   const double alone = 3356.0 + 82.0 * waves + out / waves * 0.67 + slots / (waves * 64.0) * 45.3 +
-                       steps * (34.1 / T.G + tiles * 16.0) +
+                       steps * (34.1 / T.G + tiles * clocks) +
                        (p.WK > 1 ? 455.0 + (p.WK - 1) * tiles * 460.0 / p.WK : 0.0) +
                        tiles * (c.res ? 87.0 : 58.0) / p.WK;
   return 2893.0 + std::max(rounds * alone, per_cu * work + 0.62 * alone);
@@ -640,7 +706,7 @@ bool pick_window(const Conv16Params& c, int N, int only_WK, WindowPlan* best) {
   }
   // A 1 x 1 reduction of at most four steps is not cut: all of its weights are in flight at once
   // anyway, and its sums are those of a pair of 1 x 1 convolutions in one launch (conv1x1.hip).
-  const bool whole = c.nchunk == c.cpt && c.nsteps <= 4;
+  const bool whole = c.dt != FUPR_F32 && c.nchunk == c.cpt && c.nsteps <= 4;
   double least = 0.0;
   bool any = false;
   for (int tile = 0; tile < kNumTiles; ++tile)
@@ -673,7 +739,7 @@ bool pick_for_batch(const Conv16Params& c, int N, WindowPlan* plan) {
 // The choice is a function of sizes alone; each thread remembers its answers for the sizes it
 // launched last (about 100 plans are weighed for one, several microseconds of host time).
 struct Sizes {
-  int N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two;
+  int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two;
   bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
 };
 struct Remembered {
@@ -685,7 +751,7 @@ bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
   if (tuning_any()) return pick_for_batch(c, N, plan);
   constexpr int kEntries = 256;
   thread_local Remembered table[kEntries];
-  const Sizes z = {N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp, c.cpt,
+  const Sizes z = {(int)c.dt, N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp, c.cpt,
                    c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0};
   uint32_t h = 2166136261u;
   for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
@@ -708,13 +774,14 @@ bool wanted(const Conv16Params& c, int N) {
   if (c.keep || tuning_off("conv_window")) return false;
   const int R = window_rows(c);
   if (R * c.S > kMaxTaps || (c.x2 && c.split % 8 != 0)) return false;
-  if (c.res && c.roff % 8 != 0) return false;   // 16-byte shortcut loads
+  if (c.res && c.dt != FUPR_F32 && c.roff % 8 != 0) return false;   // 16-byte shortcut loads
   if (tuning_any()) {
     char text[64];
     for (const char* other : {"patch_tile", "pipe_tile", "pipe_order", "stream_tile", "stream_blocks", "conv_tile"})
       if (tuning_text(other, text, sizeof(text))) return false;
     if (tuning_text("window_tile", text, sizeof(text))) return true;
   }
+  if (c.dt == FUPR_F32) return true;
   const double M = (double)(c.plan_N > 0 ? c.plan_N : N) * c.PQ;
   if (R == 1 && c.S == 1) {
     // Layers that are bound by the bytes of their tensors stay with the 1 x 1 kernels that keep
@@ -731,6 +798,7 @@ bool wanted(const Conv16Params& c, int N) {
 
 // What the launch list calls it: the family of kernels the layer belongs to, and the tile.
 const char* name_of(const Conv16Params& c, int tile) {
+  if (c.dt == FUPR_F32) return kTiles[tile].single;
   const int R = window_rows(c);
   if (R == 1 && c.S == 1) return kTiles[tile].one_tap;
   return R == 3 && c.S == 3 && c.stride == 1 && c.cpt >= 2 ? kTiles[tile].three : kTiles[tile].other;
@@ -748,13 +816,21 @@ const char* conv_window_name(const Conv16Params& c, int N) {
   return plan_for(c, N, &plan) ? name_of(c, plan.tile) : "conv16t_w";
 }
 
-bool launch_conv_window(const Conv16Params& c, int N, bool bf16, void* stream, fupr_status* status) {
+static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, hipStream_t st) {
+  const bool bf16 = dt == FUPR_BF16;
+  if (dt == FUPR_F32)
+    return plan.mode == kOneTap ? dispatch<FUPR_F32, kOneTap>(plan, st) : dispatch<FUPR_F32, kWindow>(plan, st);
+  if (plan.mode == kCat)
+    return bf16 ? dispatch<FUPR_BF16, kCat>(plan, st) : dispatch<FUPR_F16, kCat>(plan, st);
+  if (plan.mode == kOneTap)
+    return bf16 ? dispatch<FUPR_BF16, kOneTap>(plan, st) : dispatch<FUPR_F16, kOneTap>(plan, st);
+  return bf16 ? dispatch<FUPR_BF16, kWindow>(plan, st) : dispatch<FUPR_F16, kWindow>(plan, st);
+}
+
+bool launch_conv_window(const Conv16Params& c, int N, void* stream, fupr_status* status) {
   WindowPlan plan;
   if (!wanted(c, N) || !plan_for(c, N, &plan)) return false;
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (plan.mode == kCat) *status = bf16 ? dispatch<true, kCat>(plan, st) : dispatch<false, kCat>(plan, st);
-  else if (plan.mode == kOneTap) *status = bf16 ? dispatch<true, kOneTap>(plan, st) : dispatch<false, kOneTap>(plan, st);
-  else *status = bf16 ? dispatch<true, kWindow>(plan, st) : dispatch<false, kWindow>(plan, st);
+  *status = dispatch_window(plan, c.dt, reinterpret_cast<hipStream_t>(stream));
   return true;
 }
 

@@ -55,6 +55,12 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(const uint4& a, const uint4& b, f
   }
 }
 
+// Single precision: lane l holds row l % 16 of A and column l % 16 of B at reduction index l / 16;
+// the result lies as for the 16-bit shapes above.
+__device__ __forceinline__ f32x4 mfma_16x16x4(uint32_t a, uint32_t b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a), __uint_as_float(b), c, 0, 0, 0);
+}
+
 // D (32 x 32) += A (32 x 16) * B (16 x 32).  Lane l holds row l % 32 of A and column
 // l % 32 of B, reduction indices 8 * (l / 32) .. + 7 of each; of D it holds column
 // l % 32, rows 8 * (v / 4) + 4 * (l / 32) + v % 4 in element v.  Both shapes sustain

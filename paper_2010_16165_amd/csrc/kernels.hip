@@ -18,7 +18,8 @@ namespace fupr {
 namespace {
 
 // ---- fp32 direct convolution ------------------------------------------------
-// One thread: one output pixel x 4 consecutive filters, plain FMA.
+// One thread: one output pixel x 4 consecutive filters, plain FMA.  For what conv_window.hip does
+// not take: windows of more than 25 taps, tensors of 2 GiB or more.
 
 struct Conv32Params {
   const float* x;
@@ -231,29 +232,42 @@ fupr_status launch_status(const char* what) {
 
 namespace {
 
-// Geometry of a 16-bit convolution as the kernels take it.
+void set_filters(Conv16Params& p, const PackedLayout& L, fupr_dtype dt) {
+  p.Kp = L.Kp;
+  p.FT = (L.Kp + 15) / 16;
+  if (dt == FUPR_F32) {   // chunks of 4 channels
+    p.cpt = L.Cp / 4; p.nchunk = L.nchunk / 4; p.nsteps = (p.nchunk + 3) / 4;
+    p.w_bytes = (uint32_t)((size_t)L.nchunk * L.Kp * 4);
+  } else {
+    p.cpt = L.Cp / 8; p.nchunk = L.nchunk; p.nsteps = L.nchunk_pad / 4;
+    p.w_bytes = (uint32_t)((size_t)L.nchunk_pad * L.Kp * 16);
+  }
+}
+
+// Geometry of a convolution as the kernels take it.
 Conv16Params geometry16(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W) {
   const PackedLayout L = packed_layout(s, dt);
   Conv16Params p{};
+  p.dt = dt;
   p.H = H; p.W = W;
   p.P = out_extent(H, s.R, s.stride, s.pad);
   p.Q = out_extent(W, s.S, s.stride, s.pad);
   p.PQ = p.P * p.Q;
   p.M = (int)((int64_t)N * p.PQ);
   p.S = s.S; p.stride = s.stride; p.pad = s.pad;
-  p.Kp = L.Kp; p.FT = L.Kp / 16; p.cpt = L.Cp / 8; p.nchunk = L.nchunk; p.nsteps = L.nchunk_pad / 4;
+  set_filters(p, L, dt);
   p.xcs = L.Cp; p.ycs = min_c_stride(s.K, dt);
-  p.w_bytes = (uint32_t)((size_t)L.nchunk_pad * L.Kp * 16);
   return p;
 }
 
-// A 16-bit convolution's arguments as the kernels take them.
+// A convolution's arguments as the kernels take them.
 Conv16Params params16(const ConvArgs& a) {
   fupr_conv_shape s{a.K, a.C, a.R, a.S, a.stride, a.pad};
   const PackedLayout L = packed_layout(s, a.dt);
   const char* blob = reinterpret_cast<const char*>(a.packed);
   const int64_t M = (int64_t)a.N * a.P * a.Q;
   Conv16Params p{};
+  p.dt = a.dt;
   p.x = (const uint16_t*)a.x;
   p.w = (const uint16_t*)(blob + L.weight_offset);
   p.bias = (const float*)blob;
@@ -262,12 +276,11 @@ Conv16Params params16(const ConvArgs& a) {
   p.H = a.H; p.W = a.W; p.xcs = a.xcs;
   p.P = a.P; p.Q = a.Q; p.PQ = a.P * a.Q; p.M = (int)M; p.ycs = a.ycs;
   p.S = a.S; p.stride = a.stride; p.pad = a.pad;
-  p.Kp = L.Kp; p.FT = L.Kp / 16; p.cpt = L.Cp / 8; p.nchunk = L.nchunk; p.nsteps = L.nchunk_pad / 4;
+  set_filters(p, L, a.dt);
   p.rH = a.rH; p.rW = a.rW; p.rcs = a.rcs; p.rss = a.rss; p.roff = a.roff;
   p.relu = a.relu;
   p.plan_N = a.plan_N;
   p.x_bytes = (uint32_t)((int64_t)a.N * a.H * a.W * a.xcs * 2);
-  p.w_bytes = (uint32_t)((size_t)L.nchunk_pad * L.Kp * 16);
   p.keep = a.keep; p.keep_n = a.K; p.yC = a.yC;
   p.x2 = (const uint16_t*)a.x2;
   if (a.x2) {
@@ -293,8 +306,11 @@ bool prefer_pipe(const Conv16Params& g) {
 
 const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
                              bool indexed, bool add, int first_c) {
-  if (dt == FUPR_F32) return "conv32_direct";
   Conv16Params g = geometry16(s, dt, N, H, W);
+  if (dt == FUPR_F32) {
+    if (add) g.res = reinterpret_cast<const uint16_t*>(uintptr_t(16));   // (never dereferenced)
+    return conv_window_applies(g, N) ? conv_window_name(g, N) : "conv32_direct";
+  }
   // markers that are never dereferenced stand for the shortcut and the second tensor
   const uint16_t* const marker = reinterpret_cast<const uint16_t*>(uintptr_t(16));
   if (add && !indexed) g.res = marker;
@@ -325,26 +341,26 @@ fupr_status launch_conv(const ConvArgs& a, void* stream) {
   const PackedLayout L = packed_layout(s, a.dt);
   const int64_t M = (int64_t)a.N * a.P * a.Q;
   const char* blob = reinterpret_cast<const char*>(a.packed);
-  if (a.dt == FUPR_F32) {
-    Conv32Params p;
-    p.x = (const float*)a.x;
-    p.w = (const float*)(blob + L.weight_offset);
-    p.bias = (const float*)blob;
-    p.res = (const float*)a.res;
-    p.y = (float*)a.y;
-    p.H = a.H; p.W = a.W; p.xcs = a.xcs; p.Cp = L.Cp;
-    p.P = a.P; p.Q = a.Q; p.PQ = a.P * a.Q; p.M = (int)M; p.ycs = a.ycs;
-    p.R = a.R; p.S = a.S; p.stride = a.stride; p.pad = a.pad;
-    p.Kp = L.Kp; p.KQ = L.Kp / 4;
-    p.rH = a.rH; p.rW = a.rW; p.rcs = a.rcs; p.rss = a.rss; p.roff = a.roff;
-    p.relu = a.relu;
-    const int64_t threads = M * p.KQ;
-    hipLaunchKernelGGL(conv32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p);
-    return launch_status(__func__);
-  }
   const Conv16Params p = params16(a);
   fupr_status status;
-  if (launch_conv_window(p, a.N, a.dt == FUPR_BF16, stream, &status)) return status;
+  if (launch_conv_window(p, a.N, stream, &status)) return status;
+  if (a.dt == FUPR_F32) {
+    Conv32Params q;
+    q.x = (const float*)a.x;
+    q.w = (const float*)(blob + L.weight_offset);
+    q.bias = (const float*)blob;
+    q.res = (const float*)a.res;
+    q.y = (float*)a.y;
+    q.H = a.H; q.W = a.W; q.xcs = a.xcs; q.Cp = L.Cp;
+    q.P = a.P; q.Q = a.Q; q.PQ = a.P * a.Q; q.M = (int)M; q.ycs = a.ycs;
+    q.R = a.R; q.S = a.S; q.stride = a.stride; q.pad = a.pad;
+    q.Kp = L.Kp; q.KQ = L.Kp / 4;
+    q.rH = a.rH; q.rW = a.rW; q.rcs = a.rcs; q.rss = a.rss; q.roff = a.roff;
+    q.relu = a.relu;
+    const int64_t threads = M * q.KQ;
+    hipLaunchKernelGGL(conv32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, q);
+    return launch_status(__func__);
+  }
   if (a.x2) {   // two input tensors: the two 1 x 1 kernels read them
     if (prefer_pipe(p)) return launch_conv1x1_pipe(p, a.N, a.dt == FUPR_BF16, stream);
     if (conv1x1_stream_applies(p)) return launch_conv1x1_stream(p, a.N, a.dt == FUPR_BF16, stream);

@@ -338,6 +338,8 @@ def test_every_window_tile_forced(fx, tile, waves):
             ran += 1
             for dtype in ("bf16", "f16"):
                 conv_site(fx, case, dtype)
+            if kernel_of(B, "f32", case) == "conv32_w" + WINDOW_TILES[tile]:   # the small tiles
+                conv_site(fx, case, "f32")
     finally:
         B.fupr_tuning_set("window_tile", None)
     # the partial sums of all but one wave of the reduction, 4 bytes each, must fit in LDS
