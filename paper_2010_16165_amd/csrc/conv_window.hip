@@ -544,27 +544,33 @@ struct WindowPlan {
 
 int window_rows(const Conv16Params& c) { return c.nchunk / (c.cpt * c.S); }
 
+// What a call brings and a plan does not depend on: addresses, the output's and the shortcut's layout.
+void set_call(const Conv16Params& c, int N, WindowParams* p) {
+  const uint32_t es = c.dt == FUPR_F32 ? 4 : 2;
+  p->y_bytes = (uint32_t)c.M * (uint32_t)c.ycs * es;
+  p->res_bytes = c.res ? (uint32_t)N * (uint32_t)(c.rH * c.rW) * (uint32_t)c.rcs * es : 0;
+  p->x = c.x; p->x2 = c.x2; p->w = c.w; p->bias = c.bias; p->res = c.res; p->y = c.y;
+  p->ycs = c.ycs; p->relu = c.relu;
+  p->rH = c.rH; p->rW = c.rW; p->rcs = c.rcs; p->rss = c.rss; p->roff = c.roff;
+  p->res_linear = c.rss == 1 && c.rH == c.P && c.rW == c.Q;
+}
+
 bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowPlan* out) {
   const WindowTile& T = kTiles[tile];
   const int waves = WF * WK, R = window_rows(c);
   if (waves * 64 > T.threads) return false;
   WindowParams p{};
   const int mode = c.x2 ? kCat : (R == 1 && c.S == 1 && c.pad == 0 ? kOneTap : kWindow);
-  p.x = c.x; p.x2 = c.x2; p.w = c.w; p.bias = c.bias; p.res = c.res; p.y = c.y;
   const int es = c.dt == FUPR_F32 ? 4 : 2;
   if (es == 4 && (T.MT * T.NT > 8 || T.NT == 3)) return false;   // (not compiled for single precision)
-  const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * es, y_bytes = (uint64_t)c.M * c.ycs * es;
+  const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * es;
   const uint64_t x2_bytes = c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 * es : 0;
-  const uint64_t res_bytes = c.res ? (uint64_t)N * c.rH * c.rW * c.rcs * es : 0;
-  if (x_bytes >= kOutside || y_bytes >= kOutside || x2_bytes >= kOutside || res_bytes >= kOutside) return false;
-  p.x_bytes = (uint32_t)x_bytes; p.x2_bytes = (uint32_t)x2_bytes; p.res_bytes = (uint32_t)res_bytes;
-  p.y_bytes = (uint32_t)y_bytes; p.w_bytes = c.w_bytes;
+  p.x_bytes = (uint32_t)x_bytes; p.x2_bytes = (uint32_t)x2_bytes; p.w_bytes = c.w_bytes;
   p.H = c.H; p.W = c.W; p.pix = c.xcs * es; p.pixels = N * c.H * c.W;
-  p.P = c.P; p.Q = c.Q; p.PQ = c.PQ; p.M = c.M; p.ycs = c.ycs;
+  p.P = c.P; p.Q = c.Q; p.PQ = c.PQ; p.M = c.M;
   p.R = R; p.S = c.S; p.stride = c.stride; p.pad = c.pad;
   p.Kp = c.Kp; p.cpt = c.cpt; p.nsteps = c.nsteps;
   p.H2 = c.H2; p.W2 = c.W2; p.pix2 = c.xcs2 * es; p.stride2 = c.stride2;
-  p.rH = c.rH; p.rW = c.rW; p.rcs = c.rcs; p.rss = c.rss; p.roff = c.roff; p.relu = c.relu;
   p.WF = WF; p.WK = WK;
   while ((1 << p.log2_WF) < WF) ++p.log2_WF;
   if ((WF & (WF - 1)) || (WK & (WK - 1))) return false;
@@ -601,7 +607,6 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
     p.live2 = c.cpt - c.split;
     p.slots2 = pad_slots(round_up(p.live2, 4));
   }
-  p.res_linear = c.rss == 1 && c.rH == c.P && c.rW == c.Q;
   size_t end = round_up_sz((size_t)pixels * p.slots * 16, 1024);
   if (c.x2) {
     p.patch2_at = (int)end;
@@ -635,9 +640,10 @@ fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
     if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
   }
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.p.per_xcd * 8)), dim3(plan.p.WF * plan.p.WK * 64), plan.lds, st,
-                     plan.p);
-  return launch_status("conv_window_kernel");
+  void* list[] = {const_cast<WindowParams*>(&plan.p)};
+  return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)(plan.p.per_xcd * 8)),
+                                  dim3(plan.p.WF * plan.p.WK * 64), list, plan.lds, st),
+                  "conv_window_kernel");
   }
 }
 
@@ -739,33 +745,31 @@ bool pick_for_batch(const Conv16Params& c, int N, WindowPlan* plan) {
 // The choice is a function of sizes alone; each thread remembers its answers for the sizes it
 // launched last (about 100 plans are weighed for one, several microseconds of host time).
 struct Sizes {
-  int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two;
+  int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two, H2, W2;
   bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
 };
 struct Remembered {
   Sizes sizes;
-  int8_t tile, WF, WK;   // WF = 0: no entry; tile = -1: no plan fits
+  int state;             // 0: empty, 1: a plan, -1: none fits
+  WindowPlan plan;
 };
 
 bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
   if (tuning_any()) return pick_for_batch(c, N, plan);
-  constexpr int kEntries = 256;
+  constexpr int kEntries = 128;
   thread_local Remembered table[kEntries];
-  const Sizes z = {(int)c.dt, N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp, c.cpt,
-                   c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0};
+  const Sizes z = {(int)c.dt, N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp,
+                   c.cpt, c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0, c.H2, c.W2};
   uint32_t h = 2166136261u;
   for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
     h = (h ^ (uint32_t)reinterpret_cast<const int*>(&z)[i]) * 16777619u;
   Remembered& r = table[(h ^ (h >> 15)) % kEntries];
-  if (r.WF == 0 || !(r.sizes == z)) {
-    const bool ok = pick_for_batch(c, N, plan);
+  if (r.state == 0 || !(r.sizes == z)) {
+    r.state = pick_for_batch(c, N, &r.plan) ? 1 : -1;
     r.sizes = z;
-    r.tile = ok ? (int8_t)plan->tile : (int8_t)-1;
-    r.WF = ok ? (int8_t)plan->p.WF : (int8_t)1;
-    r.WK = ok ? (int8_t)plan->p.WK : (int8_t)1;
-    return ok;
   }
-  return r.tile >= 0 && plan_window(c, N, r.tile, r.WF, r.WK, plan);
+  if (r.state > 0) *plan = r.plan;
+  return r.state > 0;
 }
 
 // Sizes for which this kernel is the faster one.  (The switches that choose among the other
@@ -774,6 +778,11 @@ bool wanted(const Conv16Params& c, int N) {
   if (c.keep || tuning_off("conv_window")) return false;
   const int R = window_rows(c);
   if (R * c.S > kMaxTaps || (c.x2 && c.split % 8 != 0)) return false;
+  const uint64_t es = c.dt == FUPR_F32 ? 4 : 2;
+  for (uint64_t elements : {(uint64_t)N * c.H * c.W * c.xcs, (uint64_t)c.M * c.ycs,
+                            c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 : 0,
+                            c.res ? (uint64_t)N * c.rH * c.rW * c.rcs : 0})
+    if (elements * es >= kOutside) return false;
   if (c.res && c.dt != FUPR_F32 && c.roff % 8 != 0) return false;   // 16-byte shortcut loads
   if (tuning_any()) {
     char text[64];
@@ -830,6 +839,7 @@ static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, hipStr
 bool launch_conv_window(const Conv16Params& c, int N, void* stream, fupr_status* status) {
   WindowPlan plan;
   if (!wanted(c, N) || !plan_for(c, N, &plan)) return false;
+  set_call(c, N, &plan.p);
   *status = dispatch_window(plan, c.dt, reinterpret_cast<hipStream_t>(stream));
   return true;
 }

@@ -82,25 +82,14 @@ __device__ __forceinline__ f32x16 mfma_32x32x16(const uint4& a, const uint4& b, 
 // used: a chain of cache misses of several hundred clocks each at the start of a short kernel.
 template <int BYTES>
 __device__ __forceinline__ void touch_arguments() {
-  static_assert(BYTES > 192 && BYTES <= 384, "four to six lines");
-  const auto args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(BYTES > 256 && BYTES <= 320, "five lines");
   int sink;
   // (the loads have landed before the compiler can give the register to anything else)
-  if constexpr (BYTES > 256) {
-    asm volatile(
-        "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
-        "s_load_dword %0, %1, 192\n\ts_load_dword %0, %1, 256\n\ts_load_dword %0, %1, %2\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&s"(sink)
-        : "s"(args), "i"((BYTES - 1) / 64 * 64));
-  } else {
-    asm volatile(
-        "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
-        "s_load_dword %0, %1, %2\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&s"(sink)
-        : "s"(args), "i"((BYTES - 1) / 64 * 64));
-  }
+  asm volatile(
+      "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
+      "s_load_dword %0, %1, 192\n\ts_load_dword %0, %1, 256\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(sink)
+      : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
 }
 
 // floor(v / d) for 0 <= v < 2^31 as mulhi(v, mul) >> shift with shift =

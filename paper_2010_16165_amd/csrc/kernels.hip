@@ -230,6 +230,12 @@ fupr_status launch_status(const char* what) {
   return FUPR_ERR_LAUNCH;
 }
 
+fupr_status launched(int error, const char* what) {
+  if (error == (int)hipSuccess) return FUPR_OK;
+  (void)launch_status(what);   // (takes the runtime's error away again)
+  return FUPR_ERR_LAUNCH;
+}
+
 namespace {
 
 void set_filters(Conv16Params& p, const PackedLayout& L, fupr_dtype dt) {
@@ -304,20 +310,31 @@ bool prefer_pipe(const Conv16Params& g) {
 
 }  // namespace
 
-const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
-                             bool indexed, bool add, int first_c) {
+namespace {
+// geometry16 of a convolution with a shortcut (add) or of two tensors (first_c > 0)
+Conv16Params geometry_of(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c) {
   Conv16Params g = geometry16(s, dt, N, H, W);
-  if (dt == FUPR_F32) {
-    if (add) g.res = reinterpret_cast<const uint16_t*>(uintptr_t(16));   // (never dereferenced)
-    return conv_window_applies(g, N) ? conv_window_name(g, N) : "conv32_direct";
-  }
   // markers that are never dereferenced stand for the shortcut and the second tensor
   const uint16_t* const marker = reinterpret_cast<const uint16_t*>(uintptr_t(16));
-  if (add && !indexed) g.res = marker;
+  if (add) g.res = marker;
   if (first_c > 0) {
     g.x2 = marker;
     g.split = round_up(first_c, FUPR_CAT_ALIGN) / 8;
     g.xcs = min_c_stride(first_c, dt);
+  }
+  return g;
+}
+}  // namespace
+
+bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c) {
+  return conv_window_applies(geometry_of(s, dt, N, H, W, add, first_c), N);
+}
+
+const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
+                             bool indexed, bool add, int first_c) {
+  Conv16Params g = geometry_of(s, dt, N, H, W, add && !indexed, first_c);
+  if (dt == FUPR_F32) return conv_window_applies(g, N) ? conv_window_name(g, N) : "conv32_direct";
+  if (first_c > 0) {
     if (conv_window_applies(g, N)) return conv_window_name(g, N);
     if (prefer_pipe(g)) return conv1x1_pipe_name(g);
     if (conv1x1_stream_applies(g)) return conv1x1_stream_name(g);

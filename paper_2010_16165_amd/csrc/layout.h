@@ -49,6 +49,8 @@ inline PackedLayout packed_layout(const fupr_conv_shape& s, fupr_dtype dt) {
 // FUPR_OK if the HIP runtime has no pending error, else FUPR_ERR_LAUNCH (the
 // runtime's message goes to stderr when the environment has FUPR_DEBUG set).
 fupr_status launch_status(const char* what);
+// The same from what the launch itself returned (an int: hipError_t), without asking the runtime.
+fupr_status launched(int error, const char* what);
 
 // Launchers (kernels.hip); all arguments already validated.
 struct ConvArgs {
@@ -79,6 +81,9 @@ const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int
 fupr_status conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
                             int32_t x2_stride, const void* packed, const fupr_residual* res,
                             uint32_t flags, const fupr_tensor* y, int plan_N, void* stream);
+// The convolution is one that conv_window.hip takes at this batch size (arguments as for
+// conv_kernel_name).
+bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c);
 // fupr_conv_cat_fused followed by a 1 x 1 convolution of its output, in one launch
 // (what fupr_conv_conv1x1_fused is to fupr_conv_fused); for the model executor.
 fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x1,

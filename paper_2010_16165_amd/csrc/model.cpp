@@ -20,6 +20,11 @@ using namespace fupr;
 
 namespace {
 
+// One kernel launch of the per-operator schedule: `count` consecutive operators.
+struct Launch {
+  int first, count;
+};
+
 struct TensorInfo {
   int C, H, W, cs;   // per image
   int buffer;        // workspace buffer id; -1 = network input, -2 = network output
@@ -35,6 +40,7 @@ struct fupr_model {
   std::vector<fupr_op_desc> ops;
   std::vector<TensorInfo> tensors;        // n_ops + 1
   std::vector<size_t> buffer_elems;       // per image, per workspace buffer
+  std::vector<Launch> launches;           // of the current schedule with no tuning switch set
   int schedule = FUPR_SCHEDULE_AUTO;
   bool resident_ok = false;               // the whole network fits one LDS-resident kernel
   ResParams resident{};                   // x, y, y_cs filled per call
@@ -512,6 +518,7 @@ void plan_resident(fupr_model* m) {
 
 void release_side(fupr_model* m);   // below, with the forked schedule
 bool conv_conv_pair(const fupr_model* m, size_t i);   // below, with the launch list
+void set_launches(fupr_model* m);
 
 // Sizes of the one-kernel schedule's table: the layer entries, then the tap tables.
 size_t resident_layer_bytes(const fupr_model* m) {
@@ -697,6 +704,7 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
     }
   }
   plan_resident(m);
+  set_launches(m);
   *out = m;
   return FUPR_OK;
 }
@@ -705,6 +713,7 @@ extern "C" fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule) 
   if (!m) return FUPR_ERR_NULL;
   if (schedule != FUPR_SCHEDULE_AUTO && schedule != FUPR_SCHEDULE_PER_LAYER) return FUPR_ERR_ARG;
   m->schedule = schedule;
+  set_launches(m);
   return FUPR_OK;
 }
 
@@ -814,11 +823,6 @@ bool use_resident(const fupr_model* m, const fupr_tensor* input, const fupr_tens
   return output->c_stride <= limit;
 }
 
-// One kernel launch of the per-operator schedule: `count` consecutive operators.
-struct Launch {
-  int first, count;
-};
-
 // Operator i is a 16-bit 7 x 7 stem convolution with ReLU whose only reader is
 // the 3 x 3 max-pool right behind it: the two run as one kernel.
 bool stem_pool_pair(const fupr_model* m, size_t i) {
@@ -850,7 +854,7 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
   return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W);
 }
 
-std::vector<Launch> launches_of(const fupr_model* m) {
+std::vector<Launch> list_launches(const fupr_model* m) {
   std::vector<Launch> v;
   for (size_t i = 0; i < m->ops.size();) {
     const int count = (stem_pool_pair(m, i) || conv_conv_pair(m, i)) ? 2 : 1;
@@ -859,6 +863,14 @@ std::vector<Launch> launches_of(const fupr_model* m) {
   }
   return v;
 }
+
+// The list depends on the operators, the schedule and the tuning switches: the model keeps the
+// one without switches (3 us of host time for 52 operators otherwise, on every forward pass).
+std::vector<Launch> launches_of(const fupr_model* m) {
+  return tuning_any() ? list_launches(m) : m->launches;
+}
+
+void set_launches(fupr_model* m) { m->launches = list_launches(m); }
 
 // Sub-batches of the per-operator schedule.  Two sub-batches side by side let one's
 // memory-bound kernels run beside the other's arithmetic and fill launch gaps and tails.
@@ -973,11 +985,21 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
           r.spatial_stride = op.res_spatial_stride;
           r.c_offset = op.res_c_offset;
         }
-        if (op.epilogue & FUPR_FUSE_CAT) {
-          const fupr_tensor x2 = view(op.in2, n0, count);
-          st = conv_cat_conv1x1_fused(&op.conv, &x, &x2, op.in2_spatial_stride, op.packed,
-                                      op.epilogue & ~uint32_t(FUPR_FUSE_CAT), &mid, &second.conv,
-                                      second.packed, second.epilogue, &y, on);
+        const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
+        fupr_tensor x2;
+        if (cat) x2 = view(op.in2, n0, count);
+        const uint32_t flags = op.epilogue & ~uint32_t(FUPR_FUSE_CAT);
+        if (conv_is_small(op.conv, m->dt, N, x.H, x.W, add, cat ? x.C : 0)) {
+          // A batch whose tensors are small: two launches that fill the GPU are faster than one
+          // that walks it (nine images of 193 x 193, 49 x 49 pixels, 47 -> 256 -> 111 channels:
+          // 18 us in one, 12 in two; a launch more costs 1.7).
+          st = conv_fused_part(&op.conv, &x, cat ? &x2 : nullptr, op.in2_spatial_stride, op.packed,
+                               add ? &r : nullptr, flags, &mid, N, on);
+          if (st == FUPR_OK)
+            st = conv_fused_part(&second.conv, &mid, nullptr, 1, second.packed, nullptr, second.epilogue, &y, N, on);
+        } else if (cat) {
+          st = conv_cat_conv1x1_fused(&op.conv, &x, &x2, op.in2_spatial_stride, op.packed, flags, &mid,
+                                      &second.conv, second.packed, second.epilogue, &y, on);
         } else {
           st = fupr_conv_conv1x1_fused(&op.conv, &x, op.packed, add ? &r : nullptr, op.epilogue, &mid,
                                        &second.conv, second.packed, second.epilogue, &y, on);
