@@ -27,7 +27,7 @@ struct Conv16Params {
   // filter j adds into channel keep[j] of y, which already holds the shortcut,
   // and every other channel of y stays as it is.  keep = nullptr otherwise.
   // keep has keep_n ascending entries in 0 .. yC - 1, in device memory.  Only
-  // conv_tiled.hip and conv_patch.hip read these fields.
+  // conv_tiled.hip, conv_patch.hip and conv_window.hip read these fields.
   const int32_t* keep;
   int keep_n, yC;
   // A second input tensor (fupr_conv_cat_fused, 1 x 1 convolutions only): the

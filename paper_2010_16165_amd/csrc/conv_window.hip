@@ -27,7 +27,7 @@
 // Measured, before -> now (us per launch in a replayed graph): 3 x 3, 512 -> 359 at 7 x 7, one
 // image 13.9 -> 5.2; 64 -> 45 at 56 x 56, one image 6.4 -> 3.9; stride 2, 229 -> 117 at 25 x 25 x 9
 // 22.2 -> 5.7; 256 -> 180 at 14 x 14 x 20 12.5 -> 7.8, x 64 19.1 -> 14.3; 163 -> 183 at 14 x 14 x 256
-// 41 -> 29; fc, 2048 -> 1000 on 64 pixels 12.3 -> 4.6.  A kernel that does nothing takes 1.7.
+// 41 -> 29; with listed output channels 359 -> 359 of 512 at 7 x 7 x 20 16.4 -> 10.2; fc, 2048 -> 1000 on 64 pixels 12.3 -> 4.6.  A kernel that does nothing takes 1.7.
 // Single precision runs through the same code on the 16 x 16 x 4 MFMA: a chunk is then 4 channels
 // (16 bytes as well), a step 16 channels in four MFMAs, each of which takes one channel of every
 // lane's chunk.  A CIFAR-size network of 21 layers on 32 images: 410 us (one thread per pixel and
@@ -68,7 +68,9 @@ struct WindowParams {
   const uint16_t* x2;    // kCat: the channels from step split_steps on
   const uint16_t* w;
   const float* bias;
-  const uint16_t* res;
+  // A block's pruned output filters have no shortcut tensor: filter j adds into channel keep[j]
+  // of y (keep_n entries, in 0 .. yC - 1); the workgroup's part of the list lies in LDS at keep_at.
+  union { const uint16_t* res; const int32_t* keep; };
   uint16_t* y;
   uint32_t x_bytes, x2_bytes, w_bytes, res_bytes, y_bytes;
   int H, W, pix;         // input extent; bytes per pixel
@@ -76,8 +78,11 @@ struct WindowParams {
   int P, Q, PQ, M, ycs;
   int R, S, stride, pad;
   int Kp, cpt, nsteps;
-  int split_steps, H2, W2, pix2, stride2;
-  int rH, rW, rcs, rss, roff, relu;
+  union { int split_steps, keep_at; };   // (kCat, kWindow)
+  int H2, W2, pix2, stride2;
+  union { int rH, keep_n; };
+  union { int rW, yC; };
+  int rcs, rss, roff, relu;
   int mgroups, fgroups, total, per_xcd, filter_major;
   int WF, WK;            // waves along the filters, along the reduction (powers of two)
   int log2_WF;
@@ -121,8 +126,9 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 }
 
 // A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
-// wave; G: steps whose pixels are read from LDS together.
-template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES>
+// wave; G: steps whose pixels are read from LDS together.  IX: every filter adds into its listed
+// channel of y (p.keep); without it p.keep is not read.
+template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES, bool IX>
 __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams p) {
   touch_arguments<sizeof(WindowParams)>();
   constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
@@ -283,6 +289,15 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
     }
   }
 
+  // per filter of the workgroup: its channel of y, -1 for one that does not exist or points outside
+  if constexpr (IX) {
+    int* list = reinterpret_cast<int*>(lds + p.keep_at);
+    for (int i = tid; i < p.WF * NT * 16; i += stride64) {
+      const int k = fg * p.WF * NT * 16 + i, c = p.keep[min(k, p.keep_n - 1)];
+      list[i] = k < p.keep_n && (unsigned)c < (unsigned)p.yC ? c : -1;
+    }
+  }
+
   // the first wave of a column starts from the bias, the others from zero
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -406,6 +421,30 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   // The waves of a column share its pairs of filter tiles: wave e % WK finishes pair e, the
   // others hand it their sums through LDS (over the patch, which nobody reads any more).
   constexpr int NP = (NT + 1) / 2;               // pairs of filter tiles; an odd last tile is alone
+  // Listed channels are updated with 2-byte accesses (they have gaps, and the words between two
+  // waves' channels are shared).  What a wave will add to is asked for here, before the exchange
+  // of the partial sums, so that its latency passes meanwhile.
+  i32x4 channel[IX ? NT : 1];
+  uint16_t old[IX ? MT : 1][IX ? NT : 1][4];
+  auto listed_at = [&](int mt, int t, int i) {
+    const int m = m0 + mt * 16 + li, c = channel[t][i];
+    return m < p.M && c >= 0 ? (uint32_t)(m * p.ycs + c) * 2u : kOutside;
+  };
+  if constexpr (IX) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      channel[t] = *reinterpret_cast<const i32x4*>(lds + p.keep_at + ((wf * NT + t) * 16 + g * 4) * 4);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int pr = 0; pr < NP; ++pr)
+        if (((mt * NP + pr) & (p.WK - 1)) == wk)
+#pragma unroll
+          for (int t = 2 * pr; t < (2 * pr + 2 < NT ? 2 * pr + 2 : NT); ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              old[mt][t][i] = __builtin_amdgcn_raw_buffer_load_b16(yr, listed_at(mt, t, i), 0, 0);
+  }
   f32x4* part = reinterpret_cast<f32x4*>(lds);   // [giver][column][tile][lane]
   if (p.WK > 1) {
     __syncthreads();
@@ -469,6 +508,35 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
         continue;
       }
       const bool pair = t + 1 < NT;
+      auto totals = [&](f32x4* s0, f32x4* s1) {
+        // in the order of the waves, whichever of them adds up: the sum does not depend on the tile
+        *s0 = acc[mt][t];
+        *s1 = acc[mt][pair ? t + 1 : t];
+        if (p.WK > 1) {
+          const f32x4 own0 = *s0, own1 = *s1;
+          *s0 = *s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int k = 0; k < p.WK; ++k) {
+            const int from = ((k - wk) & (p.WK - 1)) - 1;          // -1: this wave itself
+            const f32x4* src = part + ((max(from, 0) * p.WF + wf) * TT + mt * NT + t) * 64 + lane;
+            const f32x4 u0 = src[0], u1 = src[pair ? 64 : 0];
+            *s0 += from < 0 ? own0 : u0;
+            *s1 += from < 0 ? own1 : u1;
+          }
+        }
+      };
+      if constexpr (IX) {
+        f32x4 s[2];
+        totals(&s[0], &s[1]);
+#pragma unroll
+        for (int u = 0; u < (pair ? 2 : 1); ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float v = s[u][i] + to_float<BF>(old[mt][t + u][i]);
+            if (p.relu) v = fmaxf(v, 0.f);
+            __builtin_amdgcn_raw_buffer_store_b16(from_float<BF>(v), yr, listed_at(mt, t + u, i), 0, 0);
+          }
+        continue;
+      }
       // after the exchange between 16-lane rows lane (pixel, g) holds channels
       // (g >> 1) * 8 .. + 7 of tile t + (g & 1): 16-byte accesses; a lone tile keeps 8 bytes
       const int k0 = f0 + t * 16 + (pair ? (g & 1) * 16 + (g >> 1) * 8 : g * 4);
@@ -484,19 +552,8 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
           r4[1] = r2[1];
         }
       }
-      // in the order of the waves, whichever of them adds up: the sum does not depend on the tile
-      f32x4 s0 = acc[mt][t], s1 = acc[mt][pair ? t + 1 : t];
-      if (p.WK > 1) {
-        const f32x4 own0 = s0, own1 = s1;
-        s0 = s1 = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < p.WK; ++k) {
-          const int from = ((k - wk) & (p.WK - 1)) - 1;          // -1: this wave itself
-          const f32x4* src = part + ((max(from, 0) * p.WF + wf) * TT + mt * NT + t) * 64 + lane;
-          const f32x4 u0 = src[0], u1 = src[pair ? 64 : 0];
-          s0 += from < 0 ? own0 : u0;
-          s1 += from < 0 ? own1 : u1;
-        }
-      }
+      f32x4 s0, s1;
+      totals(&s0, &s1);
       const uint32_t off = k0 < p.ycs ? yo + (uint32_t)k0 * 2u : kOutside;
       if (pair) {
         uint32_t ra0 = 0, ra1 = 0, rb0 = 0, rb1 = 0;
@@ -535,6 +592,8 @@ constexpr WindowTile kTiles[] = {
 };
 #undef FUPR_NAMES
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+// The tiles compiled for listed channels: what a wave adds to is held in registers.
+constexpr bool listed_tile(const WindowTile& T) { return T.MT * T.NT <= 12; }
 
 struct WindowPlan {
   WindowParams p;
@@ -553,6 +612,9 @@ void set_call(const Conv16Params& c, int N, WindowParams* p) {
   p->ycs = c.ycs; p->relu = c.relu;
   p->rH = c.rH; p->rW = c.rW; p->rcs = c.rcs; p->rss = c.rss; p->roff = c.roff;
   p->res_linear = c.rss == 1 && c.rH == c.P && c.rW == c.Q;
+  if (c.keep) {
+    p->keep = c.keep; p->keep_n = c.keep_n; p->yC = c.yC;
+  }
 }
 
 bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowPlan* out) {
@@ -563,6 +625,7 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   const int mode = c.x2 ? kCat : (R == 1 && c.S == 1 && c.pad == 0 ? kOneTap : kWindow);
   const int es = c.dt == FUPR_F32 ? 4 : 2;
   if (es == 4 && (T.MT * T.NT > 8 || T.NT == 3)) return false;   // (not compiled for single precision)
+  if (c.keep && (mode != kWindow || es != 2 || !listed_tile(T))) return false;
   const uint64_t x_bytes = (uint64_t)N * c.H * c.W * c.xcs * es;
   const uint64_t x2_bytes = c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 * es : 0;
   p.x_bytes = (uint32_t)x_bytes; p.x2_bytes = (uint32_t)x2_bytes; p.w_bytes = c.w_bytes;
@@ -618,6 +681,10 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   out->patch_slots = pixels * (p.slots + p.slots2);
   const size_t reduce = (size_t)(WK - 1) * WF * T.MT * T.NT * 1024;
   out->lds = std::max(end, reduce);
+  if (c.keep) {
+    p.keep_at = (int)round_up_sz(out->lds, 16);
+    out->lds = (size_t)p.keep_at + (size_t)NF * 4;
+  }
   if (out->lds > kLdsLimit) return false;
   p.divPQ = fast_div(p.PQ); p.divQ = fast_div(p.Q); p.divC = fast_div(p.cpt); p.divS = fast_div(p.S);
   p.divSlots = fast_div(p.slots); p.divSlots2 = fast_div(std::max(p.slots2, 1));
@@ -628,13 +695,13 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   return true;
 }
 
-template <int EL, int MODE, int TILE>
+template <int EL, int MODE, int TILE, bool IX>
 fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
   constexpr WindowTile T = kTiles[TILE];
-  if constexpr (EL == FUPR_F32 && (T.MT * T.NT > 8 || T.NT == 3)) {
+  if constexpr ((EL == FUPR_F32 && (T.MT * T.NT > 8 || T.NT == 3)) || (IX && !listed_tile(T))) {
     return FUPR_ERR_LIMIT;
   } else {
-  auto kernel = conv_window_kernel<EL, MODE, T.MT, T.NT, T.D, T.G, T.threads, T.min_waves>;
+  auto kernel = conv_window_kernel<EL, MODE, T.MT, T.NT, T.D, T.G, T.threads, T.min_waves, IX>;
   if (plan.lds > 64 * 1024) {
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
@@ -647,10 +714,10 @@ fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
   }
 }
 
-template <int EL, int MODE>
+template <int EL, int MODE, bool IX = false>
 fupr_status dispatch(const WindowPlan& plan, hipStream_t st) {
   switch (plan.tile) {
-#define FUPR_TILE(i) case i: return launch_as<EL, MODE, i>(plan, st);
+#define FUPR_TILE(i) case i: return launch_as<EL, MODE, i, IX>(plan, st);
     FUPR_TILE(0) FUPR_TILE(1) FUPR_TILE(2) FUPR_TILE(3) FUPR_TILE(4) FUPR_TILE(5)
     FUPR_TILE(6) FUPR_TILE(7) FUPR_TILE(8) FUPR_TILE(9) FUPR_TILE(10) FUPR_TILE(11)
 #undef FUPR_TILE
@@ -745,7 +812,7 @@ bool pick_for_batch(const Conv16Params& c, int N, WindowPlan* plan) {
 // The choice is a function of sizes alone; each thread remembers its answers for the sizes it
 // launched last (about 100 plans are weighed for one, several microseconds of host time).
 struct Sizes {
-  int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two, H2, W2;
+  int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two, H2, W2, listed;
   bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
 };
 struct Remembered {
@@ -759,7 +826,7 @@ bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
   constexpr int kEntries = 128;
   thread_local Remembered table[kEntries];
   const Sizes z = {(int)c.dt, N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp,
-                   c.cpt, c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0, c.H2, c.W2};
+                   c.cpt, c.xcs, c.split, c.xcs2, c.stride2, c.res ? 1 : 0, c.x2 ? 1 : 0, c.H2, c.W2, c.keep ? 1 : 0};
   uint32_t h = 2166136261u;
   for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
     h = (h ^ (uint32_t)reinterpret_cast<const int*>(&z)[i]) * 16777619u;
@@ -775,8 +842,9 @@ bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
 // Sizes for which this kernel is the faster one.  (The switches that choose among the other
 // kernels' tiles ask for those kernels.)
 bool wanted(const Conv16Params& c, int N) {
-  if (c.keep || tuning_off("conv_window")) return false;
+  if (tuning_off("conv_window")) return false;
   const int R = window_rows(c);
+  if (c.keep && (c.dt == FUPR_F32 || (R == 1 && c.S == 1))) return false;
   if (R * c.S > kMaxTaps || (c.x2 && c.split % 8 != 0)) return false;
   const uint64_t es = c.dt == FUPR_F32 ? 4 : 2;
   for (uint64_t elements : {(uint64_t)N * c.H * c.W * c.xcs, (uint64_t)c.M * c.ycs,
@@ -800,6 +868,11 @@ bool wanted(const Conv16Params& c, int N) {
     const double bytes = 2.0 * M * (c.cpt * 8.0 + c.ycs * (c.res ? 2.0 : 1.0));
     return bytes <= 36e6;
   }
+  // Listed channels are updated two bytes at a time here and mostly 16 at a time by the patch
+  // kernel, whose start costs more (this kernel against that one: 180 -> 180 of 256
+  // at 14 x 14 x 12 8.4 against 12.6 us, 90 -> 90 of 128 at 28 x 28 x 20 11.7 against 15.7; 45 -> 45 of
+  // 64 at 56 x 56 x 12, 1.8 million sums, 13.6 against 12.9, x 64 47.8 against 37.7).
+  if (c.keep && M * c.Kp > 1.6e6) return false;
   // Thin reductions over very many pixels: the patch kernel keeps its weights in LDS from tile
   // to tile (51 -> 30 channels at 56 x 56 x 149: 32.2 against 35.6 us; x 64: 21 against 20 us).
   return !(R == 3 && c.S == 3 && c.stride == 1 && c.cpt <= 8 && M > (1 << 18));
@@ -825,7 +898,7 @@ const char* conv_window_name(const Conv16Params& c, int N) {
   return plan_for(c, N, &plan) ? name_of(c, plan.tile) : "conv16t_w";
 }
 
-static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, hipStream_t st) {
+static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, bool listed, hipStream_t st) {
   const bool bf16 = dt == FUPR_BF16;
   if (dt == FUPR_F32)
     return plan.mode == kOneTap ? dispatch<FUPR_F32, kOneTap>(plan, st) : dispatch<FUPR_F32, kWindow>(plan, st);
@@ -833,6 +906,8 @@ static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, hipStr
     return bf16 ? dispatch<FUPR_BF16, kCat>(plan, st) : dispatch<FUPR_F16, kCat>(plan, st);
   if (plan.mode == kOneTap)
     return bf16 ? dispatch<FUPR_BF16, kOneTap>(plan, st) : dispatch<FUPR_F16, kOneTap>(plan, st);
+  if (listed)
+    return bf16 ? dispatch<FUPR_BF16, kWindow, true>(plan, st) : dispatch<FUPR_F16, kWindow, true>(plan, st);
   return bf16 ? dispatch<FUPR_BF16, kWindow>(plan, st) : dispatch<FUPR_F16, kWindow>(plan, st);
 }
 
@@ -840,7 +915,7 @@ bool launch_conv_window(const Conv16Params& c, int N, void* stream, fupr_status*
   WindowPlan plan;
   if (!wanted(c, N) || !plan_for(c, N, &plan)) return false;
   set_call(c, N, &plan.p);
-  *status = dispatch_window(plan, c.dt, reinterpret_cast<hipStream_t>(stream));
+  *status = dispatch_window(plan, c.dt, c.keep != nullptr, reinterpret_cast<hipStream_t>(stream));
   return true;
 }
 

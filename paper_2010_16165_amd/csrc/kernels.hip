@@ -385,7 +385,7 @@ fupr_status launch_conv(const ConvArgs& a, void* stream) {
     return FUPR_ERR_LIMIT;
   }
   if (a.R == 3 && conv_patch_applies(p, a.N)) return launch_conv_patch(p, a.N, a.dt == FUPR_BF16, stream);
-  // the indexed epilogue exists in the 3 x 3 kernel above and in the general one
+  // the indexed epilogue exists in the kernels above and in the general one
   if (a.keep) return launch_conv16_tiled(p, a.dt == FUPR_BF16, stream);
   if (a.R == 1 && prefer_pipe(p)) return launch_conv1x1_pipe(p, a.N, a.dt == FUPR_BF16, stream);
   if (a.R == 1 && conv1x1_stream_applies(p)) return launch_conv1x1_stream(p, a.N, a.dt == FUPR_BF16, stream);
@@ -541,10 +541,9 @@ fupr_status fupr::conv_fused_part(const fupr_conv_shape* shape, const fupr_tenso
   return launch_conv(a, stream);
 }
 
-extern "C" fupr_status fupr_conv_scatter_fused(const fupr_conv_shape* shape, const fupr_tensor* x,
-                                               const void* packed, const int32_t* keep_idx,
-                                               uint32_t epilogue_flags, const fupr_tensor* y,
-                                               void* stream) {
+fupr_status fupr::conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x,
+                                    const void* packed, const int32_t* keep_idx, uint32_t epilogue_flags,
+                                    const fupr_tensor* y, int plan_N, void* stream) {
   if (!shape || !x || !y || !packed || !keep_idx) return FUPR_ERR_NULL;
   if (epilogue_flags & ~uint32_t(FUPR_FUSE_RELU)) return FUPR_ERR_ARG;
   if ((reinterpret_cast<uintptr_t>(keep_idx) & 3u) != 0) return FUPR_ERR_ALIGN;
@@ -559,7 +558,15 @@ extern "C" fupr_status fupr_conv_scatter_fused(const fupr_conv_shape* shape, con
   if (a.dt == FUPR_F32) return FUPR_ERR_DTYPE;
   a.keep = keep_idx;
   a.yC = y->C;
+  a.plan_N = plan_N;
   return launch_conv(a, stream);
+}
+
+extern "C" fupr_status fupr_conv_scatter_fused(const fupr_conv_shape* shape, const fupr_tensor* x,
+                                               const void* packed, const int32_t* keep_idx,
+                                               uint32_t epilogue_flags, const fupr_tensor* y,
+                                               void* stream) {
+  return conv_scatter_part(shape, x, packed, keep_idx, epilogue_flags, y, 0, stream);
 }
 
 extern "C" fupr_status fupr_conv_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x,

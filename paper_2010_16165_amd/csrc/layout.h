@@ -81,6 +81,10 @@ const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int
 fupr_status conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
                             int32_t x2_stride, const void* packed, const fupr_residual* res,
                             uint32_t flags, const fupr_tensor* y, int plan_N, void* stream);
+// fupr_conv_scatter_fused likewise.
+fupr_status conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x, const void* packed,
+                              const int32_t* keep_idx, uint32_t flags, const fupr_tensor* y, int plan_N,
+                              void* stream);
 // The convolution is one that conv_window.hip takes at this batch size (arguments as for
 // conv_kernel_name).
 bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c);

@@ -1009,8 +1009,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
         st = fupr_conv_maxpool_fused(&op.conv, &x, op.packed, pool.conv.R, pool.conv.stride,
                                      pool.conv.pad, &y, on);
       } else if (op.kind == FUPR_OP_CONV && (op.epilogue & FUPR_FUSE_SCATTER)) {
-        st = fupr_conv_scatter_fused(&op.conv, &x, op.packed, op.keep_idx,
-                                     op.epilogue & FUPR_FUSE_RELU, &y, on);
+        st = conv_scatter_part(&op.conv, &x, op.packed, op.keep_idx, op.epilogue & FUPR_FUSE_RELU, &y, N, on);
       } else if (op.kind == FUPR_OP_CONV) {
         fupr_residual r;
         const bool add = op.res >= 0;

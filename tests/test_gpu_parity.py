@@ -1309,6 +1309,21 @@ def test_conv_scatter_site(fx, case, dtype):
     assert err <= TOL[dtype], (name, dtype, err)
 
 
+# Listed channels through the kernel with weights straight into registers, every tile it is
+# compiled for and the waves along the filters, the reduction and both; "" is the other kernels.
+@pytest.mark.parametrize("forced", [""] + [f"{t}x{w}" for t in range(8) for w in ("1x4", "2x2", "4x1")])
+def test_conv_scatter_every_kernel(fx, forced):
+    B, network, torch = fx
+    B.fupr_tuning_set("window_tile" if forced else "conv_window", forced or "0")
+    try:
+        for case in SCATTER_CASES[1:10] if forced else SCATTER_CASES:
+            for dtype in ("bf16", "f16"):
+                test_conv_scatter_site(fx, case, dtype)
+    finally:
+        B.fupr_tuning_set("window_tile", None)
+        B.fupr_tuning_set("conv_window", None)
+
+
 def test_conv_scatter_random_shapes(fx):
     """Seeded random shapes and index lists (clustered and spread, few and many
     filter groups, ragged pixel counts): the chunk ownership of the 3 x 3 kernel's
