@@ -742,6 +742,38 @@ def test_two_1x1_convolutions_rejected_when_not_a_pair(fx):
     assert e.value.status == B.ERR_LIMIT
 
 
+# Strips of 7 pool columns and of as many pool rows as the batch allows (one for a single image,
+# more for many): ends inside a strip, one pool row or column, an odd number of convolution rows.
+@pytest.mark.parametrize("n,h,w", [(1, 97, 61), (1, 7, 7), (2, 224, 29), (5, 193, 193), (64, 131, 57),
+                                   (300, 30, 33), (1200, 29, 27), (17, 3, 230)])
+def test_stem_maxpool_strips_match_two_kernels(fx, n, h, w):
+    B, network, torch = fx
+    print(f"stem {n} x {h} x {w}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(h * 1000 + w)
+    rng = np.random.default_rng(n)
+    wt = (rng.standard_normal((64, 3, 7, 7)) * 0.1).astype(np.float32)
+    sh = B.shape_of(wt, 2, 3)
+    packed = B.upload_blob(B.fupr_pack(sh, wt, rng.standard_normal(64).astype(np.float32), B.BF16))
+    x = B.DeviceTensor.empty(n, h, w, 3, B.BF16)
+    x.data.zero_()
+    x.data[..., :3] = torch.randn((n, h, w, 3), generator=gen, device="cuda")
+    ch, cw = (h - 1) // 2 + 1, (w - 1) // 2 + 1
+    p, q = (ch - 1) // 2 + 1, (cw - 1) // 2 + 1
+    conv, two, one = (B.DeviceTensor.empty(n, a, b, 64, B.BF16) for a, b in ((ch, cw), (p, q), (p, q)))
+    one.data.fill_(7.0)
+    B.fupr_conv_fused(sh, x, packed, None, B.FUSE_RELU, conv)
+    B.fupr_maxpool(conv, 3, 2, 1, two)
+    B.fupr_conv_maxpool_fused(sh, x, packed, 3, 2, 1, one)
+    torch.cuda.synchronize()
+    # the sums run over the same products in another order: a rounding may fall the other way, by
+    # one unit in the last place of bf16 (2^-7) of the value, or of the terms where they cancel
+    a, b = one.data.float(), two.data.float()
+    assert torch.equal(one.data == 0, one.data <= 0)
+    diff = (a - b).abs()
+    assert float((diff / (b.abs() + 1.0)).max()) <= 2.0 ** -7
+    assert float((diff > 0).float().mean()) <= 0.01
+
+
 def test_stem_maxpool_fused_rejects_other_shapes(fx):
     B, network, torch = fx
     wt = np.zeros((32, 3, 7, 7), np.float32)
