@@ -75,6 +75,12 @@ def group_of_device_kernel(name):
                     (num(1), num(2)))
     if fn == "conv16_tiled_kernel":
         return f"conv16t_{num(1) * 64}x{num(2) * 16}"
+    if fn == "conv_window_kernel":   # <type, one tap / window / two tensors, pixel tiles, filter tiles, ...>
+        tile = f"_w{num(2) * 16}x{num(3) * 16}"
+        if num(0) == 0:
+            return "conv32" + tile
+        # (a 3 x 3 window and any other one are one instantiation under two launch-list names)
+        return "conv1x1p" + tile if num(1) != 1 else None
     return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)
