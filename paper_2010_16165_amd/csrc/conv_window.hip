@@ -866,6 +866,11 @@ bool wanted(const Conv16Params& c, int N) {
     // against 26.7 us; 1024 -> 204 at 14 x 14 x 87, 42 MB: 19.5 against 23.0 us); below they spend
     // most of their time starting up (32 -> 256 at 56 x 56 x 10, 34 MB: 10.6 against 8.6 us).
     const double bytes = 2.0 * M * (c.cpt * 8.0 + c.ycs * (c.res ? 2.0 : 1.0));
+    // Reductions so deep that no 64-pixel tile fits LDS read all weights for every 32 pixels: from
+    // 3.2 thousand million products on the pipelined kernel's large tiles are faster (two tensors,
+    // 1280 -> 2048 channels, on 1568 pixels 25.7 against 20.6 us, on 3136 60.5 against 28.0; on
+    // 1176 pixels, 3.1 thousand million, 18.2 against 20.2).
+    if (c.cpt > 150 && M * (c.cpt * 8.0) * c.Kp > 3.2e9 && conv1x1_pipe_applies(c)) return false;
     return bytes <= 36e6;
   }
   // Listed channels are updated two bytes at a time here and mostly 16 at a time by the patch
@@ -874,8 +879,14 @@ bool wanted(const Conv16Params& c, int N) {
   // 64 at 56 x 56 x 12, 1.8 million sums, 13.6 against 12.9, x 64 47.8 against 37.7).
   if (c.keep && M * c.Kp > 1.6e6) return false;
   // Thin reductions over very many pixels: the patch kernel keeps its weights in LDS from tile
-  // to tile (51 -> 30 channels at 56 x 56 x 149: 32.2 against 35.6 us; x 64: 21 against 20 us).
-  return !(R == 3 && c.S == 3 && c.stride == 1 && c.cpt <= 8 && M > (1 << 18));
+  // to tile (51 -> 30 channels at 56 x 56 x 149: 32.2 against 35.6 us; x 64: 22.3 against 23.1 the
+  // other way).  With 33 to 64 channels that pays from some 140 000 pixels on (51 -> 45 at 56 x 56 x
+  // 64 27.7 against 25.5 us, x 48 23.0 against 22.6, x 32 17.7 against 18.6), with at most 32
+  // channels and 32 filters from 90 000 on (32 -> 32 x 64 18.9 against 16.5, x 32 13.5 against
+  // 12.7, x 24 10.5 against 12.1); measured on images of that width, and padded as that kernel wants it.
+  const bool measured = c.Q <= 64 && c.pad == 1 && c.cpt >= 2 && !c.keep;
+  const double many = measured && c.cpt > 4 ? 140e3 : measured && c.Kp <= 32 ? 90e3 : 262144;
+  return !(R == 3 && c.S == 3 && c.stride == 1 && c.cpt <= 8 && M > many);
 }
 
 // What the launch list calls it: the family of kernels the layer belongs to, and the tile.

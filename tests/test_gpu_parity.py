@@ -348,6 +348,26 @@ def test_every_window_tile_forced(fx, tile, waves):
     assert ran >= 5 if (wk - 1) * wf * mt * nt <= 160 else ran == 0
 
 
+# Both sides of the lines behind which the kernels with larger tiles take over: thin 3 x 3
+# layers of many pixels, 1 x 1 reductions too deep for a 64-pixel tile in LDS.
+WINDOW_EDGES = [
+    (("edge 3x3 C32 K32 1500x60", 1, 32, 1500, 60, 32, 3, 1, 1, None, True), True),
+    (("edge 3x3 C32 K32 1501x60", 1, 32, 1501, 60, 32, 3, 1, 1, "identity", True), False),
+    (("edge 3x3 C32 K32 1501x62 no padding", 1, 32, 1501, 62, 32, 3, 1, 0, None, True), True),
+    (("edge 3x3 C32 K32 300x301", 1, 32, 300, 301, 32, 3, 1, 1, None, True), True),
+    (("edge 3x3 C33 K17 2333x60", 1, 33, 2333, 60, 17, 3, 1, 1, None, True), True),
+    (("edge 3x3 C33 K17 2334x60", 1, 33, 2334, 60, 17, 3, 1, 1, None, False), False),
+    (("edge 1x1 C1208 K2048 1293", 1, 1208, 1, 1293, 2048, 1, 1, 0, None, True), True),
+    (("edge 1x1 C1208 K2048 1294", 1, 1208, 1, 1294, 2048, 1, 1, 0, None, True), False),
+]
+
+
+@pytest.mark.parametrize("case,window", WINDOW_EDGES, ids=[c[0][0] for c in WINDOW_EDGES])
+def test_edges_of_the_window_kernels_range(fx, case, window):
+    assert ("_w" in kernel_of(fx[0], "bf16", case)) == window
+    conv_site(fx, case, "bf16")
+
+
 @pytest.mark.parametrize("tile", [4, 5, 12], ids=["128x32", "64x64", "64x32"])
 def test_small_tiles_with_several_units_in_flight(fx, tile):
     """The small tiles of the 3 x 3 kernel load up to three units ahead through a ring
