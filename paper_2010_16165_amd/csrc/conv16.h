@@ -69,8 +69,8 @@ bool conv1x1_pipe_applies(const Conv16Params& geometry);
 const char* conv1x1_pipe_name(const Conv16Params& geometry);
 fupr_status launch_conv1x1_pipe(const Conv16Params& p, int N, bool bf16, void* stream);
 
-// conv_window.hip: any window of at most 25 taps, one or two input tensors, with the tile's
-// pixels in LDS and the weights straight from L2 into registers.  Geometry fields decide whether
+// conv_window.hip: any window of at most 25 taps padded by at most half its shorter side, one or two
+// input tensors, with the tile's pixels in LDS and the weights straight from L2 into registers.  Geometry fields decide whether
 // it takes a layer (single precision included); launch_conv_window returns false, and launches nothing, when it does not.
 bool conv_window_applies(const Conv16Params& geometry, int N);
 const char* conv_window_name(const Conv16Params& geometry, int N);

@@ -47,6 +47,7 @@
 #include "fupr.h"
 #include "layout.h"
 #include "tuning.h"
+#include "window_patch.h"
 
 namespace fupr {
 namespace {
@@ -190,13 +191,13 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   };
   int first = m0, patch_pixels = 1 + BM;
   if constexpr (MODE == kWindow) {
-    auto window_origin = [&](int m) {
+    auto origin_of = [&](int m) {
       int n, pp, qq;
       split_pixel(m, &n, &pp, &qq);
-      return (n * p.H + pp * p.stride - p.pad) * p.W + qq * p.stride - p.pad;
+      return window_origin(n, pp, qq, p.H, p.W, p.stride, p.pad);
     };
-    first = window_origin(m0);
-    const int last = window_origin(min(m0 + BM, p.M) - 1) + (p.R - 1) * p.W + p.S - 1;
+    first = origin_of(m0);
+    const int last = origin_of(min(m0 + BM, p.M) - 1) + window_reach(p.R, p.S, p.W);
     patch_pixels = 1 + last - first + 1;
   }
   const int stride64 = waves * 64;
@@ -655,12 +656,8 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   };
   int pixels = 1 + BM;
   if (mode == kWindow) {
-    // the largest distance between the window origins of a tile's first and last pixel
-    const int rows = (BM - 1 + c.Q - 1) / c.Q;               // row ends crossed, at most
-    const int images = (BM - 1 + c.PQ - 1) / c.PQ;           // image ends crossed, at most
-    const int64_t span = (int64_t)(BM - 1) * c.stride + (int64_t)rows * (c.stride * c.W - c.stride * (c.Q - 1)) +
-                         (int64_t)images * (std::max(0, c.H - c.stride * (c.P - 1)) * c.W);
-    pixels = (int)std::min<int64_t>(1 + span + (R - 1) * c.W + c.S, 1 << 20);
+    if (!window_runs_are_whole(R, c.S, c.pad)) return false;
+    pixels = (int)std::min<int64_t>(most_run_pixels(BM, R, c.S, c.stride, c.H, c.W, c.P, c.Q), 1 << 20);
     p.table_bytes = (int)(p.nsteps + (T.D + 2 * T.G + 2) * WK) * 32;
   }
   p.live = c.x2 ? std::min(c.split, c.xcs / 8) : c.cpt;

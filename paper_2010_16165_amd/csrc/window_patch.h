@@ -1,0 +1,34 @@
+// Internal: the run of input pixels that a tile of output pixels needs (conv_window.hip).  The
+// planner reserves LDS by it and the kernel fills LDS by it, from the same functions.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace fupr {
+
+// The pixels of a batch, rows and images one behind the other, are numbered as one row.  Tap (r, s)
+// of the output pixel at (n, pp, qq) reads number window_origin + r * W + s (where it is inside the image).
+constexpr int window_origin(int n, int pp, int qq, int H, int W, int stride, int pad) {
+  return (n * H + pp * stride - pad) * W + qq * stride - pad;
+}
+
+// From a window's origin to its last tap.
+constexpr int window_reach(int R, int S, int W) { return (R - 1) * W + S - 1; }
+
+// A tile's run goes from the origin of its first output pixel to the last tap of its last one.  That
+// holds every tap inside an image only while windows follow each other in it: with a padding beyond
+// half a window the first window of a row (or image) can begin before the last one of the row
+// (image) above, and with one beyond the window a run can begin behind the pixels it is for.
+constexpr bool window_runs_are_whole(int R, int S, int pad) { return 2 * pad <= (R < S ? R : S); }
+
+// The most pixels a run of BM output pixels takes, the pixel of zeros before it included.  Needs
+// window_runs_are_whole; no term is negative then, since stride * (Q - 1) <= W + 2 pad - S <= W.
+constexpr int64_t most_run_pixels(int BM, int R, int S, int stride, int H, int W, int P, int Q) {
+  const int64_t rows = (BM - 1 + Q - 1) / Q;                              // row ends crossed, at most
+  const int64_t images = (BM - 1 + (int64_t)P * Q - 1) / ((int64_t)P * Q);   // image ends crossed, at most
+  const int64_t row_end = std::max<int64_t>(0, (int64_t)stride * W - (int64_t)stride * (Q - 1));
+  const int64_t image_end = std::max<int64_t>(0, H - (int64_t)stride * (P - 1)) * W;
+  return 1 + (int64_t)(BM - 1) * stride + rows * row_end + images * image_end + window_reach(R, S, W) + 1;
+}
+
+}  // namespace fupr

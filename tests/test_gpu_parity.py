@@ -117,20 +117,21 @@ def test_conv_site(fx, case, dtype):
 
 def conv_site(fx, case, dtype):
     """One convolution with merged batch norm, shortcut and ReLU through
-    fupr_conv_fused against the oracle's conv, BN, add, ReLU."""
+    fupr_conv_fused against the oracle's conv, BN, add, ReLU.  The window's side, or both sides."""
     B, network, torch = fx
-    name, n, c, h, w, k, r, stride, pad, rkind, relu = case
+    name, n, c, h, w, k, window, stride, pad, rkind, relu = case
+    r, s = window if isinstance(window, tuple) else (window, window)
     rng = np.random.default_rng(zlib.crc32(name.encode()))
     print(f"case={name} dtype={dtype}", flush=True)
     x = rng.standard_normal((n, c, h, w)).astype(np.float32)
-    wt = (rng.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float32)
+    wt = (rng.standard_normal((k, c, r, s)) * np.sqrt(2.0 / (c * r * s))).astype(np.float32)
     bn = {"gamma": rng.uniform(0.5, 1.5, k).astype(np.float32),
           "beta": (rng.standard_normal(k) * 0.1).astype(np.float32),
           "mean": (rng.standard_normal(k) * 0.1).astype(np.float32),
           "var": rng.uniform(0.5, 1.5, k).astype(np.float32), "eps": 1e-5}
     dt = B.DTYPES[dtype]
     p = (h + 2 * pad - r) // stride + 1
-    q = (w + 2 * pad - r) // stride + 1
+    q = (w + 2 * pad - s) // stride + 1
 
     xr = round_to(x, dtype, torch)
     ref = orc.batchnorm(orc.conv2d(xr, wt, stride, pad), bn)
@@ -167,8 +168,9 @@ def conv_site(fx, case, dtype):
 def kernel_of(B, dtype, case):
     """Name of the kernel fupr_conv_fused launches for a case under the current tuning
     switches, from a one-operator model on the host (its parameter address is never read)."""
-    name, n, c, h, w, k, r, stride, pad, rkind, relu = case
-    op = B.OpDesc(B.OP_CONV, 0, -1, B.conv_shape(k, c, r, r, stride, pad), 0x1000, 0, 1, 0)
+    name, n, c, h, w, k, window, stride, pad, rkind, relu = case
+    r, s = window if isinstance(window, tuple) else (window, window)
+    op = B.OpDesc(B.OP_CONV, 0, -1, B.conv_shape(k, c, r, s, stride, pad), 0x1000, 0, 1, 0)
     return B.Model(B.DTYPES[dtype], (c, h, w), [op], None).op_stats(n, 0)["kernel"]
 
 
@@ -346,6 +348,31 @@ def test_every_window_tile_forced(fx, tile, waves):
     mt, nt = (int(v) // 16 for v in WINDOW_TILES[tile].split("x"))
     wf, wk = (int(v) for v in waves.split("x"))
     assert ran >= 5 if (wk - 1) * wf * mt * nt <= 160 else ran == 0
+
+
+# Padding beyond half a window (some of it beyond the window, or beyond its shorter side only), on
+# images narrower and wider than a tile, and the largest padding that the kernel above still takes.
+PADDING_CASES = [
+    (("padded 3x3 p2 C64 K24 14x14", 1, 64, 14, 14, 24, 3, 1, 2, None, True), False),
+    (("padded 3x3 p2 C32 K16 5x42 x2 +id", 2, 32, 5, 42, 16, 3, 1, 2, "identity", True), False),
+    (("padded 3x3 p3 C40 K20 14x14 x2", 2, 40, 14, 14, 20, 3, 1, 3, None, False), False),
+    (("padded 3x3 p2 s2 C40 K20 9x11 x3", 3, 40, 9, 11, 20, 3, 2, 2, None, False), False),
+    (("padded 1x1 p1 C72 K40 14x14", 1, 72, 14, 14, 40, 1, 1, 1, None, False), False),
+    (("padded 1x1 p2 s2 C72 K40 7x9 x3", 3, 72, 7, 9, 40, 1, 2, 2, None, False), False),
+    (("padded 5x5 p4 C32 K24 28x28", 1, 32, 28, 28, 24, 5, 1, 4, None, True), False),
+    (("padded 1x3 p1 C64 K32 8x12 x3", 3, 64, 8, 12, 32, (1, 3), 1, 1, None, True), False),
+    (("padded 5x1 p2 C64 K32 8x12 x3", 3, 64, 8, 12, 32, (5, 1), 1, 2, None, True), False),
+    (("padded 3x5 p1 C24 K32 8x12 x3 +id", 3, 24, 8, 12, 32, (3, 5), 1, 1, "identity", True), True),
+    (("padded 2x2 p1 C24 K32 9x12 x3", 3, 24, 9, 12, 32, 2, 1, 1, None, True), True),
+    (("padded 4x4 p2 s2 C24 K32 9x12 x3", 3, 24, 9, 12, 32, 4, 2, 2, None, True), True),
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("case,window", PADDING_CASES, ids=[c[0][0] for c in PADDING_CASES])
+def test_paddings_of_every_size(fx, case, window, dtype):
+    assert ("_w" in kernel_of(fx[0], dtype, case)) == window
+    conv_site(fx, case, dtype)
 
 
 # Both sides of the lines behind which the kernels with larger tiles take over: thin 3 x 3

@@ -4,6 +4,7 @@ No kernel is launched here."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -492,6 +493,39 @@ def test_kernel_selection_per_layer_class():
     assert first["flops"] == conv["flops"] and first["bytes"] == conv["bytes"] + pool["bytes"] - 2 * mid
     m.set_schedule(B.SCHEDULE_PER_LAYER)
     assert m.num_launches == m.num_ops and m.launch_stats(64, 0)["kernel"].startswith("conv16t_")
+
+
+def conv_name(dtype, n, c, h, w, k, r, s, stride, pad):
+    """The kernel one convolution operator launches at a batch of n images."""
+    op = B.OpDesc(B.OP_CONV, 0, -1, B.conv_shape(k, c, r, s, stride, pad), 0x1000, 0, 1, 0)
+    return B.Model(dtype, (c, h, w), [op], None).op_stats(n, 0)["kernel"]
+
+
+# padding beyond half a window on its shorter side, with the sides that a window needs for it
+WIDE_PADDING = [(1, 128, 14, 14, 64, 3, 3, 1, 2), (1, 256, 56, 56, 64, 3, 3, 1, 2), (2, 64, 14, 14, 64, 3, 3, 1, 3),
+                (1, 64, 30, 42, 16, 3, 3, 1, 2), (1, 256, 14, 14, 64, 1, 1, 1, 1), (1, 256, 14, 14, 64, 1, 1, 2, 2),
+                (1, 128, 28, 28, 64, 5, 5, 1, 4), (3, 64, 8, 12, 32, 1, 3, 1, 1), (3, 64, 8, 12, 32, 5, 1, 1, 2)]
+
+
+@pytest.mark.parametrize("dtype", [B.BF16, B.F16, B.F32])
+def test_paddings_over_half_a_window_stay_off_the_window_kernel(dtype):
+    """That kernel fills LDS with one run of input pixels per tile, which holds every tap only up to
+    half a window of padding: other layers go to the kernels that look every tap up by itself."""
+    for case in WIDE_PADDING:
+        assert "_w" not in conv_name(dtype, *case), case
+    for case in [(1, 64, 14, 14, 64, 3, 3, 1, 1), (1, 64, 14, 14, 64, 2, 2, 1, 1), (1, 64, 14, 14, 64, 5, 5, 1, 2),
+                 (1, 64, 14, 14, 64, 3, 5, 1, 1), (1, 64, 14, 14, 64, 1, 3, 1, 0)]:
+        assert "_w" in conv_name(dtype, *case), case
+
+
+def test_window_runs_hold_every_tap_and_fit_their_plan(tmp_path):
+    """The functions the planner and the kernel share, walked tile by tile on the host."""
+    exe = str(tmp_path / "window_runs")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2010_16165_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "window_runs.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    assert int(out.stdout) > 100000
 
 
 def test_model_create_errors():
