@@ -40,7 +40,8 @@ struct fupr_model {
   std::vector<fupr_op_desc> ops;
   std::vector<TensorInfo> tensors;        // n_ops + 1
   std::vector<size_t> buffer_elems;       // per image, per workspace buffer
-  std::vector<Launch> launches;           // of the current schedule with no tuning switch set
+  std::vector<char> pair_planned;         // per operator: the workspace lets it run together with the next one
+  std::vector<Launch> launches[2];        // per schedule, with no tuning switch set
   int schedule = FUPR_SCHEDULE_AUTO;
   bool resident_ok = false;               // the whole network fits one LDS-resident kernel
   ResParams resident{};                   // x, y, y_cs filled per call
@@ -518,7 +519,7 @@ void plan_resident(fupr_model* m) {
 
 void release_side(fupr_model* m);   // below, with the forked schedule
 bool conv_conv_pair(const fupr_model* m, size_t i);   // below, with the launch list
-void set_launches(fupr_model* m);
+std::vector<Launch> list_launches(const fupr_model* m, int schedule);
 
 // Sizes of the one-kernel schedule's table: the layer entries, then the tap tables.
 size_t resident_layer_bytes(const fupr_model* m) {
@@ -650,9 +651,16 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
     }
   }
   // two convolutions that may run as one kernel: what the first reads must
-  // outlive the second, whose output is written while the first still reads
+  // outlive the second, whose output is written while the first still reads.
+  // Which ones may does not depend on the switches of the moment: they can change
+  // between here and a forward pass.
+  m->pair_planned.assign(n, 0);
+  {
+    const WithoutTuning no_switches;
+    for (int i = 0; i + 1 < n; ++i) m->pair_planned[i] = conv_conv_pair(m, (size_t)i);
+  }
   for (int i = 0; i + 1 < n; ++i) {
-    if (!conv_conv_pair(m, (size_t)i)) continue;
+    if (!m->pair_planned[i]) continue;
     TensorInfo& tin = m->tensors[m->ops[i].in];
     tin.last_use = std::max(tin.last_use, i + 1);
     if (m->ops[i].res >= 0) {
@@ -704,7 +712,9 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
     }
   }
   plan_resident(m);
-  set_launches(m);
+  const WithoutTuning no_switches;
+  for (int schedule : {FUPR_SCHEDULE_AUTO, FUPR_SCHEDULE_PER_LAYER})
+    m->launches[schedule] = list_launches(m, schedule);
   *out = m;
   return FUPR_OK;
 }
@@ -713,7 +723,6 @@ extern "C" fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule) 
   if (!m) return FUPR_ERR_NULL;
   if (schedule != FUPR_SCHEDULE_AUTO && schedule != FUPR_SCHEDULE_PER_LAYER) return FUPR_ERR_ARG;
   m->schedule = schedule;
-  set_launches(m);
   return FUPR_OK;
 }
 
@@ -826,7 +835,7 @@ bool use_resident(const fupr_model* m, const fupr_tensor* input, const fupr_tens
 // Operator i is a 16-bit 7 x 7 stem convolution with ReLU whose only reader is
 // the 3 x 3 max-pool right behind it: the two run as one kernel.
 bool stem_pool_pair(const fupr_model* m, size_t i) {
-  if (m->schedule != FUPR_SCHEDULE_AUTO || i + 1 >= m->ops.size()) return false;
+  if (i + 1 >= m->ops.size()) return false;
   const fupr_op_desc& c = m->ops[i];
   const fupr_op_desc& q = m->ops[i + 1];
   if (c.kind != FUPR_OP_CONV || c.res >= 0 || c.epilogue != FUPR_FUSE_RELU) return false;
@@ -842,7 +851,7 @@ bool stem_pool_pair(const fupr_model* m, size_t i) {
 // block's last convolution and the next block's first): one kernel computes
 // both, the second from the first one's registers.
 bool conv_conv_pair(const fupr_model* m, size_t i) {
-  if (m->schedule != FUPR_SCHEDULE_AUTO || i + 1 >= m->ops.size()) return false;
+  if (i + 1 >= m->ops.size()) return false;
   const fupr_op_desc& a = m->ops[i];
   const fupr_op_desc& b = m->ops[i + 1];
   if (a.kind != FUPR_OP_CONV || b.kind != FUPR_OP_CONV) return false;
@@ -854,23 +863,23 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
   return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W);
 }
 
-std::vector<Launch> list_launches(const fupr_model* m) {
+std::vector<Launch> list_launches(const fupr_model* m, int schedule) {
   std::vector<Launch> v;
   for (size_t i = 0; i < m->ops.size();) {
-    const int count = (stem_pool_pair(m, i) || conv_conv_pair(m, i)) ? 2 : 1;
+    const bool pair = schedule == FUPR_SCHEDULE_AUTO &&
+                      (stem_pool_pair(m, i) || (m->pair_planned[i] && conv_conv_pair(m, i)));
+    const int count = pair ? 2 : 1;
     v.push_back(Launch{(int)i, count});
     i += count;
   }
   return v;
 }
 
-// The list depends on the operators, the schedule and the tuning switches: the model keeps the
-// one without switches (3 us of host time for 52 operators otherwise, on every forward pass).
+// The list depends on the operators, the schedule and the tuning switches: the model keeps those
+// without switches (3 us of host time for 52 operators otherwise, on every forward pass).
 std::vector<Launch> launches_of(const fupr_model* m) {
-  return tuning_any() ? list_launches(m) : m->launches;
+  return tuning_any() ? list_launches(m, m->schedule) : m->launches[m->schedule];
 }
-
-void set_launches(fupr_model* m) { m->launches = list_launches(m); }
 
 // Sub-batches of the per-operator schedule.  Two sub-batches side by side let one's
 // memory-bound kernels run beside the other's arithmetic and fill launch gaps and tails.

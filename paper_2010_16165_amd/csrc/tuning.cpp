@@ -44,6 +44,7 @@ Switch g_switches[] = {
 std::mutex g_mutex;
 std::once_flag g_env_once;
 std::atomic<int> g_with_value{0};   // switches that have a value: launchers look at this first
+thread_local int t_without = 0;     // WithoutTuning objects alive in this thread
 
 void read_environment() {
   for (Switch& s : g_switches) {
@@ -69,7 +70,11 @@ Switch* find(const char* name) {
 
 }  // namespace
 
+WithoutTuning::WithoutTuning() { ++t_without; }
+WithoutTuning::~WithoutTuning() { --t_without; }
+
 bool tuning_any() {
+  if (t_without > 0) return false;
   std::call_once(g_env_once, read_environment);
   return g_with_value.load(std::memory_order_acquire) != 0;
 }

@@ -16,4 +16,13 @@ bool tuning_text(const char* name, char* out, size_t n);
 // True when the switch is set to a value that starts with '0'.
 bool tuning_off(const char* name);
 
+// While one of these lives, its thread sees every switch unset.
+class WithoutTuning {
+ public:
+  WithoutTuning();
+  ~WithoutTuning();
+  WithoutTuning(const WithoutTuning&) = delete;
+  WithoutTuning& operator=(const WithoutTuning&) = delete;
+};
+
 }  // namespace fupr

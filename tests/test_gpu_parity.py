@@ -1324,6 +1324,46 @@ def test_sub_batches_on_forked_streams_give_identical_results(fx):
         B.fupr_tuning_set("split", None)
 
 
+def test_sub_batches_with_no_switch_set(fx):
+    """The same without any tuning switch, as a caller runs it: the launch list and the kernel choices
+    that are kept from call to call, eagerly, from another thread, and from a replayed graph."""
+    import threading
+    B, network, torch = fx
+    model = synth.make_imagenet_bottleneck_resnet(33, "f16", (2, 1, 1, 1), 300, size=32, classes=9)
+    n = 201                                     # from 192 images on there are two sub-batches
+    x = synth.make_input(33, n, model["in_shape"])
+    m, _ = network.build(network.optimise(model))
+    xd = B.DeviceTensor.from_nchw(x, B.F16)
+    out, ws = m.alloc(n)
+    B.fupr_tuning_set("split", 1)
+    try:
+        m.fupr_forward(xd, out, ws)
+        torch.cuda.synchronize()
+    finally:
+        B.fupr_tuning_set("split", None)
+    whole = out.data.clone()
+    for what in ("first", "again", "thread"):
+        print(f"sub-batches, {what}", flush=True)
+        out.data.zero_()
+        torch.cuda.synchronize()
+        if what == "thread":
+            t = threading.Thread(target=lambda: m.fupr_forward(xd, out, ws))
+            t.start()
+            t.join()
+        else:
+            m.fupr_forward(xd, out, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(whole, out.data)
+    s = torch.cuda.Stream()
+    g = m.fupr_graph_create(xd, out, ws, B.C.c_void_p(s.cuda_stream))
+    for _ in range(3):
+        out.data.zero_()
+        torch.cuda.synchronize()
+        m.fupr_graph_launch(g, B.C.c_void_p(s.cuda_stream))
+        s.synchronize()
+        assert torch.equal(whole, out.data)
+
+
 # ---- a block's pruned output filters: indexed update of the full-width stream --------------
 
 SCATTER_CASES = [

@@ -578,6 +578,43 @@ def test_largest_workload_pairs_its_first_stage_output_with_the_next_convolution
         B.fupr_tuning_set("pair_filters", None)
 
 
+def launch_list(m, batch):
+    return [(s["first_op"], s["n_ops"], s["kernel"]) for s in (m.launch_stats(batch, i) for i in range(m.num_launches))]
+
+
+@pytest.mark.parametrize("switch,value", [("conv1x1_fuse", 0), ("conv1x1_stream", 0), ("pair_filters", 16), ("split", 2)]
+                         + [("stream_tile", t) for t in range(6)])
+def test_switches_at_creation_leave_nothing_behind(switch, value):
+    """A model created while a switch is set has, once the switch is cleared, the launches and the
+    workspace of any other: pairs are planned by the layers alone.  While one is set, only pairs whose
+    tensors the workspace keeps apart are launched together."""
+    ops = lambda: fake_ops([
+        (B.OP_CONV, 0, -1, 64, 8, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 1, -1, 256, 64, 1, 1, 0, B.FUSE_RELU, 1),                  # a pair
+        (B.OP_CONV, 2, -1, 32, 256, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 3, -1, 100, 32, 1, 1, 0, B.FUSE_RELU, 1),                  # a pair only if its tile is forced
+        (B.OP_CONV, 4, -1, 40, 100, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 5, -1, 10, 40, 3, 1, 1, B.FUSE_RELU, 1),
+    ])
+    plain = B.Model(B.BF16, (8, 56, 56), ops(), None)
+    want, want_ws = launch_list(plain, 64), plain.workspace_bytes(64)
+    assert plain.num_launches == plain.num_ops - 1
+    B.fupr_tuning_set(switch, value)
+    try:
+        other = B.Model(B.BF16, (8, 56, 56), ops(), None)
+        both = [(m.num_launches, m.workspace_bytes(64)) for m in (plain, other)]
+        other.set_schedule(B.SCHEDULE_PER_LAYER)
+        assert other.num_launches == other.num_ops
+        other.set_schedule(B.SCHEDULE_AUTO)
+    finally:
+        B.fupr_tuning_set(switch, None)
+    assert both[0] == both[1] and both[0][0] >= plain.num_launches
+    for m in (plain, other):
+        assert launch_list(m, 64) == want and m.workspace_bytes(64) == want_ws
+        m.set_schedule(B.SCHEDULE_PER_LAYER)
+        assert m.num_launches == m.num_ops
+
+
 # ---- a block's pruned output filters (Alg. 1 on every non-fused operator, Sec. V-A) ---------
 
 def scatter_ops(keep=0x2000, **change):
