@@ -312,7 +312,7 @@ class Workload:
             for _ in range(reps):
                 op_ms += fm.fupr_forward_timed(self.xd, self.out, self.ws, self.sp)
         op_ms /= reps
-        n_launch = fm.num_launches
+        n_launch = fm.num_launches_at(self.batch)
         stats = [fm.launch_stats(self.batch, i) for i in range(n_launch)]
         return stats, op_ms[:n_launch]
 
@@ -349,7 +349,7 @@ class Workload:
                                  measured_traffic(self.config_index, name, default_shape))
                      for name, g in sorted(groups.items(), key=lambda kv: -kv[1]["ms"])]
         return {"workload": self.model["name"], "config_index": self.config_index, "batch": self.batch,
-                "dtype": self.model["dtype"], "kernel_launches": self.fm.num_launches,
+                "dtype": self.model["dtype"], "kernel_launches": self.fm.num_launches_at(self.batch),
                 "ms_per_step": ms_per_step, "images_per_s": self.batch / (ms_per_step * 1e-3),
                 "tflops": flops / (ms_per_step * 1e-3) / 1e12,
                 "mfma_frac": flops / (ms_per_step * 1e-3) / peak,

@@ -549,12 +549,17 @@ fupr_status fupr_model_op_stats(const fupr_model* m, int32_t batch, int32_t op, 
 int32_t fupr_model_num_ops(const fupr_model* m);
 
 /*
- * Kernel launches of one forward pass under the current schedule (1 for the
- * one-kernel schedule, else one per operator) and the algorithmic work of
- * launch i.  For the one-kernel schedule: all the network's flops; bytes = the
- * images read once + the result written once + every parameter read once.
+ * Kernel launches of one forward pass of `batch` images under the current
+ * schedule (1 for the one-kernel schedule, else one per launch group; sub-batches
+ * not counted) and the algorithmic work of launch i of that batch.  A pair of
+ * 1 x 1 convolutions is two launches at batches whose tensors are small, so the
+ * number depends on the batch; fupr_model_num_launches counts every pair as one
+ * launch, which is the fewest there are.  For the one-kernel schedule: all the
+ * network's flops; bytes = the images read once + the result written once + every
+ * parameter read once.  0 if m is NULL or batch <= 0.
  */
 int32_t fupr_model_num_launches(const fupr_model* m);
+int32_t fupr_model_num_launches_at(const fupr_model* m, int32_t batch);
 fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batch, int32_t launch,
                                     fupr_op_stats* out);
 

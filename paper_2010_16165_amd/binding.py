@@ -134,6 +134,7 @@ SIGNATURES = {
     "fupr_model_op_stats": (C.c_int32, [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(OpStats)]),
     "fupr_model_num_ops": (C.c_int32, [C.c_void_p]),
     "fupr_model_num_launches": (C.c_int32, [C.c_void_p]),
+    "fupr_model_num_launches_at": (C.c_int32, [C.c_void_p, C.c_int32]),
     "fupr_model_launch_stats": (C.c_int32, [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(OpStats)]),
     "fupr_model_set_schedule": (C.c_int32, [C.c_void_p, C.c_int32]),
     "fupr_model_table_bytes": (C.c_size_t, [C.c_void_p]),
@@ -525,6 +526,9 @@ class Model:
     @property
     def num_launches(self):
         return int(_lib.fupr_model_num_launches(self._h))
+
+    def num_launches_at(self, batch):
+        return int(_lib.fupr_model_num_launches_at(self._h, int(batch)))
 
     def set_side_streams(self, streams):
         """torch.cuda.Stream objects the per-operator schedule may fork sub-batches onto."""

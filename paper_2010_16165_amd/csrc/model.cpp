@@ -881,6 +881,28 @@ std::vector<Launch> launches_of(const fupr_model* m) {
   return tuning_any() ? list_launches(m, m->schedule) : m->launches[m->schedule];
 }
 
+// The launches of a batch of N images.  Of a pair of 1 x 1 convolutions whose tensors are small, two
+// launches that fill the GPU are faster than one that walks it (nine images of 193 x 193, 49 x 49
+// pixels, 47 -> 256 -> 111 channels: 18 us in one, 12 in two; a launch more costs 1.7).
+std::vector<Launch> launches_at(const fupr_model* m, int N) {
+  std::vector<Launch> v;
+  const std::vector<Launch> all = launches_of(m);
+  v.reserve(m->ops.size());
+  for (const Launch& l : all) {
+    const fupr_op_desc& op = m->ops[l.first];
+    const TensorInfo& x = m->tensors[op.in];
+    const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
+    if (l.count == 2 && m->ops[l.first + 1].kind == FUPR_OP_CONV &&
+        conv_is_small(op.conv, m->dt, N, x.H, x.W, op.res >= 0, cat ? x.C : 0)) {
+      v.push_back(Launch{l.first, 1});
+      v.push_back(Launch{l.first + 1, 1});
+    } else {
+      v.push_back(l);
+    }
+  }
+  return v;
+}
+
 // Sub-batches of the per-operator schedule.  Two sub-batches side by side let one's
 // memory-bound kernels run beside the other's arithmetic and fill launch gaps and tails.
 // Measured on the ImageNet-size workloads (one / two / three / four sub-batches): the
@@ -976,7 +998,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
     if (events && hipEventRecord(events[1], hs) != hipSuccess) return FUPR_ERR_LAUNCH;
     return FUPR_OK;
   }
-  const std::vector<Launch> launches = launches_of(m);
+  const std::vector<Launch> launches = launches_at(m, N);
   auto enqueue = [&](int n0, int count, void* on, bool record) -> fupr_status {
     for (size_t l = 0; l < launches.size(); ++l) {
       const size_t i = (size_t)launches[l].first;
@@ -994,21 +1016,11 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
           r.spatial_stride = op.res_spatial_stride;
           r.c_offset = op.res_c_offset;
         }
-        const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
-        fupr_tensor x2;
-        if (cat) x2 = view(op.in2, n0, count);
-        const uint32_t flags = op.epilogue & ~uint32_t(FUPR_FUSE_CAT);
-        if (conv_is_small(op.conv, m->dt, N, x.H, x.W, add, cat ? x.C : 0)) {
-          // A batch whose tensors are small: two launches that fill the GPU are faster than one
-          // that walks it (nine images of 193 x 193, 49 x 49 pixels, 47 -> 256 -> 111 channels:
-          // 18 us in one, 12 in two; a launch more costs 1.7).
-          st = conv_fused_part(&op.conv, &x, cat ? &x2 : nullptr, op.in2_spatial_stride, op.packed,
-                               add ? &r : nullptr, flags, &mid, N, on);
-          if (st == FUPR_OK)
-            st = conv_fused_part(&second.conv, &mid, nullptr, 1, second.packed, nullptr, second.epilogue, &y, N, on);
-        } else if (cat) {
-          st = conv_cat_conv1x1_fused(&op.conv, &x, &x2, op.in2_spatial_stride, op.packed, flags, &mid,
-                                      &second.conv, second.packed, second.epilogue, &y, on);
+        if (op.epilogue & FUPR_FUSE_CAT) {
+          const fupr_tensor x2 = view(op.in2, n0, count);
+          st = conv_cat_conv1x1_fused(&op.conv, &x, &x2, op.in2_spatial_stride, op.packed,
+                                      op.epilogue & ~uint32_t(FUPR_FUSE_CAT), &mid, &second.conv,
+                                      second.packed, second.epilogue, &y, on);
         } else {
           st = fupr_conv_conv1x1_fused(&op.conv, &x, op.packed, add ? &r : nullptr, op.epilogue, &mid,
                                        &second.conv, second.packed, second.epilogue, &y, on);
@@ -1089,7 +1101,7 @@ extern "C" fupr_status fupr_forward_timed(const fupr_model* m, const fupr_tensor
     st = FUPR_ERR_LAUNCH;
   if (st == FUPR_OK) {
     std::vector<float> ms(n, 0.0f);
-    const size_t launches = use_resident(m, input, output) ? 1 : launches_of(m).size();
+    const size_t launches = use_resident(m, input, output) ? 1 : launches_at(m, input->N).size();
     for (size_t i = 0; i < launches; ++i)
       if (hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]) != hipSuccess) { st = FUPR_ERR_LAUNCH; break; }
     if (st == FUPR_OK) std::copy(ms.begin(), ms.end(), op_ms);
@@ -1159,12 +1171,17 @@ extern "C" int32_t fupr_model_num_launches(const fupr_model* m) {
   return one_kernel(m) ? 1 : (int32_t)launches_of(m).size();
 }
 
+extern "C" int32_t fupr_model_num_launches_at(const fupr_model* m, int32_t batch) {
+  if (!m || batch <= 0) return 0;
+  return one_kernel(m) ? 1 : (int32_t)launches_at(m, batch).size();
+}
+
 extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batch, int32_t launch,
                                                fupr_op_stats* out) {
   if (!m || !out) return FUPR_ERR_NULL;
-  if (batch <= 0 || launch < 0 || launch >= fupr_model_num_launches(m)) return FUPR_ERR_ARG;
+  if (batch <= 0 || launch < 0 || launch >= fupr_model_num_launches_at(m, batch)) return FUPR_ERR_ARG;
   if (!one_kernel(m)) {
-    const Launch l = launches_of(m)[launch];
+    const Launch l = launches_at(m, batch)[launch];
     fupr_status st = fupr_model_op_stats(m, batch, l.first, out);
     if (st != FUPR_OK || l.count == 1) return st;
     out->n_ops = l.count;

@@ -615,9 +615,9 @@ def test_two_1x1_convolutions_in_one_kernel(fx, case, dtype):
 
 CAT_CASES = [
     # name, N, C1 (last conv's input), C2 (block input), K, P, Q, shortcut stride, then-second-conv K2 or 0
-    ("cat 38+64 -> 256 s1 (streaming kernel)", 3, 38, 64, 256, 14, 14, 1, 0),
+    ("cat 38+64 -> 256 s1", 3, 38, 64, 256, 14, 14, 1, 0),
     ("cat 38+64 -> 256 s1 then 1x1 -> 30 (pair)", 3, 38, 64, 256, 12, 14, 1, 30),
-    ("cat 64+256 -> 512 s2 (pipelined kernel)", 2, 64, 256, 512, 14, 14, 2, 0),
+    ("cat 64+256 -> 512 s2", 2, 64, 256, 512, 14, 14, 2, 0),
     ("cat 207+512 -> 300 s2 ragged", 2, 207, 512, 300, 7, 9, 2, 0),
     ("cat 12+40 -> 72 s2 odd extent", 3, 12, 40, 72, 9, 7, 2, 0),
     ("cat 96+24 -> 64 s1", 2, 96, 24, 64, 10, 10, 1, 0),
@@ -627,10 +627,14 @@ CAT_CASES = [
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("case", CAT_CASES, ids=[c[0] for c in CAT_CASES])
 def test_conv_cat_site(fx, case, dtype):
+    conv_cat_site(fx, case, dtype)
+
+
+def conv_cat_site(fx, case, dtype):
     """A projection shortcut accumulated in the accumulators of the block's last
     1 x 1 convolution (Sec. IV-B-1): the device runs ONE convolution over the two
     tensors, the oracle the original graph - two convolutions with their batch
-    norms, the addition, the ReLU."""
+    norms, the addition, the ReLU.  Returns the names of the kernels that ran."""
     B, network, torch = fx
     name, n, c1, c2, k, p, q, stride, k2 = case
     rng = np.random.default_rng(zlib.crc32(name.encode()))
@@ -664,7 +668,9 @@ def test_conv_cat_site(fx, case, dtype):
         torch.cuda.synchronize()
         assert yd.padding_is_zero()
         parity(yd.to_nchw(), ref, dtype)
-        return
+        h_op = B.OpDesc(B.OP_CONV, 0, -1, B.conv_shape(c1, c2, 1, 1, stride, 0), packed.data_ptr(), 0, 1, 0)
+        y_op = B.OpDesc(B.OP_CONV, 1, -1, shc, packed.data_ptr(), B.FUSE_CAT, 1, 0, None, 0, stride)
+        return [B.Model(dt, (c2, hx, wx), [h_op, y_op], None).op_stats(n, 1)["kernel"]]
     # followed by the next block's first convolution in the same launch: through the model
     w1 = (rng.standard_normal((k2, k, 1, 1)) * np.sqrt(2.0 / k)).astype(np.float32)
     b1 = (rng.standard_normal(k2) * 0.1).astype(np.float32)
@@ -678,7 +684,8 @@ def test_conv_cat_site(fx, case, dtype):
            B.OpDesc(B.OP_CONV, 1, -1, shc, packed.data_ptr(), B.FUSE_RELU | B.FUSE_CAT, 1, 0, None, 0, stride),
            B.OpDesc(B.OP_CONV, 2, -1, sh1, p1.data_ptr(), B.FUSE_RELU, 1, 0)]
     m = B.Model(dt, (c2, hx, wx), ops, [p0, p1, packed])
-    assert m.num_launches == 2 and m.launch_stats(n, 1)["kernel"] == "conv1x1s_256f+conv1x1"
+    kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))][1:]
+    assert len(kernels) == (1 if kernels[0] == "conv1x1s_256f+conv1x1" else 2)
     out, ws = m.alloc(n)
     m.fupr_forward(xd, out, ws)
     torch.cuda.synchronize()
@@ -694,6 +701,36 @@ def test_conv_cat_site(fx, case, dtype):
     m.fupr_forward(xd, out2, ws2)
     torch.cuda.synchronize()
     assert rel_err(out.to_nchw(), out2.to_nchw()) <= TOL[dtype] / 4
+    return kernels
+
+
+# Every family that reads two tensors (a layer this small takes the first one by itself; the pair is
+# one launch only where the streaming kernel takes its first convolution).
+CAT_FAMILIES = {"window": [], "pipelined": ["conv_window", "conv1x1_stream"],
+                "streaming": ["conv_window", "conv1x1_pipe"]}
+
+
+@pytest.mark.parametrize("family", CAT_FAMILIES)
+@pytest.mark.parametrize("case", CAT_CASES, ids=[c[0] for c in CAT_CASES])
+def test_conv_cat_every_kernel(fx, case, family):
+    B, network, torch = fx
+    channels = (case[2] + B.CAT_ALIGN - 1) // B.CAT_ALIGN * B.CAT_ALIGN + case[3]
+    if family == "streaming" and channels > 512 or family == "pipelined" and channels < 128:
+        pytest.skip("no layer of that kernel")
+    for switch in CAT_FAMILIES[family]:
+        B.fupr_tuning_set(switch, 0)
+    try:
+        for dtype in ("bf16", "f16"):
+            kernels = conv_cat_site(fx, case, dtype)
+            if family == "window":
+                assert all("_w" in k for k in kernels), kernels
+            elif family == "pipelined":
+                assert all(k.startswith("conv1x1") and k[7] in "pq" and "_w" not in k for k in kernels), kernels
+            else:
+                assert kernels == ["conv1x1s_256f+conv1x1"] if case[8] else kernels[0].startswith("conv1x1s_"), kernels
+    finally:
+        for switch in CAT_FAMILIES[family]:
+            B.fupr_tuning_set(switch, None)
 
 
 def test_conv_cat_rejects_bad_calls(fx):

@@ -528,6 +528,36 @@ def test_window_runs_hold_every_tap_and_fit_their_plan(tmp_path):
     assert int(out.stdout) > 100000
 
 
+def test_launch_list_of_a_batch_names_what_runs():
+    """A pair of 1 x 1 convolutions runs as two launches at batches whose tensors are small: the list of
+    that batch counts both, under the kernels and bytes of the two operators."""
+    ops = fake_ops([
+        (B.OP_CONV, 0, -1, 64, 8, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 1, -1, 256, 64, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 2, -1, 32, 256, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 3, -1, 10, 32, 3, 1, 1, B.FUSE_RELU, 1),
+    ])
+    m = B.Model(B.F16, (8, 56, 56), ops, None)
+    assert m.num_launches == m.num_launches_at(64) == 3 and m.num_launches_at(1) == 4
+    for batch in (1, 3, 9, 64):
+        n = m.num_launches_at(batch)
+        launches = [m.launch_stats(batch, i) for i in range(n)]
+        single = [m.op_stats(batch, i) for i in range(m.num_ops)]
+        expect(B.ERR_ARG, lambda: m.launch_stats(batch, n))
+        assert [i for s in launches for i in range(s["first_op"], s["first_op"] + s["n_ops"])] == list(range(4))
+        assert sum(s["flops"] for s in launches) == sum(s["flops"] for s in single)
+        paired = [s for s in launches if s["n_ops"] == 2]
+        saved = 2 * batch * 56 * 56 * 256 * len(paired)    # the tensor in between is not read back
+        assert sum(s["bytes"] for s in launches) == sum(s["bytes"] for s in single) - saved
+        assert all(s["kernel"] == "conv1x1s_256f+conv1x1" for s in paired)
+        assert all(s["kernel"] == single[s["first_op"]]["kernel"] for s in launches if s["n_ops"] == 1)
+        # such a pair is split exactly where the window kernel takes its first convolution
+        assert ("_w" in single[1]["kernel"]) == (not paired)
+    m.set_schedule(B.SCHEDULE_PER_LAYER)
+    assert m.num_launches == m.num_launches_at(64) == 4
+    assert B._lib.fupr_model_num_launches_at(None, 4) == 0 and m.num_launches_at(0) == 0
+
+
 def test_model_create_errors():
     ok = (B.OP_CONV, 0, -1, 16, 3, 3, 1, 1, B.FUSE_RELU, 1)
     cases = [
