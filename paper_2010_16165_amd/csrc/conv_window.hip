@@ -844,6 +844,7 @@ bool wanted(const Conv16Params& c, int N) {
   if (c.keep && (c.dt == FUPR_F32 || (R == 1 && c.S == 1))) return false;
   if (R * c.S > kMaxTaps || (c.x2 && c.split % 8 != 0)) return false;
   const uint64_t es = c.dt == FUPR_F32 ? 4 : 2;
+  if ((uint64_t)c.nsteps * 64 * (uint64_t)c.Kp >= kOutside) return false;   // bytes of the weights (w_bytes has 32 bits)
   for (uint64_t elements : {(uint64_t)N * c.H * c.W * c.xcs, (uint64_t)c.M * c.ycs,
                             c.x2 ? (uint64_t)N * c.H2 * c.W2 * c.xcs2 : 0,
                             c.res ? (uint64_t)N * c.rH * c.rW * c.rcs : 0})

@@ -19,7 +19,9 @@ namespace {
 
 // ---- fp32 direct convolution ------------------------------------------------
 // One thread: one output pixel x 4 consecutive filters, plain FMA.  For what conv_window.hip does
-// not take: windows of more than 25 taps, tensors of 2 GiB or more.
+// not take: windows of more than 25 taps or padded by more than half a window, tensors or weights of
+// 2 GiB or more, and layers of which not even 16 pixels' input, all channels, fits LDS (3 x 3 with
+// stride 2 from 128 channels at 56 x 56 on, 1 x 1 from some 2400 channels on).
 
 struct Conv32Params {
   const float* x;

@@ -375,6 +375,21 @@ def test_paddings_of_every_size(fx, case, window, dtype):
     conv_site(fx, case, dtype)
 
 
+# Single precision beyond the window kernel's LDS (all channels of a tile at once): the direct kernel.
+FP32_DIRECT = [
+    ("fp32 1x1 C2560 K12 5x5 x3 +id", 3, 2560, 5, 5, 12, 1, 1, 0, "identity", True),
+    ("fp32 3x3 C128 K10 s2 56x56", 1, 128, 56, 56, 10, 3, 2, 1, None, True),
+    ("fp32 3x3 C300 K7 20x70 x2 +optA norelu", 2, 300, 20, 70, 7, 3, 1, 1, "optionA", False),
+    ("fp32 6x6 C5 K9 s3 17x19 x2", 2, 5, 17, 19, 9, 6, 3, 2, None, True),
+]
+
+
+@pytest.mark.parametrize("case", FP32_DIRECT, ids=[c[0] for c in FP32_DIRECT])
+def test_fp32_layers_of_the_direct_kernel(fx, case):
+    assert kernel_of(fx[0], "f32", case) == "conv32_direct"
+    conv_site(fx, case, "f32")
+
+
 # Both sides of the lines behind which the kernels with larger tiles take over: thin 3 x 3
 # layers of many pixels, 1 x 1 reductions too deep for a 64-pixel tile in LDS.
 WINDOW_EDGES = [

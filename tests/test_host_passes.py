@@ -518,6 +518,17 @@ def test_paddings_over_half_a_window_stay_off_the_window_kernel(dtype):
         assert "_w" in conv_name(dtype, *case), case
 
 
+def test_weights_of_2_gib_and_more_stay_off_the_window_kernel():
+    """That kernel reads weights through 32-bit offsets; the fp32 kernel that takes such layers does not."""
+    for dtype, c, k, takes in [(B.F32, 2048, 1 << 17, True), (B.F32, 2048, (1 << 18) - 16, True),
+                               (B.F32, 2048, 1 << 18, False), (B.F32, 2048, 1 << 19, False),
+                               (B.F32, 2052, (1 << 19) - 4, False), (B.BF16, 1024, (1 << 20) - 16, True),
+                               (B.BF16, 1024, 1 << 20, False), (B.BF16, 1024, (1 << 21) - 16, False)]:
+        name = conv_name(dtype, 1, c, 1, 1, k, 1, 1, 1, 0)
+        assert ("_w" in name) == takes, (dtype, c, k, name)
+        assert takes or dtype != B.F32 or name == "conv32_direct"
+
+
 def test_window_runs_hold_every_tap_and_fit_their_plan(tmp_path):
     """The functions the planner and the kernel share, walked tile by tile on the host."""
     exe = str(tmp_path / "window_runs")
