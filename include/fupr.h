@@ -276,7 +276,8 @@ typedef struct {
  * (Sec. III; Sec. IV-B-1), accumulated in fp32; the residual is converted to
  * fp32 and added after the bias (this call; the one-kernel schedule of
  * fupr_forward orders the sum differently, see fupr_model_set_schedule); act is ReLU with FUPR_FUSE_RELU, else the
- * identity; one rounding to y's type at the end.  FUPR_FUSE_ADD requires res.
+ * identity; one rounding to y's type at the end.  Outside the image x is zero, also
+ * for an infinite weight (0 x Inf = NaN).  FUPR_FUSE_ADD requires res.
  * packed is [dev] the blob written by fupr_pack for the same shape and dtype.
  * x, y (and res) share one dtype; y->ptr is written, including its zero
  * padding lanes; y must not overlap x, and may overlap res only if res is the

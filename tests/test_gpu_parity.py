@@ -375,6 +375,43 @@ def test_paddings_of_every_size(fx, case, window, dtype):
     conv_site(fx, case, dtype)
 
 
+# Reductions that leave some waves of some tiles with steps past the end.
+@pytest.mark.parametrize("tile", ["", *range(len(WINDOW_TILES))], ids=["chosen"] + WINDOW_TILES)
+def test_infinite_weight_stays_infinite(fx, tile):
+    """A weight that overflowed the storage type makes its filter's outputs infinite (every pixel is
+    positive and no tap lies outside the image), and no other filter's: nothing multiplies it by zero."""
+    B, network, torch = fx
+    ran = 0
+    try:
+        for waves in ("1x1", "1x4", "2x2") if tile != "" else ("",):
+            B.fupr_tuning_set("window_tile", f"{tile}x{waves}" if waves else None)
+            for dtype in ("bf16", "f16", "f32"):
+                for c, r in ((8, 1), (40, 1), (72, 1), (136, 1), (328, 1), (16, 3), (40, 3)):
+                    case = (f"inf C{c} {r}x{r}", 2, c, 9, 8, 40, r, 1, 0, None, False)
+                    if "_w" not in kernel_of(B, dtype, case):
+                        continue
+                    ran += 1
+                    print(f"{case[0]} {dtype} {tile} {waves}", flush=True)
+                    gen = torch.Generator(device="cuda").manual_seed(c)
+                    x = B.DeviceTensor.empty(2, 9, 8, c, B.DTYPES[dtype])
+                    x.data.zero_()
+                    x.data[..., :c] = torch.rand((2, 9, 8, c), generator=gen, device="cuda") + 0.5
+                    wt = np.full((40, c, r, r), 0.25, np.float32)
+                    sh = B.shape_of(wt, 1, 0)
+                    y = [B.DeviceTensor.empty(2, 10 - r, 9 - r, 40, B.DTYPES[dtype]) for _ in range(2)]
+                    for value, out in ((0.25, y[0]), (np.inf, y[1])):
+                        wt[21, c - 1, r - 1, r - 1] = value
+                        packed = B.upload_blob(B.fupr_pack(sh, wt, None, B.DTYPES[dtype]))
+                        B.fupr_conv_fused(sh, x, packed, None, 0, out)
+                    torch.cuda.synchronize()
+                    want = y[0].data.clone()
+                    want[..., 21] = float("inf")
+                    assert torch.equal(y[1].data, want)
+    finally:
+        B.fupr_tuning_set("window_tile", None)
+    assert ran >= 10
+
+
 # Single precision beyond the window kernel's LDS (all channels of a tile at once): the direct kernel.
 FP32_DIRECT = [
     ("fp32 1x1 C2560 K12 5x5 x3 +id", 3, 2560, 5, 5, 12, 1, 1, 0, "identity", True),
