@@ -342,9 +342,10 @@ fupr_status fupr_global_avgpool(const fupr_tensor* x, const fupr_tensor* y, void
  * (the operator-fusion idea of Sec. IV-B applied to the one "Others" operator
  * that follows a convolution directly).  shape must be 7 x 7, stride 2, pad 3,
  * C <= 4, K = 64; x, y [dev] 16-bit NHWC, y->c_stride = 64, y->H/W the pool's
- * output extent; packed [dev] from fupr_pack.  The result equals fupr_conv_fused
- * (ReLU) followed by fupr_maxpool bit for bit: rounding is monotonic, so the
- * maximum of rounded values is the rounded maximum.
+ * output extent; packed [dev] from fupr_pack.  The result is that of fupr_conv_fused
+ * (ReLU) followed by fupr_maxpool (rounding is monotonic, so the maximum of rounded
+ * values is the rounded maximum) but for the order of the fp32 summation: a rounding
+ * may fall the other way.
  * Errors: NULL, SHAPE, DTYPE, ALIGN; LIMIT when the shape is not the one above.
  */
 fupr_status fupr_conv_maxpool_fused(const fupr_conv_shape* shape, const fupr_tensor* x,
@@ -358,10 +359,10 @@ fupr_status fupr_conv_maxpool_fused(const fupr_conv_shape* shape, const fupr_ten
  * reads y from memory (a bottleneck block's last convolution and the next
  * block's first one, Table II; operator fusion in the sense of Sec. IV-B applied
  * across a block boundary).  Both y and h are written.  shape1, shape2: 1 x 1,
- * stride 1, pad 0, shape2.C = shape1.K <= 256, shape2.K <= 64, 16-bit types;
+ * stride 1, pad 0, shape2.C = shape1.K <= 256, shape2.K <= 128, 16-bit types;
  * y->c_stride = shape1.K rounded up to 8.  Arguments as in fupr_conv_fused; the
- * second convolution has no shortcut.  h differs from fupr_conv_fused applied to
- * y only by the order of the fp32 summation inside a 32-channel step.
+ * second convolution has no shortcut.  h differs from fupr_conv_fused applied to y
+ * by the order of the fp32 summation only.
  * Errors: as fupr_conv_fused; LIMIT when the pair is not of the shape above.
  */
 fupr_status fupr_conv_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x,
@@ -424,12 +425,12 @@ void fupr_model_destroy(fupr_model* m);
  * Table II) and the caller has provided the table below, the whole network runs
  * as ONE kernel, one workgroup per image, activations never leaving LDS;
  * otherwise one kernel per launch group (an operator, or operators that have a
- * kernel together: stem convolution + max-pool, two 1 x 1 convolutions, a
- * bottleneck block).  PER_LAYER: always one kernel per operator.
+ * kernel together: stem convolution + max-pool, two 1 x 1 convolutions whose
+ * tensors are not small).  PER_LAYER: always one kernel per operator.
  * The schedules compute the same operators but round differently: the
  * one-kernel schedule starts the fp32 accumulator from the bias and adds the
  * shortcut as one more MFMA step (before, not after, the last products), and the
- * fused launch groups sum inside a 32-channel step in another order.  Results
+ * fused launch groups sum in another order.  Results
  * agree within the rounding of the storage type, not bit for bit.  The
  * one-kernel schedule also assumes FINITE activations: a shortcut value of
  * +-Inf turns all 16 filters of its tile at that pixel into NaN (0 x Inf), where
@@ -464,7 +465,8 @@ fupr_status fupr_model_set_table(fupr_model* m, const void* dev_table);
 
 /*
  * Streams the per-operator schedule may use beside the caller's stream: batches
- * of 192 images or more then run as two sub-batches side by side (images are
+ * of 192 images or more (64 or more for networks of fewer than 150 operations per
+ * byte of their tensors) then run as two sub-batches side by side (images are
  * independent; each sub-batch owns its slice of every workspace buffer), forked
  * from and joined to the stream passed to fupr_forward by events, so that the
  * call stays asynchronous, ordered on that stream, and capturable.  n = 0 .. 3

@@ -567,7 +567,7 @@ def test_global_avgpool(fx, dtype):
 @pytest.mark.parametrize("size", [(64, 64), (70, 58), (30, 26)], ids=["64x64", "70x58", "30x26"])
 def test_stem_maxpool_fused(fx, size, dtype):
     """Table II's ImageNet stem as one operator: against the oracle's conv, BN,
-    ReLU, max-pool, and bit for bit against the two separate kernels."""
+    ReLU, max-pool, and against the two separate kernels."""
     B, network, torch = fx
     h, w = size
     n, c, k = 3, 3, 64
@@ -598,7 +598,7 @@ def test_stem_maxpool_fused(fx, size, dtype):
     err = parity(got, ref, dtype)
     print(f"  max-norm rel err {err:.3e}", flush=True)
     assert err <= TOL[dtype], (size, dtype, err)
-    # the two-kernel path: same accumulation order, one rounding each, max of rounded values
+    # the two-kernel path: the same products in another order, one rounding each, max of rounded values
     mid = B.DeviceTensor.empty(n, sh_, sw_, k, dt)
     y2 = B.DeviceTensor.empty(n, p, q, k, dt)
     B.fupr_conv_fused(sh, xd, packed, None, B.FUSE_RELU, mid)
