@@ -51,7 +51,9 @@ def sources_hash():
 
 def group_of_device_kernel(name):
     """The launch-list name (fupr_op_stats.kernel) of a device kernel as rocprofv3
-    prints it, from its template arguments; None for kernels that are not the library's."""
+    prints it, from its template arguments; None for kernels that are not the library's.
+    (A 3 x 3 window and any other one are one instantiation of the window kernel under two launch-list
+    names: "conv_w..." stands for both.)"""
     m = re.match(r"(?:void )?(?:fupr::)?(?:\(anonymous namespace\)::)?(\w+)(?:<([^>]*)>)?", name)
     if not m:
         return None
@@ -79,8 +81,7 @@ def group_of_device_kernel(name):
         tile = f"_w{num(2) * 16}x{num(3) * 16}"
         if num(0) == 0:
             return "conv32" + tile
-        # (a 3 x 3 window and any other one are one instantiation under two launch-list names)
-        return "conv1x1p" + tile if num(1) != 1 else None
+        return ("conv" if num(1) == 1 else "conv1x1p") + tile
     return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)
@@ -156,13 +157,17 @@ def record_traffic(fetch_dir, write_dir, config):
     print("\n".join(ln for ln in lines if ln.startswith(f"config={config} ")))
 
 
-def measured_traffic(config, kernel, default_shape):
+def measured_traffic(config, kernel, default_shape, kernels):
     """HBM bytes per launch of a kernel group from the stored counter runs; None when
     there is no record for this configuration and kernel, when the run is not the
-    recorded shape (batch, schedule), or when the kernel sources have changed since."""
+    recorded shape (batch, schedule), or when the kernel sources have changed since.
+    kernels: all groups of the run (a record of both window names is quoted only if one of them ran)."""
     if not default_shape or not os.path.exists(TRAFFIC_TABLE):
         return None
     want = sources_hash()
+    joint = re.sub(r"^(conv3x3p|conv16t)_w", "conv_w", kernel)
+    if joint != kernel and sum(re.sub(r"^(conv3x3p|conv16t)_w", "conv_w", k) == joint for k in kernels) == 1:
+        kernel = joint
     with open(TRAFFIC_TABLE) as f:
         for ln in f:
             kv = dict(p.split("=", 1) for p in ln.split() if "=" in p)
@@ -346,7 +351,7 @@ class Workload:
         nbytes = sum(s["bytes"] for s in stats)
         groups = self.groups(stats, op_ms)
         rooflines = [roofline_of(name, g, self.dt == B.F32,
-                                 measured_traffic(self.config_index, name, default_shape))
+                                 measured_traffic(self.config_index, name, default_shape, groups))
                      for name, g in sorted(groups.items(), key=lambda kv: -kv[1]["ms"])]
         return {"workload": self.model["name"], "config_index": self.config_index, "batch": self.batch,
                 "dtype": self.model["dtype"], "kernel_launches": self.fm.num_launches_at(self.batch),

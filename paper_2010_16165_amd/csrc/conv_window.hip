@@ -2,6 +2,8 @@
 // streamed straight from L2 into registers (Sec. III, Sec. IV-B-1: operator
 // k x c x r x s with its fused epilogue).
 //
+// What it takes: windows of at most 25 taps, padded by at most half their shorter side
+// (window_patch.h), tensors and weights under 2 GiB, tiles whose input fits LDS with all channels.
 // What it is for: layers that a pipeline of LDS stages does not fill - one image or a few, deep
 // layers of any batch, strided windows.  There a chain of dependent stages (load, barrier,
 // multiply) leaves the matrix pipe idle most of the time (512 -> 359 channels, 3 x 3 on a 7 x 7
@@ -31,7 +33,7 @@
 // Single precision runs through the same code on the 16 x 16 x 4 MFMA: a chunk is then 4 channels
 // (16 bytes as well), a step 16 channels in four MFMAs, each of which takes one channel of every
 // lane's chunk.  A CIFAR-size network of 21 layers on 32 images: 410 us (one thread per pixel and
-// four filters, vector FMAs) -> 115.
+// four filters, vector FMAs) -> 111.
 // What bounds it: below some ten images latency (arguments, patch, first weights, one store);
 // then the weights, which every tile reads anew (45 bytes per clock and compute unit), and the
 // vector instructions that work out pixel addresses, beside the matrix pipe.
@@ -582,7 +584,8 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   }
 }
 
-// D: steps of weights in flight; G: steps per group of pixel reads; vgprs: as compiled.
+// D: steps of weights in flight; G: steps per group of pixel reads; vgprs: registers of the 16-bit
+// window form, as the estimate below was fitted with (one-tap forms take up to 18 more, fp32 up to 15).
 struct WindowTile {
   int MT, NT, D, G, threads, min_waves, vgprs;
   const char *three, *one_tap, *other, *single;
@@ -811,8 +814,9 @@ bool pick_for_batch(const Conv16Params& c, int N, WindowPlan* plan) {
   return pick_window(whole, c.plan_N, 0, plan) && pick_window(c, N, plan->p.WK, plan);
 }
 
-// The choice is a function of sizes alone; each thread remembers its answers for the sizes it
-// launched last (about 100 plans are weighed for one, several microseconds of host time).
+// The choice is a function of sizes alone; each thread remembers its last answer for every one of 128
+// hashes of the sizes (about 100 plans are weighed for one, 4 - 7 us of host time; sizes with one hash
+// replace each other: 11 of the 52 operators of an irregular ResNet-50 are weighed on every pass).
 struct Sizes {
   int dt, N, plan_N, H, W, P, Q, M, R, S, stride, pad, Kp, cpt, xcs, split, xcs2, stride2, res, two, H2, W2, listed;
   bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
