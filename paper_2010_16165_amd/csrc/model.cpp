@@ -885,20 +885,16 @@ std::vector<Launch> launches_of(const fupr_model* m) {
 // launches that fill the GPU are faster than one that walks it (nine images of 193 x 193, 49 x 49
 // pixels, 47 -> 256 -> 111 channels: 18 us in one, 12 in two; a launch more costs 1.7).
 std::vector<Launch> launches_at(const fupr_model* m, int N) {
-  std::vector<Launch> v;
-  const std::vector<Launch> all = launches_of(m);
-  v.reserve(m->ops.size());
-  for (const Launch& l : all) {
+  std::vector<Launch> v = launches_of(m);
+  for (size_t i = 0; i < v.size(); ++i) {
+    const Launch l = v[i];
+    if (l.count != 2 || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
     const fupr_op_desc& op = m->ops[l.first];
     const TensorInfo& x = m->tensors[op.in];
     const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
-    if (l.count == 2 && m->ops[l.first + 1].kind == FUPR_OP_CONV &&
-        conv_is_small(op.conv, m->dt, N, x.H, x.W, op.res >= 0, cat ? x.C : 0)) {
-      v.push_back(Launch{l.first, 1});
-      v.push_back(Launch{l.first + 1, 1});
-    } else {
-      v.push_back(l);
-    }
+    if (!conv_is_small(op.conv, m->dt, N, x.H, x.W, op.res >= 0, cat ? x.C : 0)) continue;
+    v[i].count = 1;
+    v.insert(v.begin() + ++i, Launch{l.first + 1, 1});
   }
   return v;
 }

@@ -1,7 +1,6 @@
 // Internal: the run of input pixels that a tile of output pixels needs (conv_window.hip).  The
 // planner reserves LDS by it and the kernel fills LDS by it, from the same functions.
 #pragma once
-#include <algorithm>
 #include <cstdint>
 
 namespace fupr {
@@ -22,12 +21,13 @@ constexpr int window_reach(int R, int S, int W) { return (R - 1) * W + S - 1; }
 constexpr bool window_runs_are_whole(int R, int S, int pad) { return 2 * pad <= (R < S ? R : S); }
 
 // The most pixels a run of BM output pixels takes, the pixel of zeros before it included.  Needs
-// window_runs_are_whole; no term is negative then, since stride * (Q - 1) <= W + 2 pad - S <= W.
+// window_runs_are_whole: no term is negative then, since stride * (Q - 1) <= W + 2 pad - S <= W and
+// likewise for the rows.
 constexpr int64_t most_run_pixels(int BM, int R, int S, int stride, int H, int W, int P, int Q) {
   const int64_t rows = (BM - 1 + Q - 1) / Q;                              // row ends crossed, at most
   const int64_t images = (BM - 1 + (int64_t)P * Q - 1) / ((int64_t)P * Q);   // image ends crossed, at most
-  const int64_t row_end = std::max<int64_t>(0, (int64_t)stride * W - (int64_t)stride * (Q - 1));
-  const int64_t image_end = std::max<int64_t>(0, H - (int64_t)stride * (P - 1)) * W;
+  const int64_t row_end = (int64_t)stride * W - (int64_t)stride * (Q - 1);
+  const int64_t image_end = (H - (int64_t)stride * (P - 1)) * W;
   return 1 + (int64_t)(BM - 1) * stride + rows * row_end + images * image_end + window_reach(R, S, W) + 1;
 }
 

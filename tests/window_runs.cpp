@@ -1,6 +1,7 @@
 // Walks every tile of many geometries as conv_window.hip does: the pixels the kernel fills must not
 // exceed those the planner reserves, and every tap inside an image must lie in the filled run.
 // Prints the number of tiles walked; exit status 1 with the first geometry that fails.
+#include <algorithm>
 #include <cstdio>
 
 #include "window_patch.h"
