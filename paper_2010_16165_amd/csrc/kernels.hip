@@ -313,12 +313,15 @@ bool prefer_pipe(const Conv16Params& g) {
 }  // namespace
 
 namespace {
-// geometry16 of a convolution with a shortcut (add) or of two tensors (first_c > 0)
-Conv16Params geometry_of(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c) {
+// geometry16 of a convolution with a shortcut (res_at >= 0) or of two tensors (first_c > 0)
+Conv16Params geometry_of(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, int res_at, int first_c) {
   Conv16Params g = geometry16(s, dt, N, H, W);
   // markers that are never dereferenced stand for the shortcut and the second tensor
   const uint16_t* const marker = reinterpret_cast<const uint16_t*>(uintptr_t(16));
-  if (add) g.res = marker;
+  if (res_at >= 0) {
+    g.res = marker;
+    g.roff = res_at;
+  }
   if (first_c > 0) {
     g.x2 = marker;
     g.split = round_up(first_c, FUPR_CAT_ALIGN) / 8;
@@ -328,13 +331,13 @@ Conv16Params geometry_of(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, 
 }
 }  // namespace
 
-bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c) {
-  return conv_window_applies(geometry_of(s, dt, N, H, W, add, first_c), N);
+bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, int res_at, int first_c) {
+  return conv_window_applies(geometry_of(s, dt, N, H, W, res_at, first_c), N);
 }
 
 const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
-                             bool indexed, bool add, int first_c) {
-  Conv16Params g = geometry_of(s, dt, N, H, W, add && !indexed, first_c);
+                             bool indexed, int res_at, int first_c) {
+  Conv16Params g = geometry_of(s, dt, N, H, W, indexed ? -1 : res_at, first_c);
   if (dt == FUPR_F32) return conv_window_applies(g, N) ? conv_window_name(g, N) : "conv32_direct";
   if (first_c > 0) {
     if (conv_window_applies(g, N)) return conv_window_name(g, N);
@@ -606,9 +609,9 @@ fupr_status fupr::conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fu
 }
 
 bool fupr::conv_pair_fusable(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fupr_dtype dt,
-                             int N, int H, int W) {
+                             int N, int H, int W, int res_at) {
   if (dt == FUPR_F32) return false;
-  Conv16Params g1 = geometry16(s1, dt, N, H, W);
+  Conv16Params g1 = geometry_of(s1, dt, N, H, W, res_at, 0);
   g1.ycs = min_c_stride(s1.K, dt);
   const Conv16Params g2 = geometry16(s2, dt, N, g1.P, g1.Q);
   return s1.R == 1 && s2.R == 1 && conv1x1_fused_pair_applies(g1, g2);

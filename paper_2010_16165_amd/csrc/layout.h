@@ -73,10 +73,11 @@ struct ConvArgs {
   int split_c;           // input channels taken from x (a multiple of 32); the others come from x2
 };
 fupr_status launch_conv(const ConvArgs& a, void* stream);
-// indexed: the convolution adds into listed channels of a wider tensor (ConvArgs::keep); add: it
-// has a shortcut; first_c > 0: it reads two tensors, the first of that many channels
+// indexed: the convolution adds into listed channels of a wider tensor (ConvArgs::keep); res_at >= 0:
+// it has a shortcut at that channel offset; first_c > 0: it reads two tensors, the first of that
+// many channels
 const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W,
-                             bool indexed = false, bool add = false, int first_c = 0);
+                             bool indexed = false, int res_at = -1, int first_c = 0);
 // fupr_conv_fused / fupr_conv_cat_fused (x2 != nullptr) on a part of a batch of plan_N images.
 fupr_status conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
                             int32_t x2_stride, const void* packed, const fupr_residual* res,
@@ -87,7 +88,7 @@ fupr_status conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x
                               void* stream);
 // The convolution is one that conv_window.hip takes at this batch size (arguments as for
 // conv_kernel_name).
-bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, bool add, int first_c);
+bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, int res_at, int first_c);
 // fupr_conv_cat_fused followed by a 1 x 1 convolution of its output, in one launch
 // (what fupr_conv_conv1x1_fused is to fupr_conv_fused); for the model executor.
 fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x1,
@@ -95,10 +96,10 @@ fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_ten
                                    uint32_t flags1, const fupr_tensor* y,
                                    const fupr_conv_shape* shape2, const void* packed2,
                                    uint32_t flags2, const fupr_tensor* h, void* stream);
-// Shapes only: can convolution s1 on an N x H x W input and convolution s2 on its
+// Shapes only: can convolution s1 on an N x H x W input (res_at as above) and convolution s2 on its
 // output run as one launch (fupr_conv_conv1x1_fused)?
 bool conv_pair_fusable(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fupr_dtype dt, int N,
-                       int H, int W);
+                       int H, int W, int res_at);
 
 // ---- whole network in one kernel, activations resident in LDS ----------------
 // One workgroup per image walks a table of layers; see resident.hip.

@@ -846,6 +846,9 @@ bool stem_pool_pair(const fupr_model* m, size_t i) {
                            q.conv.stride, q.conv.pad);
 }
 
+// First channel of y that the operator's shortcut adds to; -1: it has none.
+int shortcut_offset(const fupr_op_desc& op) { return op.res >= 0 ? op.res_c_offset : -1; }
+
 // Operator i is a 1 x 1 convolution whose whole output tile a wave holds, and
 // operator i + 1 a 1 x 1 convolution of exactly that tensor (a bottleneck
 // block's last convolution and the next block's first): one kernel computes
@@ -860,7 +863,7 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
   if ((a.epilogue & FUPR_FUSE_CAT) && a.res >= 0) return false;
   if (b.in != (int)i + 1 || b.res >= 0) return false;
   const TensorInfo& tin = m->tensors[a.in];
-  return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W);
+  return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W, shortcut_offset(a));
 }
 
 std::vector<Launch> list_launches(const fupr_model* m, int schedule) {
@@ -892,7 +895,7 @@ std::vector<Launch> launches_at(const fupr_model* m, int N) {
     const fupr_op_desc& op = m->ops[l.first];
     const TensorInfo& x = m->tensors[op.in];
     const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
-    if (!conv_is_small(op.conv, m->dt, N, x.H, x.W, op.res >= 0, cat ? x.C : 0)) continue;
+    if (!conv_is_small(op.conv, m->dt, N, x.H, x.W, shortcut_offset(op), cat ? x.C : 0)) continue;
     v[i].count = 1;
     v.insert(v.begin() + ++i, Launch{l.first + 1, 1});
   }
@@ -1142,7 +1145,7 @@ extern "C" fupr_status fupr_model_op_stats(const fupr_model* m, int32_t batch, i
     if (scatter)   // conv.K channels of the updated tensor read and written, and the index list
       s.bytes = in_b + 2.0 * es * (double)s.M * d.conv.K + es * crs * d.conv.K + 8.0 * d.conv.K;
     if (scatter) s.K = d.conv.K;
-    s.kernel = conv_kernel_name(d.conv, m->dt, batch, ti.H, ti.W, scatter, d.res >= 0,
+    s.kernel = conv_kernel_name(d.conv, m->dt, batch, ti.H, ti.W, scatter, shortcut_offset(d),
                                 (d.epilogue & FUPR_FUSE_CAT) ? ti.C : 0);
   } else {
     s.R = s.S = d.kind == FUPR_OP_MAXPOOL ? d.conv.R : ti.H;

@@ -785,6 +785,37 @@ def test_conv_cat_every_kernel(fx, case, family):
             B.fupr_tuning_set(switch, None)
 
 
+@pytest.mark.parametrize("c,k2,offset", [(64, 32, 0), (64, 32, 4), (128, 32, 0), (80, 64, 0), (80, 32, 0)])
+def test_pairs_with_a_shortcut_run_or_are_not_planned(fx, c, k2, offset):
+    """A 1 x 1 convolution with a shortcut followed by another, at a batch whose tensors are not small: the
+    first one's depth, the shortcut's offset and the second one's filters decide whether one kernel takes
+    both; either way the pass runs and gives the operators' own result."""
+    B, network, torch = fx
+    n, hw, dt = 12, 56, B.BF16
+    rng = np.random.default_rng(c * 100 + k2 + offset)
+    x = np.maximum(rng.standard_normal((n, c, hw, hw)), 0).astype(np.float32)
+    w = [(rng.standard_normal(s) * np.sqrt(2.0 / s[1])).astype(np.float32)
+         for s in ((c, c, 1, 1), (256, c, 1, 1), (k2, 256, 1, 1))]
+    shapes = [B.shape_of(v, 1, 0) for v in w]
+    packed = [B.upload_blob(B.fupr_pack(s, v, None, dt)) for s, v in zip(shapes, w)]
+    ops = [B.OpDesc(B.OP_CONV, 0, -1, shapes[0], packed[0].data_ptr(), B.FUSE_RELU, 1, 0),
+           B.OpDesc(B.OP_CONV, 1, 1, shapes[1], packed[1].data_ptr(), B.FUSE_RELU | B.FUSE_ADD, 1, offset),
+           B.OpDesc(B.OP_CONV, 2, -1, shapes[2], packed[2].data_ptr(), B.FUSE_RELU, 1, 0)]
+    m = B.Model(dt, (c, hw, hw), ops, packed)
+    pair = offset == 0 and (c, k2) in ((64, 32), (80, 32))
+    kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
+    print(c, k2, offset, kernels, flush=True)
+    assert ("conv1x1s_256f+conv1x1" in kernels) == pair and len(kernels) == 3 - pair
+    xd = B.DeviceTensor.from_nchw(x, dt)
+    out, ws = m.alloc(n)
+    m.fupr_forward(xd, out, ws)
+    m.set_schedule(B.SCHEDULE_PER_LAYER)
+    out2, ws2 = m.alloc(n)
+    m.fupr_forward(xd, out2, ws2)
+    torch.cuda.synchronize()
+    assert rel_err(out.to_nchw(), out2.to_nchw()) <= TOL["bf16"] / 4
+
+
 def test_conv_cat_rejects_bad_calls(fx):
     B, network, torch = fx
     dt = B.BF16

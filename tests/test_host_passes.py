@@ -569,6 +569,28 @@ def test_launch_list_of_a_batch_names_what_runs():
     assert B._lib.fupr_model_num_launches_at(None, 4) == 0 and m.num_launches_at(0) == 0
 
 
+@pytest.mark.parametrize("offset", [0, 4, 8, 12])
+def test_shortcut_offset_decides_kernel_and_pairs(offset):
+    """A 16-bit shortcut whose first channel is no multiple of 8 cannot be read 16 bytes at a time: such an
+    operator runs on the general kernel, under that name, and never as the first half of a pair."""
+    ops = fake_ops([
+        (B.OP_CONV, 0, -1, 32, 8, 1, 1, 0, B.FUSE_RELU, 1),
+        (B.OP_CONV, 1, 1, 64, 32, 3, 1, 1, B.FUSE_RELU | B.FUSE_ADD, 1),
+        (B.OP_CONV, 2, 1, 256, 64, 1, 1, 0, B.FUSE_RELU | B.FUSE_ADD, 1),
+        (B.OP_CONV, 3, -1, 32, 256, 1, 1, 0, B.FUSE_RELU, 1),
+    ])
+    for op in ops[1:3]:
+        op.res_c_offset = offset
+    m = B.Model(B.BF16, (8, 56, 56), ops, None)
+    for batch in (1, 64):
+        for i in (1, 2):
+            name = m.op_stats(batch, i)["kernel"]
+            general = name.startswith("conv16t_") and "_w" not in name
+            # (the pipelined 1 x 1 kernel is not chosen at 64 images, and takes the offset where it is)
+            assert general == (offset % 8 != 0), (batch, i, name)
+    assert m.num_launches == m.num_launches_at(64) == (4 if offset % 8 else 3)
+
+
 def test_model_create_errors():
     ok = (B.OP_CONV, 0, -1, 16, 3, 3, 1, 1, B.FUSE_RELU, 1)
     cases = [
