@@ -82,6 +82,8 @@ def group_of_device_kernel(name):
         if num(0) == 0:
             return "conv32" + tile
         return ("conv" if num(1) == 1 else "conv1x1p") + tile
+    if fn == "bottleneck_kernel":   # <type, pixel tiles, waves, ...>
+        return f"bottleneck_{num(1) * 16}x{num(2) * 32}"
     return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)

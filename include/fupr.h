@@ -443,6 +443,18 @@ enum { FUPR_SCHEDULE_AUTO = 0, FUPR_SCHEDULE_PER_LAYER = 1 };
 fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule);
 
 /*
+ * on = 1: AUTO also runs the last operators of a bottleneck block as ONE kernel at
+ * the batch sizes where that is faster: a 3 x 3 convolution, the 1 x 1 convolution of
+ * its output (with the shortcut, or over two tensors) and, where it follows, the 1 x 1
+ * convolution of that output, 16-bit types, tensors of the workspace only.  0 (the
+ * default): never.  The workspace is as large either way; what its buffers hold in
+ * between differs, so the setting belongs before the first forward pass or capture
+ * and between passes, not beside one.  fupr_model_num_launches does not count blocks
+ * as one launch; fupr_model_num_launches_at does.  Errors: NULL, ARG (on not 0 or 1).
+ */
+fupr_status fupr_model_fuse_blocks(fupr_model* m, int32_t on);
+
+/*
  * The table the one-kernel schedule walks (per layer: LDS offsets, strides, work
  * item shape, tap offsets).  It lives in device memory that the CALLER provides,
  * like packed parameters:
@@ -545,7 +557,8 @@ typedef struct {
   int64_t M;         /* output pixels N*P*Q */
   int32_t K, C, R, S, stride;
   int32_t first_op, n_ops; /* the operators covered: op itself for fupr_model_op_stats; a launch
-                              may cover two (stem convolution + max-pool, two 1 x 1 convolutions) */
+                              may cover two (stem convolution + max-pool, two 1 x 1 convolutions)
+                              or, of a block, up to three */
   const char* kernel;
 } fupr_op_stats;
 fupr_status fupr_model_op_stats(const fupr_model* m, int32_t batch, int32_t op, fupr_op_stats* out);
@@ -556,8 +569,8 @@ int32_t fupr_model_num_ops(const fupr_model* m);
  * schedule (1 for the one-kernel schedule, else one per launch group; sub-batches
  * not counted) and the algorithmic work of launch i of that batch.  A pair of
  * 1 x 1 convolutions is two launches at batches whose tensors are small, so the
- * number depends on the batch; fupr_model_num_launches counts every pair as one
- * launch, which is the fewest there are.  For the one-kernel schedule: all the
+ * number depends on the batch, and so does whether a block is one (fupr_model_fuse_blocks);
+ * fupr_model_num_launches counts every pair as one launch and every block as its operators.  For the one-kernel schedule: all the
  * network's flops; bytes = the images read once + the result written once + every
  * parameter read once.  0 if m is NULL or batch <= 0.
  */
@@ -600,6 +613,8 @@ void fupr_graph_destroy(fupr_graph* g);
  *                                                 workgroups per compute unit
  *   pair_filters = 16..128                        most filters of the second convolution of a pair of
  *                                                 1 x 1 convolutions in one launch
+ *   bottleneck_fuse = 0                           blocks of fupr_model_fuse_blocks as several launches
+ *   bottleneck_tile = <index>                     force a tile of the kernel that runs them
  *   split = 1..4                                  sub-batches of the per-operator schedule
  *   res_item = "M/FT/nsteps:MTxNT,..."            work-item shapes of the one-kernel schedule
  *   debug = 1                                     planner decisions and HIP error text on stderr

@@ -137,6 +137,7 @@ SIGNATURES = {
     "fupr_model_num_launches_at": (C.c_int32, [C.c_void_p, C.c_int32]),
     "fupr_model_launch_stats": (C.c_int32, [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(OpStats)]),
     "fupr_model_set_schedule": (C.c_int32, [C.c_void_p, C.c_int32]),
+    "fupr_model_fuse_blocks": (C.c_int32, [C.c_void_p, C.c_int32]),
     "fupr_model_table_bytes": (C.c_size_t, [C.c_void_p]),
     "fupr_model_table_write": (C.c_int32, [C.c_void_p, C.c_void_p, C.c_void_p]),
     "fupr_model_set_table": (C.c_int32, [C.c_void_p, C.c_void_p]),
@@ -539,6 +540,9 @@ class Model:
 
     def set_schedule(self, schedule):
         _check(_lib.fupr_model_set_schedule(self._h, int(schedule)), "fupr_model_set_schedule")
+
+    def fuse_blocks(self, on):
+        _check(_lib.fupr_model_fuse_blocks(self._h, int(on)), "fupr_model_fuse_blocks")
 
     @staticmethod
     def _stats(s):

@@ -82,14 +82,21 @@ __device__ __forceinline__ f32x16 mfma_32x32x16(const uint4& a, const uint4& b, 
 // used: a chain of cache misses of several hundred clocks each at the start of a short kernel.
 template <int BYTES>
 __device__ __forceinline__ void touch_arguments() {
-  static_assert(BYTES > 256 && BYTES <= 320, "five lines");
+  static_assert(BYTES > 256 && BYTES <= 384, "five or six lines");
   int sink;
   // (the loads have landed before the compiler can give the register to anything else)
-  asm volatile(
-      "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
-      "s_load_dword %0, %1, 192\n\ts_load_dword %0, %1, 256\n\ts_waitcnt lgkmcnt(0)"
-      : "=&s"(sink)
-      : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
+  if constexpr (BYTES <= 320)
+    asm volatile(
+        "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
+        "s_load_dword %0, %1, 192\n\ts_load_dword %0, %1, 256\n\ts_waitcnt lgkmcnt(0)"
+        : "=&s"(sink)
+        : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
+  else
+    asm volatile(
+        "s_load_dword %0, %1, 0\n\ts_load_dword %0, %1, 64\n\ts_load_dword %0, %1, 128\n\t"
+        "s_load_dword %0, %1, 192\n\ts_load_dword %0, %1, 256\n\ts_load_dword %0, %1, 320\n\ts_waitcnt lgkmcnt(0)"
+        : "=&s"(sink)
+        : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
 }
 
 // floor(v / d) for 0 <= v < 2^31 as mulhi(v, mul) >> shift with shift =

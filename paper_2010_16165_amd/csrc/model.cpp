@@ -7,10 +7,12 @@
 #include <array>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <vector>
 
+#include "bottleneck.h"
 #include "fupr.h"
 #include "layout.h"
 #include "stem_pool.h"
@@ -23,6 +25,7 @@ namespace {
 // One kernel launch of the per-operator schedule: `count` consecutive operators.
 struct Launch {
   int first, count;
+  bool block = false;   // a bottleneck block (bottleneck.hip)
 };
 
 struct TensorInfo {
@@ -41,6 +44,15 @@ struct fupr_model {
   std::vector<TensorInfo> tensors;        // n_ops + 1
   std::vector<size_t> buffer_elems;       // per image, per workspace buffer
   std::vector<char> pair_planned;         // per operator: the workspace lets it run together with the next one
+  // With fupr_model_fuse_blocks: the same workspace buffers, tensors placed so that what the
+  // operators of a block read outlives the block.
+  bool blocks = false;
+  struct Placement {
+    std::vector<char> planned;            // per operator: operators of the block that starts there, 0: none
+    std::vector<int> buffer;              // per tensor, as TensorInfo::buffer
+  };
+  Placement placed[2];                    // where a block holds the first of a pair of 1 x 1: pair, block
+  std::vector<BottleneckArgs> block_args; // shapes of the block that starts with an operator
   std::vector<Launch> launches[2];        // per schedule, with no tuning switch set
   int schedule = FUPR_SCHEDULE_AUTO;
   bool resident_ok = false;               // the whole network fits one LDS-resident kernel
@@ -519,6 +531,7 @@ void plan_resident(fupr_model* m) {
 
 void release_side(fupr_model* m);   // below, with the forked schedule
 bool conv_conv_pair(const fupr_model* m, size_t i);   // below, with the launch list
+void plan_blocks(fupr_model* m, bool over_pairs);     // likewise
 std::vector<Launch> list_launches(const fupr_model* m, int schedule);
 
 // Sizes of the one-kernel schedule's table: the layer entries, then the tap tables.
@@ -713,6 +726,7 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
   }
   plan_resident(m);
   const WithoutTuning no_switches;
+  for (bool over_pairs : {false, true}) plan_blocks(m, over_pairs);
   for (int schedule : {FUPR_SCHEDULE_AUTO, FUPR_SCHEDULE_PER_LAYER})
     m->launches[schedule] = list_launches(m, schedule);
   *out = m;
@@ -723,6 +737,13 @@ extern "C" fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule) 
   if (!m) return FUPR_ERR_NULL;
   if (schedule != FUPR_SCHEDULE_AUTO && schedule != FUPR_SCHEDULE_PER_LAYER) return FUPR_ERR_ARG;
   m->schedule = schedule;
+  return FUPR_OK;
+}
+
+extern "C" fupr_status fupr_model_fuse_blocks(fupr_model* m, int32_t on) {
+  if (!m) return FUPR_ERR_NULL;
+  if (on != 0 && on != 1) return FUPR_ERR_ARG;
+  m->blocks = on == 1;
   return FUPR_OK;
 }
 
@@ -866,6 +887,151 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
   return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W, shortcut_offset(a));
 }
 
+// Tensor t is read by one operator, as its input, and by nobody else.
+bool read_once(const fupr_model* m, size_t t) {
+  int readers = 0;
+  for (const fupr_op_desc& o : m->ops) {
+    const bool second = o.kind == FUPR_OP_CONV && (o.epilogue & FUPR_FUSE_CAT);
+    readers += (o.in == (int)t) + (o.res == (int)t) + (second && o.in2 == (int)t);
+  }
+  return readers == 1;
+}
+
+// The bottleneck block that starts with operator i: a 3 x 3 convolution, the 1 x 1 convolution of its output
+// that ends a bottleneck block, and, if the next operator is one, the 1 x 1 convolution of that
+// output.  Returns its operators, 0 if there is none.
+int bottleneck_at(const fupr_model* m, size_t i, BottleneckArgs* out) {
+  const size_t n = m->ops.size();
+  if (i + 2 >= n) return 0;            // (the network's output has strides of the caller's choice)
+  const fupr_op_desc &a = m->ops[i], &b = m->ops[i + 1];
+  if (a.kind != FUPR_OP_CONV || b.kind != FUPR_OP_CONV) return 0;
+  if (a.in == 0 || a.res >= 0 || (a.epilogue & ~uint32_t(FUPR_FUSE_RELU)) || b.in != (int)i + 1) return 0;
+  if (b.epilogue & FUPR_FUSE_SCATTER) return 0;
+  BottleneckArgs g{};
+  g.dt = m->dt;
+  g.s1 = a.conv;
+  g.s2 = b.conv;
+  const TensorInfo &tx = m->tensors[a.in], &ty = m->tensors[i + 2];
+  if (!read_once(m, i + 1)) return 0;
+  g.H = tx.H; g.W = tx.W; g.xcs = tx.cs;
+  if (b.epilogue & FUPR_FUSE_CAT) {
+    if (b.res >= 0 || b.in2 == 0) return 0;
+    const TensorInfo& t2 = m->tensors[b.in2];
+    g.two = true;
+    g.H2 = t2.H; g.W2 = t2.W; g.x2cs = t2.cs; g.stride2 = b.in2_spatial_stride;
+  }
+  if (b.res >= 0) {
+    const TensorInfo& tr = m->tensors[b.res];
+    if (b.res == 0 || b.res_spatial_stride != 1 || b.res_c_offset != 0 || tr.H != ty.H || tr.W != ty.W ||
+        tr.C != ty.C)
+      return 0;
+    g.add = true;
+  }
+  g.relu1 = (a.epilogue & FUPR_FUSE_RELU) != 0;
+  g.relu2 = (b.epilogue & FUPR_FUSE_RELU) != 0;
+  g.ycs = ty.cs;
+  int count = 2;
+  if (i + 3 < n && m->ops[i + 2].kind == FUPR_OP_CONV) {
+    const fupr_op_desc& c = m->ops[i + 2];
+    if (c.in == (int)i + 2 && c.res < 0 && !(c.epilogue & ~uint32_t(FUPR_FUSE_RELU))) {
+      BottleneckArgs third = g;
+      third.third = true;
+      third.s3 = c.conv;
+      third.relu3 = (c.epilogue & FUPR_FUSE_RELU) != 0;
+      third.hcs = m->tensors[i + 3].cs;
+      if (bottleneck_applies(third)) {
+        g = third;
+        count = 3;
+      }
+    }
+  }
+  if (count == 2 && !bottleneck_applies(g)) return 0;
+  *out = g;
+  return count;
+}
+
+// Places the tensors anew in the buffers that the workspace has, so that what a block's operators
+// read outlives the block; blocks for which there is no room are not planned.
+// over_pairs: a block that holds the first operator of a planned pair of 1 x 1 convolutions takes its
+// place (the two keep different tensors alive); else the pair stays and the block is not planned.
+void plan_blocks(fupr_model* m, bool over_pairs) {
+  const int n = (int)m->ops.size();
+  fupr_model::Placement& out = m->placed[over_pairs];
+  out.planned.assign(n, 0);
+  out.buffer.clear();
+  m->block_args.assign(n, BottleneckArgs{});
+  for (int i = 0; i < n;) {
+    int count = bottleneck_at(m, (size_t)i, &m->block_args[i]);
+    if (count) m->block_args[i].pair = m->pair_planned[i + 1] != 0;
+    if (!over_pairs && m->block_args[i].pair) count = 0;
+    out.planned[i] = (char)count;
+    i += count ? count : 1;
+  }
+  auto reads = [&](int i, auto&& fn) {
+    const fupr_op_desc& op = m->ops[i];
+    fn(op.in);
+    if (op.res >= 0) fn(op.res);
+    if (op.kind == FUPR_OP_CONV && (op.epilogue & FUPR_FUSE_CAT)) fn(op.in2);
+  };
+  for (;;) {
+    std::vector<int> last(n + 1, -1);
+    std::vector<char> inside(n, 0);      // of an operator: a block holds it
+    for (int i = 0; i < n; ++i) reads(i, [&](int t) { last[t] = i; });
+    for (int i = 0; i < n; ++i)
+      for (int k = 0; k < out.planned[i]; ++k) {
+        inside[i + k] = 1;
+        // (what the block itself makes is read by it alone, in order)
+        reads(i + k, [&](int t) { if (t <= i) last[t] = std::max(last[t], i + out.planned[i] - 1); });
+      }
+    for (int i = 0; i + 1 < n; ++i)
+      if (m->pair_planned[i] && !inside[i]) reads(i, [&](int t) { last[t] = std::max(last[t], i + 1); });
+    // the smallest free buffer that holds the tensor first, the others where that leads nowhere
+    std::vector<int> at(n + 1, -1);
+    int failed = 0, tries = 20000;
+    std::function<bool(int, const std::vector<int>&)> place = [&](int i, const std::vector<int>& held) {
+      if (i == n) return true;
+      if (--tries < 0) return false;
+      failed = std::max(failed, i);
+      const int tid = i + 1;
+      const TensorInfo& t = m->tensors[tid];
+      const size_t need = (size_t)t.H * t.W * t.cs;
+      std::vector<int> choices;
+      if (tid == n) {
+        choices.push_back(-2);
+      } else if (m->ops[i].kind == FUPR_OP_CONV && (m->ops[i].epilogue & FUPR_FUSE_SCATTER)) {
+        choices.push_back(at[m->ops[i].res]);
+      } else {
+        for (int b = 0; b < (int)held.size(); ++b)
+          if (held[b] < 0 && m->buffer_elems[b] >= need) choices.push_back(b);
+        std::stable_sort(choices.begin(), choices.end(),
+                         [&](int x, int y) { return m->buffer_elems[x] < m->buffer_elems[y]; });
+      }
+      for (int b : choices) {
+        std::vector<int> after = held;
+        if (b >= 0) after[b] = tid;
+        for (int& h : after)
+          if (h >= 0 && h != tid && last[h] <= i) h = -1;
+        at[tid] = b;
+        if (place(i + 1, after)) return true;
+      }
+      return false;
+    };
+    if (place(0, std::vector<int>(m->buffer_elems.size(), -1))) {
+      out.buffer = at;
+      return;
+    }
+    // no way past operator `failed`: the last block that starts at or before it keeps too much alive
+    int drop = -1;
+    for (int i = 0; i <= failed; ++i)
+      if (out.planned[i]) drop = i;
+    if (drop < 0) {                      // (the first plan's placement is not this one's)
+      out.planned.assign(n, 0);
+      return;
+    }
+    out.planned[drop] = 0;
+  }
+}
+
 std::vector<Launch> list_launches(const fupr_model* m, int schedule) {
   std::vector<Launch> v;
   for (size_t i = 0; i < m->ops.size();) {
@@ -884,14 +1050,46 @@ std::vector<Launch> launches_of(const fupr_model* m) {
   return tuning_any() ? list_launches(m, m->schedule) : m->launches[m->schedule];
 }
 
+// Blocks run as one launch where the workspace was placed for it.  For a batch of N images: the placement with blocks over pairs if one of those blocks is wanted.
+const fupr_model::Placement* blocks_on(const fupr_model* m, int N) {
+  if (!m->blocks || m->schedule != FUPR_SCHEDULE_AUTO) return nullptr;
+  const fupr_model::Placement &pairs = m->placed[0], &over = m->placed[1];
+  for (size_t i = 0; i < over.planned.size(); ++i)
+    if (over.planned[i] && !pairs.planned[i] && bottleneck_wanted(m->block_args[i], N))
+      return over.buffer.empty() ? nullptr : &over;
+  return pairs.buffer.empty() ? nullptr : &pairs;
+}
+
 // The launches of a batch of N images.  Of a pair of 1 x 1 convolutions whose tensors are small, two
 // launches that fill the GPU are faster than one that walks it (nine images of 193 x 193, 49 x 49
 // pixels, 47 -> 256 -> 111 channels: 18 us in one, 12 in two; a launch more costs 1.7).
 std::vector<Launch> launches_at(const fupr_model* m, int N) {
   std::vector<Launch> v = launches_of(m);
+  if (const fupr_model::Placement* placed = blocks_on(m, N)) {
+    // pairs of 1 x 1 convolutions that share an operator with a planned block are not kept apart
+    std::vector<char> inside(m->ops.size(), 0);
+    for (size_t i = 0; i < m->ops.size(); ++i)
+      for (int k = 0; k < placed->planned[i]; ++k) inside[i + k] = 1;
+    std::vector<Launch> with;
+    size_t next = 0;
+    for (const Launch& l : v)
+      for (int k = 0; k < l.count; ++k) {
+        const size_t i = (size_t)l.first + k;
+        if (i < next) continue;
+        if (placed->planned[i] && bottleneck_wanted(m->block_args[i], N)) {
+          with.push_back(Launch{(int)i, placed->planned[i], true});
+        } else if (k == 0 && l.count == 2 && !(m->ops[i + 1].kind == FUPR_OP_CONV && (inside[i] || inside[i + 1]))) {
+          with.push_back(l);
+        } else {
+          with.push_back(Launch{(int)i, 1});
+        }
+        next = i + with.back().count;
+      }
+    v = with;
+  }
   for (size_t i = 0; i < v.size(); ++i) {
     const Launch l = v[i];
-    if (l.count != 2 || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
+    if (l.count != 2 || l.block || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
     const fupr_op_desc& op = m->ops[l.first];
     const TensorInfo& x = m->tensors[op.in];
     const bool cat = (op.epilogue & FUPR_FUSE_CAT) != 0;
@@ -965,20 +1163,22 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
   // images n0 .. n0 + count - 1 of a tensor; inside a workspace buffer every
   // sub-batch owns the slice its images would need at the buffer's largest tensor
   const size_t es = elem_size(m->dt);
+  const fupr_model::Placement* placed = blocks_on(m, N);
   auto view = [&](int tid, int n0, int count) {
     const TensorInfo& t = m->tensors[tid];
+    const int buffer = placed ? placed->buffer[tid] : t.buffer;
     fupr_tensor v;
     v.N = count; v.H = t.H; v.W = t.W; v.C = t.C; v.dt = m->dt;
     char* ptr;
-    if (t.buffer == -1) {
+    if (buffer == -1) {
       v.c_stride = input->c_stride;
       ptr = (char*)input->ptr + (size_t)n0 * t.H * t.W * input->c_stride * es;
-    } else if (t.buffer == -2) {
+    } else if (buffer == -2) {
       v.c_stride = output->c_stride;
       ptr = (char*)output->ptr + (size_t)n0 * t.H * t.W * output->c_stride * es;
     } else {
       v.c_stride = t.cs;
-      ptr = base[t.buffer] + (size_t)n0 * m->buffer_elems[t.buffer] * es;
+      ptr = base[buffer] + (size_t)n0 * m->buffer_elems[buffer] * es;
     }
     v.ptr = ptr;
     return v;
@@ -1005,7 +1205,24 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
       const fupr_tensor x = view(op.in, n0, count);
       const fupr_tensor y = view((int)i + launches[l].count, n0, count);
       fupr_status st;
-      if (launches[l].count == 2 && m->ops[i + 1].kind == FUPR_OP_CONV) {
+      if (launches[l].block) {
+        BottleneckArgs g = m->block_args[i];
+        const fupr_op_desc& b = m->ops[i + 1];
+        g.x = x.ptr;
+        g.packed1 = op.packed;
+        g.packed2 = b.packed;
+        g.y = view((int)i + 2, n0, count).ptr;
+        if (g.two) g.x2 = view(b.in2, n0, count).ptr;
+        if (g.add) g.res = view(b.res, n0, count).ptr;
+        if (g.third) {
+          g.packed3 = m->ops[i + 2].packed;
+          g.h = y.ptr;
+        }
+        st = FUPR_OK;
+        for (const void* blob : {g.packed1, g.packed2, g.packed3})
+          if ((reinterpret_cast<uintptr_t>(blob) & 255u) != 0) st = FUPR_ERR_ALIGN;
+        if (st == FUPR_OK) st = launch_bottleneck(g, N, count, on);
+      } else if (launches[l].count == 2 && m->ops[i + 1].kind == FUPR_OP_CONV) {
         const fupr_op_desc& second = m->ops[i + 1];
         const fupr_tensor mid = view((int)i + 1, n0, count);
         fupr_residual r;
@@ -1184,6 +1401,21 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
     fupr_status st = fupr_model_op_stats(m, batch, l.first, out);
     if (st != FUPR_OK || l.count == 1) return st;
     out->n_ops = l.count;
+    if (l.block) {
+      // the operators of a block in one kernel: the 3 x 3 convolution's output is not written, the
+      // block's output is not read back
+      const double es = (double)elem_size(m->dt);
+      for (int k = 1; k < l.count; ++k) {
+        fupr_op_stats o;
+        st = fupr_model_op_stats(m, batch, l.first + k, &o);
+        if (st != FUPR_OK) return st;
+        const TensorInfo& t = m->tensors[l.first + k];
+        out->flops += o.flops;
+        out->bytes += o.bytes - (k == 1 ? 2.0 : 1.0) * es * batch * (double)t.H * t.W * t.C;
+      }
+      out->kernel = bottleneck_name(m->block_args[l.first], batch);
+      return FUPR_OK;
+    }
     if (m->ops[l.first + 1].kind == FUPR_OP_CONV) {
       // two convolutions in one kernel: both outputs are written, the first one's
       // is not read back

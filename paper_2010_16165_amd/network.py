@@ -244,6 +244,8 @@ def build(plan, device="cuda:0", base_address=None):
             else:
                 cur = conv_op(first + n - 1, h, res, rss, 0)
     model = B.Model(dt, plan["in_shape"], ops, keepalive=[dev], device=device)
+    if base_address is None:
+        model.fuse_blocks(True)
     model.sites = sites
     model.plan = plan
     return model, sites

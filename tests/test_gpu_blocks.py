@@ -1,0 +1,144 @@
+"""GPU tests of the launches that hold a whole block: against a plain float64
+evaluation that rounds where tensors are stored, and against one kernel per operator."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fx():
+    import torch
+    from paper_2010_16165_amd import binding as B
+    assert torch.cuda.is_available()
+    return B, torch
+
+
+class Net:
+    """Operators with seeded weights, their float64 evaluation, and a model of them."""
+
+    def __init__(self, fx, dtype, n, in_shape, seed):
+        self.B, self.torch = fx
+        self.dtype, self.dt, self.n, self.in_shape = dtype, self.B.DTYPES[dtype], n, in_shape
+        self.rng = np.random.default_rng(seed)
+        c, h, w = in_shape
+        x = np.maximum(self.rng.standard_normal((n, c, h, w)), 0).astype(np.float32)
+        self.x, self.ops, self.blobs = x, [], []
+        self.tensors = [self.stored(self.torch.from_numpy(x).double())]
+
+    def stored(self, v):
+        t = {"bf16": self.torch.bfloat16, "f16": self.torch.float16, "f32": self.torch.float32}[self.dtype]
+        return v.to(t).double()
+
+    def conv(self, tin, k, r, stride=1, add=-1, cat=-1, cat_stride=1, relu=True, add_stride=1, add_at=0):
+        B, torch = self.B, self.torch
+        a = self.tensors[tin]
+        c = a.shape[1]
+        if cat >= 0:
+            # the channels between the two tensors are zeros of the first, with zero weights
+            split = (c + B.CAT_ALIGN - 1) // B.CAT_ALIGN * B.CAT_ALIGN
+            b = self.tensors[cat][:, :, ::cat_stride, ::cat_stride][:, :, :a.shape[2], :a.shape[3]]
+            a = torch.cat([torch.nn.functional.pad(a, (0, 0, 0, 0, 0, split - c)), b], 1)
+        w = (self.rng.standard_normal((k, a.shape[1], r, r)) * np.sqrt(2.0 / (a.shape[1] * r * r))).astype(np.float32)
+        if cat >= 0:
+            w[:, c:split] = 0.0
+        bias = (self.rng.standard_normal(k) * 0.1).astype(np.float32)
+        shape = B.shape_of(w, stride, r // 2)
+        self.blobs.append(B.upload_blob(B.fupr_pack(shape, w, bias, self.dt)))
+        v = torch.nn.functional.conv2d(a, self.stored(torch.from_numpy(w).double()),
+                                       torch.from_numpy(bias).double(), stride, r // 2)
+        if add >= 0:
+            r = self.tensors[add][:, :, ::add_stride, ::add_stride][:, :, :v.shape[2], :v.shape[3]]
+            v[:, add_at:add_at + r.shape[1]] += r
+        self.tensors.append(self.stored(torch.relu(v) if relu else v))
+        flags = (B.FUSE_RELU if relu else 0) | (B.FUSE_ADD if add >= 0 else 0) | (B.FUSE_CAT if cat >= 0 else 0)
+        self.ops.append(B.OpDesc(B.OP_CONV, tin, add, shape, self.blobs[-1].data_ptr(), flags, add_stride, add_at, None,
+                                 cat, cat_stride if cat >= 0 else 0))
+        return len(self.ops)
+
+    def check(self, tile_switch, tile, expect, takes=True):
+        """The forced tile runs as one launch of `expect` if it takes the shape; the network's output
+        against both references."""
+        B, torch = self.B, self.torch
+        m = B.Model(self.dt, self.in_shape, self.ops, self.blobs)
+        m.fuse_blocks(True)
+        B.fupr_tuning_set(tile_switch, tile)
+        try:
+            kernels = [m.launch_stats(self.n, i)["kernel"] for i in range(m.num_launches_at(self.n))]
+            assert sum(k.startswith(expect) for k in kernels) == takes, kernels
+            print(self.dtype, self.n, self.in_shape, kernels, flush=True)
+            xd = B.DeviceTensor.from_nchw(self.x, self.dt)
+            out, ws = m.alloc(self.n)
+            ws.fill_(255)              # NaN wherever nothing is written
+            out.data.fill_(7.0)
+            m.fupr_forward(xd, out, ws)
+            torch.cuda.synchronize()
+            got = torch.from_numpy(np.ascontiguousarray(out.to_nchw())).double()
+            assert out.padding_is_zero()
+            again, ws2 = m.alloc(self.n)
+            ws2.fill_(255)
+            m.fupr_forward(xd, again, ws2)
+            m.set_schedule(B.SCHEDULE_PER_LAYER)
+            apart, _ = m.alloc(self.n)
+            m.fupr_forward(xd, apart, ws)
+            torch.cuda.synchronize()
+            assert torch.equal(out.data, again.data)
+        finally:
+            B.fupr_tuning_set(tile_switch, None)
+        # A stored value may round the other way after sums in another order.  Were every rounding of the
+        # two evaluations independent (2^-8 or 2^-11 of the value at most, 0.29 of that in the mean
+        # square), the nine stored tensors of a chain would add up to sqrt(2 * 9) * 0.29 = 1.2 units.
+        unit = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11, "f32": 2.0 ** -20}[self.dtype]
+        want = self.tensors[-1]
+        other = torch.from_numpy(np.ascontiguousarray(apart.to_nchw())).double()
+        for ref in (want, other):
+            assert float((got - ref).norm() / ref.norm()) <= 1.5 * unit
+            assert float((got - ref).abs().max()) <= 4 * unit * float(ref.abs().max())
+
+
+# dtype, images, rows, columns, channels in, 3 x 3 filters, its stride, wide filters, next filters (0: none),
+# how the block's input comes back: added, concatenated, or not at all
+BOTTLENECKS = [
+    ("bf16", 2, 9, 11, 24, 32, 1, 128, 32, "add"),        # less than a group of filters, one pair of tiles
+    ("f16", 1, 1, 1, 8, 16, 1, 16, 16, "none"),           # smallest there is: one pixel, one tile of filters
+    ("bf16", 3, 7, 7, 77, 45, 1, 300, 51, "add"),         # ragged channels everywhere, tiles across images
+    ("f16", 1, 15, 13, 40, 102, 2, 264, 130, "cat"),      # stride 2, two tensors, last group nearly empty
+    ("bf16", 2, 14, 14, 128, 128, 1, 512, 100, "cat"),
+    ("f16", 2, 5, 40, 96, 144, 1, 272, 240, "add"),       # more than 128 filters in the 3 x 3
+    ("bf16", 1, 8, 8, 64, 64, 1, 256, 0, "add"),          # nothing behind the block
+    ("f16", 2, 6, 6, 136, 240, 2, 320, 300, "cat"),
+]
+
+
+TILES = [(1, 8), (2, 8), (4, 8), (2, 4), (4, 4)]      # tiles of 16 pixels, waves
+
+
+@pytest.mark.parametrize("tile", range(len(TILES)))
+@pytest.mark.parametrize("case", BOTTLENECKS, ids=lambda c: "-".join(map(str, c)))
+def test_bottleneck_block(fx, case, tile):
+    dtype, n, h, w, c, k1, stride, k2, k3, back = case
+    wide = k2 if back == "add" else 56
+    net = Net(fx, dtype, n, (16, h, w), seed=sum(case[1:9]) + tile)
+    # (tensors that live side by side, so that the workspace has buffers for the block's five)
+    t = [net.conv(0, 512, 1) for _ in range(4)]
+    t_in = net.conv(net.conv(t[0], 512, 1, add=t[1]), 512, 1, add=net.conv(t[2], 512, 1, add=t[3]))
+    t_in = net.conv(t_in, wide, 1)            # the block's input
+    t_x = net.conv(t_in, c, 1)
+    if back == "add" and stride == 1:
+        t_mid = net.conv(t_x, k1, 3)
+        t_y = net.conv(t_mid, k2, 1, add=t_in)
+    elif back == "cat":
+        t_mid = net.conv(t_x, k1, 3, stride)
+        t_y = net.conv(t_mid, k2, 1, cat=t_in, cat_stride=stride)
+    else:
+        t_mid = net.conv(t_x, k1, 3, stride)
+        t_y = net.conv(t_mid, k2, 1)
+    if k3:
+        t_h = net.conv(t_y, k3, 1)
+        net.conv(t_h, 24, 1, cat=t_y)          # reads both tensors that the launch writes
+    else:
+        net.conv(t_y, 24, 3)
+    # what a wave can hold: 32 filters of the 3 x 3 convolution, eight tiles of the third
+    mt, waves = TILES[tile]
+    per_wave = -(-(-(-k3 // 16)) // waves)
+    net.check("bottleneck_tile", tile, "bottleneck_", k1 <= 32 * waves and mt * (4 if per_wave > 2 else per_wave) <= 8)

@@ -641,6 +641,42 @@ def test_largest_workload_pairs_its_first_stage_output_with_the_next_convolution
         B.fupr_tuning_set("pair_filters", None)
 
 
+def test_blocks_run_as_one_launch_only_when_asked_for():
+    """fupr_model_fuse_blocks changes the launches of a batch, never the list without a batch or the
+    workspace; what a launch covers and does adds up to the operators."""
+    model, _ = synth.make_config(3)
+    m, _ = build_host_model(network.optimise(model), 1 << 20)
+    m2, _ = build_host_model(network.optimise(model), 1 << 20)
+    assert B._lib.fupr_model_fuse_blocks(None, 1) == B.ERR_NULL
+    assert B._lib.fupr_model_fuse_blocks(m._h, 2) == B.ERR_ARG
+    m.fuse_blocks(True)
+    assert m.num_launches == m2.num_launches
+    covered = set()
+    for batch in (1, 3, 9, 24, 64, 256):
+        assert m.workspace_bytes(batch) == m2.workspace_bytes(batch)
+        launches = [m.launch_stats(batch, i) for i in range(m.num_launches_at(batch))]
+        single = [m.op_stats(batch, i) for i in range(m.num_ops)]
+        assert [i for s in launches for i in range(s["first_op"], s["first_op"] + s["n_ops"])] == list(range(m.num_ops))
+        assert sum(s["flops"] for s in launches) == sum(s["flops"] for s in single)
+        blocks = [s for s in launches if s["kernel"].startswith("bottleneck_")]
+        covered |= {s["first_op"] for s in blocks}
+        for s in blocks:
+            a, b = s["first_op"], s["first_op"] + 1
+            assert single[a]["R"] == 3 and single[b]["R"] == 1
+            mid, y = ([2 * single[i]["M"] * single[i]["K"] for i in (a, b)])
+            assert s["bytes"] == sum(single[i]["bytes"] for i in range(a, a + s["n_ops"])) - 2 * mid - y * (s["n_ops"] - 2)
+        assert blocks and m2.num_launches_at(batch) == m.num_launches_at(batch) + sum(s["n_ops"] - 1 for s in blocks) \
+            - sum(s["n_ops"] == 2 and s["kernel"].startswith("conv1x1s") for s in
+                  (m2.launch_stats(batch, i) for i in range(m2.num_launches_at(batch)))) \
+            + sum(s["n_ops"] == 2 and s["kernel"].startswith("conv1x1s") for s in launches)
+    assert len(covered) >= 12         # of 16 blocks, at one batch or another
+    m.set_schedule(B.SCHEDULE_PER_LAYER)
+    assert m.num_launches_at(9) == m.num_ops
+    m.set_schedule(B.SCHEDULE_AUTO)
+    m.fuse_blocks(False)
+    assert m.num_launches_at(9) == m2.num_launches_at(9)
+
+
 def launch_list(m, batch):
     return [(s["first_op"], s["n_ops"], s["kernel"]) for s in (m.launch_stats(batch, i) for i in range(m.num_launches))]
 
