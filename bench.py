@@ -84,6 +84,8 @@ def group_of_device_kernel(name):
         return ("conv" if num(1) == 1 else "conv1x1p") + tile
     if fn == "bottleneck_kernel":   # <type, pixel tiles, waves, ...>
         return f"bottleneck_{num(1) * 16}x{num(2) * 32}"
+    if fn == "basic_block_kernel":
+        return "basic_block"        # (its rectangle is an argument)
     return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)
@@ -168,6 +170,8 @@ def measured_traffic(config, kernel, default_shape, kernels):
         return None
     want = sources_hash()
     joint = re.sub(r"^(conv3x3p|conv16t)_w", "conv_w", kernel)
+    if kernel.startswith("basic_block_") and sum(k.startswith("basic_block_") for k in kernels) == 1:
+        kernel = "basic_block"
     if joint != kernel and sum(re.sub(r"^(conv3x3p|conv16t)_w", "conv_w", k) == joint for k in kernels) == 1:
         kernel = joint
     with open(TRAFFIC_TABLE) as f:

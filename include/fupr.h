@@ -443,14 +443,17 @@ enum { FUPR_SCHEDULE_AUTO = 0, FUPR_SCHEDULE_PER_LAYER = 1 };
 fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule);
 
 /*
- * on = 1: AUTO also runs the last operators of a bottleneck block as ONE kernel at
- * the batch sizes where that is faster: a 3 x 3 convolution, the 1 x 1 convolution of
- * its output (with the shortcut, or over two tensors) and, where it follows, the 1 x 1
- * convolution of that output, 16-bit types, tensors of the workspace only.  0 (the
- * default): never.  The workspace is as large either way; what its buffers hold in
- * between differs, so the setting belongs before the first forward pass or capture
- * and between passes, not beside one.  fupr_model_num_launches does not count blocks
- * as one launch; fupr_model_num_launches_at does.  Errors: NULL, ARG (on not 0 or 1).
+ * on = 1: AUTO also runs operators of a residual block as ONE kernel at the batch
+ * sizes where that is faster: of a bottleneck block the 3 x 3 convolution, the
+ * 1 x 1 convolution of its output (with the shortcut, or over two tensors) and,
+ * where it follows, the 1 x 1 convolution of that output (16-bit types, tensors of
+ * the workspace only); of a basic block both 3 x 3 convolutions.  0 (the default):
+ * never.  The workspace is as large either way; what its buffers hold in between
+ * differs, so the setting belongs before the first forward pass or capture and
+ * between passes, not beside one.  fupr_model_num_launches does not count blocks as
+ * one launch; fupr_model_num_launches_at does.  Where they are placed is worked out
+ * at the first pass of a batch size and kept by the model (host memory, at most 256
+ * batch sizes).  Errors: NULL, ARG (on not 0 or 1).
  */
 fupr_status fupr_model_fuse_blocks(fupr_model* m, int32_t on);
 
@@ -613,8 +616,10 @@ void fupr_graph_destroy(fupr_graph* g);
  *                                                 workgroups per compute unit
  *   pair_filters = 16..128                        most filters of the second convolution of a pair of
  *                                                 1 x 1 convolutions in one launch
- *   bottleneck_fuse = 0                           blocks of fupr_model_fuse_blocks as several launches
- *   bottleneck_tile = <index>                     force a tile of the kernel that runs them
+ *   bottleneck_fuse, basic_fuse = 0               blocks of fupr_model_fuse_blocks as several launches
+ *   bottleneck_tile = <index>                     force a tile of the kernel that runs bottleneck blocks
+ *   basic_tile = <rectangle>x<f>                  force a rectangle of the kernel that runs basic blocks,
+ *                                                 f waves along the filters (a power of two, up to 8)
  *   split = 1..4                                  sub-batches of the per-operator schedule
  *   res_item = "M/FT/nsteps:MTxNT,..."            work-item shapes of the one-kernel schedule
  *   debug = 1                                     planner decisions and HIP error text on stderr

@@ -11,10 +11,10 @@ LIB = os.path.join(HERE, "libfupr.so")
 MEASURE_DIR = os.path.join(HERE, "measure")
 MEASURE_LIB = os.path.join(MEASURE_DIR, "libfupr_measure.so")
 SOURCES = ["host_passes.cpp", "tuning.cpp", "kernels.hip", "conv_tiled.hip", "conv_patch.hip", "conv_window.hip",
-           "stem_pool.hip", "bottleneck.hip", "conv1x1.hip", "conv1x1_pipe.hip", "resident.hip", "model.cpp",
+           "stem_pool.hip", "bottleneck.hip", "basic_block.hip", "conv1x1.hip", "conv1x1_pipe.hip", "resident.hip", "model.cpp",
            "static_workspace.hip"]
 HEADERS = [os.path.join(ROOT, "include", "fupr.h")] + [
-    os.path.join(CSRC, h) for h in ("layout.h", "device_utils.h", "conv16.h", "stem_pool.h", "bottleneck.h",
+    os.path.join(CSRC, h) for h in ("layout.h", "device_utils.h", "conv16.h", "stem_pool.h", "bottleneck.h", "basic_block.h",
                                     "tuning.h", "window_patch.h")]
 MEASURE_SOURCES = [os.path.join(MEASURE_DIR, "peaks.hip")]
 MEASURE_HEADERS = [os.path.join(ROOT, "include", "fupr_measure.h")]

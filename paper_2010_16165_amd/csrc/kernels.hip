@@ -535,6 +535,11 @@ extern "C" fupr_status fupr_conv_cat_fused(const fupr_conv_shape* shape, const f
   return st != FUPR_OK ? st : launch_conv(a, stream);
 }
 
+fupr_status fupr::conv_args(const fupr_conv_shape* shape, const fupr_tensor* x, const void* packed,
+                            const fupr_residual* res, uint32_t flags, const fupr_tensor* y, ConvArgs* out) {
+  return check_conv(shape, x, packed, res, flags, y, out);
+}
+
 fupr_status fupr::conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
                                   int32_t x2_stride, const void* packed, const fupr_residual* res,
                                   uint32_t flags, const fupr_tensor* y, int plan_N, void* stream) {

@@ -82,6 +82,9 @@ const char* conv_kernel_name(const fupr_conv_shape& s, fupr_dtype dt, int N, int
 fupr_status conv_fused_part(const fupr_conv_shape* shape, const fupr_tensor* x, const fupr_tensor* x2,
                             int32_t x2_stride, const void* packed, const fupr_residual* res,
                             uint32_t flags, const fupr_tensor* y, int plan_N, void* stream);
+// What fupr_conv_fused checks, and the launcher's arguments of a call that passes.
+fupr_status conv_args(const fupr_conv_shape* shape, const fupr_tensor* x, const void* packed,
+                      const fupr_residual* res, uint32_t flags, const fupr_tensor* y, ConvArgs* out);
 // fupr_conv_scatter_fused likewise.
 fupr_status conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x, const void* packed,
                               const int32_t* keep_idx, uint32_t flags, const fupr_tensor* y, int plan_N,

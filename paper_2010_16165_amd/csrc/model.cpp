@@ -8,10 +8,13 @@
 #include <cstdio>
 #include <cstdlib>
 #include <functional>
+#include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
 
+#include "basic_block.h"
 #include "bottleneck.h"
 #include "fupr.h"
 #include "layout.h"
@@ -23,9 +26,11 @@ using namespace fupr;
 namespace {
 
 // One kernel launch of the per-operator schedule: `count` consecutive operators.
+enum { kBottleneck = 1, kBasic = 2 };   // bottleneck.hip, basic_block.hip
+
 struct Launch {
   int first, count;
-  bool block = false;   // a bottleneck block (bottleneck.hip)
+  int block = 0;        // kBottleneck or kBasic: a block in one launch
 };
 
 struct TensorInfo {
@@ -44,15 +49,23 @@ struct fupr_model {
   std::vector<TensorInfo> tensors;        // n_ops + 1
   std::vector<size_t> buffer_elems;       // per image, per workspace buffer
   std::vector<char> pair_planned;         // per operator: the workspace lets it run together with the next one
-  // With fupr_model_fuse_blocks: the same workspace buffers, tensors placed so that what the
-  // operators of a block read outlives the block.
-  bool blocks = false;
+  bool blocks = false;                    // fupr_model_fuse_blocks
+  // Blocks as one launch at a batch size: the same workspace buffers, tensors placed in them so that
+  // what a block reads outlives the block.  Made at the first pass of that many images and kept.
   struct Placement {
-    std::vector<char> planned;            // per operator: operators of the block that starts there, 0: none
-    std::vector<int> buffer;              // per tensor, as TensorInfo::buffer
+    std::vector<Launch> launches;
+    std::vector<int> buffer;              // per tensor, as TensorInfo::buffer; -3: not needed
   };
-  Placement placed[2];                    // where a block holds the first of a pair of 1 x 1: pair, block
-  std::vector<BottleneckArgs> block_args; // shapes of the block that starts with an operator
+  std::map<int, std::shared_ptr<const Placement>> placed;
+  std::mutex placed_mutex;
+  // shapes of the block that starts with an operator
+  struct Block {
+    int kind;                             // kBottleneck, kBasic, or 0
+    int count;                            // its operators
+    BottleneckArgs bottleneck;
+    BasicBlockArgs basic;
+  };
+  std::vector<Block> block_args;
   std::vector<Launch> launches[2];        // per schedule, with no tuning switch set
   int schedule = FUPR_SCHEDULE_AUTO;
   bool resident_ok = false;               // the whole network fits one LDS-resident kernel
@@ -531,7 +544,7 @@ void plan_resident(fupr_model* m) {
 
 void release_side(fupr_model* m);   // below, with the forked schedule
 bool conv_conv_pair(const fupr_model* m, size_t i);   // below, with the launch list
-void plan_blocks(fupr_model* m, bool over_pairs);     // likewise
+void find_blocks(fupr_model* m);                      // likewise
 std::vector<Launch> list_launches(const fupr_model* m, int schedule);
 
 // Sizes of the one-kernel schedule's table: the layer entries, then the tap tables.
@@ -726,7 +739,7 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
   }
   plan_resident(m);
   const WithoutTuning no_switches;
-  for (bool over_pairs : {false, true}) plan_blocks(m, over_pairs);
+  find_blocks(m);
   for (int schedule : {FUPR_SCHEDULE_AUTO, FUPR_SCHEDULE_PER_LAYER})
     m->launches[schedule] = list_launches(m, schedule);
   *out = m;
@@ -950,43 +963,98 @@ int bottleneck_at(const fupr_model* m, size_t i, BottleneckArgs* out) {
   return count;
 }
 
-// Places the tensors anew in the buffers that the workspace has, so that what a block's operators
-// read outlives the block; blocks for which there is no room are not planned.
-// over_pairs: a block that holds the first operator of a planned pair of 1 x 1 convolutions takes its
-// place (the two keep different tensors alive); else the pair stays and the block is not planned.
-void plan_blocks(fupr_model* m, bool over_pairs) {
-  const int n = (int)m->ops.size();
-  fupr_model::Placement& out = m->placed[over_pairs];
-  out.planned.assign(n, 0);
-  out.buffer.clear();
-  m->block_args.assign(n, BottleneckArgs{});
-  for (int i = 0; i < n;) {
-    int count = bottleneck_at(m, (size_t)i, &m->block_args[i]);
-    if (count) m->block_args[i].pair = m->pair_planned[i + 1] != 0;
-    if (!over_pairs && m->block_args[i].pair) count = 0;
-    out.planned[i] = (char)count;
-    i += count ? count : 1;
+// The basic block that starts with operator i: two 3 x 3 convolutions, the second of the first one's
+// output.  Returns its operators, 0 if there is none.
+int basic_block_at(const fupr_model* m, size_t i, BasicBlockArgs* out) {
+  const size_t n = m->ops.size();
+  if (i + 1 >= n) return 0;
+  const fupr_op_desc &a = m->ops[i], &b = m->ops[i + 1];
+  if (a.kind != FUPR_OP_CONV || b.kind != FUPR_OP_CONV) return 0;
+  if (a.res >= 0 || (a.epilogue & ~uint32_t(FUPR_FUSE_RELU)) || b.in != (int)i + 1 || b.res == (int)i + 1) return 0;
+  if (b.epilogue & ~uint32_t(FUPR_FUSE_RELU | FUPR_FUSE_ADD)) return 0;
+  if (!read_once(m, i + 1)) return 0;
+  const TensorInfo& tx = m->tensors[a.in];
+  BasicBlockArgs g{};
+  g.dt = m->dt;
+  g.s1 = a.conv;
+  g.s2 = b.conv;
+  g.H = tx.H;
+  g.W = tx.W;
+  g.add = b.res >= 0;
+  if (!basic_block_applies(g)) return 0;
+  *out = g;
+  return 2;
+}
+
+// Whether a batch of N images runs the block that starts with operator i as one launch.
+bool block_wanted(const fupr_model* m, size_t i, int N) {
+  const fupr_model::Block& b = m->block_args[i];
+  if (b.kind == kBottleneck) return bottleneck_wanted(b.bottleneck, N);
+  if (b.kind != kBasic) return false;
+  // 32-bit byte offsets into every tensor
+  for (int t : {m->ops[i].in, (int)i + 2, std::max(m->ops[i + 1].res, 0)}) {
+    const TensorInfo& ti = m->tensors[t];
+    if ((int64_t)N * ti.H * ti.W * ti.cs * (int64_t)elem_size(m->dt) >= (int64_t(1) << 31)) return false;
   }
+  return basic_block_wanted(b.basic, N);
+}
+
+void find_blocks(fupr_model* m) {
+  const int n = (int)m->ops.size();
+  m->block_args.assign(n, fupr_model::Block{});
+  for (int i = 0; i < n; ++i) {
+    fupr_model::Block& b = m->block_args[i];
+    if ((b.count = bottleneck_at(m, (size_t)i, &b.bottleneck)) > 0) {
+      b.kind = kBottleneck;
+      b.bottleneck.pair = m->pair_planned[i + 1] != 0;
+    } else if ((b.count = basic_block_at(m, (size_t)i, &b.basic)) > 0) {
+      b.kind = kBasic;
+    }
+  }
+}
+
+// Places the tensors anew in the buffers that the workspace has, for a batch of N images whose wanted
+// blocks run as one launch each; blocks for which there is no room do not.  Empty if there is no block.
+std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, int N) {
+  const int n = (int)m->ops.size();
+  auto out = std::make_shared<fupr_model::Placement>();
+  std::vector<char> chosen(n, 0);          // operators of the block that starts there
+  bool any = false;
+  for (int i = 0; i < n; i += chosen[i] ? chosen[i] : 1)
+    if (block_wanted(m, (size_t)i, N)) {
+      chosen[i] = (char)m->block_args[i].count;
+      any = true;
+    }
   auto reads = [&](int i, auto&& fn) {
     const fupr_op_desc& op = m->ops[i];
     fn(op.in);
     if (op.res >= 0) fn(op.res);
     if (op.kind == FUPR_OP_CONV && (op.epilogue & FUPR_FUSE_CAT)) fn(op.in2);
   };
-  for (;;) {
+  while (any) {
+    // the launches, and the last operator that reads each tensor
     std::vector<int> last(n + 1, -1);
-    std::vector<char> inside(n, 0);      // of an operator: a block holds it
-    for (int i = 0; i < n; ++i) reads(i, [&](int t) { last[t] = i; });
-    for (int i = 0; i < n; ++i)
-      for (int k = 0; k < out.planned[i]; ++k) {
-        inside[i + k] = 1;
-        // (what the block itself makes is read by it alone, in order)
-        reads(i + k, [&](int t) { if (t <= i) last[t] = std::max(last[t], i + out.planned[i] - 1); });
+    std::vector<char> hidden(n + 1, 0);    // tensors that stay inside a launch
+    out->launches.clear();
+    for (int i = 0; i < n;) {
+      Launch l{i, 1};
+      if (chosen[i]) {
+        l = Launch{i, chosen[i], m->block_args[i].kind};
+        // (a block on the caller's own tensors can turn out to be two launches: their sizes and places
+        // are known when it runs)
+        hidden[i + 1] = m->ops[i].in != 0 && m->ops[i + 1].res != 0 && i + 2 != n;
+      } else if (i + 1 < n && !chosen[i + 1] && (m->pair_planned[i] || stem_pool_pair(m, (size_t)i))) {
+        l.count = 2;
       }
-    for (int i = 0; i + 1 < n; ++i)
-      if (m->pair_planned[i] && !inside[i]) reads(i, [&](int t) { last[t] = std::max(last[t], i + 1); });
-    // the smallest free buffer that holds the tensor first, the others where that leads nowhere
-    std::vector<int> at(n + 1, -1);
+      const bool together = l.block || m->pair_planned[i];
+      for (int k = 0; k < l.count; ++k)
+        reads(i + k, [&](int t) { last[t] = std::max(last[t], together && t <= i ? i + l.count - 1 : i + k); });
+      out->launches.push_back(l);
+      i += l.count;
+    }
+    // the smallest free buffer that holds a tensor first, the others where that leads nowhere
+    out->buffer.assign(n + 1, -3);
+    out->buffer[0] = -1;
     int failed = 0, tries = 20000;
     std::function<bool(int, const std::vector<int>&)> place = [&](int i, const std::vector<int>& held) {
       if (i == n) return true;
@@ -998,8 +1066,10 @@ void plan_blocks(fupr_model* m, bool over_pairs) {
       std::vector<int> choices;
       if (tid == n) {
         choices.push_back(-2);
+      } else if (hidden[tid]) {
+        choices.push_back(-3);
       } else if (m->ops[i].kind == FUPR_OP_CONV && (m->ops[i].epilogue & FUPR_FUSE_SCATTER)) {
-        choices.push_back(at[m->ops[i].res]);
+        choices.push_back(out->buffer[m->ops[i].res]);
       } else {
         for (int b = 0; b < (int)held.size(); ++b)
           if (held[b] < 0 && m->buffer_elems[b] >= need) choices.push_back(b);
@@ -1011,25 +1081,23 @@ void plan_blocks(fupr_model* m, bool over_pairs) {
         if (b >= 0) after[b] = tid;
         for (int& h : after)
           if (h >= 0 && h != tid && last[h] <= i) h = -1;
-        at[tid] = b;
+        out->buffer[tid] = b;
         if (place(i + 1, after)) return true;
       }
       return false;
     };
-    if (place(0, std::vector<int>(m->buffer_elems.size(), -1))) {
-      out.buffer = at;
-      return;
-    }
+    if (place(0, std::vector<int>(m->buffer_elems.size(), -1))) return out;
     // no way past operator `failed`: the last block that starts at or before it keeps too much alive
     int drop = -1;
+    any = false;
     for (int i = 0; i <= failed; ++i)
-      if (out.planned[i]) drop = i;
-    if (drop < 0) {                      // (the first plan's placement is not this one's)
-      out.planned.assign(n, 0);
-      return;
-    }
-    out.planned[drop] = 0;
+      if (chosen[i]) drop = i;
+    if (drop >= 0) chosen[drop] = 0;
+    for (int i = 0; drop >= 0 && i < n; ++i) any = any || chosen[i];
   }
+  out->launches.clear();
+  out->buffer.clear();
+  return out;
 }
 
 std::vector<Launch> list_launches(const fupr_model* m, int schedule) {
@@ -1050,43 +1118,33 @@ std::vector<Launch> launches_of(const fupr_model* m) {
   return tuning_any() ? list_launches(m, m->schedule) : m->launches[m->schedule];
 }
 
-// Blocks run as one launch where the workspace was placed for it.  For a batch of N images: the placement with blocks over pairs if one of those blocks is wanted.
-const fupr_model::Placement* blocks_on(const fupr_model* m, int N) {
+// The placement of a batch of N images, null if none of its blocks runs as one launch.
+std::shared_ptr<const fupr_model::Placement> blocks_on(const fupr_model* m, int N) {
   if (!m->blocks || m->schedule != FUPR_SCHEDULE_AUTO) return nullptr;
-  const fupr_model::Placement &pairs = m->placed[0], &over = m->placed[1];
-  for (size_t i = 0; i < over.planned.size(); ++i)
-    if (over.planned[i] && !pairs.planned[i] && bottleneck_wanted(m->block_args[i], N))
-      return over.buffer.empty() ? nullptr : &over;
-  return pairs.buffer.empty() ? nullptr : &pairs;
+  std::shared_ptr<const fupr_model::Placement> p;
+  if (tuning_any()) {
+    p = place_blocks(m, N);              // (switches decide it as well)
+  } else {
+    fupr_model* const keeper = const_cast<fupr_model*>(m);
+    std::lock_guard<std::mutex> lock(keeper->placed_mutex);
+    const auto known = m->placed.find(N);
+    if (known != m->placed.end()) {
+      p = known->second;
+    } else {
+      p = place_blocks(m, N);
+      if (m->placed.size() >= 256) keeper->placed.clear();
+      keeper->placed.emplace(N, p);
+    }
+  }
+  return p->buffer.empty() ? nullptr : p;
 }
 
 // The launches of a batch of N images.  Of a pair of 1 x 1 convolutions whose tensors are small, two
 // launches that fill the GPU are faster than one that walks it (nine images of 193 x 193, 49 x 49
 // pixels, 47 -> 256 -> 111 channels: 18 us in one, 12 in two; a launch more costs 1.7).
 std::vector<Launch> launches_at(const fupr_model* m, int N) {
-  std::vector<Launch> v = launches_of(m);
-  if (const fupr_model::Placement* placed = blocks_on(m, N)) {
-    // pairs of 1 x 1 convolutions that share an operator with a planned block are not kept apart
-    std::vector<char> inside(m->ops.size(), 0);
-    for (size_t i = 0; i < m->ops.size(); ++i)
-      for (int k = 0; k < placed->planned[i]; ++k) inside[i + k] = 1;
-    std::vector<Launch> with;
-    size_t next = 0;
-    for (const Launch& l : v)
-      for (int k = 0; k < l.count; ++k) {
-        const size_t i = (size_t)l.first + k;
-        if (i < next) continue;
-        if (placed->planned[i] && bottleneck_wanted(m->block_args[i], N)) {
-          with.push_back(Launch{(int)i, placed->planned[i], true});
-        } else if (k == 0 && l.count == 2 && !(m->ops[i + 1].kind == FUPR_OP_CONV && (inside[i] || inside[i + 1]))) {
-          with.push_back(l);
-        } else {
-          with.push_back(Launch{(int)i, 1});
-        }
-        next = i + with.back().count;
-      }
-    v = with;
-  }
+  const auto placed = blocks_on(m, N);
+  std::vector<Launch> v = placed ? placed->launches : launches_of(m);
   for (size_t i = 0; i < v.size(); ++i) {
     const Launch l = v[i];
     if (l.count != 2 || l.block || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
@@ -1163,7 +1221,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
   // images n0 .. n0 + count - 1 of a tensor; inside a workspace buffer every
   // sub-batch owns the slice its images would need at the buffer's largest tensor
   const size_t es = elem_size(m->dt);
-  const fupr_model::Placement* placed = blocks_on(m, N);
+  const auto placed = blocks_on(m, N);
   auto view = [&](int tid, int n0, int count) {
     const TensorInfo& t = m->tensors[tid];
     const int buffer = placed ? placed->buffer[tid] : t.buffer;
@@ -1176,6 +1234,9 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
     } else if (buffer == -2) {
       v.c_stride = output->c_stride;
       ptr = (char*)output->ptr + (size_t)n0 * t.H * t.W * output->c_stride * es;
+    } else if (buffer < 0) {             // (a tensor that stays inside a launch)
+      v.c_stride = t.cs;
+      ptr = nullptr;
     } else {
       v.c_stride = t.cs;
       ptr = base[buffer] + (size_t)n0 * m->buffer_elems[buffer] * es;
@@ -1198,6 +1259,41 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
     return FUPR_OK;
   }
   const std::vector<Launch> launches = launches_at(m, N);
+  auto residual = [&](const fupr_op_desc& op, int n0, int count) {
+    fupr_residual r{};
+    if (op.res >= 0) {
+      r.t = view(op.res, n0, count);
+      r.spatial_stride = op.res_spatial_stride;
+      r.c_offset = op.res_c_offset;
+    }
+    return r;
+  };
+  // Operators i and i + 1 as one launch, after the checks that each of them gets by itself; as two
+  // where tensors need more than 32-bit offsets or the output overlaps what the first reads (its own
+  // launch reads it before the other's writes).
+  auto basic_block = [&](size_t i, const fupr_tensor& x, const fupr_tensor& y, int n0, int count,
+                         void* on) -> fupr_status {
+    const fupr_op_desc &a = m->ops[i], &b = m->ops[i + 1];
+    fupr_tensor mid = view((int)i + 1, n0, count);
+    const bool hidden = mid.ptr == nullptr;
+    // (a marker for the checks, that is never dereferenced)
+    if (hidden) mid.ptr = reinterpret_cast<void*>(uintptr_t(256));
+    const fupr_residual r = residual(b, n0, count);
+    ConvArgs first, second;
+    fupr_status st = conv_args(&a.conv, &x, a.packed, nullptr, a.epilogue, &mid, &first);
+    if (st != FUPR_OK) return st;
+    st = conv_args(&b.conv, &mid, b.packed, b.res >= 0 ? &r : nullptr, b.epilogue, &y, &second);
+    if (st != FUPR_OK) return st;
+    auto bytes = [&](const fupr_tensor& t) { return (size_t)t.N * t.H * t.W * t.c_stride * es; };
+    const uintptr_t x0 = (uintptr_t)x.ptr, y0 = (uintptr_t)y.ptr;
+    bool apart = x0 < y0 + bytes(y) && y0 < x0 + bytes(x);
+    for (size_t size : {bytes(x), bytes(y), b.res >= 0 ? bytes(r.t) : 0}) apart = apart || size >= (size_t(1) << 31);
+    if (hidden && apart) return FUPR_ERR_LIMIT;   // (block_wanted takes no such sizes)
+    if (!apart) return launch_basic_block(m->block_args[i].basic, first, second, N, count, on);
+    st = conv_fused_part(&a.conv, &x, nullptr, 0, a.packed, nullptr, a.epilogue, &mid, N, on);
+    if (st != FUPR_OK) return st;
+    return conv_fused_part(&b.conv, &mid, nullptr, 0, b.packed, b.res >= 0 ? &r : nullptr, b.epilogue, &y, N, on);
+  };
   auto enqueue = [&](int n0, int count, void* on, bool record) -> fupr_status {
     for (size_t l = 0; l < launches.size(); ++l) {
       const size_t i = (size_t)launches[l].first;
@@ -1205,8 +1301,10 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
       const fupr_tensor x = view(op.in, n0, count);
       const fupr_tensor y = view((int)i + launches[l].count, n0, count);
       fupr_status st;
-      if (launches[l].block) {
-        BottleneckArgs g = m->block_args[i];
+      if (launches[l].block == kBasic) {
+        st = basic_block(i, x, y, n0, count, on);
+      } else if (launches[l].block) {
+        BottleneckArgs g = m->block_args[i].bottleneck;
         const fupr_op_desc& b = m->ops[i + 1];
         g.x = x.ptr;
         g.packed1 = op.packed;
@@ -1413,7 +1511,8 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
         out->flops += o.flops;
         out->bytes += o.bytes - (k == 1 ? 2.0 : 1.0) * es * batch * (double)t.H * t.W * t.C;
       }
-      out->kernel = bottleneck_name(m->block_args[l.first], batch);
+      const fupr_model::Block& b = m->block_args[l.first];
+      out->kernel = l.block == kBasic ? basic_block_name(b.basic, batch) : bottleneck_name(b.bottleneck, batch);
       return FUPR_OK;
     }
     if (m->ops[l.first + 1].kind == FUPR_OP_CONV) {

@@ -38,6 +38,8 @@ Switch g_switches[] = {
     {"pair_filters", false, {0}},    // most filters of such a pair's second convolution (up to 128)
     {"bottleneck_fuse", false, {0}},      // 0: bottleneck blocks run as several launches
     {"bottleneck_tile", false, {0}},      // index of the bottleneck kernel's tile
+    {"basic_fuse", false, {0}},      // 0: basic blocks run as two launches
+    {"basic_tile", false, {0}},      // <rectangle>x<waves along the filters> of the kernel that runs them
     {"split", false, {0}},           // sub-batches of the per-operator schedule
     {"res_item", false, {0}},        // work-item shapes of the one-kernel schedule
     {"debug", false, {0}},           // non-empty: planner and HIP error text on stderr

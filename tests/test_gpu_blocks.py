@@ -61,6 +61,7 @@ class Net:
         against both references."""
         B, torch = self.B, self.torch
         m = B.Model(self.dt, self.in_shape, self.ops, self.blobs)
+        assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)   # no one-kernel schedule
         m.fuse_blocks(True)
         B.fupr_tuning_set(tile_switch, tile)
         try:
@@ -142,3 +143,36 @@ def test_bottleneck_block(fx, case, tile):
     mt, waves = TILES[tile]
     per_wave = -(-(-(-k3 // 16)) // waves)
     net.check("bottleneck_tile", tile, "bottleneck_", k1 <= 32 * waves and mt * (4 if per_wave > 2 else per_wave) <= 8)
+
+
+RECTANGLES = [(2, 8), (4, 4), (4, 8), (7, 7), (8, 8), (7, 14), (8, 16), (14, 14)]
+# dtype, images, rows, columns, channels, first filters, its stride, second filters, shortcut: the block's
+# input, its every other pixel in channels from 8 on, another tensor, none
+BASIC_BLOCKS = [
+    ("f32", 1, 32, 32, 16, 12, 1, 16, "input"),
+    ("bf16", 2, 9, 11, 24, 45, 1, 24, "input"),           # ragged channels, rectangles over the edges
+    ("f16", 1, 1, 1, 8, 16, 1, 16, "none"),               # one pixel: every tap but one outside
+    ("f32", 2, 15, 13, 20, 23, 2, 40, "strided"),         # stride 2, zero-padded shortcut
+    ("bf16", 3, 14, 17, 64, 77, 1, 100, "other"),
+    ("f16", 1, 30, 28, 16, 130, 2, 48, "strided"),        # second pass over the filters
+]
+
+
+@pytest.mark.parametrize("rectangle", range(len(RECTANGLES)))
+@pytest.mark.parametrize("wf", [1, 2, 4, 8])
+@pytest.mark.parametrize("case", BASIC_BLOCKS, ids=lambda c: "-".join(map(str, c)))
+def test_basic_block(fx, case, rectangle, wf):
+    dtype, n, h, w, c, k1, stride, k2, back = case
+    net = Net(fx, dtype, n, (16, h, w), seed=sum(case[1:8]) + 8 * rectangle + wf)
+    t = [net.conv(0, 128, 1) for _ in range(4)]       # (for the workspace, as above)
+    t_x = net.conv(net.conv(t[0], 128, 1, add=t[1]), 128, 1, add=net.conv(t[2], 128, 1, add=t[3]))
+    t_x = net.conv(t_x, c, 1)
+    t_r = net.conv(t_x, k2, 1) if back == "other" else -1
+    t_mid = net.conv(t_x, k1, 3, stride)
+    add = {"input": t_x, "strided": t_x, "other": t_r, "none": -1}[back]
+    net.conv(net.conv(t_mid, k2, 3, add=add, add_stride=stride, add_at=8 if back == "strided" else 0), 24, 1)
+    rows, cols = (-(-e // stride) for e in (h, w))
+    th, tw = min(RECTANGLES[rectangle][0], rows), min(RECTANGLES[rectangle][1], cols)
+    tiles = [-(-(-(-px // 16)) // (8 // wf)) for px in ((th + 2) * (tw + 2), th * tw)]
+    fits = any(tiles[0] <= a and tiles[1] <= b for a, b in [(2, 1), (3, 2), (4, 3), (6, 4), (8, 7), (16, 13)])
+    net.check("basic_tile", f"{rectangle}x{wf}", "basic_block_", fits)

@@ -677,6 +677,30 @@ def test_blocks_run_as_one_launch_only_when_asked_for():
     assert m.num_launches_at(9) == m2.num_launches_at(9)
 
 
+@pytest.mark.parametrize("config,kinds", [(0, 1), (2, 4)])
+def test_basic_blocks_run_as_one_launch(config, kinds):
+    """Both 3 x 3 convolutions of a basic block, the block of a two-operator model included: what the launch
+    does not write and read is the tensor between them."""
+    model, _ = synth.make_config(config)
+    m, _ = build_host_model(network.optimise(model), 1 << 20)
+    m.fuse_blocks(True)
+    covered = set()
+    for batch in (1, 8, 64):
+        launches = [m.launch_stats(batch, i) for i in range(m.num_launches_at(batch))]
+        single = [m.op_stats(batch, i) for i in range(m.num_ops)]
+        assert [i for s in launches for i in range(s["first_op"], s["first_op"] + s["n_ops"])] == list(range(m.num_ops))
+        for s in launches:
+            if not s["kernel"].startswith("basic_block_"):
+                continue
+            a, b = (single[i] for i in (s["first_op"], s["first_op"] + 1))
+            assert s["n_ops"] == 2 and a["R"] == b["R"] == 3 and b["stride"] == 1
+            size = 4 if config == 0 else 2
+            assert s["flops"] == a["flops"] + b["flops"]
+            assert s["bytes"] == a["bytes"] + b["bytes"] - 2 * size * a["M"] * a["K"]
+            covered.add(s["first_op"])
+    assert len(covered) >= kinds
+
+
 def launch_list(m, batch):
     return [(s["first_op"], s["n_ops"], s["kernel"]) for s in (m.launch_stats(batch, i) for i in range(m.num_launches))]
 
