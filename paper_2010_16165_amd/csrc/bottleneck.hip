@@ -760,10 +760,13 @@ bool choose(const BottleneckArgs& a, int N, int count, BlockPlan* plan) {
   if (!pick_block(a, N, 0, plan, &cost)) return false;
   // 5 % less than the launches apart, which is what the two estimates are uncertain by; 15 % where the
   // two 1 x 1 convolutions would run as a pair (32 -> 256 -> 32 at 56 x 56 x 24 29 against 33 us, x 64 59
-  // against 55).  All were fitted to launches between events, which takes 2.5 us more for each than one
-  // after the other.
-  if (tuning_int("bottleneck_tile", -1) < 0 && 
-      cost - 2.5 >= (a.pair ? 0.85 : 0.95) * (estimate_apart(a, M) - (a.third ? 7.5 : 5.0))) return false;
+  // against 55).  Both were fitted to launches between events, which takes some 1.5 us more for each than one
+  // after the other: that decides where they are short (nine irregular images 269 -> 264 us; a network at 64
+  // images, whose sub-batches run side by side, 684 against 670 when it is counted there too).
+  const double gap = M < 8192 ? 1.5 : 0.0;
+  if (tuning_int("bottleneck_tile", -1) < 0 &&
+      cost - gap >= (a.pair ? 0.85 : 0.95) * (estimate_apart(a, M) - gap * (a.third ? 3 : 2)))
+    return false;
   return count == N || pick_block(a, count, kTiles[plan->tile].waves, plan, &cost);
 }
 
