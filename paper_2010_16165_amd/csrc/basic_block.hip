@@ -191,6 +191,23 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
     }
   };
 
+  // (the first weights are the last to arrive in a cold L2: they are asked for before anything else; single
+  // precision, which loads them four bytes at a time, asks for its pixels first)
+  uint4 a[D];
+  auto load1 = [&](int f) {
+    return [&, f](int step, uint4& v) { load_fragment(w1r, f, step, p.steps1, p.Kp1, v); };
+  };
+  auto load2 = [&](int f) {
+    return [&, f](int step, uint4& v) { load_fragment(w2r, f, step, p.steps2, p.Kp2, v); };
+  };
+  auto first_weights = [&] {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load1(wf * 16)(d, a[d]);
+  };
+  if constexpr (!F32) first_weights();
+  const f32x4 b1v = *reinterpret_cast<const f32x4*>(p.b1 + min(wf * 16 + g * 4, p.Kp1 - 4));
+  const f32x4 b2v = *reinterpret_cast<const f32x4*>(p.b2 + min(wf * 16 + g * 4, p.Kp2 - 4));
+
   // ---- the rectangle's input into LDS ----
   {
     const i32x4 xr = make_rsrc(p.x, p.x_bytes);
@@ -220,6 +237,7 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       off += turn ? turn_off : 0u;
     }
   }
+  if constexpr (F32) first_weights();
   // All workgroups of an XCD walk the weights in step: its first ones ask for all of them at once, a
   // share each, so that the loop below finds them in L2 (into 1 KB of LDS that nobody reads).
   {
@@ -234,16 +252,6 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       ask(p.w2, p.w2_bytes);
     }
   }
-
-  uint4 a[D];
-  auto load1 = [&](int f) {
-    return [&, f](int step, uint4& v) { load_fragment(w1r, f, step, p.steps1, p.Kp1, v); };
-  };
-  auto load2 = [&](int f) {
-    return [&, f](int step, uint4& v) { load_fragment(w2r, f, step, p.steps2, p.Kp2, v); };
-  };
-#pragma unroll
-  for (int d = 0; d < D; ++d) load1(wf * 16)(d, a[d]);
 
   // per chunk of 16 bytes: its LDS distance from the first tap
   uint32_t* table1 = reinterpret_cast<uint32_t*>(lds + p.table1_at);
@@ -279,8 +287,6 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       origin += over ? turn : 0u;
     }
   }
-  const f32x4 b1v = *reinterpret_cast<const f32x4*>(p.b1 + min(wf * 16 + g * 4, p.Kp1 - 4));
-  const f32x4 b2v = *reinterpret_cast<const f32x4*>(p.b2 + min(wf * 16 + g * 4, p.Kp2 - 4));
 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -592,9 +598,15 @@ bool choose(const BasicBlockArgs& a, int N, int count, BasicPlan* plan) {
   double cost;
   if (!pick_basic(a, N, plan, &cost)) return false;
   char text[32];
-  // 5 % less than the launches apart, which is what the two estimates are uncertain by; both were fitted to
-  // launches between events, which takes some 1.5 us more for each than one after the other.
-  if (!tuning_text("basic_tile", text, sizeof(text)) && cost - 1.5 >= 0.95 * (estimate_apart(a, pixels) - 3.0)) return false;
+  if (!tuning_text("basic_tile", text, sizeof(text))) {
+    // Short launches: 5 % less than the launches apart, which is what the two estimates are uncertain by;
+    // both were fitted to launches between events, which takes some 1.5 us more for each than one after
+    // the other.  Long ones, one after the other, take longer than alone by more than the launches apart
+    // do (a network of 64 images 1.04x faster, of 100 0.99x, of 250, whose sub-batches run side by side, 0.91x
+    // with every block that is 5 % better by the estimate): a fifth less.
+    const double apart = estimate_apart(a, pixels);
+    if (apart > 30.0 ? cost >= 0.8 * apart : cost - 1.5 >= 0.95 * (apart - 3.0)) return false;
+  }
   return count == N || pick_basic(a, count, plan, &cost);
 }
 
