@@ -8,15 +8,19 @@
 //   * WF waves lie along the filters, one tile of 16 each at a time, the others along the pixels; a wave's
 //     weights come from L2 straight into registers, D steps ahead.
 //   * Outside the image the second convolution reads zeros: the first one's values there are not stored.
-//   * Sums run over the reduction in one order whatever the rectangle.
+//   * Sums run over the reduction in one order whatever the rectangle, except in rectangles of 14 columns and 6 or 14
+//     rows at stride 1 in 16 bits.  With the ring their rows are tiles of 16 pixels, and what is read from LDS
+//     for one row is multiplied for the three output rows that have a tap there (multiply_rows).
 //
 // Measured, two launches -> one (us, event-timed): 64 -> 45 -> 64 channels at 56 x 56, one image 13.0 -> 8.8, 8
-// images 20.0 -> 13.5, 64 images 54 -> 42; 128 -> 90 -> 128 at 28 x 28 x 64 45 -> 36; single precision, 16 -> 12 ->
-// 16 at 32 x 32 x 32 images 16.4 -> 11.0, 32 -> 23 -> 32 at 16 x 16 x 32 16.3 -> 12.  Networks: ResNet-18, one image
-// 97.7 -> 93.9, 64 images 381 -> 367; ResNet-20 in single precision, 32 images 111 -> 101.
+// images 20.0 -> 13.5, 32 images 35.5 -> 20.8, 64 images 54.7 -> 36.0 (43.2 not by rows), 250 images 137 -> 121 (150);
+// 128 -> 90 -> 128 at 28 x 28 x 64 44.9 -> 31.1 (36.9); single precision, 16 -> 12 -> 16 at 32 x 32 x 32 images
+// 16.4 -> 11.0, 32 -> 23 -> 32 at 16 x 16 x 32 16.3 -> 12.  Networks: ResNet-18, one image 97.6 -> 92.9, 64 images
+// 381 -> 330; ResNet-20 in single precision, 32 images 111 -> 101.
 // What bounds it: at a few images the start (index arithmetic, arguments, first weights: 4000 of 11 000
-// clocks) and the weights' latency; at many, LDS: one read of 1 KB, 8 clocks, for every MFMA of 4 clocks per
-// compute unit (14 x 14: 1600 reads, 12 700 clocks of some 19 000 per rectangle).
+// clocks) and the weights' latency; at many, LDS where a read of 1 KB, 8 clocks, serves one MFMA of 4 clocks
+// per compute unit, and by rows the serial chain of a workgroup, load, multiply, multiply, store, of which
+// one or two fit into LDS together (64 images: 100 MB in 36 us, 2.8 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -57,6 +61,7 @@ struct BasicParams {
   int mids, outs;                   // (TH + 2) * (TW + 2), TH * TW
   int Kp1, cpt1, nchunk1, steps1, Kp2, cpt2, nchunk2, steps2;
   int rH, rW, rcs, rss, roff, ycs, relu1, relu2;
+  int rows1, rows2;                 // steps of one row of taps (multiply_rows)
   int slots1, slots2, in_pixels;
   int mid_at, table1_at, table2_at, zero_at;   // LDS byte offsets (the input starts at 0)
   int WF, log2_WF, tiles_w, tiles, total, per_xcd;
@@ -154,8 +159,72 @@ __device__ __forceinline__ void multiply(const char* lds, const uint32_t (&origi
   round(std::false_type{}, steps - s0);
 }
 
-// MA, MB: tiles of 16 pixels per wave of the first and of the second convolution.
-template <int EL, int MA, int MB, int D, int NB, int MINWAVES>
+// M tiles of 16 pixels that are M rows of a tensor in LDS, one below the other, x one tile of 16 filters.  The
+// reduction goes row of taps by row of taps, each padded to whole steps: a step's pixels at one row of the
+// tensor are read once and multiplied for the three output rows that have a tap there, (M + 2) / (3 M) LDS
+// reads per MFMA instead of one (64 x 56 x 56 x 64 -> 45 -> 64 43 -> 36 us, 64 x 28 x 28 x 128 -> 90 -> 128
+// 36.9 -> 31.1 us).  a holds the three rows' weights of the first DQ steps: more of them spill with eight
+// rows in 128 registers and were slower (41 us at four).
+template <bool BF, int M, int DQ, class Load>
+__device__ __forceinline__ void multiply_rows(const char* lds, uint32_t base, uint32_t row_stride, const uint32_t* table,
+                                              int g, uint32_t zero_at, int steps, uint4 (&a)[DQ][3], f32x4 (&acc)[M],
+                                              Load&& load) {
+  constexpr int ROWS = M + 2, NB = DQ * ROWS % 4 == 0 ? 4 : 3;
+  static_assert(DQ * ROWS % NB == 0, "the pixel buffers in turn, over a round");
+  uint4 b[NB];
+  // (the chunks that pad a row's last step: zeros at every row)
+  uint32_t at[2], stride[2];               // this step's and the next one's
+  auto start = [&](int step, int k) {
+    const uint32_t entry = table[min(step, steps) * 4 + g];
+    const bool pad = entry == kOutside;
+    at[k] = pad ? zero_at : base + entry;
+    stride[k] = pad ? 0u : row_stride;
+  };
+  auto read = [&](int k, uint4& v) {
+    v = *reinterpret_cast<const uint4*>(lds + min(at[k], zero_at));
+    at[k] += stride[k];
+  };
+  start(0, 0);
+  start(1, 1);
+#pragma unroll
+  for (int i = 0; i < NB - 1; ++i) read(0, b[i]);
+  int s0 = 0;
+  auto round = [&](auto more, int left) {
+#pragma unroll
+    for (int d = 0; d < DQ; ++d) {
+      if (!more.value && d > 0 && d >= left) break;
+      if (!more.value && d == left - 1) {
+        // the weights beside a padding chunk are another row's
+        const bool pad = stride[0] == 0u;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) a[d][r] = pad ? uint4{0u, 0u, 0u, 0u} : a[d][r];
+      }
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        const int now = (d * ROWS + i) % NB;
+        if (i + NB - 1 < ROWS) read(0, b[(now + NB - 1) % NB]);
+        else read(1, b[(now + NB - 1) % NB]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          if (i - r >= 0 && i - r < M) acc[i - r] = mfma_16x16x32<BF>(a[d][r], b[now], acc[i - r]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      at[0] = at[1];
+      stride[0] = stride[1];
+      start(s0 + d + 2, 1);
+      if constexpr (more.value)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) load(s0 + d + DQ, r, a[d][r]);
+    }
+  };
+  for (; s0 + DQ < steps; s0 += DQ) round(std::true_type{}, DQ);
+  round(std::false_type{}, steps - s0);
+}
+
+// MA, MB: tiles of 16 pixels per wave of the first and of the second convolution.  ROWS: the tiles are rows of
+// the rectangle, 16 pixels with its ring, and multiply_rows multiplies them (16-bit types, stride 1).
+template <int EL, int MA, int MB, int D, int NB, int MINWAVES, bool ROWS>
 __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const BasicParams p) {
   touch_arguments<sizeof(BasicParams)>();
   constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
@@ -203,9 +272,30 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
   auto load2 = [&](int f) {
     return [&, f](int step, uint4& v) { load_fragment(w2r, f, step, p.steps2, p.Kp2, v); };
   };
+  // ROWS: the weights of tap row r, step q of a row
+  constexpr int DQ = ROWS ? D : 1;
+  uint4 ar[DQ][3];
+  auto load_row = [&](const __amdgpu_buffer_rsrc_t& rsrc, int f, int q, int r, int steps, int cpt, int Kp, uint4& v) {
+    const uint32_t at = (uint32_t)(g * Kp + min(f, Kp - 16) + li) * 16u;
+    const uint32_t so = (uint32_t)(r * 3 * cpt + min(q, steps - 1) * 4) * (uint32_t)(Kp * 16);
+    v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, so, 0));
+  };
+  auto load_rows1 = [&](int f) {
+    return [&, f](int q, int r, uint4& v) { load_row(w1r, f, q, r, p.rows1, p.cpt1, p.Kp1, v); };
+  };
+  auto load_rows2 = [&](int f) {
+    return [&, f](int q, int r, uint4& v) { load_row(w2r, f, q, r, p.rows2, p.cpt2, p.Kp2, v); };
+  };
   auto first_weights = [&] {
+    if constexpr (ROWS) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) load1(wf * 16)(d, a[d]);
+      for (int d = 0; d < DQ; ++d)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) load_rows1(wf * 16)(d, r, ar[d][r]);
+    } else {
+#pragma unroll
+      for (int d = 0; d < D; ++d) load1(wf * 16)(d, a[d]);
+    }
   };
   if constexpr (!F32) first_weights();
   const f32x4 b1v = *reinterpret_cast<const f32x4*>(p.b1 + min(wf * 16 + g * 4, p.Kp1 - 4));
@@ -266,16 +356,29 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       table[j] = j < nchunk ? (uint32_t)(((r * width + s) * slots + cc) * 16) : kOutside;
     }
   };
-  make_table(table1, p.steps1, p.nchunk1, p.cpt1, p.divC1, p.IW, p.slots1);
-  make_table(table2, p.steps2, p.nchunk2, p.cpt2, p.divC2, p.MW, p.slots2);
+  if constexpr (ROWS) {
+    auto make_row_table = [&](uint32_t* table, int steps, int cpt, const FastDiv& by, int slots) {
+      for (int j = tid; j < (steps + 1) * 4; j += kThreads) {
+        const int s = div_by(j, by), cc = j - s * cpt;
+        table[j] = s < 3 ? (uint32_t)((s * slots + cc) * 16) : kOutside;
+      }
+    };
+    make_row_table(table1, p.rows1, p.cpt1, p.divC1, p.slots1);
+    make_row_table(table2, p.rows2, p.cpt2, p.divC2, p.slots2);
+  } else {
+    make_table(table1, p.steps1, p.nchunk1, p.cpt1, p.divC1, p.IW, p.slots1);
+    make_table(table2, p.steps2, p.nchunk2, p.cpt2, p.divC2, p.MW, p.slots2);
+  }
   if (tid < 64) reinterpret_cast<uint32_t*>(lds + p.zero_at)[tid] = 0u;
 
   // Pixels of a wave lie WP * 16 apart: the row and column of the first are divided out, the others stepped.
-  const int apart = WP * 16;
+  // (ROWS: a wave's tiles are rows one below the other, 16 pixels apart.)
+  const int apart = ROWS ? 16 : WP * 16;
   uint32_t origin_a[MA];
-  const int first_a = wp * 16 + li, dr_a = div_by(apart, p.divMW), dc_a = apart - dr_a * p.MW;
-  const int r_a = div_by(first_a, p.divMW), c_a = first_a - r_a * p.MW;
-  {
+  const int first_a = ROWS ? wp * MA * 16 + li : wp * 16 + li;
+  const int dr_a = ROWS ? 1 : div_by(apart, p.divMW), dc_a = ROWS ? 0 : apart - dr_a * p.MW;
+  const int r_a = ROWS ? wp * MA : div_by(first_a, p.divMW), c_a = ROWS ? li : first_a - r_a * p.MW;
+  if constexpr (!ROWS) {
     const uint32_t unit = (uint32_t)(p.stride * p.slots1 * 16);
     const uint32_t step = (uint32_t)(dr_a * p.IW + dc_a) * unit, turn = (uint32_t)(p.IW - p.MW) * unit;
     uint32_t origin = (uint32_t)(r_a * p.IW + c_a) * unit;
@@ -298,15 +401,26 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
   {
     for (int f = wf * 16; f < p.Kp1; f += p.WF * 16) {
       if (f != wf * 16) {
+        if constexpr (ROWS) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) load1(f)(d, a[d]);
+          for (int d = 0; d < DQ; ++d)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) load_rows1(f)(d, r, ar[d][r]);
+        } else {
+#pragma unroll
+          for (int d = 0; d < D; ++d) load1(f)(d, a[d]);
+        }
       }
       f32x4 acc[MA];
       f32x4 b4 = b1v;
       if (f != wf * 16) b4 = *reinterpret_cast<const f32x4*>(p.b1 + min(f + g * 4, p.Kp1 - 4));
 #pragma unroll
       for (int mt = 0; mt < MA; ++mt) acc[mt] = b4;
-      multiply<EL, MA, D, NB>(lds, origin_a, table1, g, (uint32_t)p.zero_at, p.steps1, a, acc, load1(f));
+      if constexpr (ROWS)
+        multiply_rows<BF, MA, DQ>(lds, (uint32_t)((r_a * p.IW + li) * p.slots1 * 16), (uint32_t)(p.IW * p.slots1 * 16),
+                                  table1, g, (uint32_t)p.zero_at, p.rows1, ar, acc, load_rows1(f));
+      else
+        multiply<EL, MA, D, NB>(lds, origin_a, table1, g, (uint32_t)p.zero_at, p.steps1, a, acc, load1(f));
       const uint32_t floor2 = p.relu1 ? 0u : 0x80008000u;
       int r = r_a, c = c_a;
       char* to = lds + p.mid_at + first_a * p.slots2 * 16 + (f + g * 4) * ES;
@@ -316,7 +430,7 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
         const bool inside = (unsigned)(oh0 - 1 + r) < (unsigned)p.P && (unsigned)(ow0 - 1 + c) < (unsigned)p.Q;
         c += dc_a;
         r += dr_a;
-        const bool over = c >= p.MW;
+        const bool over = !ROWS && c >= p.MW;
         c -= over ? p.MW : 0;
         r += over ? 1 : 0;
         if (first_a + mt * apart >= p.mids || (F32 && f + g * 4 >= p.Kp1)) continue;
@@ -339,12 +453,20 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
   // ---- the second convolution, shortcut, ReLU, one rounding ----
   const __amdgpu_buffer_rsrc_t rr = buffer_of(p.res, p.res_bytes);
   const __amdgpu_buffer_rsrc_t yr = buffer_of(p.y, p.y_bytes);
+  if constexpr (ROWS) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) load2(wf * 16)(d, a[d]);
+    for (int d = 0; d < DQ; ++d)
+#pragma unroll
+      for (int r = 0; r < 3; ++r) load_rows2(wf * 16)(d, r, ar[d][r]);
+  } else {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load2(wf * 16)(d, a[d]);
+  }
   uint32_t origin_b[MB], y_at[MB], r_at[MB];
   {
-    const int first = wp * 16 + li, dr = div_by(apart, p.divTW), dc = apart - dr * p.TW;
-    int r = div_by(first, p.divTW), c = first - r * p.TW;
+    // (ROWS: 16 lanes for a row of TW pixels)
+    const int first = wp * 16 + li, dr = ROWS ? 1 : div_by(apart, p.divTW), dc = ROWS ? 0 : apart - dr * p.TW;
+    int r = ROWS ? wp * MB : div_by(first, p.divTW), c = ROWS ? li : first - r * p.TW;
     const uint32_t unit = (uint32_t)(p.slots2 * 16), yu = (uint32_t)(p.ycs * ES), ru = (uint32_t)(p.rss * p.rcs * ES);
     uint32_t origin = (uint32_t)p.mid_at + (uint32_t)(r * p.MW + c) * unit;
     uint32_t y = (uint32_t)((n * p.P + oh0 + r) * p.Q + ow0 + c) * yu;
@@ -354,7 +476,7 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
     const uint32_t r_step = (uint32_t)(dr * p.rW + dc) * ru, r_turn = (uint32_t)(p.rW - p.TW) * ru;
 #pragma unroll
     for (int mt = 0; mt < MB; ++mt) {
-      const bool in = first + mt * apart < p.outs, ok = in && oh0 + r < p.P && ow0 + c < p.Q;
+      const bool in = ROWS ? c < p.TW : first + mt * apart < p.outs, ok = in && oh0 + r < p.P && ow0 + c < p.Q;
       origin_b[mt] = in ? origin : (uint32_t)p.mid_at;
       y_at[mt] = ok ? y : kOutside;
       r_at[mt] = ok ? res : kOutside;
@@ -363,7 +485,7 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       origin += step;
       y += y_step;
       res += r_step;
-      const bool over = c >= p.TW;
+      const bool over = !ROWS && c >= p.TW;
       c -= over ? p.TW : 0;
       r += over ? 1 : 0;
       origin += over ? turn : 0u;
@@ -374,8 +496,15 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
   __syncthreads();
   for (int f = wf * 16; f < p.Kp2; f += p.WF * 16) {
     if (f != wf * 16) {
+      if constexpr (ROWS) {
 #pragma unroll
-      for (int d = 0; d < D; ++d) load2(f)(d, a[d]);
+        for (int d = 0; d < DQ; ++d)
+#pragma unroll
+          for (int r = 0; r < 3; ++r) load_rows2(f)(d, r, ar[d][r]);
+      } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load2(f)(d, a[d]);
+      }
     }
     const int k0 = f + g * 4, kk = k0 - p.roff;
     f32x4 acc[MB];
@@ -383,9 +512,19 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
     if (f != wf * 16) b4 = *reinterpret_cast<const f32x4*>(p.b2 + min(k0, p.Kp2 - 4));
 #pragma unroll
     for (int mt = 0; mt < MB; ++mt) acc[mt] = b4;
-    multiply<EL, MB, D, NB>(lds, origin_b, table2, g, (uint32_t)p.zero_at, p.steps2, a, acc, load2(f));
     // (without a shortcut its extent is 0: zeros)
     const bool in_res = kk >= 0 && kk < p.rcs;
+    u32x2 early[MB];                       // ROWS: registers to spare for the shortcut while it multiplies
+    if constexpr (ROWS)
+#pragma unroll
+      for (int mt = 0; mt < MB; ++mt)
+        early[mt] = __builtin_amdgcn_raw_buffer_load_b64(rr, in_res ? r_at[mt] + (uint32_t)kk * 2u : kOutside, 0, 0);
+    if constexpr (ROWS)
+      multiply_rows<BF, MB, DQ>(lds, (uint32_t)(p.mid_at + (wp * MB * 16 + li) * p.slots2 * 16),
+                                (uint32_t)(16 * p.slots2 * 16), table2, g, (uint32_t)p.zero_at, p.rows2, ar, acc,
+                                load_rows2(f));
+    else
+      multiply<EL, MB, D, NB>(lds, origin_b, table2, g, (uint32_t)p.zero_at, p.steps2, a, acc, load2(f));
     const uint32_t floor2 = p.relu2 ? 0u : 0x80008000u;
     if constexpr (F32) {
       f32x4 r[MB];
@@ -407,7 +546,8 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
       u32x2 r[MB];
 #pragma unroll
       for (int mt = 0; mt < MB; ++mt)
-        r[mt] = __builtin_amdgcn_raw_buffer_load_b64(rr, in_res ? r_at[mt] + (uint32_t)kk * 2u : kOutside, 0, 0);
+        r[mt] = ROWS ? early[mt] : __builtin_amdgcn_raw_buffer_load_b64(
+                                       rr, in_res ? r_at[mt] + (uint32_t)kk * 2u : kOutside, 0, 0);
 #pragma unroll
       for (int mt = 0; mt < MB; ++mt) {
         const f32x4& v = acc[mt];
@@ -423,21 +563,28 @@ __global__ __launch_bounds__(kThreads, MINWAVES) void basic_block_kernel(const B
 }
 
 // MA, MB: most tiles of 16 pixels per wave; D: steps of weights in flight; NB: pixel buffers; min_waves:
-// waves per SIMD the registers allow (a third buffer would spill 91 of 128 with eight tiles).
+// waves per SIMD the registers allow (a third buffer would spill 91 of 128 with eight tiles).  rows: the
+// tiles are rows (MA and MB rows per wave exactly).
 struct BasicTile {
   int MA, MB, D, NB, min_waves;
+  bool rows;
 };
-constexpr BasicTile kTiles[] = {{2, 1, 6, 3, 4}, {3, 2, 6, 3, 4}, {4, 3, 6, 3, 4},
-                                {6, 4, 6, 2, 4}, {8, 7, 6, 2, 4}, {16, 13, 6, 3, 2}};
+constexpr BasicTile kTiles[] = {{2, 1, 6, 3, 4, false},  {3, 2, 6, 3, 4, false}, {4, 3, 6, 3, 4, false},
+                                {6, 4, 6, 2, 4, false},  {8, 7, 6, 2, 4, false}, {16, 13, 6, 3, 2, false},
+                                {4, 3, 4, 2, 4, true},   {8, 6, 4, 2, 2, true},
+                                {8, 7, 2, 2, 4, true},   {16, 14, 4, 2, 2, true}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-// Rectangles that are weighed, rows x columns, and the name of each.
+// Rectangles that are weighed, rows x columns, and the name of each.  The last two are multiplied by rows.
 struct Rectangle {
   int rows, cols;
+  bool by_rows;
   const char* name;
 };
-constexpr Rectangle kRectangles[] = {{2, 8, "basic_block_2x8"},   {4, 4, "basic_block_4x4"},   {4, 8, "basic_block_4x8"},
-                                     {7, 7, "basic_block_7x7"},   {8, 8, "basic_block_8x8"},   {7, 14, "basic_block_7x14"},
-                                     {8, 16, "basic_block_8x16"}, {14, 14, "basic_block_14x14"}};
+constexpr Rectangle kRectangles[] = {
+    {2, 8, false, "basic_block_2x8"},     {4, 4, false, "basic_block_4x4"},   {4, 8, false, "basic_block_4x8"},
+    {7, 7, false, "basic_block_7x7"},     {8, 8, false, "basic_block_8x8"},   {7, 14, false, "basic_block_7x14"},
+    {8, 16, false, "basic_block_8x16"},   {14, 14, false, "basic_block_14x14"},
+    {6, 14, true, "basic_block_6x14r"},   {14, 14, true, "basic_block_14x14r"}};
 constexpr int kNumRectangles = sizeof(kRectangles) / sizeof(kRectangles[0]);
 
 // LDS slots of 16 bytes per pixel: 16 lanes read 16 bytes each of neighbouring pixels, which is free
@@ -476,9 +623,20 @@ bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan
   p.WF = WF;
   while ((1 << p.log2_WF) < WF) ++p.log2_WF;
   const int WP = kWaves / WF;
-  const int ma = ((p.mids + 15) / 16 + WP - 1) / WP, mb = ((p.outs + 15) / 16 + WP - 1) / WP;
+  p.rows1 = (3 * p.cpt1 + 3) / 4;
+  p.rows2 = (3 * p.cpt2 + 3) / 4;
+  int ma = ((p.mids + 15) / 16 + WP - 1) / WP, mb = ((p.outs + 15) / 16 + WP - 1) / WP;
+  if (R.by_rows) {
+    if (es == 4 || p.stride != 1 || p.TH != R.rows || p.TW != R.cols || p.MW != 16) return false;
+    ma = (p.TH + 2) / WP;
+    mb = p.TH / WP;
+  }
   out->tile = 0;
-  while (out->tile < kNumTiles && (kTiles[out->tile].MA < ma || kTiles[out->tile].MB < mb)) ++out->tile;
+  auto fits = [&](const BasicTile& T) {
+    return T.rows == R.by_rows && (T.rows ? T.MA == ma && T.MB == mb && ma * WP == p.TH + 2 && mb * WP == p.TH
+                                          : T.MA >= ma && T.MB >= mb);
+  };
+  while (out->tile < kNumTiles && !fits(kTiles[out->tile])) ++out->tile;
   if (out->tile == kNumTiles) return false;
   p.slots1 = pad_slots(p.cpt1, p.stride == 2);
   p.slots2 = pad_slots(std::max(p.cpt2, p.Kp1 / per_chunk), false);
@@ -509,16 +667,20 @@ bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan
 template <int EL, int TILE>
 fupr_status launch_as(const BasicPlan& plan, hipStream_t st) {
   constexpr BasicTile T = kTiles[TILE];
-  auto kernel = basic_block_kernel<EL, T.MA, T.MB, T.D, T.NB, T.min_waves>;
-  if (plan.lds > 64 * 1024) {
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
-    if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
+  if constexpr (T.rows && EL == FUPR_F32) {
+    return FUPR_ERR_LIMIT;             // (no such plan)
+  } else {
+    auto kernel = basic_block_kernel<EL, T.MA, T.MB, T.D, T.NB, T.min_waves, T.rows>;
+    if (plan.lds > 64 * 1024) {
+      static const hipError_t attr = hipFuncSetAttribute(
+          reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+      if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
+    }
+    void* list[] = {const_cast<BasicParams*>(&plan.p)};
+    return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)(plan.p.per_xcd * 8)),
+                                    dim3(kThreads), list, plan.lds, st),
+                    "basic_block_kernel");
   }
-  void* list[] = {const_cast<BasicParams*>(&plan.p)};
-  return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)(plan.p.per_xcd * 8)),
-                                  dim3(kThreads), list, plan.lds, st),
-                  "basic_block_kernel");
 }
 
 template <int EL>
@@ -530,6 +692,10 @@ fupr_status dispatch(const BasicPlan& plan, hipStream_t st) {
     case 3: return launch_as<EL, 3>(plan, st);
     case 4: return launch_as<EL, 4>(plan, st);
     case 5: return launch_as<EL, 5>(plan, st);
+    case 6: return launch_as<EL, 6>(plan, st);
+    case 7: return launch_as<EL, 7>(plan, st);
+    case 8: return launch_as<EL, 8>(plan, st);
+    case 9: return launch_as<EL, 9>(plan, st);
   }
   return FUPR_ERR_LIMIT;
 }
@@ -543,6 +709,22 @@ double estimate(const BasicBlockArgs& a, const BasicPlan& plan) {
   const int WP = kWaves / p.WF, ft1 = (p.Kp1 + 15) / 16, ft2 = (p.Kp2 + 15) / 16;
   const double mfma = a.dt == FUPR_F32 ? 128.0 : 16.0;   // clocks of the matrix pipe per tile and step
   const double es = (double)elem_size(a.dt), slots = (double)p.in_pixels * p.slots1;
+  const int per_cu = (p.total + kComputeUnits - 1) / kComputeUnits;
+  const int resident = std::max(1, std::min({per_cu, T.min_waves / 2, (int)(kLdsLimit / plan.lds)}));
+  const double pixels = (double)p.total / p.tiles * p.P * p.Q;
+  const double hbm = pixels * es * (p.stride * p.stride * a.s1.C + 2.0 * a.s2.K) / 4.5e6;
+  if (T.rows) {
+    // (the same form, fitted to 128 launches of 41 blocks to 7 %; LDS reads are hidden)
+    const int st1 = 3 * p.rows1, st2 = 3 * p.rows2;
+    const double alone = 8042.0 + 2.75 * slots + (ft1 + p.WF - 1) / p.WF * st1 * T.MA * 16.0 +
+                         (ft2 + p.WF - 1) / p.WF * T.MB * (st2 * 16.0 + 328.0);
+    const double matrix = 4.92 * WP * (ft1 * T.MA * st1 + ft2 * T.MB * st2);
+    const double memory = ((ft1 * st1 + ft2 * st2) * 1024.0 * WP + p.in_pixels * a.s1.C * es + 140.0 * slots +
+                           2.0 * p.outs * a.s2.K * es) / 76.8;
+    const double clocks = std::max((per_cu + resident - 1) / resident * alone,
+                                   per_cu * (std::max(matrix, memory) + 0.40 * (matrix + memory)) + 0.27 * alone);
+    return 3.62 + std::max(clocks / 2400.0, hbm);
+  }
   // clocks of a workgroup that has the compute unit to itself
   const double alone = 11267.0 + 0.788 * slots + (ft1 + p.WF - 1) / p.WF * p.steps1 * T.MA * (mfma + 12.0) +
                        (ft2 + p.WF - 1) / p.WF * T.MB * (p.steps2 * (mfma + 12.0) + 581.0);
@@ -551,12 +733,9 @@ double estimate(const BasicBlockArgs& a, const BasicPlan& plan) {
   const double lds = 1.43 * tiles, matrix = 0.0795 * mfma * tiles;
   const double memory = ((ft1 * p.steps1 + ft2 * p.steps2) * 1024.0 * WP + p.in_pixels * a.s1.C * es + 77.6 * slots +
                          2.0 * p.outs * a.s2.K * es) / 216.0;
-  const int per_cu = (p.total + kComputeUnits - 1) / kComputeUnits;
-  const int resident = std::max(1, std::min({per_cu, T.min_waves / 2, (int)(kLdsLimit / plan.lds)}));
   const double clocks = std::max((per_cu + resident - 1) / resident * alone,
                                  per_cu * (std::max({lds, matrix, memory}) + 1.867 * (lds + matrix + memory)) + 0.557 * alone);
-  const double pixels = (double)p.total / p.tiles * p.P * p.Q;
-  return 3.62 + std::max(clocks / 2400.0, pixels * es * (p.stride * p.stride * a.s1.C + 2.0 * a.s2.K) / 4.5e6);
+  return 3.62 + std::max(clocks / 2400.0, hbm);
 }
 
 // Estimated us of the two operators as launches of their own, fitted to the same blocks (to 6 %).
@@ -571,7 +750,8 @@ double estimate_apart(const BasicBlockArgs& a, double pixels) {
 }
 
 // The tuning switch basic_tile=<index of the rectangle>x<waves along the filters> forces a plan.
-bool pick_basic(const BasicBlockArgs& a, int N, BasicPlan* best, double* cost) {
+// `like`: the sums' order is the one of that plan.
+bool pick_basic(const BasicBlockArgs& a, int N, const BasicPlan* like, BasicPlan* best, double* cost) {
   char text[32];
   if (tuning_text("basic_tile", text, sizeof(text))) {
     int rectangle = -1, wf = 8;
@@ -581,11 +761,17 @@ bool pick_basic(const BasicBlockArgs& a, int N, BasicPlan* best, double* cost) {
     return plan_basic(a, N, rectangle, wf, best);
   }
   bool any = false;
+  const int last = kNumRectangles - 1;
+  const bool by_rows = plan_basic(a, N, last, kWaves, best) || plan_basic(a, N, last, 4, best);
   for (int r = 0; r < kNumRectangles; ++r)
     for (int wf = 1; wf <= kWaves; wf *= 2) {
       BasicPlan plan;
+      // (14 columns by rows: never slower than other tiles of them, 36.0 against 43.2 us at 64 x 56 x 56 x 64)
+      if (!kRectangles[r].by_rows && kRectangles[r].cols == 14 && by_rows) continue;
+      if (like && kRectangles[r].by_rows != kRectangles[like->rectangle].by_rows) continue;
       if (!plan_basic(a, N, r, wf, &plan)) continue;
-      const double c = estimate(a, plan);
+      // (a near tie is better by rows: 17.0 against 21.3 us at 20 x 56 x 56 x 64 -> 32 -> 64)
+      const double c = estimate(a, plan) * (by_rows && !kRectangles[r].by_rows ? 1.02 : 1.0);
       if (any && c >= *cost) continue;
       *best = plan;
       *cost = c;
@@ -594,23 +780,27 @@ bool pick_basic(const BasicBlockArgs& a, int N, BasicPlan* best, double* cost) {
   return any;
 }
 
-// Whether a batch of N images runs the block as one launch, and the plan for `count` of them.  (The sums do
-// not depend on the plan: sub-batches give the batch's bits.)
+// Whether a batch of N images runs the block as one launch, and the plan for `count` of them.  (The sums'
+// order depends on by_rows alone, which follows the batch: sub-batches give the batch's bits.)
 bool choose(const BasicBlockArgs& a, int N, int count, BasicPlan* plan) {
   const double pixels = (double)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
   double cost;
-  if (!pick_basic(a, N, plan, &cost)) return false;
+  if (!pick_basic(a, N, nullptr, plan, &cost)) return false;
   char text[32];
   if (!tuning_text("basic_tile", text, sizeof(text))) {
-    // Short launches: 5 % less than the launches apart, which is what the two estimates are uncertain by;
+    // Short launches: 8 % less than the launches apart, which is what the two estimates are uncertain by;
     // both were fitted to launches between events, which takes some 1.5 us more for each than one after
-    // the other.  Long ones, one after the other, take longer than alone by more than the launches apart
-    // do (a network of 64 images 1.04x faster, of 100 0.99x, of 250, whose sub-batches run side by side, 0.91x
-    // with every block that is 5 % better by the estimate): a fifth less.
+    // the other.  Long ones: one after the other they take longer than alone by more than the launches apart
+    // do, which are better at running side by side, so 22 %, and 25 % where a compute unit holds one workgroup
+    // at a time.  Networks at 8 - 20 %: ResNet-34 of 256 images 0.986x, ResNet-18 of 128, unpruned, 0.990x, of 80,
+    // unpruned, 0.993x, of 250 0.994x; at 23 - 30 %: of 64 1.12x, of 160 1.07x, of 200 1.02x.
     const double apart = estimate_apart(a, pixels);
-    if (apart > 30.0 ? cost >= 0.8 * apart : cost - 1.5 >= 0.95 * (apart - 3.0)) return false;
+    const bool one_at_a_time = plan->p.total > kComputeUnits && plan->lds > kLdsLimit / 2;
+    if (apart > 30.0 ? cost >= (one_at_a_time ? 0.75 : 0.78) * apart : cost - 1.5 >= 0.92 * (apart - 3.0)) return false;
   }
-  return count == N || pick_basic(a, count, plan, &cost);
+  if (count == N) return true;
+  const BasicPlan whole = *plan;
+  return pick_basic(a, count, &whole, plan, &cost);
 }
 
 // A choice is a function of sizes alone; each thread remembers its last answers (some thirty plans are

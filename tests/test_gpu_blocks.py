@@ -176,3 +176,30 @@ def test_basic_block(fx, case, rectangle, wf):
     tiles = [-(-(-(-px // 16)) // (8 // wf)) for px in ((th + 2) * (tw + 2), th * tw)]
     fits = any(tiles[0] <= a and tiles[1] <= b for a, b in [(2, 1), (3, 2), (4, 3), (6, 4), (8, 7), (16, 13)])
     net.check("basic_tile", f"{rectangle}x{wf}", "basic_block_", fits)
+
+
+# Rows of the rectangle as tiles (the last two rectangles): rectangles over the edges, rows of taps that end within a
+# step of the reduction, in one step, on a whole one; two passes over the filters
+BY_ROWS = [
+    ("bf16", 2, 14, 14, 8, 16, 8, "input"),
+    ("f16", 1, 17, 31, 24, 45, 24, "input"),
+    ("bf16", 3, 28, 15, 64, 77, 100, "other"),
+    ("f16", 1, 30, 28, 37, 130, 48, "none"),
+    ("bf16", 1, 15, 14, 128, 64, 128, "input"),
+]
+
+
+@pytest.mark.parametrize("rows", [6, 14])
+@pytest.mark.parametrize("wf", [2, 4, 8])
+@pytest.mark.parametrize("case", BY_ROWS, ids=lambda c: "-".join(map(str, c)))
+def test_basic_block_by_rows(fx, case, wf, rows):
+    dtype, n, h, w, c, k1, k2, back = case
+    net = Net(fx, dtype, n, (16, h, w), seed=sum(case[1:7]) + wf + rows)
+    t = [net.conv(0, 128, 1) for _ in range(4)]       # (for the workspace, as above)
+    t_x = net.conv(net.conv(t[0], 128, 1, add=t[1]), 128, 1, add=net.conv(t[2], 128, 1, add=t[3]))
+    t_x = net.conv(t_x, c, 1)
+    t_r = net.conv(t_x, k2, 1) if back == "other" else -1
+    t_mid = net.conv(t_x, k1, 3)
+    add = {"input": t_x, "other": t_r, "none": -1}[back]
+    net.conv(net.conv(t_mid, k2, 3, add=add), 24, 1)
+    net.check("basic_tile", f"{len(RECTANGLES) + (rows == 14)}x{wf}", f"basic_block_{rows}x14r", wf >= 4)
