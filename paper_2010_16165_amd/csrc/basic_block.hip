@@ -16,7 +16,7 @@
 // images 20.0 -> 13.5, 32 images 35.5 -> 20.8, 64 images 54.7 -> 36.0 (43.2 not by rows), 250 images 137 -> 121 (150);
 // 128 -> 90 -> 128 at 28 x 28 x 64 44.9 -> 31.1 (36.9); single precision, 16 -> 12 -> 16 at 32 x 32 x 32 images
 // 16.4 -> 11.0, 32 -> 23 -> 32 at 16 x 16 x 32 16.3 -> 12.  Networks: ResNet-18, one image 97.6 -> 92.9, 64 images
-// 381 -> 330; ResNet-20 in single precision, 32 images 111 -> 101.
+// 377 -> 345; ResNet-20 in single precision, 32 images 111 -> 103.
 // What bounds it: at a few images the start (index arithmetic, arguments, first weights: 4000 of 11 000
 // clocks) and the weights' latency; at many, LDS where a read of 1 KB, 8 clocks, serves one MFMA of 4 clocks
 // per compute unit, and by rows the serial chain of a workgroup, load, multiply, multiply, store, of which
@@ -102,7 +102,7 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 // M tiles of 16 pixels x one tile of 16 filters over all steps of a reduction, pixels from LDS.  a holds
 // the weights of the first D steps.  (Single precision adds each step's 16 products up on their own, then the sum
 // to the others': a quarter as many roundings at the size of the whole sum.  Without it the error of a block of 16
-// channels against 64 bits was 2.0e-7 of the result, 1.2e-7 with two launches.)
+// channels against 64 bits was 2.0e-7 of the result, 1.2e-7 with two launches; with it 1.1e-7.)
 template <int EL, int M, int D, int NB, class Load>
 __device__ __forceinline__ void multiply(const char* lds, const uint32_t (&origin)[M], const uint32_t* table, int g,
                                          uint32_t zero_at, int steps, uint4 (&a)[D], f32x4 (&acc)[M], Load&& load) {
