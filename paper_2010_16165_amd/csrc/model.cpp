@@ -900,6 +900,11 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
   return conv_pair_fusable(a.conv, b.conv, m->dt, 1, tin.H, tin.W, shortcut_offset(a));
 }
 
+// Operators i and i + 1 are one launch under the switches of the moment: planned as one, and not refused now.
+bool runs_as_pair(const fupr_model* m, size_t i) {
+  return stem_pool_pair(m, i) || (m->pair_planned[i] && conv_conv_pair(m, i));
+}
+
 // Tensor t is read by one operator, as its input, and by nobody else.
 bool read_once(const fupr_model* m, size_t t) {
   int readers = 0;
@@ -1043,7 +1048,7 @@ std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, i
         // (a block on the caller's own tensors can turn out to be two launches: their sizes and places
         // are known when it runs)
         hidden[i + 1] = m->ops[i].in != 0 && m->ops[i + 1].res != 0 && i + 2 != n;
-      } else if (i + 1 < n && !chosen[i + 1] && (m->pair_planned[i] || stem_pool_pair(m, (size_t)i))) {
+      } else if (i + 1 < n && !chosen[i + 1] && runs_as_pair(m, (size_t)i)) {
         l.count = 2;
       }
       const bool together = l.block || m->pair_planned[i];
@@ -1103,9 +1108,7 @@ std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, i
 std::vector<Launch> list_launches(const fupr_model* m, int schedule) {
   std::vector<Launch> v;
   for (size_t i = 0; i < m->ops.size();) {
-    const bool pair = schedule == FUPR_SCHEDULE_AUTO &&
-                      (stem_pool_pair(m, i) || (m->pair_planned[i] && conv_conv_pair(m, i)));
-    const int count = pair ? 2 : 1;
+    const int count = schedule == FUPR_SCHEDULE_AUTO && runs_as_pair(m, i) ? 2 : 1;
     v.push_back(Launch{(int)i, count});
     i += count;
   }

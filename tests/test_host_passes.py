@@ -738,6 +738,26 @@ def test_switches_at_creation_leave_nothing_behind(switch, value):
         assert m.num_launches == m.num_ops
 
 
+@pytest.mark.parametrize("switch,value", [("conv1x1_fuse", 0), ("conv1x1_stream", 0), ("pair_filters", 16)]
+                         + [("stream_tile", t) for t in range(6)])
+def test_switches_decide_pairs_beside_blocks(switch, value):
+    """With blocks in one launch a batch lists a pair of 1 x 1 convolutions only where it does without
+    them: one that the switches of the moment refuse would end the pass when it is reached."""
+    plan = network.optimise(synth.make_config(3)[0])
+    models = [build_host_model(plan, 1 << 20)[0] for _ in range(2)]
+    models[0].fuse_blocks(True)
+    B.fupr_tuning_set(switch, value)
+    try:
+        for batch in (9, 64, 256):
+            with_blocks, without = ([m.launch_stats(batch, i) for i in range(m.num_launches_at(batch))] for m in models)
+            assert any(s["kernel"].startswith("bottleneck_") for s in with_blocks)
+            pairs = [{(s["first_op"], s["kernel"]) for s in v if s["n_ops"] == 2 and s["kernel"].startswith("conv1x1s")}
+                     for v in (with_blocks, without)]
+            assert pairs[0] <= pairs[1]
+    finally:
+        B.fupr_tuning_set(switch, None)
+
+
 # ---- a block's pruned output filters (Alg. 1 on every non-fused operator, Sec. V-A) ---------
 
 def scatter_ops(keep=0x2000, **change):
