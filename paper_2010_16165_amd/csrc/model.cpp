@@ -544,6 +544,7 @@ void plan_resident(fupr_model* m) {
 
 void release_side(fupr_model* m);   // below, with the forked schedule
 bool conv_conv_pair(const fupr_model* m, size_t i);   // below, with the launch list
+bool stem_pool_pair(const fupr_model* m, size_t i);
 void find_blocks(fupr_model* m);                      // likewise
 std::vector<Launch> list_launches(const fupr_model* m, int schedule);
 
@@ -676,14 +677,14 @@ extern "C" fupr_status fupr_model_create(const fupr_graph_desc* g, fupr_model** 
       return FUPR_ERR_ARG;
     }
   }
-  // two convolutions that may run as one kernel: what the first reads must
+  // two operators that may run as one kernel: what the first reads must
   // outlive the second, whose output is written while the first still reads.
   // Which ones may does not depend on the switches of the moment: they can change
   // between here and a forward pass.
   m->pair_planned.assign(n, 0);
   {
     const WithoutTuning no_switches;
-    for (int i = 0; i + 1 < n; ++i) m->pair_planned[i] = conv_conv_pair(m, (size_t)i);
+    for (int i = 0; i + 1 < n; ++i) m->pair_planned[i] = conv_conv_pair(m, (size_t)i) || stem_pool_pair(m, (size_t)i);
   }
   for (int i = 0; i + 1 < n; ++i) {
     if (!m->pair_planned[i]) continue;
@@ -902,7 +903,7 @@ bool conv_conv_pair(const fupr_model* m, size_t i) {
 
 // Operators i and i + 1 are one launch under the switches of the moment: planned as one, and not refused now.
 bool runs_as_pair(const fupr_model* m, size_t i) {
-  return stem_pool_pair(m, i) || (m->pair_planned[i] && conv_conv_pair(m, i));
+  return m->pair_planned[i] && (stem_pool_pair(m, i) || conv_conv_pair(m, i));
 }
 
 // Tensor t is read by one operator, as its input, and by nobody else.

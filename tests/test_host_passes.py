@@ -459,6 +459,24 @@ def test_model_plan_shares_buffers_and_reports_shapes():
     assert s["kernel"].startswith("conv")
 
 
+def test_input_of_a_stem_with_its_pool_outlives_the_launch():
+    """A 7 x 7 convolution and its max-pool run as one kernel wherever they stand: the pool's output is
+    written while other workgroups still read the convolution's input, so the two share no buffer."""
+    ops = fake_ops([
+        (B.OP_CONV, 0, -1, 3, 3, 1, 1, 0, B.FUSE_RELU, 1),                   # t1 3x64x64
+        (B.OP_CONV, 1, -1, 64, 3, 7, 2, 3, B.FUSE_RELU, 1),                  # t2 64x32x32
+        (B.OP_MAXPOOL, 2, -1, 64, 64, 3, 2, 1, 0, 1),                        # t3 64x16x16
+        (B.OP_CONV, 3, -1, 10, 64, 1, 1, 0, 0, 1),
+    ])
+    m = B.Model(B.BF16, (3, 64, 64), ops, None)
+    assert [m.launch_stats(1, i)["kernel"] for i in range(m.num_launches_at(1))][1] == "stem7x7_maxpool"
+    assert m.workspace_bytes(1) == 2 * (64 * 64 * 8 + 32 * 32 * 64 + 16 * 16 * 64)
+    # ... and a stem that reads the network's input needs no more than its two tensors
+    m = B.Model(B.BF16, (3, 64, 64), [B.OpDesc(o.kind, o.in_ - 1, -1, o.conv, 0x1000, o.epilogue, 1, 0) for o in ops[1:]],
+                None)
+    assert m.workspace_bytes(1) == 2 * (32 * 32 * 64 + 16 * 16 * 64)
+
+
 def test_kernel_selection_per_layer_class():
     """Which kernel an operator launches is decided on the host from its shape
     alone: every layer class of the ImageNet workloads must get its own kernel."""
