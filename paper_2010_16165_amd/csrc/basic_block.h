@@ -12,14 +12,16 @@ struct BasicBlockArgs {
   bool add;              // the second adds a shortcut
 };
 
-// Shapes alone: the kernel can run these operators (at any batch size that basic_block_wanted takes).
+// Shapes alone: the kernel can run these operators (at any batch size that basic_block_plan takes).
 bool basic_block_applies(const BasicBlockArgs& a);
-// ... and is the faster way to at N images.
-bool basic_block_wanted(const BasicBlockArgs& a, int N);
-const char* basic_block_name(const BasicBlockArgs& a, int N);
-// `count` images of a batch of N; the two convolutions' arguments as they would run by themselves (the
-// tensor between them is neither read nor written).
-fupr_status launch_basic_block(const BasicBlockArgs& a, const ConvArgs& first, const ConvArgs& second, int N, int count,
-                               void* stream);
+// The plan for a batch of N images, a number of this kernel's own; -1: the operators run apart.
+int basic_block_plan(const BasicBlockArgs& a, int N);
+// ... for `count` images of a batch that runs `plan`, which give that batch's bits.
+int basic_block_plan_part(const BasicBlockArgs& a, int plan, int count);
+const char* basic_block_name(int plan);
+// The two convolutions' arguments as they would run by themselves (the tensor between them is neither read
+// nor written).
+fupr_status launch_basic_block(const BasicBlockArgs& a, const ConvArgs& first, const ConvArgs& second, int plan,
+                               int count, void* stream);
 
 }  // namespace fupr

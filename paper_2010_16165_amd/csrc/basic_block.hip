@@ -27,7 +27,6 @@
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
-#include <cstring>
 #include <type_traits>
 
 #include "basic_block.h"
@@ -750,8 +749,9 @@ double estimate_apart(const BasicBlockArgs& a, double pixels) {
 }
 
 // The tuning switch basic_tile=<index of the rectangle>x<waves along the filters> forces a plan.
-// `like`: the sums' order is the one of that plan.
-bool pick_basic(const BasicBlockArgs& a, int N, const BasicPlan* like, BasicPlan* best, double* cost) {
+// like >= 0: only rectangles whose sums' order is that one's.  (Some thirty plans: a model asks once for a batch size
+// and keeps the answer.)
+bool pick_basic(const BasicBlockArgs& a, int N, int like, BasicPlan* best, double* cost) {
   char text[32];
   if (tuning_text("basic_tile", text, sizeof(text))) {
     int rectangle = -1, wf = 8;
@@ -768,7 +768,7 @@ bool pick_basic(const BasicBlockArgs& a, int N, const BasicPlan* like, BasicPlan
       BasicPlan plan;
       // (14 columns by rows: never slower than other tiles of them, 36.0 against 43.2 us at 64 x 56 x 56 x 64)
       if (!kRectangles[r].by_rows && kRectangles[r].cols == 14 && by_rows) continue;
-      if (like && kRectangles[r].by_rows != kRectangles[like->rectangle].by_rows) continue;
+      if (like >= 0 && kRectangles[r].by_rows != kRectangles[like].by_rows) continue;
       if (!plan_basic(a, N, r, wf, &plan)) continue;
       // (a near tie is better by rows: 17.0 against 21.3 us at 20 x 56 x 56 x 64 -> 32 -> 64)
       const double c = estimate(a, plan) * (by_rows && !kRectangles[r].by_rows ? 1.02 : 1.0);
@@ -780,59 +780,10 @@ bool pick_basic(const BasicBlockArgs& a, int N, const BasicPlan* like, BasicPlan
   return any;
 }
 
-// Whether a batch of N images runs the block as one launch, and the plan for `count` of them.  (The sums'
-// order depends on by_rows alone, which follows the batch: sub-batches give the batch's bits.)
-bool choose(const BasicBlockArgs& a, int N, int count, BasicPlan* plan) {
-  const double pixels = (double)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
-  double cost;
-  if (!pick_basic(a, N, nullptr, plan, &cost)) return false;
-  char text[32];
-  if (!tuning_text("basic_tile", text, sizeof(text))) {
-    // Short launches: 8 % less than the launches apart, which is what the two estimates are uncertain by;
-    // both were fitted to launches between events, which takes some 1.5 us more for each than one after
-    // the other.  Long ones: one after the other they take longer than alone by more than the launches apart
-    // do, which are better at running side by side, so 22 %, and 25 % where a compute unit holds one workgroup
-    // at a time.  Networks at 8 - 20 %: ResNet-34 of 256 images 0.986x, ResNet-18 of 128, unpruned, 0.990x, of 80,
-    // unpruned, 0.993x, of 250 0.994x; at 23 - 30 %: of 64 1.12x, of 160 1.07x, of 200 1.02x.
-    const double apart = estimate_apart(a, pixels);
-    const bool one_at_a_time = plan->p.total > kComputeUnits && plan->lds > kLdsLimit / 2;
-    if (apart > 30.0 ? cost >= (one_at_a_time ? 0.75 : 0.78) * apart : cost - 1.5 >= 0.92 * (apart - 3.0)) return false;
-  }
-  if (count == N) return true;
-  const BasicPlan whole = *plan;
-  return pick_basic(a, count, &whole, plan, &cost);
-}
-
-// A choice is a function of sizes alone; each thread remembers its last answers (some thirty plans are
-// weighed for one).
-struct Sizes {
-  int N, count, dt, H, W, add;
-  fupr_conv_shape s1, s2;
-  bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
-};
-static_assert(sizeof(Sizes) == 18 * sizeof(int), "no padding: compared and hashed as words");
-
-bool choose_or_recall(const BasicBlockArgs& a, int N, int count, BasicPlan* plan) {
-  if (tuning_any()) return !tuning_off("basic_fuse") && choose(a, N, count, plan);
-  struct Remembered {
-    Sizes sizes;
-    int state;           // 0: empty, 1: a plan, -1: not as one launch
-    BasicPlan plan;
-  };
-  constexpr int kEntries = 64;
-  thread_local Remembered table[kEntries];
-  const Sizes z = {N, count, (int)a.dt, a.H, a.W, a.add, a.s1, a.s2};
-  uint32_t h = 2166136261u;
-  for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
-    h = (h ^ (uint32_t)reinterpret_cast<const int*>(&z)[i]) * 16777619u;
-  Remembered& r = table[(h ^ (h >> 15)) % kEntries];
-  if (r.state == 0 || !(r.sizes == z)) {
-    r.state = choose(a, N, count, &r.plan) ? 1 : -1;
-    r.sizes = z;
-  }
-  if (r.state > 0) *plan = r.plan;
-  return r.state > 0;
-}
+// A plan's number.
+int number_of(const BasicPlan& plan) { return plan.rectangle * (kWaves + 1) + plan.p.WF; }
+int rectangle_of(int number) { return number / (kWaves + 1); }
+int waves_of(int number) { return number % (kWaves + 1); }
 
 }  // namespace
 
@@ -848,20 +799,40 @@ bool basic_block_applies(const BasicBlockArgs& a) {
   return false;
 }
 
-bool basic_block_wanted(const BasicBlockArgs& a, int N) {
+int basic_block_plan(const BasicBlockArgs& a, int N) {
+  if (tuning_off("basic_fuse")) return -1;
+  const double pixels = (double)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
   BasicPlan plan;
-  return choose_or_recall(a, N, N, &plan);
+  double cost;
+  if (!pick_basic(a, N, -1, &plan, &cost)) return -1;
+  char text[32];
+  if (!tuning_text("basic_tile", text, sizeof(text))) {
+    // Short launches: 8 % less than the launches apart, which is what the two estimates are uncertain by;
+    // both were fitted to launches between events, which takes some 1.5 us more for each than one after
+    // the other.  Long ones: one after the other they take longer than alone by more than the launches apart
+    // do, which are better at running side by side, so 22 %, and 25 % where a compute unit holds one workgroup
+    // at a time.  Networks at 8 - 20 %: ResNet-34 of 256 images 0.986x, ResNet-18 of 128, unpruned, 0.990x, of 80,
+    // unpruned, 0.993x, of 250 0.994x; at 23 - 30 %: of 64 1.12x, of 160 1.07x, of 200 1.02x.
+    const double apart = estimate_apart(a, pixels);
+    const bool one_at_a_time = plan.p.total > kComputeUnits && plan.lds > kLdsLimit / 2;
+    if (apart > 30.0 ? cost >= (one_at_a_time ? 0.75 : 0.78) * apart : cost - 1.5 >= 0.92 * (apart - 3.0)) return -1;
+  }
+  return number_of(plan);
 }
 
-const char* basic_block_name(const BasicBlockArgs& a, int N) {
-  BasicPlan plan;
-  return choose_or_recall(a, N, N, &plan) ? kRectangles[plan.rectangle].name : "none";
+// The sums' order depends on by_rows alone: a part keeps its batch's.
+int basic_block_plan_part(const BasicBlockArgs& a, int plan, int count) {
+  BasicPlan part;
+  double cost;
+  return pick_basic(a, count, rectangle_of(plan), &part, &cost) ? number_of(part) : plan;
 }
 
-fupr_status launch_basic_block(const BasicBlockArgs& a, const ConvArgs& first, const ConvArgs& second, int N, int count,
-                               void* stream) {
+const char* basic_block_name(int plan) { return kRectangles[rectangle_of(plan)].name; }
+
+fupr_status launch_basic_block(const BasicBlockArgs& a, const ConvArgs& first, const ConvArgs& second, int number,
+                               int count, void* stream) {
   BasicPlan plan;
-  if (!choose_or_recall(a, N, count, &plan)) return FUPR_ERR_LIMIT;
+  if (!plan_basic(a, count, rectangle_of(number), waves_of(number), &plan)) return FUPR_ERR_LIMIT;
   BasicParams& p = plan.p;
   const uint32_t es = (uint32_t)elem_size(a.dt);
   p.x = first.x; p.res = second.res; p.y = second.y;

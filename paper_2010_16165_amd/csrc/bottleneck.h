@@ -21,12 +21,13 @@ struct BottleneckArgs {
   int relu1, relu2, relu3;
 };
 
-// Shapes alone: the kernel can run these operators (at any batch size that bottleneck_wanted takes).
+// Shapes alone: the kernel can run these operators (at any batch size that bottleneck_plan takes).
 bool bottleneck_applies(const BottleneckArgs& a);
-// ... and is the faster way to at N images.
-bool bottleneck_wanted(const BottleneckArgs& a, int N);
-const char* bottleneck_name(const BottleneckArgs& a, int N);
-// `count` images of a batch of N.
-fupr_status launch_bottleneck(const BottleneckArgs& a, int N, int count, void* stream);
+// The plan for a batch of N images, a number of this kernel's own; -1: the operators run apart.
+int bottleneck_plan(const BottleneckArgs& a, int N);
+// ... for `count` images of a batch that runs `plan`, which give that batch's bits.
+int bottleneck_plan_part(const BottleneckArgs& a, int plan, int count);
+const char* bottleneck_name(int plan);
+fupr_status launch_bottleneck(const BottleneckArgs& a, int plan, int count, void* stream);
 
 }  // namespace fupr

@@ -31,7 +31,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
-#include <cstring>
 #include <type_traits>
 
 #include "bottleneck.h"
@@ -727,7 +726,8 @@ double estimate_apart(const BottleneckArgs& a, int64_t M) {
          (a.third ? one(m * 2 * (a.s2.K + a.s3.K), m * 2 * a.s2.K * a.s3.K) : 0.0);
 }
 
-// The tile with the least estimate; only those with that many waves if waves > 0.
+// The tile with the least estimate; only those with that many waves if waves > 0.  (About ten plans, 2 us of host
+// time: a model asks once for a batch size and keeps the answer.)
 bool pick_block(const BottleneckArgs& a, int N, int waves, BlockPlan* best, double* cost) {
   const int forced = tuning_int("bottleneck_tile", -1);
   if (forced >= 0) {
@@ -747,61 +747,6 @@ bool pick_block(const BottleneckArgs& a, int N, int waves, BlockPlan* best, doub
   return any;
 }
 
-// Whether a batch of N images runs the block as one launch, and the plan for `count` of them.  The
-// order of the 3 x 3 convolution's sums depends on the number of waves, so the whole batch decides it:
-// sub-batches give the batch's bits.
-bool choose(const BottleneckArgs& a, int N, int count, BlockPlan* plan) {
-  const int64_t M = (int64_t)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
-  // 32-bit byte offsets into every tensor
-  for (int64_t elements : {(int64_t)N * a.H * a.W * a.xcs, M * a.ycs, a.two ? (int64_t)N * a.H2 * a.W2 * a.x2cs : 0,
-                           a.third ? M * a.hcs : 0})
-    if (elements * 2 >= (int64_t)kOutside) return false;
-  double cost;
-  if (!pick_block(a, N, 0, plan, &cost)) return false;
-  // 5 % less than the launches apart, which is what the two estimates are uncertain by; 15 % where the
-  // two 1 x 1 convolutions would run as a pair (32 -> 256 -> 32 at 56 x 56 x 24 29 against 33 us, x 64 59
-  // against 55).  Both were fitted to launches between events, which takes some 1.5 us more for each than one
-  // after the other: that decides where they are short (nine irregular images 269 -> 264 us; a network at 64
-  // images, whose sub-batches run side by side, 684 against 670 when it is counted there too).
-  const double gap = M < 8192 ? 1.5 : 0.0;
-  if (tuning_int("bottleneck_tile", -1) < 0 &&
-      cost - gap >= (a.pair ? 0.85 : 0.95) * (estimate_apart(a, M) - gap * (a.third ? 3 : 2)))
-    return false;
-  return count == N || pick_block(a, count, kTiles[plan->tile].waves, plan, &cost);
-}
-
-// A choice is a function of sizes alone; each thread remembers its last answers (about ten plans are
-// weighed for one, 2 us of host time).
-struct Sizes {
-  int N, count, dt, H, W, xcs, H2, W2, x2cs, stride2, third, two, pair, ycs, hcs;
-  fupr_conv_shape s1, s2, s3;
-  bool operator==(const Sizes& o) const { return std::memcmp(this, &o, sizeof(o)) == 0; }
-};
-static_assert(sizeof(Sizes) == 33 * sizeof(int), "no padding: compared and hashed as words");
-
-bool choose_or_recall(const BottleneckArgs& a, int N, int count, BlockPlan* plan) {
-  if (tuning_any()) return !tuning_off("bottleneck_fuse") && choose(a, N, count, plan);
-  struct Remembered {
-    Sizes sizes;
-    int state;           // 0: empty, 1: a plan, -1: not as one launch
-    BlockPlan plan;
-  };
-  constexpr int kEntries = 64;
-  thread_local Remembered table[kEntries];
-  const Sizes z = {N, count, (int)a.dt, a.H, a.W, a.xcs, a.H2, a.W2, a.x2cs, a.stride2, a.third, a.two, a.pair, a.ycs, a.hcs,
-                   a.s1, a.s2, a.s3};
-  uint32_t h = 2166136261u;
-  for (size_t i = 0; i < sizeof(z) / sizeof(int); ++i)
-    h = (h ^ (uint32_t)reinterpret_cast<const int*>(&z)[i]) * 16777619u;
-  Remembered& r = table[(h ^ (h >> 15)) % kEntries];
-  if (r.state == 0 || !(r.sizes == z)) {
-    r.state = choose(a, N, count, &r.plan) ? 1 : -1;
-    r.sizes = z;
-  }
-  if (r.state > 0) *plan = r.plan;
-  return r.state > 0;
-}
-
 }  // namespace
 
 bool bottleneck_applies(const BottleneckArgs& a) {
@@ -815,19 +760,40 @@ bool bottleneck_applies(const BottleneckArgs& a) {
   return false;
 }
 
-bool bottleneck_wanted(const BottleneckArgs& a, int N) {
+int bottleneck_plan(const BottleneckArgs& a, int N) {
+  if (tuning_off("bottleneck_fuse")) return -1;
+  const int64_t M = (int64_t)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
+  // 32-bit byte offsets into every tensor
+  for (int64_t elements : {(int64_t)N * a.H * a.W * a.xcs, M * a.ycs, a.two ? (int64_t)N * a.H2 * a.W2 * a.x2cs : 0,
+                           a.third ? M * a.hcs : 0})
+    if (elements * 2 >= (int64_t)kOutside) return -1;
   BlockPlan plan;
-  return choose_or_recall(a, N, N, &plan);
+  double cost;
+  if (!pick_block(a, N, 0, &plan, &cost)) return -1;
+  // 5 % less than the launches apart, which is what the two estimates are uncertain by; 15 % where the
+  // two 1 x 1 convolutions would run as a pair (32 -> 256 -> 32 at 56 x 56 x 24 29 against 33 us, x 64 59
+  // against 55).  Both were fitted to launches between events, which takes some 1.5 us more for each than one
+  // after the other: that decides where they are short (nine irregular images 269 -> 264 us; a network at 64
+  // images, whose sub-batches run side by side, 684 against 670 when it is counted there too).
+  const double gap = M < 8192 ? 1.5 : 0.0;
+  if (tuning_int("bottleneck_tile", -1) < 0 &&
+      cost - gap >= (a.pair ? 0.85 : 0.95) * (estimate_apart(a, M) - gap * (a.third ? 3 : 2)))
+    return -1;
+  return plan.tile;
 }
 
-const char* bottleneck_name(const BottleneckArgs& a, int N) {
-  BlockPlan plan;
-  return choose_or_recall(a, N, N, &plan) ? kTiles[plan.tile].name : "none";
+// The order of the 3 x 3 convolution's sums depends on the number of waves: a part keeps its batch's.
+int bottleneck_plan_part(const BottleneckArgs& a, int plan, int count) {
+  BlockPlan part;
+  double cost;
+  return pick_block(a, count, kTiles[plan].waves, &part, &cost) ? part.tile : plan;
 }
 
-fupr_status launch_bottleneck(const BottleneckArgs& a, int N, int count, void* stream) {
+const char* bottleneck_name(int plan) { return kTiles[plan].name; }
+
+fupr_status launch_bottleneck(const BottleneckArgs& a, int tile, int count, void* stream) {
   BlockPlan plan;
-  if (!choose_or_recall(a, N, count, &plan)) return FUPR_ERR_LIMIT;
+  if (!plan_block(a, count, tile, &plan)) return FUPR_ERR_LIMIT;
   BlockParams& p = plan.p;
   const PackedLayout L1 = packed_layout(a.s1, a.dt), L2 = packed_layout(a.s2, a.dt);
   auto weights = [](const void* blob, const PackedLayout& L) {

@@ -31,6 +31,7 @@ enum { kBottleneck = 1, kBasic = 2 };   // bottleneck.hip, basic_block.hip
 struct Launch {
   int first, count;
   int block = 0;        // kBottleneck or kBasic: a block in one launch
+  int plan = -1;        // ... and its kernel's plan for the batch
 };
 
 struct TensorInfo {
@@ -55,6 +56,10 @@ struct fupr_model {
   struct Placement {
     std::vector<Launch> launches;
     std::vector<int> buffer;              // per tensor, as TensorInfo::buffer; -3: not needed
+    // per number of images of a sub-batch (up to two for each of at most four splits): the block's plan
+    // per operator that starts one
+    mutable std::map<int, std::shared_ptr<const std::vector<int>>> parts;
+    mutable std::mutex parts_mutex;
   };
   std::map<int, std::shared_ptr<const Placement>> placed;
   std::mutex placed_mutex;
@@ -992,17 +997,17 @@ int basic_block_at(const fupr_model* m, size_t i, BasicBlockArgs* out) {
   return 2;
 }
 
-// Whether a batch of N images runs the block that starts with operator i as one launch.
-bool block_wanted(const fupr_model* m, size_t i, int N) {
+// The plan with which a batch of N images runs the block that starts with operator i as one launch, -1: it does not.
+int block_plan(const fupr_model* m, size_t i, int N) {
   const fupr_model::Block& b = m->block_args[i];
-  if (b.kind == kBottleneck) return bottleneck_wanted(b.bottleneck, N);
-  if (b.kind != kBasic) return false;
+  if (b.kind == kBottleneck) return bottleneck_plan(b.bottleneck, N);
+  if (b.kind != kBasic) return -1;
   // 32-bit byte offsets into every tensor
   for (int t : {m->ops[i].in, (int)i + 2, std::max(m->ops[i + 1].res, 0)}) {
     const TensorInfo& ti = m->tensors[t];
-    if ((int64_t)N * ti.H * ti.W * ti.cs * (int64_t)elem_size(m->dt) >= (int64_t(1) << 31)) return false;
+    if ((int64_t)N * ti.H * ti.W * ti.cs * (int64_t)elem_size(m->dt) >= (int64_t(1) << 31)) return -1;
   }
-  return basic_block_wanted(b.basic, N);
+  return basic_block_plan(b.basic, N);
 }
 
 void find_blocks(fupr_model* m) {
@@ -1025,9 +1030,10 @@ std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, i
   const int n = (int)m->ops.size();
   auto out = std::make_shared<fupr_model::Placement>();
   std::vector<char> chosen(n, 0);          // operators of the block that starts there
+  std::vector<int> plan(n, -1);
   bool any = false;
   for (int i = 0; i < n; i += chosen[i] ? chosen[i] : 1)
-    if (block_wanted(m, (size_t)i, N)) {
+    if ((plan[i] = block_plan(m, (size_t)i, N)) >= 0) {
       chosen[i] = (char)m->block_args[i].count;
       any = true;
     }
@@ -1045,7 +1051,7 @@ std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, i
     for (int i = 0; i < n;) {
       Launch l{i, 1};
       if (chosen[i]) {
-        l = Launch{i, chosen[i], m->block_args[i].kind};
+        l = Launch{i, chosen[i], m->block_args[i].kind, plan[i]};
         // (a block on the caller's own tensors can turn out to be two launches: their sizes and places
         // are known when it runs)
         hidden[i + 1] = m->ops[i].in != 0 && m->ops[i + 1].res != 0 && i + 2 != n;
@@ -1143,12 +1149,22 @@ std::shared_ptr<const fupr_model::Placement> blocks_on(const fupr_model* m, int 
   return p->buffer.empty() ? nullptr : p;
 }
 
-// The launches of a batch of N images.  Of a pair of 1 x 1 convolutions whose tensors are small, two
-// launches that fill the GPU are faster than one that walks it (nine images of 193 x 193, 49 x 49
-// pixels, 47 -> 256 -> 111 channels: 18 us in one, 12 in two; a launch more costs 1.7).
-std::vector<Launch> launches_at(const fupr_model* m, int N) {
-  const auto placed = blocks_on(m, N);
-  std::vector<Launch> v = placed ? placed->launches : launches_of(m);
+// The launches of a batch and the placement that they need, null for the model's own.  Looked up once
+// for a pass: a launch is right only with the tensors where its list has them, and switches may change
+// between two looks.
+struct Scheduled {
+  std::vector<Launch> launches;
+  std::shared_ptr<const fupr_model::Placement> placed;
+};
+
+// Of a pair of 1 x 1 convolutions whose tensors are small, two launches that fill the GPU are faster than
+// one that walks it (nine images of 193 x 193, 49 x 49 pixels, 47 -> 256 -> 111 channels: 18 us in one,
+// 12 in two; a launch more costs 1.7).
+Scheduled scheduled_at(const fupr_model* m, int N) {
+  Scheduled out;
+  out.placed = blocks_on(m, N);
+  std::vector<Launch>& v = out.launches;
+  v = out.placed ? out.placed->launches : launches_of(m);
   for (size_t i = 0; i < v.size(); ++i) {
     const Launch l = v[i];
     if (l.count != 2 || l.block || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
@@ -1159,7 +1175,23 @@ std::vector<Launch> launches_at(const fupr_model* m, int N) {
     v[i].count = 1;
     v.insert(v.begin() + ++i, Launch{l.first + 1, 1});
   }
-  return v;
+  return out;
+}
+
+// The plans of a batch's blocks for `count` of its images, per operator that starts one.
+std::shared_ptr<const std::vector<int>> plans_of_part(const fupr_model* m, const fupr_model::Placement& placed, int count) {
+  std::lock_guard<std::mutex> lock(placed.parts_mutex);
+  std::shared_ptr<const std::vector<int>>& known = placed.parts[count];
+  if (!known) {
+    std::vector<int> plans(m->ops.size(), -1);
+    for (const Launch& l : placed.launches) {
+      const fupr_model::Block& b = m->block_args[l.first];
+      if (l.block == kBottleneck) plans[l.first] = bottleneck_plan_part(b.bottleneck, l.plan, count);
+      else if (l.block == kBasic) plans[l.first] = basic_block_plan_part(b.basic, l.plan, count);
+    }
+    known = std::make_shared<const std::vector<int>>(std::move(plans));
+  }
+  return known;
 }
 
 // Sub-batches of the per-operator schedule.  Two sub-batches side by side let one's
@@ -1198,8 +1230,9 @@ void release_side(fupr_model* m) {
   m->n_side = 0;
 }
 
+// events: one before and one behind every launch, whose number is written to *n_launches.
 fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor* output,
-                void* workspace, size_t workspace_bytes, void* stream, hipEvent_t* events) {
+                void* workspace, size_t workspace_bytes, void* stream, hipEvent_t* events, size_t* n_launches) {
   if (!m || !input || !output || !workspace) return FUPR_ERR_NULL;
   if (!input->ptr || !output->ptr) return FUPR_ERR_NULL;
   if (input->dt != m->dt || output->dt != m->dt) return FUPR_ERR_DTYPE;
@@ -1225,7 +1258,8 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
   // images n0 .. n0 + count - 1 of a tensor; inside a workspace buffer every
   // sub-batch owns the slice its images would need at the buffer's largest tensor
   const size_t es = elem_size(m->dt);
-  const auto placed = blocks_on(m, N);
+  Scheduled schedule;
+  const fupr_model::Placement* placed = nullptr;
   auto view = [&](int tid, int n0, int count) {
     const TensorInfo& t = m->tensors[tid];
     const int buffer = placed ? placed->buffer[tid] : t.buffer;
@@ -1260,9 +1294,13 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
     const fupr_status st = launch_resident(R, N, m->dt, stream);
     if (st != FUPR_OK) return st;
     if (events && hipEventRecord(events[1], hs) != hipSuccess) return FUPR_ERR_LAUNCH;
+    if (n_launches) *n_launches = 1;
     return FUPR_OK;
   }
-  const std::vector<Launch> launches = launches_at(m, N);
+  schedule = scheduled_at(m, N);
+  placed = schedule.placed.get();
+  const std::vector<Launch>& launches = schedule.launches;
+  if (n_launches) *n_launches = launches.size();
   auto residual = [&](const fupr_op_desc& op, int n0, int count) {
     fupr_residual r{};
     if (op.res >= 0) {
@@ -1275,7 +1313,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
   // Operators i and i + 1 as one launch, after the checks that each of them gets by itself; as two
   // where tensors need more than 32-bit offsets or the output overlaps what the first reads (its own
   // launch reads it before the other's writes).
-  auto basic_block = [&](size_t i, const fupr_tensor& x, const fupr_tensor& y, int n0, int count,
+  auto basic_block = [&](size_t i, int plan, const fupr_tensor& x, const fupr_tensor& y, int n0, int count,
                          void* on) -> fupr_status {
     const fupr_op_desc &a = m->ops[i], &b = m->ops[i + 1];
     fupr_tensor mid = view((int)i + 1, n0, count);
@@ -1292,21 +1330,23 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
     const uintptr_t x0 = (uintptr_t)x.ptr, y0 = (uintptr_t)y.ptr;
     bool apart = x0 < y0 + bytes(y) && y0 < x0 + bytes(x);
     for (size_t size : {bytes(x), bytes(y), b.res >= 0 ? bytes(r.t) : 0}) apart = apart || size >= (size_t(1) << 31);
-    if (hidden && apart) return FUPR_ERR_LIMIT;   // (block_wanted takes no such sizes)
-    if (!apart) return launch_basic_block(m->block_args[i].basic, first, second, N, count, on);
+    if (hidden && apart) return FUPR_ERR_LIMIT;   // (block_plan takes no such sizes)
+    if (!apart) return launch_basic_block(m->block_args[i].basic, first, second, plan, count, on);
     st = conv_fused_part(&a.conv, &x, nullptr, 0, a.packed, nullptr, a.epilogue, &mid, N, on);
     if (st != FUPR_OK) return st;
     return conv_fused_part(&b.conv, &mid, nullptr, 0, b.packed, b.res >= 0 ? &r : nullptr, b.epilogue, &y, N, on);
   };
   auto enqueue = [&](int n0, int count, void* on, bool record) -> fupr_status {
+    const auto part = placed && count != N ? plans_of_part(m, *placed, count) : nullptr;
     for (size_t l = 0; l < launches.size(); ++l) {
       const size_t i = (size_t)launches[l].first;
       const fupr_op_desc& op = m->ops[i];
       const fupr_tensor x = view(op.in, n0, count);
       const fupr_tensor y = view((int)i + launches[l].count, n0, count);
+      const int plan = part ? (*part)[i] : launches[l].plan;
       fupr_status st;
       if (launches[l].block == kBasic) {
-        st = basic_block(i, x, y, n0, count, on);
+        st = basic_block(i, plan, x, y, n0, count, on);
       } else if (launches[l].block) {
         BottleneckArgs g = m->block_args[i].bottleneck;
         const fupr_op_desc& b = m->ops[i + 1];
@@ -1323,7 +1363,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
         st = FUPR_OK;
         for (const void* blob : {g.packed1, g.packed2, g.packed3})
           if ((reinterpret_cast<uintptr_t>(blob) & 255u) != 0) st = FUPR_ERR_ALIGN;
-        if (st == FUPR_OK) st = launch_bottleneck(g, N, count, on);
+        if (st == FUPR_OK) st = launch_bottleneck(g, plan, count, on);
       } else if (launches[l].count == 2 && m->ops[i + 1].kind == FUPR_OP_CONV) {
         const fupr_op_desc& second = m->ops[i + 1];
         const fupr_tensor mid = view((int)i + 1, n0, count);
@@ -1402,7 +1442,7 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
 extern "C" fupr_status fupr_forward(const fupr_model* m, const fupr_tensor* input,
                                     const fupr_tensor* output, void* workspace,
                                     size_t workspace_bytes, void* stream) {
-  return run(m, input, output, workspace, workspace_bytes, stream, nullptr);
+  return run(m, input, output, workspace, workspace_bytes, stream, nullptr, nullptr);
 }
 
 extern "C" fupr_status fupr_forward_timed(const fupr_model* m, const fupr_tensor* input,
@@ -1414,12 +1454,12 @@ extern "C" fupr_status fupr_forward_timed(const fupr_model* m, const fupr_tensor
   fupr_status st = FUPR_OK;
   for (size_t i = 0; i <= n; ++i)
     if (hipEventCreate(&ev[i]) != hipSuccess) { st = FUPR_ERR_LAUNCH; break; }
-  if (st == FUPR_OK) st = run(m, input, output, workspace, workspace_bytes, stream, ev.data());
+  size_t launches = 0;
+  if (st == FUPR_OK) st = run(m, input, output, workspace, workspace_bytes, stream, ev.data(), &launches);
   if (st == FUPR_OK && hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)) != hipSuccess)
     st = FUPR_ERR_LAUNCH;
   if (st == FUPR_OK) {
     std::vector<float> ms(n, 0.0f);
-    const size_t launches = use_resident(m, input, output) ? 1 : launches_at(m, input->N).size();
     for (size_t i = 0; i < launches; ++i)
       if (hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]) != hipSuccess) { st = FUPR_ERR_LAUNCH; break; }
     if (st == FUPR_OK) std::copy(ms.begin(), ms.end(), op_ms);
@@ -1491,15 +1531,19 @@ extern "C" int32_t fupr_model_num_launches(const fupr_model* m) {
 
 extern "C" int32_t fupr_model_num_launches_at(const fupr_model* m, int32_t batch) {
   if (!m || batch <= 0) return 0;
-  return one_kernel(m) ? 1 : (int32_t)launches_at(m, batch).size();
+  return one_kernel(m) ? 1 : (int32_t)scheduled_at(m, batch).launches.size();
 }
 
 extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batch, int32_t launch,
                                                fupr_op_stats* out) {
   if (!m || !out) return FUPR_ERR_NULL;
-  if (batch <= 0 || launch < 0 || launch >= fupr_model_num_launches_at(m, batch)) return FUPR_ERR_ARG;
-  if (!one_kernel(m)) {
-    const Launch l = launches_at(m, batch)[launch];
+  if (batch <= 0 || launch < 0) return FUPR_ERR_ARG;
+  if (one_kernel(m)) {
+    if (launch > 0) return FUPR_ERR_ARG;
+  } else {
+    const std::vector<Launch> launches = scheduled_at(m, batch).launches;
+    if ((size_t)launch >= launches.size()) return FUPR_ERR_ARG;
+    const Launch l = launches[launch];
     fupr_status st = fupr_model_op_stats(m, batch, l.first, out);
     if (st != FUPR_OK || l.count == 1) return st;
     out->n_ops = l.count;
@@ -1515,8 +1559,7 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
         out->flops += o.flops;
         out->bytes += o.bytes - (k == 1 ? 2.0 : 1.0) * es * batch * (double)t.H * t.W * t.C;
       }
-      const fupr_model::Block& b = m->block_args[l.first];
-      out->kernel = l.block == kBasic ? basic_block_name(b.basic, batch) : bottleneck_name(b.bottleneck, batch);
+      out->kernel = l.block == kBasic ? basic_block_name(l.plan) : bottleneck_name(l.plan);
       return FUPR_OK;
     }
     if (m->ops[l.first + 1].kind == FUPR_OP_CONV) {
@@ -1583,7 +1626,7 @@ extern "C" fupr_status fupr_graph_create(const fupr_model* m, const fupr_tensor*
     delete g;
     return FUPR_ERR_LAUNCH;
   }
-  const fupr_status st = run(m, input, output, workspace, workspace_bytes, stream, nullptr);
+  const fupr_status st = run(m, input, output, workspace, workspace_bytes, stream, nullptr, nullptr);
   const hipError_t e = hipStreamEndCapture(hs, &g->graph);
   if (st != FUPR_OK || e != hipSuccess || !g->graph) {
     if (g->graph) (void)hipGraphDestroy(g->graph);

@@ -203,3 +203,52 @@ def test_basic_block_by_rows(fx, case, wf, rows):
     add = {"input": t_x, "other": t_r, "none": -1}[back]
     net.conv(net.conv(t_mid, k2, 3, add=add), 24, 1)
     net.check("basic_tile", f"{len(RECTANGLES) + (rows == 14)}x{wf}", f"basic_block_{rows}x14r", wf >= 4)
+
+
+def test_one_pass_sees_one_schedule(fx):
+    """A tuning switch that another thread turns while passes are enqueued: each pass has the launches and the
+    tensors of one setting or of the other, never of both."""
+    import threading
+    B, torch = fx
+    net = Net(fx, "bf16", 8, (16, 28, 28), seed=5)
+    t = net.conv(0, 64, 1)
+    for _ in range(3):
+        t = net.conv(net.conv(t, 45, 3), 64, 3, add=t)
+    net.conv(t, 24, 1)
+    m = B.Model(net.dt, net.in_shape, net.ops, net.blobs)
+    assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)
+    m.fuse_blocks(True)
+    xd = B.DeviceTensor.from_nchw(net.x, net.dt)
+    out, ws = m.alloc(net.n)
+
+    def one():
+        out.data.fill_(7.0)
+        m.fupr_forward(xd, out, ws)
+        torch.cuda.synchronize()
+        return out.data.clone()
+
+    want, launches = [], []
+    done = threading.Event()
+
+    def turn():
+        while not done.is_set():
+            B.fupr_tuning_set("basic_fuse", 0)
+            B.fupr_tuning_set("basic_fuse", None)
+
+    try:
+        for value in (None, 0):
+            B.fupr_tuning_set("basic_fuse", value)
+            launches.append(m.num_launches_at(net.n))
+            want.append(one())
+        assert launches[0] < launches[1]
+        thread = threading.Thread(target=turn)
+        thread.start()
+        try:
+            for _ in range(200):
+                got = one()
+                assert any(torch.equal(got, w) for w in want)
+        finally:
+            done.set()
+            thread.join()
+    finally:
+        B.fupr_tuning_set("basic_fuse", None)

@@ -5,6 +5,7 @@ import ctypes as C
 import os
 import re
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -773,6 +774,39 @@ def test_switches_decide_pairs_beside_blocks(switch, value):
                      for v in (with_blocks, without)]
             assert pairs[0] <= pairs[1]
     finally:
+        B.fupr_tuning_set(switch, None)
+
+
+@pytest.mark.parametrize("config,switch", [(3, "bottleneck_fuse"), (2, "basic_fuse")])
+def test_a_launch_list_is_worked_out_once(config, switch):
+    """Switches may change while a list is looked at: what a launch is, which plan it has and what it does
+    come from one look."""
+    m, _ = build_host_model(network.optimise(synth.make_config(config)[0]), 1 << 20)
+    m.fuse_blocks(True)
+    block = {2: "basic_block_", 3: "bottleneck_"}[config]
+    done = threading.Event()
+
+    def turn():
+        while not done.is_set():
+            B.fupr_tuning_set(switch, 0)
+            B.fupr_tuning_set(switch, None)
+
+    t = threading.Thread(target=turn)
+    t.start()
+    try:
+        seen = set()
+        for i in list(range(m.num_ops)) * 10:
+            out = B.OpStats()
+            st = B._lib.fupr_model_launch_stats(m._h, 64, i, B.C.byref(out))
+            assert st in (B.FUPR_OK, B.ERR_ARG)        # (one list is shorter than the other)
+            if st == B.FUPR_OK:
+                name = out.kernel.decode()
+                seen.add(name.startswith(block))
+                assert name.startswith(block) or out.n_ops <= 2 and not name.startswith("none"), (i, name, out.n_ops)
+        assert seen == {True, False}
+    finally:
+        done.set()
+        t.join()
         B.fupr_tuning_set(switch, None)
 
 
