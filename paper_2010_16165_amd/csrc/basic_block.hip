@@ -605,6 +605,7 @@ bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan
   BasicParams p{};
   const int es = (int)elem_size(a.dt), per_chunk = 16 / es;
   const PackedLayout L1 = packed_layout(a.s1, a.dt), L2 = packed_layout(a.s2, a.dt);
+  if (std::max(weight_bytes(L1), weight_bytes(L2)) >= kOutside) return false;   // (32-bit offsets)
   p.H = a.H; p.W = a.W; p.stride = a.s1.stride;
   p.P = out_extent(a.H, 3, p.stride, 1);
   p.Q = out_extent(a.W, 3, p.stride, 1);

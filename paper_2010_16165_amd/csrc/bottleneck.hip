@@ -587,6 +587,7 @@ bool plan_block(const BottleneckArgs& a, int N, int tile, BlockPlan* out) {
   const int BM = T.MT * 16, GF = T.waves * 32;
   BlockParams p{};
   const PackedLayout L1 = packed_layout(a.s1, a.dt), L2 = packed_layout(a.s2, a.dt);
+  if (std::max(weight_bytes(L1), weight_bytes(L2)) >= kOutside) return false;   // (32-bit offsets)
   p.H = a.H; p.W = a.W; p.pix = a.xcs * 2; p.pixels = N * a.H * a.W;
   const int P = out_extent(a.H, 3, a.s1.stride, 1);
   p.Q = out_extent(a.W, 3, a.s1.stride, 1);
@@ -616,6 +617,7 @@ bool plan_block(const BottleneckArgs& a, int N, int tile, BlockPlan* out) {
   out->nt3 = 0;
   if (a.third) {
     const PackedLayout L3 = packed_layout(a.s3, a.dt);
+    if (weight_bytes(L3) >= kOutside) return false;
     p.Kp3 = L3.Kp; p.steps3 = L3.nchunk_pad / 4;
     p.w3_bytes = (uint32_t)p.steps3 * 64u * (uint32_t)p.Kp3;
     const int per_wave = (p.Kp3 / 16 + T.waves - 1) / T.waves;

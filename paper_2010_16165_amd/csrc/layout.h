@@ -46,6 +46,8 @@ inline PackedLayout packed_layout(const fupr_conv_shape& s, fupr_dtype dt) {
   return L;
 }
 
+inline size_t weight_bytes(const PackedLayout& L) { return L.total_bytes - L.weight_offset; }
+
 // FUPR_OK if the HIP runtime has no pending error, else FUPR_ERR_LAUNCH (the
 // runtime's message goes to stderr when the environment has FUPR_DEBUG set).
 fupr_status launch_status(const char* what);

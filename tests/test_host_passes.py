@@ -777,6 +777,42 @@ def test_switches_decide_pairs_beside_blocks(switch, value):
         B.fupr_tuning_set(switch, None)
 
 
+def test_weights_of_2_gib_and_more_stay_out_of_blocks():
+    """The kernels of whole blocks read weights through 32-bit offsets, whatever tile is forced."""
+    def in_blocks(switch, tile, specs):
+        m = B.Model(B.BF16, (16, 2, 2), fake_ops(specs), None)
+        m.fuse_blocks(True)
+        B.fupr_tuning_set(switch, tile)
+        try:
+            launches = [m.launch_stats(1, i) for i in range(m.num_launches_at(1))]
+            return sum(s["n_ops"] for s in launches if s["kernel"].startswith(("basic_block_", "bottleneck_")))
+        finally:
+            B.fupr_tuning_set(switch, None)
+
+    def basic(k2):
+        return in_blocks("basic_tile", "0x8", [(B.OP_CONV, 0, -1, 16, 16, 3, 1, 1, B.FUSE_RELU, 1),
+                                               (B.OP_CONV, 1, -1, k2, 16, 3, 1, 1, B.FUSE_RELU, 1),
+                                               (B.OP_AVGPOOL, 2, -1, 1, 1, 1, 1, 0, 0, 1)])
+
+    def bottleneck(k1, k2, k3):
+        add = B.FUSE_RELU | B.FUSE_ADD       # (three tensors side by side: buffers for the block's)
+        return in_blocks("bottleneck_tile", 0, [(B.OP_CONV, 0, -1, 16, 16, 1, 1, 0, B.FUSE_RELU, 1),
+                                                (B.OP_CONV, 1, -1, 16, 16, 1, 1, 0, B.FUSE_RELU, 1),
+                                                (B.OP_CONV, 1, 2, 16, 16, 1, 1, 0, add, 1),
+                                                (B.OP_CONV, 3, -1, k1, 16, 3, 1, 1, B.FUSE_RELU, 1),
+                                                (B.OP_CONV, 4, -1, k2, k1, 1, 1, 0, B.FUSE_RELU, 1),
+                                                (B.OP_CONV, 5, -1, k3, k2, 1, 1, 0, B.FUSE_RELU, 1),
+                                                (B.OP_AVGPOOL, 6, -1, 1, 1, 1, 1, 0, 0, 1)])
+
+    # 20 chunks of 16 bytes per filter of the second 3 x 3: 2 GiB at 6.7 million, 4 GiB at 13.4 million
+    for k2, takes in [(6 << 20, 2), (7 << 20, 0), (14 << 20, 0)]:
+        assert basic(k2) == takes, k2
+    # 64 bytes per filter of the second; 2 per filter of the third and channel, which can stay outside
+    for k2, k3, takes in [(1 << 20, 16, 3), (31 << 20, 16, 3), (33 << 20, 16, 0), (65 << 20, 16, 0),
+                          (8 << 20, 112, 3), (8 << 20, 128, 2)]:
+        assert bottleneck(16, k2, k3) == takes, (k2, k3)
+
+
 @pytest.mark.parametrize("config,switch", [(3, "bottleneck_fuse"), (2, "basic_fuse")])
 def test_a_launch_list_is_worked_out_once(config, switch):
     """Switches may change while a list is looked at: what a launch is, which plan it has and what it does
