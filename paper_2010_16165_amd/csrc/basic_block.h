@@ -10,6 +10,7 @@ struct BasicBlockArgs {
   fupr_conv_shape s1, s2;
   int H, W;              // input of the first
   bool add;              // the second adds a shortcut
+  bool alone;            // nothing runs before or behind the block
 };
 
 // Shapes alone: the kernel can run these operators (at any batch size that basic_block_plan takes).

@@ -802,21 +802,36 @@ bool basic_block_applies(const BasicBlockArgs& a) {
 
 int basic_block_plan(const BasicBlockArgs& a, int N) {
   if (tuning_off("basic_fuse")) return -1;
-  const double pixels = (double)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
   BasicPlan plan;
   double cost;
   if (!pick_basic(a, N, -1, &plan, &cost)) return -1;
   char text[32];
-  if (!tuning_text("basic_tile", text, sizeof(text))) {
-    // Short launches: 8 % less than the launches apart, which is what the two estimates are uncertain by;
-    // both were fitted to launches between events, which takes some 1.5 us more for each than one after
-    // the other.  Long ones: one after the other they take longer than alone by more than the launches apart
-    // do, which are better at running side by side, so 22 %, and 25 % where a compute unit holds one workgroup
-    // at a time.  Networks at 8 - 20 %: ResNet-34 of 256 images 0.986x, ResNet-18 of 128, unpruned, 0.990x, of 80,
-    // unpruned, 0.993x, of 250 0.994x; at 23 - 30 %: of 64 1.12x, of 160 1.07x, of 200 1.02x.
-    const double apart = estimate_apart(a, pixels);
-    const bool one_at_a_time = plan.p.total > kComputeUnits && plan.lds > kLdsLimit / 2;
-    if (apart > 30.0 ? cost >= (one_at_a_time ? 0.75 : 0.78) * apart : cost - 1.5 >= 0.92 * (apart - 3.0)) return -1;
+  if (tuning_text("basic_tile", text, sizeof(text))) return number_of(plan);
+  // Short launches: 8 % less than the launches apart, which is what the two estimates are uncertain by;
+  // both were fitted to launches between events, which takes some 1.5 us more for each than one after
+  // the other.  Long ones: one after the other they take longer than alone by more than the launches apart
+  // do, which are better at running side by side, so 22 %, and 25 % where a compute unit holds one workgroup
+  // at a time.  Networks at 8 - 20 %: ResNet-34 of 256 images 0.986x, ResNet-18 of 128, unpruned, 0.990x, of 80,
+  // unpruned, 0.993x, of 250 0.994x; at 23 - 30 %: of 64 1.12x, of 160 1.07x, of 200 1.02x.
+  const double apart =
+      estimate_apart(a, (double)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1));
+  const bool one_at_a_time = plan.p.total > kComputeUnits && plan.lds > kLdsLimit / 2;
+  if (apart > 30.0 ? cost >= (one_at_a_time ? 0.75 : 0.78) * apart : cost - 1.5 >= 0.92 * (apart - 3.0)) return -1;
+  if (a.alone) return number_of(plan);   // (the call's own time, which one launch less shortens: 8.6 -> 7.9 us)
+  // Inside a network, each block by itself as one launch and as two, us of the captured pass:
+  if (a.dt == FUPR_F32) {
+    // The two launches are 3 - 4 us shorter than between events, and shorter still below some 128K
+    // elements: blocks of 16 channels at 32 x 32 gain 0.5 us at 8 images and lose 1.3 at one to four, where whole
+    // networks took 1.05 times as long (20 layers, 4 images: 83.0 us apart, 88.0 as blocks).
+    // Past 12.5 us the launches apart have the faster pixels (64 images, 56 layers: 375 - 410 us apart, 433 as blocks).
+    if (cost + 3.4 > apart || cost > 12.5 || (int64_t)N * a.H * a.W * a.s1.C < (1 << 17)) return -1;
+  } else {
+    // From 192 images on two sub-batches run side by side (split_count in model.cpp), which short launches apart are
+    // better at: 3.6 - 4.5 us a block lost at 24 x 24 (ResNet-18 of 192 images of 96 x 96 206.4 us apart, 213.6 as
+    // blocks); 5.9 gained at 56 x 56.
+    if (N >= 192 && apart < 60.0) return -1;
+    // The shortest ones have to be clearly shorter (10.5 of 13.2 us lost 0.7, 9.5 of 13.3 gains 1.0).
+    if (apart < 14.5 && cost + 1.5 > 0.88 * apart) return -1;
   }
   return number_of(plan);
 }

@@ -777,10 +777,17 @@ int bottleneck_plan(const BottleneckArgs& a, int N) {
   // against 55).  Both were fitted to launches between events, which takes some 1.5 us more for each than one
   // after the other: that decides where they are short (nine irregular images 269 -> 264 us; a network at 64
   // images, whose sub-batches run side by side, 684 against 670 when it is counted there too).
-  const double gap = M < 8192 ? 1.5 : 0.0;
-  if (tuning_int("bottleneck_tile", -1) < 0 &&
-      cost - gap >= (a.pair ? 0.85 : 0.95) * (estimate_apart(a, M) - gap * (a.third ? 3 : 2)))
-    return -1;
+  if (tuning_int("bottleneck_tile", -1) >= 0) return plan.tile;
+  const double gap = M < 8192 ? 1.5 : 0.0, apart = estimate_apart(a, M);
+  if (cost - gap >= (a.pair ? 0.85 : 0.95) * (apart - gap * (a.third ? 3 : 2))) return -1;
+  // Under 4096 pixels even tiles of 16 leave compute units idle, and the launches apart, which split their filters as
+  // well, are shorter inside a network than between events.  Each block by itself as one launch and as several, us
+  // of the captured pass, blocks without a pair: of 208 taken without these lines 109 lost; of the 93 taken with them 13 lose,
+  // up to 0.7 % of a pass (13.8 of 21.6 us estimated gains 1.0 at 12 x 12 x 16 images, 20.4 of 25.9 loses 1.8
+  // at 14 x 14 x 16).  Where two sub-batches overlap (from 64 images on, split_count in model.cpp) 38 of 40 lost, up
+  // to 19 us (231 -> 1024 -> 231 channels, 6 x 6 x 192 images, 38 of 46 us estimated).
+  const bool halves = N >= 64;
+  if (!a.pair && M < (halves ? 8192 : 4096) && (halves || cost + 2.0 > 0.78 * apart)) return -1;
   return plan.tile;
 }
 

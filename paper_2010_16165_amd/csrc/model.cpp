@@ -993,6 +993,7 @@ int basic_block_at(const fupr_model* m, size_t i, BasicBlockArgs* out) {
   g.H = tx.H;
   g.W = tx.W;
   g.add = b.res >= 0;
+  g.alone = n == 2;
   if (!basic_block_applies(g)) return 0;
   *out = g;
   return 2;

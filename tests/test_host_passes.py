@@ -720,6 +720,28 @@ def test_basic_blocks_run_as_one_launch(config, kinds):
     assert len(covered) >= kinds
 
 
+def test_blocks_only_where_networks_gain_from_them():
+    """Short single-precision blocks, basic blocks of batches that run as two sub-batches and 1 x 1
+    convolutions that are no pair at small extents: slower in one launch inside a network, so apart."""
+    def blocks(make, *args, batch, **kwargs):
+        m, _ = build_host_model(network.optimise(make(3, *args, **kwargs)), 1 << 20)
+        m.fuse_blocks(True)
+        launches = [m.launch_stats(batch, i) for i in range(m.num_launches_at(batch))]
+        return [s for s in launches if s["kernel"].startswith(("basic_block_", "bottleneck_"))]
+
+    cifar = lambda n: blocks(synth.make_cifar_resnet, "f32", 3, 200, batch=n)
+    assert [len(cifar(n)) for n in (1, 2, 4)] == [0, 0, 0]
+    assert len(cifar(8)) == 3 and len(cifar(16)) >= 3 and len(cifar(32)) == 6
+    # nothing before or behind the block: one launch less is what the caller waits for
+    assert len(blocks(synth.make_block_model, "f32", 16, 32, 250, batch=1)) == 1
+    basic = lambda n: blocks(synth.make_imagenet_basic_resnet, "bf16", (2, 2, 2, 2), 500, batch=n, size=96)
+    assert basic(1) and basic(128) and not basic(192) and not basic(256)
+    # the deepest stages: little but weights
+    deep = [s for s in blocks(synth.make_imagenet_bottleneck_resnet, "f16", (3, 4, 6, 3), 300, batch=192, size=96)
+            if s["M"] == 192 * 6 * 6 and s["n_ops"] == 3]
+    assert not deep
+
+
 def launch_list(m, batch):
     return [(s["first_op"], s["n_ops"], s["kernel"]) for s in (m.launch_stats(batch, i) for i in range(m.num_launches))]
 
