@@ -602,7 +602,9 @@ struct BasicPlan {
 
 bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan* out) {
   const Rectangle& R = kRectangles[rectangle];
-  BasicParams p{};
+  if (R.by_rows && (a.dt == FUPR_F32 || a.s1.stride != 1)) return false;
+  BasicParams& p = out->p;
+  p = BasicParams{};
   const int es = (int)elem_size(a.dt), per_chunk = 16 / es;
   const PackedLayout L1 = packed_layout(a.s1, a.dt), L2 = packed_layout(a.s2, a.dt);
   if (std::max(weight_bytes(L1), weight_bytes(L2)) >= kOutside) return false;   // (32-bit offsets)
@@ -627,7 +629,7 @@ bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan
   p.rows2 = (3 * p.cpt2 + 3) / 4;
   int ma = ((p.mids + 15) / 16 + WP - 1) / WP, mb = ((p.outs + 15) / 16 + WP - 1) / WP;
   if (R.by_rows) {
-    if (es == 4 || p.stride != 1 || p.TH != R.rows || p.TW != R.cols || p.MW != 16) return false;
+    if (p.TH != R.rows || p.TW != R.cols || p.MW != 16) return false;
     ma = (p.TH + 2) / WP;
     mb = p.TH / WP;
   }
@@ -656,12 +658,15 @@ bool plan_basic(const BasicBlockArgs& a, int N, int rectangle, int WF, BasicPlan
   if (total >= (int64_t(1) << 28)) return false;
   p.total = (int)total;
   p.per_xcd = (p.total + 7) / 8;
+  out->rectangle = rectangle;
+  return true;
+}
+
+// What only a launch needs: plans that are weighed do without.
+void set_divisions(BasicParams& p) {
   p.divC1 = fast_div(p.cpt1); p.divC2 = fast_div(p.cpt2); p.divMW = fast_div(p.MW); p.divTW = fast_div(p.TW);
   p.divSlots = fast_div(p.slots1); p.divIW = fast_div(p.IW); p.divTiles = fast_div(p.tiles);
   p.divTilesW = fast_div(p.tiles_w);
-  out->p = p;
-  out->rectangle = rectangle;
-  return true;
 }
 
 template <int EL, int TILE>
@@ -850,6 +855,7 @@ fupr_status launch_basic_block(const BasicBlockArgs& a, const ConvArgs& first, c
   BasicPlan plan;
   if (!plan_basic(a, count, rectangle_of(number), waves_of(number), &plan)) return FUPR_ERR_LIMIT;
   BasicParams& p = plan.p;
+  set_divisions(p);
   const uint32_t es = (uint32_t)elem_size(a.dt);
   p.x = first.x; p.res = second.res; p.y = second.y;
   p.w1 = reinterpret_cast<const char*>(first.packed) + packed_layout(a.s1, a.dt).weight_offset;

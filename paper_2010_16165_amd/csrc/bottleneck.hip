@@ -644,11 +644,15 @@ bool plan_block(const BottleneckArgs& a, int N, int tile, BlockPlan* out) {
   if (out->lds > kLdsLimit) return false;
   p.total = (p.M + BM - 1) / BM;
   p.per_xcd = (p.total + 7) / 8;
-  p.divPQ = fast_div(p.PQ); p.divQ = fast_div(p.Q); p.divC = fast_div(p.cpt);
-  p.divSlots = fast_div(p.slots); p.divSlots2 = fast_div(std::max(p.slots2, 1));
   out->p = p;
   out->tile = tile;
   return true;
+}
+
+// What only a launch needs: plans that are weighed do without.
+void set_divisions(BlockParams& p) {
+  p.divPQ = fast_div(p.PQ); p.divQ = fast_div(p.Q); p.divC = fast_div(p.cpt);
+  p.divSlots = fast_div(p.slots); p.divSlots2 = fast_div(std::max(p.slots2, 1));
 }
 
 template <bool BF, int TILE, int NT3>
@@ -804,6 +808,7 @@ fupr_status launch_bottleneck(const BottleneckArgs& a, int tile, int count, void
   BlockPlan plan;
   if (!plan_block(a, count, tile, &plan)) return FUPR_ERR_LIMIT;
   BlockParams& p = plan.p;
+  set_divisions(p);
   const PackedLayout L1 = packed_layout(a.s1, a.dt), L2 = packed_layout(a.s2, a.dt);
   auto weights = [](const void* blob, const PackedLayout& L) {
     return reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(blob) + L.weight_offset);
