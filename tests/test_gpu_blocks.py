@@ -252,3 +252,133 @@ def test_one_pass_sees_one_schedule(fx):
             thread.join()
     finally:
         B.fupr_tuning_set("basic_fuse", None)
+
+
+def block_model(fx, dtype, n, in_shape, k1, k2, add, seed):
+    """A model that is one basic block, on the caller's tensors, and its per-layer twin."""
+    net = Net(fx, dtype, n, in_shape, seed)
+    net.conv(net.conv(0, k1, 3), k2, 3, add=0 if add else -1)
+    B = net.B
+    models = [B.Model(net.dt, in_shape, net.ops, net.blobs) for _ in range(2)]
+    for m in models:
+        assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)   # no one-kernel schedule
+    models[0].fuse_blocks(True)
+    models[1].set_schedule(B.SCHEDULE_PER_LAYER)
+    assert models[0].num_launches_at(n) == 1 and models[1].num_launches_at(n) == 2
+    return net, models
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("how", ["in place", "in place with the shortcut", "shifted"])
+def test_block_whose_output_overlaps_its_input(fx, dtype, how):
+    """A launch of the whole block would write pixels that its other workgroups still read: such a call runs as
+    two launches, and gives their bits."""
+    B, torch = fx
+    n, c, h, w = 2, 16, 20, 24
+    net, (m, apart) = block_model(fx, dtype, n, (c, h, w), 12, c, how == "in place with the shortcut", 11)
+    x = B.DeviceTensor.from_nchw(net.x, net.dt)
+    want, ws = apart.alloc(n)
+    apart.fupr_forward(x, want, ws)
+    elements = n * h * w * c
+    base = torch.zeros(2 * elements, dtype=x.data.dtype, device="cuda")
+    base[:elements] = x.data.flatten()
+    at = 3 * w * c if how == "shifted" else 0
+    xin = B.DeviceTensor(base[:elements].view(n, h, w, c), c, net.dt)
+    out = B.DeviceTensor(base[at:at + elements].view(n, h, w, c), c, net.dt)
+    _, ws2 = m.alloc(n)
+    ws2.fill_(255)
+    m.fupr_forward(xin, out, ws2)
+    torch.cuda.synchronize()
+    assert torch.equal(out.data, want.data)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("add", [False, True])
+def test_block_on_tensors_with_wider_strides(fx, dtype, add):
+    """The caller's strides, on both sides of the block and for its shortcut; what lies between C and the
+    stride is zeros."""
+    B, torch = fx
+    n, c, h, w, k2 = 3, 20, 11, 18, 20
+    net, (m, _) = block_model(fx, dtype, n, (c, h, w), 23, k2, add, 12)
+    unit = {"bf16": 2.0 ** -8, "f32": 2.0 ** -20}[dtype]
+    want = net.tensors[-1]
+    # (an output's stride goes up to the packed filters)
+    for xcs, ycs in ((24, 20), (40, 20)) if dtype == "f32" else ((24, 24), (40, 24), (24, 32), (48, 32)):
+        print(dtype, add, xcs, ycs, flush=True)
+        x = B.DeviceTensor.from_nchw(net.x, net.dt, c_stride=xcs)
+        out = B.DeviceTensor.empty(n, h, w, k2, net.dt, c_stride=ycs)
+        out.data.fill_(7.0)
+        _, ws = m.alloc(n)
+        ws.fill_(255)
+        m.fupr_forward(x, out, ws)
+        torch.cuda.synchronize()
+        assert out.padding_is_zero()
+        got = torch.from_numpy(np.ascontiguousarray(out.to_nchw())).double()
+        # two stored tensors, each rounded once in either evaluation
+        assert float((got - want).norm() / want.norm()) <= unit
+        assert float((got - want).abs().max()) <= 4 * unit * float(want.abs().max())
+
+
+@pytest.mark.parametrize("rows", [6, 14])
+@pytest.mark.parametrize("layer", [0, 1])
+def test_infinite_weights_beside_a_padded_step_by_rows(fx, rows, layer):
+    """With three chunks to a row of taps the fourth of its step is the next row's first: its weights, infinite
+    here, meet zeros that stand for nothing, and must not be multiplied."""
+    B, torch = fx
+    n, c, h, w = 1, 8, 28, 28
+    net = Net(fx, "bf16", n, (c, h, w), 13)
+    rng = net.rng
+    blobs, ops = [], []
+    for i in range(2):
+        wt = rng.uniform(0.01, 0.1, (8, 8, 3, 3)).astype(np.float32)
+        if i == layer:
+            wt[0, 0, 1, 0] = np.inf                      # first chunk of the second row of taps
+        shape = B.shape_of(wt, 1, 1)
+        blobs.append(B.upload_blob(B.fupr_pack(shape, wt, np.full(8, 0.1, np.float32), net.dt)))
+        ops.append(B.OpDesc(B.OP_CONV, i, -1, shape, blobs[-1].data_ptr(), B.FUSE_RELU, 1, 0))
+    m = B.Model(net.dt, (c, h, w), ops, blobs)
+    assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)
+    m.fuse_blocks(True)
+    B.fupr_tuning_set("basic_tile", f"{len(RECTANGLES) + (rows == 14)}x4")
+    try:
+        assert [s["kernel"] for s in [m.launch_stats(n, 0)]] == [f"basic_block_{rows}x14r"]
+        x = B.DeviceTensor.from_nchw(np.abs(net.x) + 0.5, net.dt)
+        out, ws = m.alloc(n)
+        m.fupr_forward(x, out, ws)
+        torch.cuda.synchronize()
+    finally:
+        B.fupr_tuning_set("basic_tile", None)
+    y = out.data[..., :8].float()
+    inner = y[:, 3:-3, 3:-3]                             # (zeros outside the image times infinity are NaN)
+    assert bool(torch.isposinf(inner[..., 0]).all())
+    if layer == 1:
+        assert bool(torch.isfinite(y[..., 1:]).all())
+    else:
+        assert bool(torch.isposinf(inner).all())         # every filter reads the infinite channel
+
+
+def test_sub_batches_of_blocks_by_rows(fx):
+    """The order of a block's sums depends on whether its tiles are rows, which the whole batch decides: parts of
+    it give the same bits, with the count forced and without."""
+    import synth
+    from paper_2010_16165_amd import network
+    B, torch = fx
+    model = synth.make_imagenet_basic_resnet(31, "bf16", (1, 1, 1, 1), 300, widths=(16, 24, 32, 40), size=112, classes=9)
+    n = 96
+    m, _ = network.build(network.optimise(model))
+    kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
+    assert "basic_block_14x14r" in kernels, kernels
+    x = B.DeviceTensor.from_nchw(synth.make_input(31, n, model["in_shape"]), B.BF16)
+    whole = None
+    try:
+        for parts in (1, 2, 3, 4, None):
+            print("sub-batches:", parts, flush=True)
+            B.fupr_tuning_set("split", parts)
+            out, ws = m.alloc(n)
+            ws.fill_(255)
+            m.fupr_forward(x, out, ws)
+            torch.cuda.synchronize()
+            whole = out.data.clone() if whole is None else whole
+            assert torch.equal(whole, out.data)
+    finally:
+        B.fupr_tuning_set("split", None)

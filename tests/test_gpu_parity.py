@@ -1405,6 +1405,10 @@ def test_forward_is_deterministic_and_graph_replays(fx):
             assert torch.equal(first, out2.data)
 
 
+def launch_kernels(m, n):
+    return [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
+
+
 def test_sub_batches_on_forked_streams_give_identical_results(fx):
     """Large batches run as sub-batches on streams that fork from and join the
     caller's stream; images are independent, so the result must not change by a
@@ -1415,6 +1419,7 @@ def test_sub_batches_on_forked_streams_give_identical_results(fx):
     n = 26
     x = synth.make_input(31, n, model["in_shape"])
     m, _ = network.build(network.optimise(model))
+    assert any(k.startswith("basic_block_") for k in launch_kernels(m, n))
     xd = B.DeviceTensor.from_nchw(x, B.BF16)
     out, ws = m.alloc(n)
     try:
@@ -1453,6 +1458,7 @@ def test_sub_batches_with_no_switch_set(fx):
     n = 201                                     # from 192 images on there are two sub-batches
     x = synth.make_input(33, n, model["in_shape"])
     m, _ = network.build(network.optimise(model))
+    assert any(k.startswith("bottleneck_") for k in launch_kernels(m, n))
     xd = B.DeviceTensor.from_nchw(x, B.F16)
     out, ws = m.alloc(n)
     B.fupr_tuning_set("split", 1)
