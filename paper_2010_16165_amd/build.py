@@ -15,7 +15,7 @@ SOURCES = ["host_passes.cpp", "tuning.cpp", "kernels.hip", "conv_tiled.hip", "co
            "static_workspace.hip"]
 HEADERS = [os.path.join(ROOT, "include", "fupr.h")] + [
     os.path.join(CSRC, h) for h in ("layout.h", "device_utils.h", "conv16.h", "stem_pool.h", "bottleneck.h", "basic_block.h",
-                                    "tuning.h", "window_patch.h")]
+                                    "recall.h", "tuning.h", "window_patch.h")]
 MEASURE_SOURCES = [os.path.join(MEASURE_DIR, "peaks.hip")]
 MEASURE_HEADERS = [os.path.join(ROOT, "include", "fupr_measure.h")]
 

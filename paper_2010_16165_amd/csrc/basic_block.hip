@@ -33,6 +33,7 @@
 #include "device_utils.h"
 #include "fupr.h"
 #include "layout.h"
+#include "recall.h"
 #include "tuning.h"
 
 namespace fupr {
@@ -755,8 +756,8 @@ double estimate_apart(const BasicBlockArgs& a, double pixels) {
 }
 
 // The tuning switch basic_tile=<index of the rectangle>x<waves along the filters> forces a plan.
-// like >= 0: only rectangles whose sums' order is that one's.  (Some thirty plans: a model asks once for a batch size
-// and keeps the answer.)
+// like >= 0: only rectangles whose sums' order is that one's.  (Some thirty plans, 2 - 20 us of host time: a model
+// asks once for a batch size and keeps the answer, a thread remembers it for the next model.)
 bool pick_basic(const BasicBlockArgs& a, int N, int like, BasicPlan* best, double* cost) {
   char text[32];
   if (tuning_text("basic_tile", text, sizeof(text))) {
@@ -791,21 +792,8 @@ int number_of(const BasicPlan& plan) { return plan.rectangle * (kWaves + 1) + pl
 int rectangle_of(int number) { return number / (kWaves + 1); }
 int waves_of(int number) { return number % (kWaves + 1); }
 
-}  // namespace
-
-bool basic_block_applies(const BasicBlockArgs& a) {
-  for (const fupr_conv_shape* s : {&a.s1, &a.s2})
-    if (s->R != 3 || s->S != 3 || s->pad != 1) return false;
-  if ((a.s1.stride != 1 && a.s1.stride != 2) || a.s2.stride != 1) return false;
-  const WithoutTuning no_switches;   // (they can change between a model's plan and its passes)
-  BasicPlan plan;
-  for (int r = 0; r < kNumRectangles; ++r)
-    for (int wf = 1; wf <= kWaves; wf *= 2)
-      if (plan_basic(a, 1, r, wf, &plan)) return true;
-  return false;
-}
-
-int basic_block_plan(const BasicBlockArgs& a, int N) {
+// The plan with which a batch of N images runs the block as one launch, -1: it runs as two.
+int choose(const BasicBlockArgs& a, int N) {
   if (tuning_off("basic_fuse")) return -1;
   BasicPlan plan;
   double cost;
@@ -839,6 +827,26 @@ int basic_block_plan(const BasicBlockArgs& a, int N) {
     if (apart < 14.5 && cost + 1.5 > 0.88 * apart) return -1;
   }
   return number_of(plan);
+}
+
+}  // namespace
+
+bool basic_block_applies(const BasicBlockArgs& a) {
+  for (const fupr_conv_shape* s : {&a.s1, &a.s2})
+    if (s->R != 3 || s->S != 3 || s->pad != 1) return false;
+  if ((a.s1.stride != 1 && a.s1.stride != 2) || a.s2.stride != 1) return false;
+  const WithoutTuning no_switches;   // (they can change between a model's plan and its passes)
+  BasicPlan plan;
+  for (int r = 0; r < kNumRectangles; ++r)
+    for (int wf = 1; wf <= kWaves; wf *= 2)
+      if (plan_basic(a, 1, r, wf, &plan)) return true;
+  return false;
+}
+
+int basic_block_plan(const BasicBlockArgs& a, int N) {
+  if (tuning_any()) return choose(a, N);
+  const WithoutTuning no_switches;   // (one that is set meanwhile is in no answer that is kept)
+  return recall<BasicBlockArgs, choose>(a, N);
 }
 
 // The sums' order depends on by_rows alone: a part keeps its batch's.

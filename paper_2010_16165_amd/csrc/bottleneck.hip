@@ -37,6 +37,7 @@
 #include "device_utils.h"
 #include "fupr.h"
 #include "layout.h"
+#include "recall.h"
 #include "tuning.h"
 #include "window_patch.h"
 
@@ -753,20 +754,8 @@ bool pick_block(const BottleneckArgs& a, int N, int waves, BlockPlan* best, doub
   return any;
 }
 
-}  // namespace
-
-bool bottleneck_applies(const BottleneckArgs& a) {
-  if (a.dt == FUPR_F32 || a.s1.R != 3 || a.s1.S != 3 || a.s1.pad != 1 || a.s1.stride < 1 || a.s1.stride > 2) return false;
-  if (a.s2.R != 1 || a.s2.S != 1 || a.s2.stride != 1 || a.s2.pad != 0) return false;
-  if (a.third && (a.s3.R != 1 || a.s3.S != 1 || a.s3.stride != 1 || a.s3.pad != 0)) return false;
-  const WithoutTuning no_switches;   // (they can change between a model's plan and its passes)
-  BlockPlan plan;
-  for (int tile = 0; tile < kNumTiles; ++tile)
-    if (plan_block(a, 1, tile, &plan)) return true;
-  return false;
-}
-
-int bottleneck_plan(const BottleneckArgs& a, int N) {
+// The plan with which a batch of N images runs the block as one launch, -1: the operators run apart.
+int choose(const BottleneckArgs& a, int N) {
   if (tuning_off("bottleneck_fuse")) return -1;
   const int64_t M = (int64_t)N * out_extent(a.H, 3, a.s1.stride, 1) * out_extent(a.W, 3, a.s1.stride, 1);
   // 32-bit byte offsets into every tensor
@@ -793,6 +782,25 @@ int bottleneck_plan(const BottleneckArgs& a, int N) {
   const bool halves = N >= 64;
   if (!a.pair && M < (halves ? 8192 : 4096) && (halves || cost + 2.0 > 0.78 * apart)) return -1;
   return plan.tile;
+}
+
+}  // namespace
+
+bool bottleneck_applies(const BottleneckArgs& a) {
+  if (a.dt == FUPR_F32 || a.s1.R != 3 || a.s1.S != 3 || a.s1.pad != 1 || a.s1.stride < 1 || a.s1.stride > 2) return false;
+  if (a.s2.R != 1 || a.s2.S != 1 || a.s2.stride != 1 || a.s2.pad != 0) return false;
+  if (a.third && (a.s3.R != 1 || a.s3.S != 1 || a.s3.stride != 1 || a.s3.pad != 0)) return false;
+  const WithoutTuning no_switches;   // (they can change between a model's plan and its passes)
+  BlockPlan plan;
+  for (int tile = 0; tile < kNumTiles; ++tile)
+    if (plan_block(a, 1, tile, &plan)) return true;
+  return false;
+}
+
+int bottleneck_plan(const BottleneckArgs& a, int N) {
+  if (tuning_any()) return choose(a, N);
+  const WithoutTuning no_switches;   // (one that is set meanwhile is in no answer that is kept)
+  return recall<BottleneckArgs, choose>(a, N);
 }
 
 // The order of the 3 x 3 convolution's sums depends on the number of waves: a part keeps its batch's.

@@ -7,7 +7,6 @@
 #include <array>
 #include <cstdio>
 #include <cstdlib>
-#include <cstring>
 #include <functional>
 #include <map>
 #include <memory>
@@ -1012,19 +1011,6 @@ int block_plan(const fupr_model* m, size_t i, int N) {
   return basic_block_plan(b.basic, N);
 }
 
-// Two operators start blocks of the same shapes (unequal padding bytes would only make it say no).
-bool same_block(const fupr_model* m, int i, int j) {
-  const fupr_model::Block &a = m->block_args[i], &b = m->block_args[j];
-  if (a.kind != b.kind || a.count != b.count) return false;
-  if (a.kind == kBottleneck) return std::memcmp(&a.bottleneck, &b.bottleneck, sizeof(a.bottleneck)) == 0;
-  // (what block_plan looks at beside the shapes: tensors of the same strides follow from them, but the shortcut's)
-  auto shortcut = [&](int k) {
-    const int t = m->ops[k + 1].res;
-    return t < 0 ? (int64_t)0 : (int64_t)m->tensors[t].H * m->tensors[t].W * m->tensors[t].cs;
-  };
-  return std::memcmp(&a.basic, &b.basic, sizeof(a.basic)) == 0 && shortcut(i) == shortcut(j);
-}
-
 void find_blocks(fupr_model* m) {
   const int n = (int)m->ops.size();
   m->block_args.assign(n, fupr_model::Block{});
@@ -1046,18 +1032,9 @@ std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, i
   auto out = std::make_shared<fupr_model::Placement>();
   std::vector<char> chosen(n, 0);          // operators of the block that starts there
   std::vector<int> plan(n, -1);
-  // (a network repeats its blocks, and a plan is 2 - 20 us of host time)
-  std::vector<int> kinds;                  // one operator of every kind of block so far
-  auto plan_of = [&](int i) {
-    if (m->block_args[i].kind == 0) return -1;
-    for (int k : kinds)
-      if (same_block(m, k, i)) return plan[k];
-    kinds.push_back(i);
-    return block_plan(m, (size_t)i, N);
-  };
   bool any = false;
   for (int i = 0; i < n; i += chosen[i] ? chosen[i] : 1)
-    if ((plan[i] = plan_of(i)) >= 0) {
+    if ((plan[i] = block_plan(m, (size_t)i, N)) >= 0) {
       chosen[i] = (char)m->block_args[i].count;
       any = true;
     }
