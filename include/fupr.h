@@ -451,7 +451,9 @@ fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule);
  * never.  The workspace is as large either way; what its buffers hold in between
  * differs, so the setting belongs before the first forward pass or capture and
  * between passes, not beside one.  fupr_model_num_launches does not count blocks as
- * one launch; fupr_model_num_launches_at does.  Where they are placed is worked out
+ * one launch; fupr_model_num_launches_at does, also for a pass in which a basic block
+ * on the caller's own tensors runs as two because its output overlaps its input or a
+ * stride makes a tensor 2 GiB.  Where they are placed is worked out
  * at the first pass of a batch size and kept by the model (host memory, at most 256
  * batch sizes).  Errors: NULL, ARG (on not 0 or 1).
  */

@@ -20,7 +20,8 @@
 // What bounds it: at a few images the start (index arithmetic, arguments, first weights: 4000 of 11 000
 // clocks) and the weights' latency; at many, LDS where a read of 1 KB, 8 clocks, serves one MFMA of 4 clocks
 // per compute unit, and by rows the serial chain of a workgroup, load, multiply, multiply, store, of which
-// one or two fit into LDS together (64 images: 100 MB in 36 us, 2.8 TB/s).
+// one or two fit into LDS together (ResNet-18's three at 64 images: 45 MB each in 35 us by counters, 1.3 TB/s; the
+// matrix pipe busy 42 % of it).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -708,7 +709,9 @@ fupr_status dispatch(const BasicPlan& plan, hipStream_t st) {
 
 // Estimated us of a plan: a fit over 228 blocks (ResNet-18's at several image sizes, CIFAR-size ones in single
 // precision, 1 - 128 images) x every rectangle and wave arrangement, 6015 launches, to 9 % in the mean
-// square; the plan with the least estimate is 1.8 % slower than the best one in the mean, 20 % at worst.
+// square; the plan with the least estimate is 1.8 % slower than the best one in the mean, 20 % at worst.  (Single
+// precision before its sums of a step were added up apart, which took 2 us of 103 of a network of six blocks:
+// the rule that takes a plan asks for a larger gain there.)
 double estimate(const BasicBlockArgs& a, const BasicPlan& plan) {
   const BasicParams& p = plan.p;
   const BasicTile& T = kTiles[plan.tile];

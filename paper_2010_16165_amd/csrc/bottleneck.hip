@@ -19,13 +19,13 @@
 //     LDS in the order of the waves.
 //
 // Measured, three launches -> one (us, event-timed; the channels in, 3 x 3, wide, next): 64, 64, 512, 64 at
-// 28 x 28 x 64 images 57 -> 39; 128, 128, 1024, 128 at 14 x 14 x 64 46 -> 28, x 9 22.5 -> 19.4, one image 19.3
+// 28 x 28 x 64 images 57 -> 39; 128, 128, 1024, 128 at 14 x 14 x 64 46 -> 28, x 9 22.5 -> 19.4 (but longer inside a network: stays apart), one image 19.3
 // against 22 here (stays apart); 32, 32, 256, 64 at 56 x 56 x 9 25.7 -> 15.4, one image 19 -> 9.7, x 64 55
 // against 59 (stays apart).  ResNet-50: 64 images 772 -> 670, nine irregular ones of 193 x 193 296 -> 269.
-// What bounds it: weights, which every tile reads anew through the vector path (36 - 45 bytes per clock and
-// compute unit: 820 KB and 20 000 of the 43 000 clocks of a tile of the second shape, whose other parts,
-// 5500 to start, 5500 around the 3 x 3, wait for memory with one workgroup per compute unit); at large
-// batches the shortcut values in flight, 2.9 TB/s where the kernels apart reach 4 - 5.
+// What bounds it: weights, which every tile reads anew through the vector path (with the pixels 21 - 41 bytes per clock
+// and compute unit over whole launches, by counters), and the start and the 3 x 3, which wait for memory with one workgroup
+// per compute unit; at large batches little is in flight: 1.9 - 3.0 TB/s counted at 256 images where the launches
+// apart stream at 4.7 - 4.8.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -709,7 +709,7 @@ double estimate(const BottleneckArgs& a, const BlockPlan& plan) {
   const double wide = a.two ? 32.0 * (p.steps2 - p.split_steps) : a.s2.K;
   const double in = 1.0 * p.stride * p.stride * a.s1.C, out = (double)a.s2.K + (a.third ? a.s3.K : 0);
   // clocks of a workgroup that has the compute unit to itself; of its weights and pixels on the way
-  // from L2 to the compute unit (36 bytes per clock); all tensors at memory's rate
+  // from L2 to the compute unit (fitted: 36 bytes per clock); all tensors at memory's rate
   const double alone = ((p.steps1 + WK - 1) / WK) * (96.5 + 88.1 * T.MT) +
                        p.groups * (764.0 + p.steps2 * (49.7 + 83.5 * T.MT) +
                                    T.waves * (451.0 + 59.1 * T.MT * plan.nt3)) +
