@@ -1142,6 +1142,7 @@ std::shared_ptr<const fupr_model::Placement> blocks_on(const fupr_model* m, int 
     if (known != m->placed.end()) {
       p = known->second;
     } else {
+      const WithoutTuning no_switches;   // (one that another thread sets meanwhile has no place in what is kept)
       p = place_blocks(m, N);
       if (m->placed.size() >= 256) keeper->placed.clear();
       keeper->placed.emplace(N, p);

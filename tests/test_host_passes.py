@@ -799,6 +799,37 @@ def test_switches_decide_pairs_beside_blocks(switch, value):
         B.fupr_tuning_set(switch, None)
 
 
+def test_switches_set_meanwhile_are_in_no_list_that_is_kept():
+    """A list that is worked out with no switch set is kept: one that another thread sets at that moment has to
+    stay out of it."""
+    plan = network.optimise(synth.make_config(3)[0])
+    m, other = (build_host_model(plan, 1 << 20)[0] for _ in range(2))
+    for model in (m, other):
+        model.fuse_blocks(True)
+    done = threading.Event()
+
+    def turn():
+        while not done.is_set():
+            for switch in ("bottleneck_fuse", "conv1x1_fuse"):
+                B.fupr_tuning_set(switch, 0)
+                B.fupr_tuning_set(switch, None)
+
+    batches = range(1, 200)
+    t = threading.Thread(target=turn)
+    t.start()
+    try:
+        for n in batches:
+            for _ in range(20):
+                m.num_launches_at(n)
+    finally:
+        done.set()
+        t.join()
+        for switch in ("bottleneck_fuse", "conv1x1_fuse"):
+            B.fupr_tuning_set(switch, None)
+    for n in batches:
+        assert m.num_launches_at(n) == other.num_launches_at(n), n
+
+
 def test_weights_of_2_gib_and_more_stay_out_of_blocks():
     """The kernels of whole blocks read weights through 32-bit offsets, whatever tile is forced."""
     def in_blocks(switch, tile, specs):
