@@ -839,6 +839,7 @@ struct Remembered {
 
 bool plan_for(const Conv16Params& c, int N, WindowPlan* plan) {
   if (tuning_any()) return pick_for_batch(c, N, plan);
+  const WithoutTuning no_switches;   // (one that another thread sets meanwhile is in no plan that is kept)
   constexpr int kEntries = 128;
   thread_local Remembered table[kEntries];
   const Sizes z = {(int)c.dt, N, c.plan_N, c.H, c.W, c.P, c.Q, c.M, window_rows(c), c.S, c.stride, c.pad, c.Kp,
