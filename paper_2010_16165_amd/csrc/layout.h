@@ -111,6 +111,8 @@ bool conv_pair_fusable(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fup
 
 constexpr int kResMaxLayers = 256;
 constexpr int kResThreads = 1024;
+// the kernel of row layers: waves that compute, and threads with those that stage parameters
+constexpr int kResRowWaves = 8, kResRowThreads = 768;
 constexpr size_t kResLdsLimit = 160 * 1024;
 constexpr int kResScratchBytes = 2048;            // start of LDS: partial sums of the mean layer
 
@@ -167,6 +169,48 @@ constexpr int kResFullPixels = 16, kResReuse = 32, kResLikeOut = 64, kResFullFil
 // room in LDS during the layer before it.
 constexpr int kResTablePad = 8;   // steps of padding after a tap table (2 * deepest prefetch)
 
+// A row layer: a 3 x 3 convolution in tiles that are neighbours along the columns (rows_item in resident.hip), each
+// computing wave at most one work item.  A network whose convolutions are row layers all, then a global mean and
+// a 1 x 1 convolution of it, runs on a kernel of its own that reads one of these per layer (of the last two the
+// staging part only); what a wave needs is worked out on the host.
+struct ResRow {
+  // staging the NEXT layer's parameters, and the halo this layer zeroes when kResZeroHalo is in flags
+  const void* next_packed;
+  const void* next_table;
+  int32_t next_blob_units, next_tab_units, next_w_off, next_tab_off;
+  int32_t flags;             // as in ResLayer
+  int32_t hz_org, hz_P, hz_Q, hz_Wh, hz_ps2, hz_chunks, hz_hp;
+  // the work: LDS byte offsets and strides
+  int32_t kind;              // row_kind(), + kResRowRelu, + kResRowHalves
+  int32_t wts_off, kp16;     // weights (the bias lies 256 bytes in front of them); bytes per chunk of all filters
+  int32_t in_org, out_org, res_org;   // tap (0, 0) of pixel (0, 0); pixel (0, 0); likewise, < 0: no shortcut
+  int32_t tap_row, tap_col;  // from a tap to the next one down / to the right
+  int32_t out_row, out_col, res_row, res_col;
+  int32_t half_in, half_out, half_res;   // kResRowHalves: from a tile's first eight pixels to the other eight
+  int32_t res_cs;            // lanes held per shortcut pixel
+  // per computing wave, in 16-byte units from the tensor's first pixel: the item's first pixel in the input
+  // (+ filter tile << 14; kResNoItem: nothing to do), the output and the shortcut tensor
+  uint16_t wave_in[kResRowWaves], wave_out[kResRowWaves], wave_res[kResRowWaves];
+  int32_t swizzle;           // shift | mask << 2, of the input; << 4 of the output; << 8 of the shortcut tensor
+  int32_t res_step;          // columns of the shortcut tensor between neighbouring pixels
+  int32_t pad_[2];
+};
+static_assert(sizeof(ResRow) == 192 && offsetof(ResRow, kind) == 64 && offsetof(ResRow, wave_in) == 128, "ResRow is read in parts");
+constexpr uint16_t kResNoItem = 0xffff;
+constexpr int kResRowRelu = 256, kResRowHalves = 512;
+// Pixel strides of row layers are multiples of 32 bytes.  Reads of 16 pixels x 4 chunks run at LDS's full rate at odd
+// ones; at 64 and 128 bytes the pairs of chunks of a pixel in column x (halo included) lie in another order:
+// 32-byte pair j at j ^ (x >> 2 & 1) or j ^ (x >> 1 & 3).
+constexpr int row_swizzle_shift(int ps) { return ps == 64 ? 2 : 1; }
+constexpr int row_swizzle_mask(int ps) { return ps == 64 ? 1 : ps == 128 ? 3 : 0; }
+constexpr int kResNothing = -1, kResTail = -2;   // kinds: an entry that only stages; the mean and what follows
+// The sizes that exist: cpt 8-channel chunks per tap, m tiles per work item; -1: not one of them.
+constexpr int row_kind(int stride, int cpt, int m) {
+  const int most = stride == 1 ? (m == 8 ? 2 : m == 4 ? 4 : m == 2 ? 8 : 0) : (m == 4 ? 2 : m == 2 ? 4 : 0);
+  if (cpt > most) return -1;
+  return cpt - 1 + (stride == 1 ? (m == 2 ? 0 : m == 4 ? 8 : 12) : (m == 2 ? 14 : 18));
+}
+
 struct ResParams {
   const void* x;             // N images, NHWC
   void* y;                   // N x out_pixels x y_cs
@@ -178,6 +222,7 @@ struct ResParams {
   int y_cs, out_pixels;
   int n_layers;
   int lds_bytes;
+  const ResRow* rows;        // device memory: the layers for the kernel of row layers; nullptr: the other kernel
 };
 
 fupr_status launch_resident(const ResParams& p, int N, fupr_dtype dt, void* stream);

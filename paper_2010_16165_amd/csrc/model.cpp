@@ -76,6 +76,7 @@ struct fupr_model {
   bool resident_ok = false;               // the whole network fits one LDS-resident kernel
   ResParams resident{};                   // x, y, y_cs filled per call
   std::vector<ResLayer> res_layers;       // host copy of the layer table
+  std::vector<ResRow> res_rows;           // and of the table of row layers; empty: they are not all row layers
   std::vector<int32_t> res_tables;        // tap tables of all layers, back to back
   std::vector<size_t> res_table_at;       // first entry of each layer's table
   const void* res_dev = nullptr;          // the caller's device copy of the table (fupr_model_set_table)
@@ -143,6 +144,64 @@ void resident_item_shape(int M, int FT, int nsteps, bool has_res, int* MT_out, i
       *NT_out = nt;
     }
   }
+}
+
+// Tiles per work item of a row layer: `chains` chains of `chain` vertical neighbours x FT filter tiles on eight waves;
+// 0: it does not fit them.  A tall item reads fewer rows per tile, but two waves on a SIMD hide each other's waits:
+// the sizes that keep all eight busy first.
+int row_tiles(int stride, int cpt, int chain, int chains, int FT) {
+  int best = 0, most = 0;
+  for (int m : {8, 4, 2}) {
+    if (chain % m != 0 || row_kind(stride, cpt, m) < 0) continue;
+    const int items = chains * (chain / m) * FT;
+    if (items <= kResRowWaves && items > most) {
+      best = m;
+      most = items;
+    }
+  }
+  return best;
+}
+
+// Describes convolution `op` from ti to to as a row layer, given the layer's place in LDS; false: it is none.
+bool describe_row(const fupr_op_desc& op, const TensorInfo& ti, const TensorInfo& to, const ResLayer& L, const PackedLayout& PL,
+                  int in_ps, int out_ps, int res_ps, int halo, ResRow* r) {
+  const fupr_conv_shape& s = op.conv;
+  if (s.R != 3 || s.S != 3 || s.pad != 1 || halo != 1 || (s.stride != 1 && s.stride != 2) || PL.Kp > 64) return false;
+  if (PL.Kp * 2 > out_ps) return false;         // all 16 channels of a filter tile are stored
+  if (op.res >= 0 && s.stride != 1) return false;
+  // a tile is 16 pixels of a row, or 8 of row t and 8 of row t + P / 2
+  const bool halves = to.W == 8 && to.H % 2 == 0;
+  if (!halves && to.W % 16 != 0) return false;
+  const int chain = halves ? to.H / 2 : to.H, side = halves ? 1 : to.W / 16, cpt = PL.Cp / 8;
+  const int m = row_tiles(s.stride, cpt, chain, side, L.FT);
+  if (m == 0) return false;
+  if (m == 8 && (row_swizzle_mask(in_ps) || row_swizzle_mask(out_ps) || row_swizzle_mask(res_ps))) return false;
+  r->kind = row_kind(s.stride, cpt, m) + ((op.epilogue & FUPR_FUSE_RELU) ? kResRowRelu : 0) + (halves ? kResRowHalves : 0);
+  r->wts_off = L.wts_off;
+  r->kp16 = PL.Kp * 16;
+  r->in_org = L.in_org;
+  r->out_org = L.out_org;
+  r->res_org = L.res_org;
+  r->tap_row = L.in_row / s.stride;
+  r->tap_col = in_ps;
+  r->out_row = L.out_row;
+  r->out_col = L.out_col;
+  r->res_row = L.res_row;
+  r->res_col = L.res_col;
+  r->half_in = halves ? chain * L.in_row : 0;
+  r->half_out = halves ? chain * L.out_row : 0;
+  r->half_res = halves ? chain * L.res_row : 0;
+  r->res_cs = L.res_cs;
+  auto swizzle = [](int ps) { return row_swizzle_shift(ps) | row_swizzle_mask(ps) << 2; };
+  r->swizzle = swizzle(in_ps) | swizzle(out_ps) << 4 | swizzle(res_ps) << 8;
+  r->res_step = op.res_spatial_stride;
+  for (int w = 0; w < kResRowWaves && w < side * (chain / m) * L.FT; ++w) {
+    const int ft = w % L.FT, at = w / L.FT, col = at % side * 16, row = at / side * m;
+    r->wave_in[w] = (uint16_t)((row * L.in_row + col * L.in_col) / 16 | ft << 14);
+    r->wave_out[w] = (uint16_t)((row * L.out_row + col * L.out_col) / 16);
+    r->wave_res[w] = (uint16_t)((row * L.res_row + col * L.res_col) / 16);
+  }
+  return true;
 }
 
 // A block of LDS with a lifetime in layers; blocks whose lifetimes intersect
@@ -213,8 +272,10 @@ size_t assign_offsets(std::vector<LdsBlock>& blocks) {
 // that are not multiples of 64, 8.7 at odd multiples of 64 and 16.7 at
 // multiples of 128.  mode 0: the nearest odd multiple of 32; 1: the nearest
 // stride that is not a multiple of 64; 2: dense.
+constexpr int kRowStride = 3;   // mode of row layers (row_swizzle_mask)
 int lds_pixel_stride(int cs, int mode) {
   const int dense = cs * 2;
+  if (mode == kRowStride) return round_up(dense, 32);
   if (mode == 2) return dense;
   if (mode == 1) return dense % 64 == 0 ? dense + 16 : dense;
   int ps2 = dense;
@@ -308,6 +369,8 @@ void plan_resident(fupr_model* m) {
   }
   std::stable_sort(candidates.begin(), candidates.end(),
                    [](const auto& a, const auto& b) { return a.first < b.first; });
+  // first of all as row layers, which have the smallest strides
+  candidates.insert(candidates.begin(), {-1.0, std::vector<int>(k, kRowStride)});
 
   // Parameter blocks by size, largest first: when nothing fits with every
   // layer's parameters staged one layer ahead, the largest ones are staged at
@@ -324,6 +387,7 @@ void plan_resident(fupr_model* m) {
   std::vector<char> late(n, 0);
   for (size_t j = 0; j < n_late; ++j) late[by_size[j]] = 1;
   for (const auto& cand : candidates) {
+    const bool as_rows = cand.first < 0.0;
     std::vector<int> ps2(n + 1);
     for (int tid = 0; tid <= n; ++tid) {
       const int c = class_of[tid];
@@ -350,9 +414,11 @@ void plan_resident(fupr_model* m) {
       if (m->ops[i].kind == FUPR_OP_CONV) {
         const PackedLayout PL = packed_layout(m->ops[i].conv, m->dt);
         if (PL.nchunk_pad / 4 + kResTablePad > 64) ok = false;   // one wave stages the table
-        b.units = PL.nchunk_pad / 4 + kResTablePad + PL.total_bytes / 16;   // table (16 bytes per step), blob
+        b.units = PL.total_bytes / 16;
+        if (!as_rows || i + 1 == n) b.units += PL.nchunk_pad / 4 + kResTablePad;   // table (16 bytes per step), blob
       }
     }
+    if (!ok && as_rows) continue;
     if (!ok) return;
     const size_t extent = assign_offsets(blocks);
     if (tuning_int("debug", 0)) {
@@ -383,7 +449,7 @@ void plan_resident(fupr_model* m) {
         for (int col = 0; col < Wh; ++col) {
           if (row >= h && row < t.H + h && col >= h && col < t.W + h) continue;
           const size_t u = (size_t)pixel_at(tid, row, col) / 16;
-          for (int c = 0; c < t.cs / 8; ++c) fn(u + c);
+          for (int c = 0; c < (as_rows ? ps2[tid] / 16 : t.cs / 8); ++c) fn(u + c);
         }
     };
     auto write_interior = [&](int tid) {
@@ -412,6 +478,8 @@ void plan_resident(fupr_model* m) {
     std::array<int, 8> prev_geometry;
     prev_geometry.fill(-1);
     m->res_layers.clear();
+    m->res_rows.clear();
+    bool rows = as_rows && n >= 3;   // every layer so far is a row layer, or one of the last two
     m->res_tables.clear();
     m->res_table_at.clear();
     for (int i = 0; i < n; ++i) {
@@ -420,6 +488,10 @@ void plan_resident(fupr_model* m) {
       const TensorInfo& to = m->tensors[i + 1];
       const bool last = i + 1 == n;
       ResLayer L{};
+      ResRow no_row{};
+      no_row.kind = kResNothing;
+      std::fill(no_row.wave_in, no_row.wave_in + kResRowWaves, kResNoItem);
+      ResRow row = no_row;
       size_t table_at = 0;
       L.flags = last ? kResLast : 0;
       if (late[i]) {
@@ -428,6 +500,7 @@ void plan_resident(fupr_model* m) {
         stage.res_org = -1;
         stage.MT = stage.NT = stage.n_fgroups = stage.Q = stage.M = 1;   // a conv entry without work items
         m->res_layers.push_back(stage);
+        m->res_rows.push_back(no_row);
         m->res_table_at.push_back(0);
         if (blocks[n + 1 + i].units) mark(blocks[n + 1 + i].offset, blocks[n + 1 + i].units, 0);
       }
@@ -454,7 +527,7 @@ void plan_resident(fupr_model* m) {
         const int nsteps = PL.nchunk_pad / 4, cpt = PL.Cp / 8;
         L.packed = op.packed;
         L.blob_units = (int32_t)(PL.total_bytes / 16);
-        L.tab_units = nsteps + kResTablePad;
+        L.tab_units = as_rows && !last ? 0 : nsteps + kResTablePad;
         L.tab_off = (int32_t)(blocks[n + 1 + i].offset * 16);
         L.w_off = L.tab_off + L.tab_units * 16;
         L.wts_off = L.w_off + (int32_t)PL.weight_offset;
@@ -508,6 +581,16 @@ void plan_resident(fupr_model* m) {
           m->res_tables.push_back(L.in_org + e);
         }
       }
+      // (the mean and the convolution behind it run on the kernel's general path)
+      const bool tail = i + 2 == n ? (L.flags & kResMean) != 0 && kResRowWaves * to.cs * 4 <= kResScratchBytes
+                                   : last && op.kind == FUPR_OP_CONV && op.conv.R == 1 && op.conv.S == 1 && op.res < 0 &&
+                                         L.MT == 1 && L.NT <= 2;
+      if (op.kind == FUPR_OP_CONV && i + 2 < n)
+        rows = rows && describe_row(op, ti, to, L, packed_layout(op.conv, m->dt), ps2[op.in], ps2[i + 1],
+                                    ps2[op.res >= 0 ? op.res : op.in], halo_of(ti), &row);
+      else
+        rows = rows && tail, row.kind = kResTail;
+      if (as_rows && !rows) break;
       L.magicQ = reciprocal_u16(L.Q);
       L.magicF = reciprocal_u16(L.n_fgroups);
       if (!last) {
@@ -520,7 +603,7 @@ void plan_resident(fupr_model* m) {
           L.hz_Q = to.W;
           L.hz_Wh = row_of(to);
           L.hz_ps2 = ps2[i + 1];
-          L.hz_chunks = to.cs / 8;
+          L.hz_chunks = as_rows ? ps2[i + 1] / 16 : to.cs / 8;
           L.hz_hp = halo_of(to);
           halo_units(i + 1, [&](size_t u) { clean[u] = 1; });
         }
@@ -530,14 +613,28 @@ void plan_resident(fupr_model* m) {
       if (i + 1 < n && !late[i + 1] && blocks[n + 2 + i].units)
         mark(blocks[n + 2 + i].offset, blocks[n + 2 + i].units, 0);
       m->res_layers.push_back(L);
+      row.flags = L.flags;
+      row.hz_org = L.hz_org;
+      row.hz_P = L.hz_P;
+      row.hz_Q = L.hz_Q;
+      row.hz_Wh = L.hz_Wh;
+      row.hz_ps2 = L.hz_ps2;
+      row.hz_chunks = L.hz_chunks;
+      row.hz_hp = L.hz_hp;
+      m->res_rows.push_back(row);
       m->res_table_at.push_back(table_at);
       if (tuning_int("debug", 0))
         std::fprintf(stderr, "resident layer %d: M %d FT %d steps %d item %dx%d items %d ps2 in %d out %d "
                      "zero_halo %d res %d\n", i, L.M, L.FT, L.nsteps, L.MT, L.NT, L.n_items, ps2[op.in],
                      ps2[i + 1], (L.flags & kResZeroHalo) != 0, L.res_org >= 0);
     }
+    if (as_rows && !rows) {
+      m->res_rows.clear();
+      continue;
+    }
     if (m->res_layers.size() > (size_t)kResMaxLayers) return;
     R.n_layers = (int)m->res_layers.size();
+    if (!as_rows) m->res_rows.clear();
     if (tuning_int("debug", 0))
       std::fprintf(stderr, "resident plan: %d bytes of LDS, %d table entries for %d layers\n",
                    R.lds_bytes, R.n_layers, n);
@@ -560,6 +657,8 @@ size_t resident_layer_bytes(const fupr_model* m) {
 size_t resident_table_bytes(const fupr_model* m) {
   return round_up_sz(m->res_tables.size() * sizeof(int32_t), 256) + 256;
 }
+// behind them, the table of row layers
+size_t resident_rows_bytes(const fupr_model* m) { return round_up_sz(m->res_rows.size() * sizeof(ResRow), 256); }
 
 }  // namespace
 
@@ -768,7 +867,7 @@ extern "C" fupr_status fupr_model_fuse_blocks(fupr_model* m, int32_t on) {
 
 extern "C" size_t fupr_model_table_bytes(const fupr_model* m) {
   if (!m || !m->resident_ok) return 0;
-  return resident_layer_bytes(m) + resident_table_bytes(m);
+  return resident_layer_bytes(m) + resident_table_bytes(m) + resident_rows_bytes(m);
 }
 
 extern "C" fupr_status fupr_model_table_write(const fupr_model* m, const void* dev_table,
@@ -791,7 +890,18 @@ extern "C" fupr_status fupr_model_table_write(const fupr_model* m, const void* d
     layers[i].next_tab_off = layers[i + 1].tab_off;
   }
   char* out = reinterpret_cast<char*>(host_out);
-  std::fill(out, out + layer_bytes + resident_table_bytes(m), 0);
+  std::fill(out, out + layer_bytes + resident_table_bytes(m) + resident_rows_bytes(m), 0);
+  std::vector<ResRow> rows = m->res_rows;
+  for (size_t i = 0; i + 1 < rows.size(); ++i) {
+    rows[i].next_packed = layers[i].next_packed;
+    rows[i].next_table = layers[i].next_table;
+    rows[i].next_blob_units = layers[i].next_blob_units;
+    rows[i].next_tab_units = layers[i].next_tab_units;
+    rows[i].next_w_off = layers[i].next_w_off;
+    rows[i].next_tab_off = layers[i].next_tab_off;
+  }
+  std::copy(reinterpret_cast<const char*>(rows.data()), reinterpret_cast<const char*>(rows.data() + rows.size()),
+            out + layer_bytes + resident_table_bytes(m));
   std::copy(reinterpret_cast<const char*>(layers.data()),
             reinterpret_cast<const char*>(layers.data()) + n * sizeof(ResLayer), out);
   std::copy(reinterpret_cast<const char*>(m->res_tables.data()),
@@ -1290,6 +1400,9 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
   if (use_resident(m, input, output)) {
     ResParams R = m->resident;
     R.layers = reinterpret_cast<const ResLayer*>(m->res_dev);
+    R.rows = m->res_rows.empty() ? nullptr
+                                 : reinterpret_cast<const ResRow*>(static_cast<const char*>(m->res_dev) + resident_layer_bytes(m) +
+                                                                   resident_table_bytes(m));
     R.x = input->ptr;
     R.y = output->ptr;
     R.y_cs = output->c_stride;
