@@ -34,6 +34,11 @@
 // (16 bytes as well), a step 16 channels in four MFMAs, each of which takes one channel of every
 // lane's chunk.  A CIFAR-size network of 21 layers on 32 images: 410 us (one thread per pixel and
 // four filters, vector FMAs) -> 111.
+// Clocks of a launch of one image (3 x 3, 256 -> 180 at 14 x 14, eight waves, about 10 000 with the 3600 that an empty
+// launch takes): arguments 430, first weights asked for 400, pixels 1100, tables and the wait 1400, multiplication 1500,
+// exchange 500, sums and store 1100.  Arguments in one go, tables by waves of their own, the shortcut asked for with the
+// pixels, partial sums beside the patch and added up without choices: ResNet-18, one image 92.8 -> 88.9 us, ResNet-50, 9 images
+// 264 -> 257, ResNet-34, 20 images 353 -> 347.
 // What bounds it: below some ten images latency (arguments, patch, first weights, one store);
 // then the weights, which every tile reads anew (45 bytes per clock and compute unit), and the
 // vector instructions that work out pixel addresses, beside the matrix pipe.
@@ -43,6 +48,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 
 #include "conv16.h"
 #include "device_utils.h"
@@ -95,7 +101,10 @@ struct WindowParams {
   int table_at, table_bytes, pixels_at, patch2_at;   // LDS byte offsets (the patch starts at 0)
   FastDiv divPQ, divQ, divC, divS, divSlots, divSlots2;
   FastDiv divG;          // by mgroups or fgroups, whichever runs fastest
+  int part_at;           // LDS byte offset of the partial sums; 0: over the patch, after a barrier
+  int pad_[4];
 };
+static_assert(sizeof(WindowParams) == 320, "load_arguments");
 
 __device__ __forceinline__ uint32_t clamp_below(uint32_t v, uint32_t floor2) {
   const short2_t a = __builtin_bit_cast(short2_t, v), f = __builtin_bit_cast(short2_t, floor2);
@@ -131,9 +140,13 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 // A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
 // wave; G: steps whose pixels are read from LDS together.  IX: every filter adds into its listed
 // channel of y (p.keep); without it p.keep is not read.
+// Tiles so small that the wave which finishes one hands its own sum over as well: what it adds up is then read in
+// a row without a choice, 60 instructions for eight waves in place of 200 (1200 clocks of a launch of 10 000).
+constexpr bool all_partial_sums(int tiles) { return tiles <= 4; }
+
 template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES, bool IX>
-__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams p) {
-  touch_arguments<sizeof(WindowParams)>();
+__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams) {
+  const WindowParams p = load_arguments<WindowParams>();
   constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
   constexpr uint32_t ES = F32 ? 4 : 2;       // bytes per element
   extern __shared__ uint4 lds4[];
@@ -162,9 +175,12 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
                    : (uint32_t)(g * p.Kp + min(f0 + t * 16, p.Kp - 16) + li) * 16u;
   const uint32_t a_step = (uint32_t)p.Kp * 64u;
   uint4 a[D][NT];
-  auto load_weights = [&](int step, uint4* av) {
-    // (steps past the end read the last step's weights, and are not multiplied)
-    const uint32_t so = (uint32_t)min(step, p.nsteps - 1) * a_step;
+  // of this wave's next step (steps past the end read the last step's weights, and are not multiplied)
+  const uint32_t w_last = (uint32_t)(p.nsteps - 1) * a_step, w_step = (uint32_t)p.WK * a_step;
+  uint32_t w_at = min((uint32_t)wk * a_step, w_last);
+  auto load_weights = [&](uint4* av) {
+    const uint32_t so = w_at;
+    w_at = min(w_at + w_step, w_last);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if constexpr (F32) {
@@ -185,13 +201,9 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   // arrive in a cold L2: they are asked for before anything else (a 16-bit network of 22 short launches 93.9 ->
   // 92.9 us).  Single precision loads them four bytes at a time and asks for its pixels first (101.3 against
   // 103.9 us for 15 launches); so do tiles of more than two, which are long launches and gain nothing.
-  int next = wk;
   auto first_weights = [&] {
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      load_weights(next, a[d]);
-      next += p.WK;
-    }
+    for (int d = 0; d < D; ++d) load_weights(a[d]);
   };
   constexpr bool kWeightsFirst = !F32 && MT <= 2;
   if constexpr (kWeightsFirst) first_weights();
@@ -268,16 +280,19 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   }
   if constexpr (!kWeightsFirst) first_weights();
 
-  // per chunk of 8 channels: its LDS distance from the window origin, and its tap
+  // The two tables of a window, by waves of their own where there are enough.  Per chunk of 8 channels: its LDS
+  // distance from the window origin, and its tap.  (What is multiplied here lies inside the patch: 24 bits.)
   u32x2* table = reinterpret_cast<u32x2*>(lds + p.table_at);
-  if constexpr (MODE == kWindow) {
+  constexpr int kPixelWaves = (BM + 63) / 64;
+  const int apart = waves > kPixelWaves ? kPixelWaves : 0;   // waves that leave the taps to the others
+  if (MODE == kWindow && wave >= apart) {
     const int entries = p.table_bytes / 8;
-    for (int j = tid; j < entries; j += waves * 64) {
-      const int tap = div_by(j, p.divC), cc = j - tap * p.cpt;
-      const int r = div_by(tap, p.divS), s = tap - r * p.S;
+    for (int j = tid - apart * 64; j < entries; j += stride64 - apart * 64) {
+      const int tap = div_by(j, p.divC), cc = j - __mul24(tap, p.cpt);
+      const int r = div_by(tap, p.divS), s = tap - __mul24(r, p.S);
       const bool ok = tap < p.R * p.S;
       u32x2 e;
-      e[0] = ok ? (uint32_t)(((r * p.W + s) * p.slots + cc) * 16) : 0u;
+      e[0] = ok ? (uint32_t)((__mul24(__mul24(r, p.W) + s, p.slots) + cc) * 16) : 0u;
       e[1] = ok ? (uint32_t)tap : 31u;
       table[j] = e;
     }
@@ -285,7 +300,7 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
 
   // per pixel of the tile: LDS address of the window origin, and which taps lie inside the image
   u32x2* pixel_table = reinterpret_cast<u32x2*>(lds + p.pixels_at);
-  if constexpr (MODE == kWindow) {
+  if (MODE == kWindow && (apart == 0 || wave < apart)) {
     for (int i = tid; i < BM; i += stride64) {
       const int m = m0 + i;
       int n, pp, qq;
@@ -310,6 +325,57 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
       const int k = fg * p.WF * NT * 16 + i, c = p.keep[min(k, p.keep_n - 1)];
       list[i] = k < p.keep_n && (unsigned)c < (unsigned)p.yC ? c : -1;
     }
+  }
+
+  // The shortcut, of the pairs of filter tiles that this wave will finish (an odd last tile is alone).  After
+  // the exchange between 16-lane rows lane (pixel, g) holds channels (g >> 1) * 8 .. + 7 of tile t + (g & 1): 16-byte
+  // accesses; a lone tile keeps 8 bytes.  Small tiles ask for it here, where it arrives with the pixels; the others, whose
+  // registers are taken, all at once when they have multiplied (asked for pair by pair in front of each store it
+  // cost a memory latency per pair).
+  constexpr int NP = (NT + 1) / 2;
+  constexpr int NR = IX ? 1 : F32 ? NT : NP;     // (single precision: 16 bytes a tile)
+  constexpr bool kShortcutFirst = !IX && MT * NR <= 2, kShortcutLater = !IX && !kShortcutFirst;
+  const __amdgpu_buffer_rsrc_t rr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.res), 0, p.res_bytes, 0x00020000);
+  auto res_at = [&](int m) {     // byte offset of output pixel m's shortcut pixel
+    if (p.res_linear) return (uint32_t)(m * p.rcs) * ES;
+    int n, pp, qq;
+    split_pixel(m, &n, &pp, &qq);
+    return (uint32_t)(((n * p.rH + pp * p.rss) * p.rW + qq * p.rss) * p.rcs) * ES;
+  };
+
+  u32x4 shortcut[IX ? 1 : MT][NR];
+  auto ask_shortcut = [&] {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = m0 + mt * 16 + li;
+      const uint32_t ro = m < p.M ? res_at(m) : 0u;
+#pragma unroll
+      for (int pr = 0; pr < NP; ++pr) {
+        if (((mt * NP + pr) & (p.WK - 1)) != wk) continue;
+        if constexpr (F32) {
+#pragma unroll
+          for (int u = 2 * pr; u < (2 * pr + 2 < NT ? 2 * pr + 2 : NT); ++u) {
+            const int kk = f0 + u * 16 + g * 4 - p.roff;
+            shortcut[mt][u] = __builtin_amdgcn_raw_buffer_load_b128(
+                rr, m < p.M && kk >= 0 && kk < p.rcs ? ro + (uint32_t)kk * 4u : kOutside, 0, 0);
+          }
+          continue;
+        }
+        const bool pair = 2 * pr + 1 < NT;
+        const int kk = f0 + pr * 32 + (pair ? (g & 1) * 16 + (g >> 1) * 8 : g * 4) - p.roff;
+        const uint32_t at = m < p.M && kk >= 0 && kk < p.rcs ? ro + (uint32_t)kk * 2u : kOutside;
+        if (pair) {
+          shortcut[mt][pr] = __builtin_amdgcn_raw_buffer_load_b128(rr, at, 0, 0);
+        } else {
+          const u32x2 r2 = __builtin_amdgcn_raw_buffer_load_b64(rr, at, 0, 0);
+          shortcut[mt][pr] = u32x4{r2[0], r2[1], 0u, 0u};
+        }
+      }
+    }
+  };
+  if constexpr (kShortcutFirst) {
+    if (p.res) ask_shortcut();
   }
 
   // the first wave of a column starts from the bias, the others from zero
@@ -408,10 +474,7 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
             acc[mt][t] = mfma_16x16x32<BF>(a[d][t], b[gi & 1][i][mt], acc[mt][t]);
           }
         }
-      if (more) {
-        load_weights(next, a[d]);
-        next += p.WK;
-      }
+      if (more) load_weights(a[d]);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -425,20 +488,13 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
     if (gi * G < left) group(gi, false);
 
   // ---- epilogue: shortcut, ReLU, one rounding ----
-  const __amdgpu_buffer_rsrc_t rr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.res), 0, p.res_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
+  if constexpr (kShortcutLater) {
+    if (p.res) ask_shortcut();
+  }
   const uint32_t floor2 = p.relu ? 0u : 0x80008000u;
-  auto res_at = [&](int m) {     // byte offset of output pixel m's shortcut pixel
-    if (p.res_linear) return (uint32_t)(m * p.rcs) * ES;
-    int n, pp, qq;
-    split_pixel(m, &n, &pp, &qq);
-    return (uint32_t)(((n * p.rH + pp * p.rss) * p.rW + qq * p.rss) * p.rcs) * ES;
-  };
-
   // The waves of a column share its pairs of filter tiles: wave e % WK finishes pair e, the
-  // others hand it their sums through LDS (over the patch, which nobody reads any more).
-  constexpr int NP = (NT + 1) / 2;               // pairs of filter tiles; an odd last tile is alone
+  // others hand it their sums through LDS (where that is short over the patch, which nobody reads any more).
   // Listed channels are updated with 2-byte accesses (they have gaps, and the words between two
   // waves' channels are shared).  What a wave will add to is asked for here, before the exchange
   // of the partial sums, so that its latency passes meanwhile.
@@ -463,15 +519,18 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
             for (int i = 0; i < 4; ++i)
               old[mt][t][i] = __builtin_amdgcn_raw_buffer_load_b16(yr, listed_at(mt, t, i), 0, 0);
   }
-  f32x4* part = reinterpret_cast<f32x4*>(lds);   // [giver][column][tile][lane]
+  // [giver][column][tile][lane]; small tiles: [wave along the reduction] and so on
+  f32x4* part = reinterpret_cast<f32x4*>(lds + p.part_at);
+  constexpr bool kAll = all_partial_sums(TT);
   if (p.WK > 1) {
-    __syncthreads();
+    if (p.part_at == 0) __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int giver = (wk - (mt * NP + t / 2)) & (p.WK - 1);   // 0: the owner
-        if (giver > 0) part[(((giver - 1) * p.WF + wf) * TT + mt * NT + t) * 64 + lane] = acc[mt][t];
+        if constexpr (kAll) part[((wk * p.WF + wf) * TT + mt * NT + t) * 64 + lane] = acc[mt][t];
+        else if (giver > 0) part[(((giver - 1) * p.WF + wf) * TT + mt * NT + t) * 64 + lane] = acc[mt][t];
       }
     __syncthreads();
   }
@@ -501,15 +560,30 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
         // single precision: a lane's four channels of a tile are 16 bytes
 #pragma unroll
         for (int u = t; u < (t + 2 < NT ? t + 2 : NT); ++u) {
-          const int k0 = f0 + u * 16 + g * 4, kk = k0 - p.roff;
+          const int k0 = f0 + u * 16 + g * 4;
           f32x4 r4 = {0.f, 0.f, 0.f, 0.f};
-          if (p.res)
-            r4 = __builtin_bit_cast(
-                f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                           rr, m < p.M && kk >= 0 && kk < p.rcs ? res_at(m) + (uint32_t)kk * 4u : kOutside, 0, 0));
+          if (p.res) r4 = __builtin_bit_cast(f32x4, shortcut[mt][u]);
           f32x4 v = acc[mt][u];
           if (p.WK > 1) {
             v = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kAll) {
+              const f32x4* src = part + (wf * TT + mt * NT + u) * 64 + lane;
+              const int next = p.WF * TT * 64;
+              auto add_up = [&](auto waves_along) {
+                constexpr int W = waves_along.value;
+                f32x4 q[W];
+#pragma unroll
+                for (int k = 0; k < W; ++k) q[k] = src[k * next];
+#pragma unroll
+                for (int k = 0; k < W; ++k) v += q[k];
+                asm volatile("; %0 partial sums" ::"n"(W));
+              };
+              if (p.WK == 8) add_up(std::integral_constant<int, 8>{});
+              else if (p.WK == 4) add_up(std::integral_constant<int, 4>{});
+              else if (p.WK == 2) add_up(std::integral_constant<int, 2>{});
+              else
+                for (int k = 0; k < p.WK; ++k) v += src[k * next];
+            } else
             for (int k = 0; k < p.WK; ++k) {
               const int from = ((k - wk) & (p.WK - 1)) - 1;
               const f32x4 q = part[((max(from, 0) * p.WF + wf) * TT + mt * NT + u) * 64 + lane];
@@ -533,6 +607,36 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
         if (p.WK > 1) {
           const f32x4 own0 = *s0, own1 = *s1;
           *s0 = *s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (kAll) {
+            // all of them are there, this wave's own too, and are asked for at once
+            const f32x4* src = part + (wf * TT + mt * NT + t) * 64 + lane;
+            const int next = p.WF * TT * 64;
+            auto add_up = [&](auto waves_along) {
+              constexpr int W = waves_along.value;
+              f32x4 u[W][2];
+#pragma unroll
+              for (int k = 0; k < W; ++k) {
+                u[k][0] = src[k * next];
+                if (pair) u[k][1] = src[k * next + 64];
+              }
+#pragma unroll
+              for (int k = 0; k < W; ++k) {
+                *s0 += u[k][0];
+                if (pair) *s1 += u[k][1];
+              }
+              // (the compiler joins the last reads of the three sums, and loses the address of one)
+              asm volatile("; %0 partial sums" ::"n"(W));
+            };
+            if (p.WK == 8) add_up(std::integral_constant<int, 8>{});
+            else if (p.WK == 4) add_up(std::integral_constant<int, 4>{});
+            else if (p.WK == 2) add_up(std::integral_constant<int, 2>{});
+            else
+              for (int k = 0; k < p.WK; ++k) {
+                *s0 += src[k * next];
+                if (pair) *s1 += src[k * next + 64];
+              }
+            return;
+          }
           for (int k = 0; k < p.WK; ++k) {
             const int from = ((k - wk) & (p.WK - 1)) - 1;          // -1: this wave itself
             const f32x4* src = part + ((max(from, 0) * p.WF + wf) * TT + mt * NT + t) * 64 + lane;
@@ -555,21 +659,9 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
           }
         continue;
       }
-      // after the exchange between 16-lane rows lane (pixel, g) holds channels
-      // (g >> 1) * 8 .. + 7 of tile t + (g & 1): 16-byte accesses; a lone tile keeps 8 bytes
       const int k0 = f0 + t * 16 + (pair ? (g & 1) * 16 + (g >> 1) * 8 : g * 4);
       u32x4 r4 = {0u, 0u, 0u, 0u};
-      if (p.res) {
-        const int kk = k0 - p.roff;
-        const uint32_t ro = m < p.M && kk >= 0 && kk < p.rcs ? res_at(m) + (uint32_t)kk * 2u : kOutside;
-        if (pair) {
-          r4 = __builtin_amdgcn_raw_buffer_load_b128(rr, ro, 0, 0);
-        } else {
-          const u32x2 r2 = __builtin_amdgcn_raw_buffer_load_b64(rr, ro, 0, 0);
-          r4[0] = r2[0];
-          r4[1] = r2[1];
-        }
-      }
+      if (p.res) r4 = shortcut[mt][pr];
       f32x4 s0, s1;
       totals(&s0, &s1);
       const uint32_t off = k0 < p.ycs ? yo + (uint32_t)k0 * 2u : kOutside;
@@ -694,8 +786,15 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   p.pixels_at = p.table_at + p.table_bytes;
   if (mode == kWindow) end = (size_t)p.pixels_at + (size_t)BM * 8;
   out->patch_slots = pixels * (p.slots + p.slots2);
-  const size_t reduce = (size_t)(WK - 1) * WF * T.MT * T.NT * 1024;
+  // The partial sums lie beside the patch, which saves a barrier, where no workgroup less fits a compute unit for it.
+  const int givers = WK == 1 ? 0 : all_partial_sums(T.MT * T.NT) ? WK : WK - 1;
+  const size_t reduce = (size_t)givers * WF * T.MT * T.NT * 1024, beside = round_up_sz(end, 1024) + reduce;
   out->lds = std::max(end, reduce);
+  const int by_waves = std::max(1, std::min(32 / waves, 512 / T.vgprs * 4 / waves));
+  if (reduce > 0 && beside <= kLdsLimit && std::min((int)(kLdsLimit / out->lds), by_waves) <= (int)(kLdsLimit / beside)) {
+    p.part_at = (int)round_up_sz(end, 1024);
+    out->lds = beside;
+  }
   if (c.keep) {
     p.keep_at = (int)round_up_sz(out->lds, 16);
     out->lds = (size_t)p.keep_at + (size_t)NF * 4;

@@ -99,6 +99,24 @@ __device__ __forceinline__ void touch_arguments() {
         : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
 }
 
+// A kernel's arguments, all of them in scalar registers at once: whole 64-byte lines, one wait.  Left to the compiler,
+// each group is loaded where it is first used, a wait of 100 clocks and more every time, six to ten of them in
+// front of the first multiplication of a short kernel.  (The loads have landed before anything reads their registers.)
+template <class Params>
+__device__ __forceinline__ Params load_arguments() {
+  static_assert(sizeof(Params) == 320, "five lines");
+  typedef int i32x16 __attribute__((ext_vector_type(16)));
+  struct Lines {
+    i32x16 v[5];
+  } lines;
+  asm volatile(
+      "s_load_dwordx16 %0, %5, 0\n\ts_load_dwordx16 %1, %5, 64\n\ts_load_dwordx16 %2, %5, 128\n\t"
+      "s_load_dwordx16 %3, %5, 192\n\ts_load_dwordx16 %4, %5, 256\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(lines.v[0]), "=&s"(lines.v[1]), "=&s"(lines.v[2]), "=&s"(lines.v[3]), "=&s"(lines.v[4])
+      : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
+  return __builtin_bit_cast(Params, lines);
+}
+
 // floor(v / d) for 0 <= v < 2^31 as mulhi(v, mul) >> shift with shift =
 // ceil(log2 d) - 1, mul = ceil(2^(32 + shift) / d) < 2^32 (the error mul * d -
 // 2^(32 + shift) is below d <= 2^(shift + 1), hence exact while v < 2^31);
