@@ -618,6 +618,7 @@ void fupr_graph_destroy(fupr_graph* g);
  *                                                 workgroups per compute unit
  *   pair_filters = 16..128                        most filters of the second convolution of a pair of
  *                                                 1 x 1 convolutions in one launch
+ *   conv_two = 0                                  two convolutions of one tensor as two launches
  *   bottleneck_fuse, basic_fuse = 0               blocks of fupr_model_fuse_blocks as several launches
  *   bottleneck_tile = <index>                     force a tile of the kernel that runs bottleneck blocks
  *   basic_tile = <rectangle>x<f>                  force a rectangle of the kernel that runs basic blocks,

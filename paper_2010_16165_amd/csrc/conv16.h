@@ -76,5 +76,8 @@ fupr_status launch_conv1x1_pipe(const Conv16Params& p, int N, bool bf16, void* s
 bool conv_window_applies(const Conv16Params& geometry, int N);
 const char* conv_window_name(const Conv16Params& geometry, int N);
 bool launch_conv_window(const Conv16Params& p, int N, void* stream, fupr_status* status);
+// A convolution with a window and a 1 x 1 convolution, both of which it takes, as one launch; likewise.
+bool conv_window_two_applies(const Conv16Params& window, const Conv16Params& tap, int N);
+bool launch_conv_window_two(const Conv16Params& window, const Conv16Params& tap, int N, void* stream, fupr_status* status);
 
 }  // namespace fupr

@@ -48,6 +48,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <type_traits>
 
 #include "conv16.h"
@@ -144,9 +145,9 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 // a row without a choice, 60 instructions for eight waves in place of 200 (1200 clocks of a launch of 10 000).
 constexpr bool all_partial_sums(int tiles) { return tiles <= 4; }
 
-template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES, bool IX>
-__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams) {
-  const WindowParams p = load_arguments<WindowParams>();
+template <int EL, int MODE, int MT, int NT, int D, int G, bool IX>
+__device__ __forceinline__ void window_tile(const int which) {
+  const WindowParams p = load_arguments<WindowParams>(which);
   constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
   constexpr uint32_t ES = F32 ? 4 : 2;       // bytes per element
   extern __shared__ uint4 lds4[];
@@ -156,6 +157,7 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int waves = p.WF * p.WK;
+  if (wave >= waves) return;                 // (conv_window_two_kernel)
   const int wk = wave >> p.log2_WF, wf = wave & (p.WF - 1);
 
   const int l = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
@@ -686,6 +688,11 @@ __global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const Wi
   }
 }
 
+template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES, bool IX>
+__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams) {
+  window_tile<EL, MODE, MT, NT, D, G, IX>(0);
+}
+
 // D: steps of weights in flight; G: steps per group of pixel reads; vgprs: registers of the 16-bit
 // window form, as the estimate below was fitted with (one-tap forms take up to 18 more, fp32 up to 15).
 struct WindowTile {
@@ -807,6 +814,63 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   out->tile = tile;
   out->mode = mode;
   return true;
+}
+
+// Two convolutions of one tensor that do not need each other (a block's first 3 x 3 and its projection shortcut) as
+// one launch: blockIdx.y says which, each with the tile, the waves and the bits it has alone.  Saves a launch,
+// whose start and end cost 3600 clocks with nothing in between, and the smaller one runs where the other leaves
+// compute units free.  Workgroups have the waves of the larger one; what the other does not need of them ends at once.
+struct TwoWindowParams {
+  WindowParams p[2];
+};
+
+template <int EL, int WINDOW, int TAP>
+__global__ __launch_bounds__(kTiles[WINDOW].threads, kTiles[WINDOW].min_waves) void conv_window_two_kernel(const TwoWindowParams) {
+  constexpr WindowTile A = kTiles[WINDOW], B = kTiles[TAP];
+  if (blockIdx.y == 0) window_tile<EL, kWindow, A.MT, A.NT, A.D, A.G, false>(0);
+  else window_tile<EL, kOneTap, B.MT, B.NT, B.D, B.G, false>(1);
+}
+// The tiles that it is compiled for, of the window and of the 1 x 1 convolution.
+constexpr int kTwoWindow[] = {0, 2, 4, 6, 7, 10}, kTwoTap[] = {0, 2, 6};
+
+template <int EL, int WINDOW, int TAP>
+fupr_status launch_two_as(const WindowPlan& a, const WindowPlan& b, hipStream_t st) {
+  auto kernel = conv_window_two_kernel<EL, WINDOW, TAP>;
+  const size_t lds = std::max(a.lds, b.lds);
+  if (lds > 64 * 1024) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+    if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
+  }
+  TwoWindowParams two{{a.p, b.p}};
+  void* list[] = {&two};
+  const unsigned blocks = (unsigned)std::max(a.p.per_xcd, b.p.per_xcd) * 8;
+  const unsigned threads = (unsigned)std::max(a.p.WF * a.p.WK, b.p.WF * b.p.WK) * 64;
+  return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(blocks, 2), dim3(threads), list, lds, st),
+                  "conv_window_two_kernel");
+}
+
+template <int EL, int WINDOW>
+fupr_status launch_two_of(const WindowPlan& a, const WindowPlan& b, hipStream_t st) {
+  switch (b.tile) {
+    case 0: return launch_two_as<EL, WINDOW, 0>(a, b, st);
+    case 2: return launch_two_as<EL, WINDOW, 2>(a, b, st);
+    case 6: return launch_two_as<EL, WINDOW, 6>(a, b, st);
+  }
+  return FUPR_ERR_LIMIT;
+}
+
+template <int EL>
+fupr_status launch_two(const WindowPlan& a, const WindowPlan& b, hipStream_t st) {
+  switch (a.tile) {
+    case 0: return launch_two_of<EL, 0>(a, b, st);
+    case 2: return launch_two_of<EL, 2>(a, b, st);
+    case 4: return launch_two_of<EL, 4>(a, b, st);
+    case 6: return launch_two_of<EL, 6>(a, b, st);
+    case 7: return launch_two_of<EL, 7>(a, b, st);
+    case 10: return launch_two_of<EL, 10>(a, b, st);
+  }
+  return FUPR_ERR_LIMIT;
 }
 
 template <int EL, int MODE, int TILE, bool IX>
@@ -1037,6 +1101,50 @@ static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, bool l
   if (listed)
     return bf16 ? dispatch<FUPR_BF16, kWindow, true>(plan, st) : dispatch<FUPR_F16, kWindow, true>(plan, st);
   return bf16 ? dispatch<FUPR_BF16, kWindow>(plan, st) : dispatch<FUPR_F16, kWindow>(plan, st);
+}
+
+// Both convolutions' plans, if they can run as one launch.
+static bool plan_two(const Conv16Params& window, const Conv16Params& tap, int N, WindowPlan* a, WindowPlan* b) {
+  if (window.dt == FUPR_F32 || window.keep || tap.keep || window.x2 || tap.x2 || tuning_off("conv_two")) return false;
+  // Up to some 1800 output pixels the workgroups of both run at once.  ResNet-18's three pairs one at a time, 1 - 250 images of
+  // 128 and 224 pixels, us of the network: up to 1764 pixels -2.7 .. +0.1 (one image, all three -6 .. -8.4); at 2352 pixels
+  // -1.3 .. +3.3; at 3136 to 25 000 -2 .. +10: there the 1 x 1 convolution's many short workgroups, which it can place four
+  // or more to a compute unit, wait for places as large as the other's.
+  if (window.M > 1800) return false;
+  if (!wanted(window, N) || !wanted(tap, N) || !plan_for(window, N, a) || !plan_for(tap, N, b)) return false;
+  if (a->mode != kWindow || b->mode != kOneTap) return false;
+  if (std::find(std::begin(kTwoWindow), std::end(kTwoWindow), a->tile) == std::end(kTwoWindow)) return false;
+  // The 1 x 1 convolution with as many waves as the other has, its reduction cut as when it is alone: with workgroups of
+  // its own one or two waves, and the others of each ending at once, ResNet-34 of 20 images took 391 us in place of 347.
+  const int waves = a->p.WF * a->p.WK, WK = b->p.WK;
+  double least = 0.0;
+  bool any = false;
+  for (int tile : kTwoTap) {
+    WindowPlan plan;
+    const int WF = waves / WK;
+    if (WF < 1 || (WF > 1 && (WF / 2) * kTiles[tile].NT * 16 >= tap.Kp) || !plan_window(tap, N, tile, WF, WK, &plan)) continue;
+    const double cost = estimate(tap, plan);
+    if (any && cost >= least) continue;
+    *b = plan;
+    least = cost;
+    any = true;
+  }
+  return any;
+}
+
+bool conv_window_two_applies(const Conv16Params& window, const Conv16Params& tap, int N) {
+  WindowPlan a, b;
+  return plan_two(window, tap, N, &a, &b);
+}
+
+bool launch_conv_window_two(const Conv16Params& window, const Conv16Params& tap, int N, void* stream, fupr_status* status) {
+  WindowPlan a, b;
+  if (!plan_two(window, tap, N, &a, &b)) return false;
+  set_call(window, N, &a.p);
+  set_call(tap, N, &b.p);
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  *status = window.dt == FUPR_BF16 ? launch_two<FUPR_BF16>(a, b, st) : launch_two<FUPR_F16>(a, b, st);
+  return true;
 }
 
 bool launch_conv_window(const Conv16Params& c, int N, void* stream, fupr_status* status) {

@@ -102,8 +102,9 @@ __device__ __forceinline__ void touch_arguments() {
 // A kernel's arguments, all of them in scalar registers at once: whole 64-byte lines, one wait.  Left to the compiler,
 // each group is loaded where it is first used, a wait of 100 clocks and more every time, six to ten of them in
 // front of the first multiplication of a short kernel.  (The loads have landed before anything reads their registers.)
+// `which`: of several in a row.
 template <class Params>
-__device__ __forceinline__ Params load_arguments() {
+__device__ __forceinline__ Params load_arguments(int which = 0) {
   static_assert(sizeof(Params) == 320, "five lines");
   typedef int i32x16 __attribute__((ext_vector_type(16)));
   struct Lines {
@@ -113,7 +114,7 @@ __device__ __forceinline__ Params load_arguments() {
       "s_load_dwordx16 %0, %5, 0\n\ts_load_dwordx16 %1, %5, 64\n\ts_load_dwordx16 %2, %5, 128\n\t"
       "s_load_dwordx16 %3, %5, 192\n\ts_load_dwordx16 %4, %5, 256\n\ts_waitcnt lgkmcnt(0)"
       : "=&s"(lines.v[0]), "=&s"(lines.v[1]), "=&s"(lines.v[2]), "=&s"(lines.v[3]), "=&s"(lines.v[4])
-      : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr()));
+      : "s"((uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + (uint64_t)which * sizeof(Params)));
   return __builtin_bit_cast(Params, lines);
 }
 

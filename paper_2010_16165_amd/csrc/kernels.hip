@@ -551,6 +551,35 @@ fupr_status fupr::conv_fused_part(const fupr_conv_shape* shape, const fupr_tenso
   return launch_conv(a, stream);
 }
 
+bool fupr::convs_beside(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fupr_dtype dt, int N, int H, int W) {
+  if (dt == FUPR_F32) return false;
+  const Conv16Params a = geometry_of(s1, dt, N, H, W, -1, 0), b = geometry_of(s2, dt, N, H, W, -1, 0);
+  return s1.R * s1.S > 1 ? conv_window_two_applies(a, b, N) : conv_window_two_applies(b, a, N);
+}
+
+fupr_status fupr::convs_beside_part(const fupr_conv_shape* shape1, const void* packed1, uint32_t flags1,
+                                    const fupr_tensor* y1, const fupr_conv_shape* shape2, const void* packed2,
+                                    uint32_t flags2, const fupr_tensor* y2, const fupr_tensor* x, int plan_N,
+                                    void* stream) {
+  ConvArgs a, b;
+  fupr_status st = check_conv(shape1, x, packed1, nullptr, flags1, y1, &a);
+  if (st == FUPR_OK) st = check_conv(shape2, x, packed2, nullptr, flags2, y2, &b);
+  if (st != FUPR_OK) return st;
+  a.plan_N = b.plan_N = plan_N;
+  auto overlap = [](const fupr_tensor* s, const fupr_tensor* t) {
+    auto bytes = [](const fupr_tensor* v) { return (size_t)v->N * v->H * v->W * v->c_stride * elem_size(v->dt); };
+    const uintptr_t s0 = (uintptr_t)s->ptr, t0 = (uintptr_t)t->ptr;
+    return s0 < t0 + bytes(t) && t0 < s0 + bytes(s);
+  };
+  if (a.dt != FUPR_F32 && !overlap(y1, y2) && !overlap(x, y1) && !overlap(x, y2)) {
+    const Conv16Params p = params16(a), q = params16(b);
+    const bool first_wide = a.R * a.S > 1;
+    if (launch_conv_window_two(first_wide ? p : q, first_wide ? q : p, a.N, stream, &st)) return st;
+  }
+  st = launch_conv(a, stream);
+  return st == FUPR_OK ? launch_conv(b, stream) : st;
+}
+
 fupr_status fupr::conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x,
                                     const void* packed, const int32_t* keep_idx, uint32_t epilogue_flags,
                                     const fupr_tensor* y, int plan_N, void* stream) {

@@ -94,6 +94,12 @@ fupr_status conv_scatter_part(const fupr_conv_shape* shape, const fupr_tensor* x
 // The convolution is one that conv_window.hip takes at this batch size (arguments as for
 // conv_kernel_name).
 bool conv_is_small(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W, int res_at, int first_c);
+// Two convolutions of the same tensor, neither with a shortcut, that can run as one launch: one with a window, the
+// other 1 x 1, in either order.  convs_beside_part runs them, as two launches where a tensor overlaps another.
+bool convs_beside(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fupr_dtype dt, int N, int H, int W);
+fupr_status convs_beside_part(const fupr_conv_shape* shape1, const void* packed1, uint32_t flags1, const fupr_tensor* y1,
+                              const fupr_conv_shape* shape2, const void* packed2, uint32_t flags2, const fupr_tensor* y2,
+                              const fupr_tensor* x, int plan_N, void* stream);
 // fupr_conv_cat_fused followed by a 1 x 1 convolution of its output, in one launch
 // (what fupr_conv_conv1x1_fused is to fupr_conv_fused); for the model executor.
 fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x1,

@@ -26,11 +26,11 @@ using namespace fupr;
 namespace {
 
 // One kernel launch of the per-operator schedule: `count` consecutive operators.
-enum { kBottleneck = 1, kBasic = 2 };   // bottleneck.hip, basic_block.hip
+enum { kBottleneck = 1, kBasic = 2, kBeside = 3 };   // bottleneck.hip, basic_block.hip, conv_window.hip
 
 struct Launch {
   int first, count;
-  int block = 0;        // kBottleneck or kBasic: a block in one launch
+  int block = 0;        // kBottleneck or kBasic: a block in one launch; kBeside: two convolutions of one tensor
   int plan = -1;        // ... and its kernel's plan for the batch
 };
 
@@ -1287,6 +1287,20 @@ Scheduled scheduled_at(const fupr_model* m, int N) {
     v[i].count = 1;
     v.insert(v.begin() + ++i, Launch{l.first + 1, 1});
   }
+  // A projection shortcut and its block's first convolution as one launch (with fupr_model_fuse_blocks: launch counts
+  // are else as they were).  Neither's output may lie where the other reads or writes: what the first one writes has
+  // to be read later, or its place would be free again.
+  for (size_t i = 0; m->blocks && m->schedule == FUPR_SCHEDULE_AUTO && i + 1 < v.size(); ++i) {
+    if (v[i].count != 1 || v[i + 1].count != 1 || v[i].block || v[i + 1].block) continue;
+    const fupr_op_desc &a = m->ops[v[i].first], &b = m->ops[v[i + 1].first];
+    if (a.kind != FUPR_OP_CONV || b.kind != FUPR_OP_CONV || a.in != b.in || a.res >= 0 || b.res >= 0) continue;
+    if ((a.epilogue | b.epilogue) & ~uint32_t(FUPR_FUSE_RELU)) continue;
+    if (m->tensors[v[i].first + 1].last_use <= v[i + 1].first) continue;
+    const TensorInfo& x = m->tensors[a.in];
+    if (!convs_beside(a.conv, b.conv, m->dt, N, x.H, x.W)) continue;
+    v[i] = Launch{v[i].first, 2, kBeside};
+    v.erase(v.begin() + i + 1);
+  }
   return out;
 }
 
@@ -1460,7 +1474,11 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
       const fupr_tensor y = view((int)i + launches[l].count, n0, count);
       const int plan = part ? (*part)[i] : launches[l].plan;
       fupr_status st;
-      if (launches[l].block == kBasic) {
+      if (launches[l].block == kBeside) {
+        const fupr_op_desc& b = m->ops[i + 1];
+        const fupr_tensor first = view((int)i + 1, n0, count);
+        st = convs_beside_part(&op.conv, op.packed, op.epilogue, &first, &b.conv, b.packed, b.epilogue, &y, &x, N, on);
+      } else if (launches[l].block == kBasic) {
         st = basic_block(i, plan, x, y, n0, count, on);
       } else if (launches[l].block) {
         BottleneckArgs g = m->block_args[i].bottleneck;
@@ -1662,6 +1680,17 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
     fupr_status st = fupr_model_op_stats(m, batch, l.first, out);
     if (st != FUPR_OK || l.count == 1) return st;
     out->n_ops = l.count;
+    if (l.block == kBeside) {
+      // both outputs are written, the input is read once
+      fupr_op_stats second;
+      st = fupr_model_op_stats(m, batch, l.first + 1, &second);
+      if (st != FUPR_OK) return st;
+      const TensorInfo& x = m->tensors[m->ops[l.first].in];
+      out->flops += second.flops;
+      out->bytes += second.bytes - (double)elem_size(m->dt) * batch * (double)x.H * x.W * x.C;
+      out->kernel = "conv_w+conv1x1p_w";
+      return FUPR_OK;
+    }
     if (l.block) {
       // the operators of a block in one kernel: the 3 x 3 convolution's output is not written, the
       // block's output is not read back

@@ -382,3 +382,46 @@ def test_sub_batches_of_blocks_by_rows(fx):
             assert torch.equal(whole, out.data)
     finally:
         B.fupr_tuning_set("split", None)
+
+
+# images, rows, columns, channels in, filters of the 3 x 3 and of the 1 x 1 convolution
+BESIDE = [(1, 14, 14, 64, 90, 128), (2, 15, 9, 45, 20, 33), (3, 7, 7, 136, 200, 72), (1, 1, 1, 8, 16, 80), (5, 13, 37, 24, 40, 264)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("tile", ["", "0x2x2", "2x1x4", "4x2x4", "6x4x1", "7x2x2", "10x4x1", "0x1x8"])
+@pytest.mark.parametrize("case", BESIDE, ids=lambda c: "-".join(map(str, c)))
+def test_projection_beside_the_first_convolution(fx, case, tile, dtype):
+    """A block's stride-2 convolution and its projection in one launch: against both references, and
+    the bits of the two launches."""
+    B, torch = fx
+    n, h, w, c, k1, k2 = case
+    net = Net(fx, dtype, n, (16, h, w), seed=sum(case))
+    t_x = net.conv(net.conv(0, 24, 1), c, 1)
+    t_p = net.conv(t_x, k2, 1, stride=2, relu=False)
+    t_1 = net.conv(t_x, k1, 3, stride=2)
+    net.conv(net.conv(t_1, k2, 3, add=t_p), 24, 1)
+    B.fupr_tuning_set("basic_fuse", 0)
+    try:
+        m = B.Model(net.dt, net.in_shape, net.ops, net.blobs)
+        assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)
+        m.fuse_blocks(True)
+        B.fupr_tuning_set("window_tile", tile or None)
+        x = B.DeviceTensor.from_nchw(net.x, net.dt)
+        outs = []
+        for two in (None, 0):
+            B.fupr_tuning_set("conv_two", two)
+            kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
+            assert ("conv_w+conv1x1p_w" in kernels) == (two is None) or tile == "7x2x2", kernels
+            out, ws = m.alloc(n)
+            ws.fill_(255)
+            m.fupr_forward(x, out, ws)
+            torch.cuda.synchronize()
+            outs.append(out.data.clone())
+        assert torch.equal(*outs)
+        B.fupr_tuning_set("conv_two", None)
+        net.check("window_tile", tile or None, "conv_w+conv1x1p_w", takes="conv_w+conv1x1p_w" in [
+            m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))])
+    finally:
+        for switch in ("basic_fuse", "window_tile", "conv_two"):
+            B.fupr_tuning_set(switch, None)
