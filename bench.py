@@ -86,7 +86,10 @@ def group_of_device_kernel(name):
         return f"bottleneck_{num(1) * 16}x{num(2) * 32}"
     if fn == "basic_block_kernel":
         return "basic_block"        # (its rectangle is an argument)
+    if fn == "conv_window_two_kernel":
+        return "conv_w+conv1x1p_w"
     return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
+            "resident_rows_kernel": "resident_network", "mean_fc_kernel": "mean_fc",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)
 

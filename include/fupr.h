@@ -447,7 +447,9 @@ fupr_status fupr_model_set_schedule(fupr_model* m, int32_t schedule);
  * sizes where that is faster: of a bottleneck block the 3 x 3 convolution, the
  * 1 x 1 convolution of its output (with the shortcut, or over two tensors) and,
  * where it follows, the 1 x 1 convolution of that output (16-bit types, tensors of
- * the workspace only); of a basic block both 3 x 3 convolutions.  0 (the default):
+ * the workspace only); of a basic block both 3 x 3 convolutions.  In 16-bit types at
+ * few images also: a block's projection shortcut beside its first convolution, and
+ * the global mean with the layer behind it.  0 (the default):
  * never.  The workspace is as large either way; what its buffers hold in between
  * differs, so the setting belongs before the first forward pass or capture and
  * between passes, not beside one.  fupr_model_num_launches does not count blocks as
@@ -574,8 +576,8 @@ int32_t fupr_model_num_ops(const fupr_model* m);
  * schedule (1 for the one-kernel schedule, else one per launch group; sub-batches
  * not counted) and the algorithmic work of launch i of that batch.  A pair of
  * 1 x 1 convolutions is two launches at batches whose tensors are small, so the
- * number depends on the batch, and so does whether a block is one (fupr_model_fuse_blocks);
- * fupr_model_num_launches counts every pair as one launch and every block as its operators.  For the one-kernel schedule: all the
+ * number depends on the batch, and so does what fupr_model_fuse_blocks puts in one launch;
+ * fupr_model_num_launches counts every pair as one launch and all that as its operators.  For the one-kernel schedule: all the
  * network's flops; bytes = the images read once + the result written once + every
  * parameter read once.  0 if m is NULL or batch <= 0.
  */
@@ -619,6 +621,7 @@ void fupr_graph_destroy(fupr_graph* g);
  *   pair_filters = 16..128                        most filters of the second convolution of a pair of
  *                                                 1 x 1 convolutions in one launch
  *   conv_two = 0                                  two convolutions of one tensor as two launches
+ *   mean_fc = 0                                   a global mean and the layer behind it as two launches
  *   bottleneck_fuse, basic_fuse = 0               blocks of fupr_model_fuse_blocks as several launches
  *   bottleneck_tile = <index>                     force a tile of the kernel that runs bottleneck blocks
  *   basic_tile = <rectangle>x<f>                  force a rectangle of the kernel that runs basic blocks,

@@ -100,6 +100,11 @@ bool convs_beside(const fupr_conv_shape& s1, const fupr_conv_shape& s2, fupr_dty
 fupr_status convs_beside_part(const fupr_conv_shape* shape1, const void* packed1, uint32_t flags1, const fupr_tensor* y1,
                               const fupr_conv_shape* shape2, const void* packed2, uint32_t flags2, const fupr_tensor* y2,
                               const fupr_tensor* x, int plan_N, void* stream);
+// A global mean and the 1 x 1 convolution of its 1 x 1 image (fc) as one launch, for few images.  mid: the mean, which
+// only a run as two launches writes (where a tensor overlaps another).
+bool mean_fc_applies(const fupr_conv_shape& s, fupr_dtype dt, int N, int H, int W);
+fupr_status mean_fc_part(const fupr_tensor* x, const fupr_tensor* mid, const fupr_conv_shape* shape, const void* packed,
+                         uint32_t flags, const fupr_tensor* y, int plan_N, void* stream);
 // fupr_conv_cat_fused followed by a 1 x 1 convolution of its output, in one launch
 // (what fupr_conv_conv1x1_fused is to fupr_conv_fused); for the model executor.
 fupr_status conv_cat_conv1x1_fused(const fupr_conv_shape* shape1, const fupr_tensor* x1,

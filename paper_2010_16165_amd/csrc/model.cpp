@@ -26,11 +26,12 @@ using namespace fupr;
 namespace {
 
 // One kernel launch of the per-operator schedule: `count` consecutive operators.
-enum { kBottleneck = 1, kBasic = 2, kBeside = 3 };   // bottleneck.hip, basic_block.hip, conv_window.hip
+enum { kBottleneck = 1, kBasic = 2, kBeside = 3, kMeanFc = 4 };   // bottleneck.hip, basic_block.hip, conv_window.hip
 
 struct Launch {
   int first, count;
-  int block = 0;        // kBottleneck or kBasic: a block in one launch; kBeside: two convolutions of one tensor
+  int block = 0;        // kBottleneck or kBasic: a block in one launch; kBeside: two convolutions of one tensor;
+                        // kMeanFc: a global mean and the layer behind it
   int plan = -1;        // ... and its kernel's plan for the batch
 };
 
@@ -1293,6 +1294,13 @@ Scheduled scheduled_at(const fupr_model* m, int N) {
   for (size_t i = 0; m->blocks && m->schedule == FUPR_SCHEDULE_AUTO && i + 1 < v.size(); ++i) {
     if (v[i].count != 1 || v[i + 1].count != 1 || v[i].block || v[i + 1].block) continue;
     const fupr_op_desc &a = m->ops[v[i].first], &b = m->ops[v[i + 1].first];
+    if (a.kind == FUPR_OP_AVGPOOL && b.kind == FUPR_OP_CONV && b.in == v[i].first + 1 && b.res < 0 &&
+        !(b.epilogue & ~uint32_t(FUPR_FUSE_RELU)) && m->tensors[b.in].last_use == v[i + 1].first &&
+        mean_fc_applies(b.conv, m->dt, N, m->tensors[a.in].H, m->tensors[a.in].W)) {
+      v[i] = Launch{v[i].first, 2, kMeanFc};
+      v.erase(v.begin() + i + 1);
+      continue;
+    }
     if (a.kind != FUPR_OP_CONV || b.kind != FUPR_OP_CONV || a.in != b.in || a.res >= 0 || b.res >= 0) continue;
     if ((a.epilogue | b.epilogue) & ~uint32_t(FUPR_FUSE_RELU)) continue;
     if (m->tensors[v[i].first + 1].last_use <= v[i + 1].first) continue;
@@ -1474,7 +1482,11 @@ fupr_status run(const fupr_model* m, const fupr_tensor* input, const fupr_tensor
       const fupr_tensor y = view((int)i + launches[l].count, n0, count);
       const int plan = part ? (*part)[i] : launches[l].plan;
       fupr_status st;
-      if (launches[l].block == kBeside) {
+      if (launches[l].block == kMeanFc) {
+        const fupr_op_desc& b = m->ops[i + 1];
+        const fupr_tensor mean = view((int)i + 1, n0, count);
+        st = mean_fc_part(&x, &mean, &b.conv, b.packed, b.epilogue, &y, N, on);
+      } else if (launches[l].block == kBeside) {
         const fupr_op_desc& b = m->ops[i + 1];
         const fupr_tensor first = view((int)i + 1, n0, count);
         st = convs_beside_part(&op.conv, op.packed, op.epilogue, &first, &b.conv, b.packed, b.epilogue, &y, &x, N, on);
@@ -1680,6 +1692,16 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
     fupr_status st = fupr_model_op_stats(m, batch, l.first, out);
     if (st != FUPR_OK || l.count == 1) return st;
     out->n_ops = l.count;
+    if (l.block == kMeanFc) {
+      // the mean is neither written nor read
+      fupr_op_stats second;
+      st = fupr_model_op_stats(m, batch, l.first + 1, &second);
+      if (st != FUPR_OK) return st;
+      out->flops += second.flops;
+      out->bytes += second.bytes - 2.0 * (double)elem_size(m->dt) * batch * (double)m->tensors[l.first + 1].C;
+      out->kernel = "mean_fc";
+      return FUPR_OK;
+    }
     if (l.block == kBeside) {
       // both outputs are written, the input is read once
       fupr_op_stats second;

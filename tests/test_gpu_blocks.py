@@ -425,3 +425,23 @@ def test_projection_beside_the_first_convolution(fx, case, tile, dtype):
     finally:
         for switch in ("basic_fuse", "window_tile", "conv_two"):
             B.fupr_tuning_set(switch, None)
+
+
+# images, rows, columns, channels, filters: a whole pass of the lanes, one chunk, ragged channels, the largest image
+MEAN_FC = [(1, 7, 7, 512, 1000), (32, 1, 1, 8, 10), (3, 3, 5, 45, 65), (2, 16, 8, 256, 129), (5, 8, 9, 333, 16)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", MEAN_FC, ids=lambda c: "-".join(map(str, c)))
+def test_mean_and_the_layer_behind_it(fx, case, dtype):
+    """The global mean and fc in one launch, and in two with the switch off: against both references
+    (Net.check's bound, derived for nine stored tensors; there are five here)."""
+    B, torch = fx
+    n, h, w, c, k = case
+    net = Net(fx, dtype, n, (8, h, w), seed=sum(case))
+    t = net.conv(net.conv(0, 24, 3), c, 1)
+    net.ops.append(B.OpDesc(B.OP_AVGPOOL, t, -1, B.conv_shape(1, 1, 1, 1, 1, 0), None, 0, 1, 0, None, -1, 0))
+    net.tensors.append(net.stored(net.tensors[t].mean((2, 3), keepdim=True)))
+    net.conv(t + 1, k, 1, relu=bool(n & 1))
+    net.check("mean_fc", None, "mean_fc")
+    net.check("mean_fc", 0, "mean_fc", takes=False)
