@@ -160,8 +160,8 @@ __device__ __forceinline__ void window_tile(const int which) {
   if (wave >= waves) return;                 // (conv_window_two_kernel)
   const int wk = wave >> p.log2_WF, wf = wave & (p.WF - 1);
 
-  const int l = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
-  if (l >= p.total) return;
+  const int l = tile_of_workgroup(blockIdx.x, p.per_xcd, p.total);
+  if (l < 0) return;
   const int slow = div_by(l, p.divG);
   const int fast = l - slow * (p.filter_major ? p.mgroups : p.fgroups);
   const int mg = p.filter_major ? fast : slow, fg = p.filter_major ? slow : fast;
@@ -761,7 +761,7 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
   const int64_t total = (int64_t)p.mgroups * p.fgroups;
   if (total >= (int64_t(1) << 28)) return false;
   p.total = (int)total;
-  p.per_xcd = (p.total + 7) / 8;
+  p.per_xcd = tiles_per_xcd(p.total);
   p.filter_major = (uint64_t)c.w_bytes > x_bytes + x2_bytes;
   // LDS slots per pixel: 16 lanes read 16 bytes each of neighbouring output pixels, which is
   // free of bank conflicts at odd multiples of 32 bytes
@@ -817,9 +817,10 @@ bool plan_window(const Conv16Params& c, int N, int tile, int WF, int WK, WindowP
 }
 
 // Two convolutions of one tensor that do not need each other (a block's first 3 x 3 and its projection shortcut) as
-// one launch: blockIdx.y says which, each with the tile, the waves and the bits it has alone.  Saves a launch,
-// whose start and end cost 3600 clocks with nothing in between, and the smaller one runs where the other leaves
-// compute units free.  Workgroups have the waves of the larger one; what the other does not need of them ends at once.
+// one launch: blockIdx.y says which.  The window has the plan it has alone, the 1 x 1 convolution the cut of its reduction,
+// hence both their bits.  Saves a launch, whose start and end cost 3600 clocks with nothing in between, and the smaller one
+// runs where the other leaves compute units free.  The grid and the waves of a workgroup are the larger one's: waves that the
+// other does not need end at once, and so do workgroups beyond its tiles (tile_of_workgroup).
 struct TwoWindowParams {
   WindowParams p[2];
 };
@@ -844,7 +845,7 @@ fupr_status launch_two_as(const WindowPlan& a, const WindowPlan& b, hipStream_t 
   }
   TwoWindowParams two{{a.p, b.p}};
   void* list[] = {&two};
-  const unsigned blocks = (unsigned)std::max(a.p.per_xcd, b.p.per_xcd) * 8;
+  const unsigned blocks = (unsigned)std::max(a.p.per_xcd, b.p.per_xcd) * kXcds;
   const unsigned threads = (unsigned)std::max(a.p.WF * a.p.WK, b.p.WF * b.p.WK) * 64;
   return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(blocks, 2), dim3(threads), list, lds, st),
                   "conv_window_two_kernel");
@@ -886,7 +887,7 @@ fupr_status launch_as(const WindowPlan& plan, hipStream_t st) {
     if (attr != hipSuccess) return FUPR_ERR_LAUNCH;
   }
   void* list[] = {const_cast<WindowParams*>(&plan.p)};
-  return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)(plan.p.per_xcd * 8)),
+  return launched(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)(plan.p.per_xcd * kXcds)),
                                   dim3(plan.p.WF * plan.p.WK * 64), list, plan.lds, st),
                   "conv_window_kernel");
   }
@@ -1106,16 +1107,17 @@ static fupr_status dispatch_window(const WindowPlan& plan, fupr_dtype dt, bool l
 // Both convolutions' plans, if they can run as one launch.
 static bool plan_two(const Conv16Params& window, const Conv16Params& tap, int N, WindowPlan* a, WindowPlan* b) {
   if (window.dt == FUPR_F32 || window.keep || tap.keep || window.x2 || tap.x2 || tuning_off("conv_two")) return false;
-  // Up to some 1800 output pixels the workgroups of both run at once.  ResNet-18's three pairs one at a time, 1 - 250 images of
-  // 128 and 224 pixels, us of the network: up to 1764 pixels -2.7 .. +0.1 (one image, all three -6 .. -8.4); at 2352 pixels
-  // -1.3 .. +3.3; at 3136 to 25 000 -2 .. +10: there the 1 x 1 convolution's many short workgroups, which it can place four
-  // or more to a compute unit, wait for places as large as the other's.
+  // Up to some 1800 output pixels two launches in one are the faster ones, although a workgroup of the 1 x 1 convolution
+  // (3 - 18 KB of LDS) then takes the room of one of the other's (30 - 152 KB).  Pairs of ResNet-18 and -34 one at a time, 1 - 250
+  // images of 128 and 224 pixels, 0 - 50 % pruned, us of the network: up to 1764 pixels -3.3 .. -0.2, but for 64 channels of 128
+  // filters pruned by half at 1024 and 1536 pixels (+0.6, +1.2); at 2048 to 5120 -3.6 .. +5.1; above -7 .. +7.2 of 200 - 1160.
   if (window.M > 1800) return false;
   if (!wanted(window, N) || !wanted(tap, N) || !plan_for(window, N, a) || !plan_for(tap, N, b)) return false;
   if (a->mode != kWindow || b->mode != kOneTap) return false;
   if (std::find(std::begin(kTwoWindow), std::end(kTwoWindow), a->tile) == std::end(kTwoWindow)) return false;
-  // The 1 x 1 convolution with as many waves as the other has, its reduction cut as when it is alone: with workgroups of
-  // its own one or two waves, and the others of each ending at once, ResNet-34 of 20 images took 391 us in place of 347.
+  // The 1 x 1 convolution with as many waves as the other has, its reduction cut as when it is alone: with the plan it has alone,
+  // often one or two waves of a workgroup of eight, ResNet-34 of 20 images took 346.0 us in place of 344.5, ResNet-18 of 12 138.2
+  // in place of 137.1, of one image 76.4 in place of 76.7.
   const int waves = a->p.WF * a->p.WK, WK = b->p.WK;
   double least = 0.0;
   bool any = false;

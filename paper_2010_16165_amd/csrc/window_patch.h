@@ -1,5 +1,6 @@
 // Internal: the run of input pixels that a tile of output pixels needs (conv_window.hip).  The
-// planner reserves LDS by it and the kernel fills LDS by it, from the same functions.
+// planner reserves LDS by it and the kernel fills LDS by it, from the same functions.  And which
+// tile a workgroup takes.
 #pragma once
 #include <cstdint>
 
@@ -29,6 +30,16 @@ constexpr int64_t most_run_pixels(int BM, int R, int S, int stride, int H, int W
   const int64_t row_end = (int64_t)stride * W - (int64_t)stride * (Q - 1);
   const int64_t image_end = (H - (int64_t)stride * (P - 1)) * W;
   return 1 + (int64_t)(BM - 1) * stride + rows * row_end + images * image_end + window_reach(R, S, W) + 1;
+}
+
+// Workgroups are given to the eight XCDs in turn, and an XCD takes per_xcd tiles that follow each other: the tile
+// of a workgroup, or -1 where it has none.  A grid may be larger than total tiles need (the other convolution's of a
+// launch of two): a workgroup beyond its XCD's share must not go on into the next XCD's.
+constexpr int kXcds = 8;
+constexpr int tiles_per_xcd(int total) { return (total + kXcds - 1) / kXcds; }
+constexpr int tile_of_workgroup(uint32_t block, int per_xcd, int total) {
+  const int in_xcd = (int)(block / kXcds), tile = (int)(block % kXcds) * per_xcd + in_xcd;
+  return in_xcd < per_xcd && tile < total ? tile : -1;
 }
 
 }  // namespace fupr

@@ -558,6 +558,16 @@ def test_window_runs_hold_every_tap_and_fit_their_plan(tmp_path):
     assert int(out.stdout) > 100000
 
 
+def test_every_tile_of_two_convolutions_in_one_launch_is_taken_once(tmp_path):
+    """The function by which a workgroup finds its tile, walked over grids that are larger than one of the two needs."""
+    exe = str(tmp_path / "window_tiles")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2010_16165_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "window_tiles.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    assert int(out.stdout) > 20000
+
+
 def test_launch_list_of_a_batch_names_what_runs():
     """A pair of 1 x 1 convolutions runs as two launches at batches whose tensors are small: the list of
     that batch counts both, under the kernels and bytes of the two operators."""
