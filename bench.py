@@ -88,7 +88,7 @@ def group_of_device_kernel(name):
         return "basic_block"        # (its rectangle is an argument)
     if fn == "conv_window_two_kernel":
         return "conv_w+conv1x1p_w"
-    return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network",
+    return {"stem_pool_kernel": "stem7x7_maxpool", "resident_kernel": "resident_network_taps",
             "resident_rows_kernel": "resident_network", "mean_fc_kernel": "mean_fc",
             "maxpool_kernel": "maxpool", "avgpool_kernel": "global_avgpool",
             "conv32_kernel": "conv32_direct"}.get(fn)

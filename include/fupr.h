@@ -627,6 +627,8 @@ void fupr_graph_destroy(fupr_graph* g);
  *   basic_tile = <rectangle>x<f>                  force a rectangle of the kernel that runs basic blocks,
  *                                                 f waves along the filters (a power of two, up to 8)
  *   split = 1..4                                  sub-batches of the per-operator schedule
+ *   resident_rows = 0                             models made meanwhile: the one-kernel schedule without its
+ *                                                 kernel for networks of 3 x 3 convolutions
  *   res_item = "M/FT/nsteps:MTxNT,..."            work-item shapes of the one-kernel schedule
  *   debug = 1                                     planner decisions and HIP error text on stderr
  * Errors: NULL, ARG (unknown name, value of 128 characters or more).

@@ -371,7 +371,7 @@ void plan_resident(fupr_model* m) {
   std::stable_sort(candidates.begin(), candidates.end(),
                    [](const auto& a, const auto& b) { return a.first < b.first; });
   // first of all as row layers, which have the smallest strides
-  candidates.insert(candidates.begin(), {-1.0, std::vector<int>(k, kRowStride)});
+  if (!tuning_off("resident_rows")) candidates.insert(candidates.begin(), {-1.0, std::vector<int>(k, kRowStride)});
 
   // Parameter blocks by size, largest first: when nothing fits with every
   // layer's parameters staged one layer ahead, the largest ones are staged at
@@ -1775,7 +1775,7 @@ extern "C" fupr_status fupr_model_launch_stats(const fupr_model* m, int32_t batc
     if (d.kind == FUPR_OP_CONV)
       s.bytes += es * (double)d.conv.C * d.conv.R * d.conv.S * d.conv.K + 4.0 * d.conv.K;
   }
-  s.kernel = "resident_network";
+  s.kernel = m->res_rows.empty() ? "resident_network_taps" : "resident_network";
   *out = s;
   return FUPR_OK;
 }

@@ -43,6 +43,7 @@ Switch g_switches[] = {
     {"basic_fuse", false, {0}},      // 0: basic blocks run as two launches
     {"basic_tile", false, {0}},      // <rectangle>x<waves along the filters> of the kernel that runs them
     {"split", false, {0}},           // sub-batches of the per-operator schedule
+    {"resident_rows", false, {0}},   // 0: the one-kernel schedule without its kernel of row layers
     {"res_item", false, {0}},        // work-item shapes of the one-kernel schedule
     {"debug", false, {0}},           // non-empty: planner and HIP error text on stderr
 };

@@ -445,3 +445,69 @@ def test_mean_and_the_layer_behind_it(fx, case, dtype):
     net.conv(t + 1, k, 1, relu=bool(n & 1))
     net.check("mean_fc", None, "mean_fc")
     net.check("mean_fc", 0, "mean_fc", takes=False)
+
+
+# channels in, rows, columns, images, filters of the 3 x 3 convolutions: (filters, stride, tensor that is added or -1, its
+# stride).  Every size of work item of the row kernel, images that are not square, tiles of half rows
+ROW_NETS = [
+    (16, 6, 16, 2, [(24, 1, -1, 1), (24, 1, 1, 1)]),
+    (8, 4, 48, 1, [(16, 1, -1, 1), (16, 1, 1, 1)]),
+    (8, 2, 64, 3, [(16, 1, -1, 1)]),
+    (16, 12, 8, 2, [(32, 1, -1, 1), (24, 1, -1, 1)]),
+    (16, 8, 8, 2, [(32, 1, -1, 1), (64, 1, -1, 1), (50, 1, -1, 1), (64, 1, 2, 1)]),
+    (16, 8, 16, 1, [(64, 1, -1, 1)]),
+    (8, 12, 32, 2, [(16, 1, -1, 1), (32, 2, -1, 1), (32, 1, 1, 2), (20, 1, -1, 1)]),
+    (20, 4, 96, 2, [(13, 1, -1, 1), (30, 2, -1, 1), (27, 1, -1, 1), (30, 1, 2, 1), (12, 1, -1, 1)]),
+    (32, 16, 16, 1, [(48, 2, -1, 1), (41, 1, -1, 1), (48, 1, 1, 1)]),
+]
+
+
+def row_model(fx, net):
+    """The model of a Net twice: as its kernel of row layers runs it, and tap by tap."""
+    B, _ = fx
+    models = []
+    for rows in (None, 0):
+        B.fupr_tuning_set("resident_rows", rows)
+        try:
+            models.append(B.Model(net.dt, net.in_shape, net.ops, net.blobs))
+        finally:
+            B.fupr_tuning_set("resident_rows", None)
+    assert [m.launch_stats(net.n, 0)["kernel"] for m in models] == ["resident_network", "resident_network_taps"]
+    return models
+
+
+def with_mean(B, net, classes):
+    """Net with a global mean and a layer behind it."""
+    t = len(net.ops)
+    net.ops.append(B.OpDesc(B.OP_AVGPOOL, t, -1, B.conv_shape(1, 1, 1, 1, 1, 0), None, 0, 1, 0, None, -1, 0))
+    net.tensors.append(net.stored(net.tensors[t].mean((2, 3), keepdim=True)))
+    net.conv(t + 1, classes, 1, relu=False)
+    return net
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", ROW_NETS, ids=lambda c: "-".join(map(str, c[:4])))
+def test_row_layers(fx, case, dtype):
+    """Networks of row layers against their float64 evaluation and against the kernel that goes tap by tap (the bounds of
+    Net.check: no more than nine stored tensors), the same bits every time."""
+    B, torch = fx
+    c, h, w, n, layers = case
+    net = Net(fx, dtype, n, (c, h, w), seed=h * w + c)
+    for i, (k, stride, add, add_stride) in enumerate(layers):
+        net.conv(i, k, 3, stride=stride, add=add, add_stride=add_stride)
+    with_mean(B, net, 10)
+    xd = B.DeviceTensor.from_nchw(net.x, net.dt)
+    outs = []
+    for m in row_model(fx, net):
+        for _ in range(2):
+            out, ws = m.alloc(n)
+            out.data.fill_(7.0)
+            m.fupr_forward(xd, out, ws)
+            torch.cuda.synchronize()
+            assert out.padding_is_zero()
+            outs.append(torch.from_numpy(np.ascontiguousarray(out.to_nchw())).double())
+    assert torch.equal(outs[0], outs[1])
+    unit = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    for ref in (net.tensors[-1], outs[2]):
+        assert float((outs[0] - ref).norm() / ref.norm()) <= 1.5 * unit
+        assert float((outs[0] - ref).abs().max()) <= 4 * unit * float(ref.abs().max())

@@ -1230,32 +1230,40 @@ def test_one_kernel_schedule_equals_per_layer_schedule(fx, mi):
 @pytest.mark.parametrize("widths,permille,dtype", [
     # 8-channel chunks per tap of the first / second convolutions, by stage (8 wide: tiles of two half rows)
     ((8, 24, 40), 0, "bf16"),       # 1/1, 3/3, 5/5
-    ((16, 32, 64), 0, "f16"),       # 2/2, 4/4, 8/8: the largest filters that stay in LDS twice
+    ((16, 32, 64), 0, "f16"),       # 2/2, 4/4, 8/8: the largest filters, three of them staged by entries of their own
     ((16, 32, 64), 300, "bf16"),    # 2/2, 4/3, 8/6
     ((12, 28, 52), 450, "f16"),     # 2/1, 4/2, 7/4: channels and filters that fill no chunk and no tile
     ((16, 20, 56), 100, "bf16"),    # 2/2, 3/3, 7/7
 ])
 def test_one_kernel_schedule_of_row_layers(fx, widths, permille, dtype):
     """Networks whose 3 x 3 convolutions all run as row layers (strides 1 and 2, with and without a
-    shortcut, shortcuts that subsample): against the oracle, and against the per-layer schedule
-    within half the tolerance (bounds as above)."""
+    shortcut, shortcuts that subsample): against the oracle, and against the one-kernel schedule
+    that goes tap by tap and the per-layer schedule within half the tolerance (bounds as above)."""
     B, network, torch = fx
     model = synth.make_cifar_resnet(51, dtype, 2, permille, widths=widths, size=32)
     n = 3
     x = synth.make_input(52, n, model["in_shape"])
     m, _ = network.build(network.optimise(model))
-    assert m.num_launches == 1
+    B.fupr_tuning_set("resident_rows", 0)
+    try:
+        taps, _ = network.build(network.optimise(model))
+    finally:
+        B.fupr_tuning_set("resident_rows", None)
+    assert m.num_launches == taps.num_launches == 1
+    assert m.launch_stats(n, 0)["kernel"] == "resident_network"
+    assert taps.launch_stats(n, 0)["kernel"] == "resident_network_taps"
     xd = B.DeviceTensor.from_nchw(x, B.DTYPES[dtype])
     outs = []
-    for schedule in (B.SCHEDULE_AUTO, B.SCHEDULE_PER_LAYER):
-        m.set_schedule(schedule)
-        out, ws = m.alloc(n)
+    for model_, schedule in ((m, B.SCHEDULE_AUTO), (taps, B.SCHEDULE_AUTO), (m, B.SCHEDULE_PER_LAYER)):
+        model_.set_schedule(schedule)
+        out, ws = model_.alloc(n)
         out.data.fill_(9.0)
-        m.fupr_forward(xd, out, ws)
+        model_.fupr_forward(xd, out, ws)
         torch.cuda.synchronize()
         assert out.padding_is_zero()
         outs.append(out.to_nchw()[:, :, 0, 0])
     assert rel_err(outs[0], outs[1]) <= TOL[dtype] / 2
+    assert rel_err(outs[0], outs[2]) <= TOL[dtype] / 2
     parity(outs[0], orc.forward(model, round_to(x, dtype, torch), masks=orc.select_masks(model)), dtype)
 
 

@@ -558,6 +558,54 @@ def test_window_runs_hold_every_tap_and_fit_their_plan(tmp_path):
     assert int(out.stdout) > 100000
 
 
+def one_kernel_of(in_shape, specs):
+    """The kernel of a whole network's one launch, "" where it has none (the table is never read here)."""
+    m = B.Model(B.BF16, in_shape, fake_ops(specs), None)
+    if B._lib.fupr_model_set_table(m._h, B.C.c_void_p(1 << 20)) != B.FUPR_OK or m.num_launches != 1:
+        return ""
+    return m.launch_stats(2, 0)["kernel"]
+
+
+def network_of(c, layers, classes=10):
+    """3 x 3 convolutions (filters, stride, tensor that is added or -1, its stride), their mean and a layer behind it."""
+    specs, width = [], c
+    for i, (k, stride, add, add_stride) in enumerate(layers):
+        specs.append((B.OP_CONV, i, add, k, width, 3, stride, 1, B.FUSE_RELU | (B.FUSE_ADD if add >= 0 else 0), add_stride))
+        width = k
+    specs.append((B.OP_AVGPOOL, len(layers), -1, 1, 1, 1, 1, 0, 0, 1))
+    return specs + [(B.OP_CONV, len(layers) + 1, -1, classes, width, 1, 1, 0, 0, 1)]
+
+
+ROWS, TAPS = "resident_network", "resident_network_taps"
+
+
+@pytest.mark.parametrize("in_shape,layers,kernel", [
+    ((3, 32, 32), [(16, 1, -1, 1), (16, 1, 1, 1)], ROWS),
+    ((16, 6, 16), [(24, 1, -1, 1), (24, 1, 1, 1)], ROWS),      # not square
+    ((8, 4, 48), [(16, 1, -1, 1), (16, 1, 1, 1)], ROWS),       # three tiles a row
+    ((8, 2, 64), [(16, 1, -1, 1)], ROWS),                      # rows in pairs
+    ((16, 8, 8), [(32, 1, -1, 1), (64, 1, -1, 1)], ROWS),      # tiles of two half rows
+    ((16, 12, 8), [(32, 1, -1, 1), (24, 1, -1, 1)], ROWS),
+    ((8, 12, 32), [(16, 1, -1, 1), (32, 2, -1, 1), (32, 1, 1, 2)], ROWS),
+    ((16, 8, 16), [(64, 1, -1, 1)], ROWS),                     # eight work items of four filter tiles
+    ((16, 16, 48), [(32, 1, -1, 1)], TAPS),                    # more work items than waves
+    ((3, 24, 24), [(16, 1, -1, 1), (16, 1, 1, 1)], TAPS),      # rows of no whole tiles
+    ((16, 7, 8), [(16, 1, -1, 1)], TAPS),                      # half rows of an odd number of rows
+    ((16, 3, 16), [(16, 1, -1, 1)], TAPS),                     # an odd number of rows
+    ((16, 16, 16), [(80, 1, -1, 1)], TAPS),                    # more than 64 filters
+    ((40, 16, 32), [(16, 2, -1, 1)], TAPS),                    # a stride of 2 over more than 32 channels
+])
+def test_networks_of_row_layers(in_shape, layers, kernel):
+    """Which networks the kernel of row layers takes, by their sizes, and that a switch leaves it out."""
+    specs = network_of(in_shape[0], layers)
+    assert one_kernel_of(in_shape, specs) == kernel
+    B.fupr_tuning_set("resident_rows", 0)
+    try:
+        assert one_kernel_of(in_shape, specs) == TAPS
+    finally:
+        B.fupr_tuning_set("resident_rows", None)
+
+
 def test_every_tile_of_two_convolutions_in_one_launch_is_taken_once(tmp_path):
     """The function by which a workgroup finds its tile, walked over grids that are larger than one of the two needs."""
     exe = str(tmp_path / "window_tiles")
