@@ -367,7 +367,9 @@ __device__ __forceinline__ RowWork load_work(ConstWords entry, int wave) {
 // multiplied for all tiles that have a tap there, and at stride 1 an item reads M + 2 rows where tile by tile it
 // would read 3 M.  The 3 * CPT chunks of a row of taps are FULL steps of four chunks and REM chunks over;
 // those of two or three rows of taps share a step where they fit one (REM 2 and 1).  Lanes with nothing left
-// multiply finite pixels with the zero chunks that pad the weights (there is one: 9 * CPT is no multiple of 4 then).
+// multiply zeros with the zero chunks that pad the weights (there is one: 9 * CPT is no multiple of 4 then): the left
+// halo, or where the lane's pixels are another tile's (REM 2) zeros in their place.  (Any pixel would do but for
+// an infinite one, 0 x Inf; ResNet-56, 128 images, 81.3 us with pixels of the window or the row below it, 81.5 so.)
 // The filters of an item stay in registers.
 //
 // A layer is some 50 MFMAs per wave, so instructions in front of them count: what depends on the wave comes
@@ -407,13 +409,13 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
   }
   int last_at = 0;   // REM 2: the last row's step, whose second half is not needed
   if constexpr (CPT == 1) {
-    const int s = g < 3 ? g : 2;
-    at[0] = lp + __mul24(s, ps) + (s == 0 ? flip[0] : s == 1 ? flip[1] : flip[2]);
+    at[0] = g == 3 ? L.in_org : lp + __mul24(g, ps) + (g == 0 ? flip[0] : g == 1 ? flip[1] : flip[2]);
   } else if constexpr (REM > 0) {
     // (the chunks over are the last ones of the third tap)
-    const int chunk = (C0 - 2 * CPT + (REM == 3 ? (g < 3 ? g : 2) : REM == 2 ? (g & 1) : 0)) * 16;
+    const int chunk = (C0 - 2 * CPT + (REM == 3 ? g : REM == 2 ? (g & 1) : 0)) * 16;
     last_at = lp + 2 * ps + (chunk ^ flip[2]);
     at[FULL] = last_at + (REM == 2 ? (g >= 2 ? row : 0) : REM == 1 ? (g >= 2 ? 2 * row : g == 1 ? row : 0) : 0);
+    if (REM != 2 && g == 3) at[FULL] = L.in_org;
   }
   uint4 b[AHEAD + 1][NB];
   auto read_row = [&](int i, uint4* bv) {
@@ -513,7 +515,10 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
         if (tile(r) >= 0) acc[tile(r)] = mfma_16x16x32<BF>(ax[r], bv[FULL], acc[tile(r)]);
     } else if constexpr (REM == 2) {
       if (tile(0) >= 0) acc[tile(0)] = mfma_16x16x32<BF>(ax[0], bv[FULL], acc[tile(0)]);
-      if (tile(2) >= 0) acc[tile(2)] = mfma_16x16x32<BF>(ax[1], bv[FULL], acc[tile(2)]);
+      if (tile(2) >= 0) {
+        const uint4 &v = bv[FULL], own = {g < 2 ? v.x : 0u, g < 2 ? v.y : 0u, g < 2 ? v.z : 0u, g < 2 ? v.w : 0u};
+        acc[tile(2)] = mfma_16x16x32<BF>(ax[1], own, acc[tile(2)]);
+      }
     } else if constexpr (REM == 1) {
       if (tile(0) >= 0) acc[tile(0)] = mfma_16x16x32<BF>(ax[0], bv[FULL], acc[tile(0)]);
     }

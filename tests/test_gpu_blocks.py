@@ -511,3 +511,43 @@ def test_row_layers(fx, case, dtype):
     for ref in (net.tensors[-1], outs[2]):
         assert float((outs[0] - ref).norm() / ref.norm()) <= 1.5 * unit
         assert float((outs[0] - ref).abs().max()) <= 4 * unit * float(ref.abs().max())
+
+
+class Positive:
+    """A generator whose normal numbers are all positive."""
+
+    def __init__(self, seed):
+        self.rng = np.random.default_rng(seed)
+
+    def standard_normal(self, shape):
+        return np.abs(self.rng.standard_normal(shape))
+
+
+# channels in, rows, columns, stride: 1 - 8 chunks of channels a tap, each size of work item
+INFINITE = ([(8 * c, 8, 16, 1) for c in range(1, 9)] + [(8 * c, 16, 16, 1) for c in range(1, 5)]
+            + [(8 * c, 16, 32, 2) for c in range(1, 5)] + [(8, 32, 32, 2), (16, 32, 32, 2), (48, 8, 8, 1), (16, 16, 8, 1)])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", INFINITE, ids=lambda c: "-".join(map(str, c)))
+def test_row_layers_keep_infinities_to_their_window(fx, case, dtype):
+    """With positive weights an infinite pixel makes what sees it +Inf.  A lane whose weights are the zeros that fill a
+    step up has to multiply zeros, or 0 x Inf is NaN somewhere, and the mean over all pixels shows it."""
+    B, torch = fx
+    c, h, w, stride = case
+    net = Net(fx, dtype, 2, (c, h, w), seed=h * w + c)
+    net.rng = Positive(c)
+    net.conv(0, 32, 3, stride=stride, relu=False)     # (NaN with a sign is 0 behind a ReLU)
+    with_mean(B, net, 10)
+    m, _ = row_model(fx, net)
+    for channel in (0, c - 1):
+        for row, col in ((0, 0), (h // 2, w // 2), (h // 2 + 1, 3), (h - 1, w - 1)):
+            x = net.x.copy()
+            x[0, channel, row, col] = np.inf
+            out, ws = m.alloc(2)
+            m.fupr_forward(B.DeviceTensor.from_nchw(x, net.dt), out, ws)
+            torch.cuda.synchronize()
+            got = np.ascontiguousarray(out.to_nchw())[:, :, 0, 0]
+            assert (got[0] == np.inf).all(), (channel, row, col, got[0])
+            want = net.tensors[-1].numpy()[1, :, 0, 0]
+            assert np.abs(got[1] - want).max() <= 4 * {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] * np.abs(want).max()
