@@ -551,3 +551,43 @@ def test_row_layers_keep_infinities_to_their_window(fx, case, dtype):
             assert (got[0] == np.inf).all(), (channel, row, col, got[0])
             want = net.tensors[-1].numpy()[1, :, 0, 0]
             assert np.abs(got[1] - want).max() <= 4 * {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] * np.abs(want).max()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("relu", [False, True])
+def test_mean_and_the_layer_behind_it_keep_what_is_no_number(fx, relu, dtype):
+    """NaN and infinities come out of the one launch as out of the two.  Behind a ReLU NaN is 0 in either: one takes
+    the larger of two numbers, the other of two 16-bit patterns, and every NaN of the matrix unit has a sign."""
+    B, torch = fx
+    net = Net(fx, dtype, 4, (512, 5, 3), seed=5)
+    net.ops.append(B.OpDesc(B.OP_AVGPOOL, 0, -1, B.conv_shape(1, 1, 1, 1, 1, 0), None, 0, 1, 0, None, -1, 0))
+    net.tensors.append(net.stored(net.tensors[0].mean((2, 3), keepdim=True)))
+    net.conv(1, 130, 1, relu=relu)
+    bias = net.blobs[-1].view(torch.int32)         # (the blob's first floats)
+    bias[5], bias[77] = 0x7fc00000, 0xffc00000 - 2 ** 32
+    m = B.Model(net.dt, net.in_shape, net.ops, net.blobs)
+    assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)
+    m.fuse_blocks(True)
+    x = net.x.copy()
+    x[0, 3, 2, 1] = np.nan
+    x[1, 9, 4, 2] = np.inf
+    x[2, 4, 0, 0] = x[2, 36, 4, 1] = np.inf        # channels of two steps, so of two waves
+    xd = B.DeviceTensor.from_nchw(x, net.dt)
+    got = []
+    for switch in (None, 0):
+        B.fupr_tuning_set("mean_fc", switch)
+        try:
+            assert (m.launch_stats(4, m.num_launches_at(4) - 1)["kernel"] == "mean_fc") == (switch is None)
+            out, ws = m.alloc(4)
+            m.fupr_forward(xd, out, ws)
+            torch.cuda.synchronize()
+        finally:
+            B.fupr_tuning_set("mean_fc", None)
+        got.append(np.ascontiguousarray(out.to_nchw())[:, :, 0, 0])
+    one, two = got
+    assert np.isnan(two[:, 6]).any() != relu and np.isnan(two[3, 5]) != relu and np.isinf(two[1]).any()
+    assert np.array_equal(np.isnan(one), np.isnan(two))
+    assert np.array_equal(np.isinf(one), np.isinf(two)) and np.array_equal(one[np.isinf(one)], two[np.isinf(two)])
+    unit = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    fine = np.delete(np.arange(130), (5, 77))
+    assert np.abs(one[3] - two[3])[fine].max() <= 4 * unit * np.abs(two[3, fine]).max()
