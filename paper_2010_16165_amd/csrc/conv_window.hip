@@ -49,7 +49,6 @@
 #include <cstdio>
 #include <cstring>
 #include <iterator>
-#include <type_traits>
 
 #include "conv16.h"
 #include "device_utils.h"
@@ -138,13 +137,44 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
   return r;
 }
 
-// A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
-// wave; G: steps whose pixels are read from LDS together.  IX: every filter adds into its listed
-// channel of y (p.keep); without it p.keep is not read.
 // Tiles so small that the wave which finishes one hands its own sum over as well: what it adds up is then read in
 // a row without a choice, 60 instructions for eight waves in place of 200 (1200 clocks of a launch of 10 000).
 constexpr bool all_partial_sums(int tiles) { return tiles <= 4; }
 
+// Adds the partial sums of WK = 2, 4, 8 (or 16) waves up, in their order, for TILES tiles that follow each other; up to
+// eight waves' are asked for before the first is added.  Every read stands here once and the numbers are told apart by what is
+// left out: with a variant for each, the last read of all three became one instruction, and structurizecfg (AMD clang 22.0.0git,
+// roc-7.2.0) left its address undefined where WK is 2 (right before that pass, poison behind it).
+template <int TILES>
+__device__ __forceinline__ void add_up(const f32x4* src, int next, int WK, f32x4* sums) {
+  f32x4 u[8][TILES];
+  auto ask = [&](int from, int to) {
+#pragma unroll
+    for (int k = from; k < to; ++k)
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) u[k][t] = src[k * next + t * 64];
+  };
+  auto add = [&](int from, int to) {
+#pragma unroll
+    for (int k = from; k < to; ++k)
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) sums[t] += u[k][t];
+  };
+  ask(0, 2);
+  if (WK > 2) ask(2, 4);
+  if (WK > 4) ask(4, 8);
+  add(0, 2);
+  if (WK > 2) add(2, 4);
+  if (WK > 4) add(4, 8);
+#pragma unroll 1
+  for (int k = 8; k < WK; ++k)
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) sums[t] += src[k * next + t * 64];
+}
+
+// A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
+// wave; G: steps whose pixels are read from LDS together.  IX: every filter adds into its listed
+// channel of y (p.keep); without it p.keep is not read.
 template <int EL, int MODE, int MT, int NT, int D, int G, bool IX>
 __device__ __forceinline__ void window_tile(const int which) {
   const WindowParams p = load_arguments<WindowParams>(which);
@@ -569,22 +599,7 @@ __device__ __forceinline__ void window_tile(const int which) {
           if (p.WK > 1) {
             v = f32x4{0.f, 0.f, 0.f, 0.f};
             if constexpr (kAll) {
-              const f32x4* src = part + (wf * TT + mt * NT + u) * 64 + lane;
-              const int next = p.WF * TT * 64;
-              auto add_up = [&](auto waves_along) {
-                constexpr int W = waves_along.value;
-                f32x4 q[W];
-#pragma unroll
-                for (int k = 0; k < W; ++k) q[k] = src[k * next];
-#pragma unroll
-                for (int k = 0; k < W; ++k) v += q[k];
-                asm volatile("; %0 partial sums" ::"n"(W));
-              };
-              if (p.WK == 8) add_up(std::integral_constant<int, 8>{});
-              else if (p.WK == 4) add_up(std::integral_constant<int, 4>{});
-              else if (p.WK == 2) add_up(std::integral_constant<int, 2>{});
-              else
-                for (int k = 0; k < p.WK; ++k) v += src[k * next];
+              add_up<1>(part + (wf * TT + mt * NT + u) * 64 + lane, p.WF * TT * 64, p.WK, &v);
             } else
             for (int k = 0; k < p.WK; ++k) {
               const int from = ((k - wk) & (p.WK - 1)) - 1;
@@ -610,33 +625,12 @@ __device__ __forceinline__ void window_tile(const int which) {
           const f32x4 own0 = *s0, own1 = *s1;
           *s0 = *s1 = f32x4{0.f, 0.f, 0.f, 0.f};
           if constexpr (kAll) {
-            // all of them are there, this wave's own too, and are asked for at once
+            f32x4 sums[2] = {*s0, *s1};
             const f32x4* src = part + (wf * TT + mt * NT + t) * 64 + lane;
-            const int next = p.WF * TT * 64;
-            auto add_up = [&](auto waves_along) {
-              constexpr int W = waves_along.value;
-              f32x4 u[W][2];
-#pragma unroll
-              for (int k = 0; k < W; ++k) {
-                u[k][0] = src[k * next];
-                if (pair) u[k][1] = src[k * next + 64];
-              }
-#pragma unroll
-              for (int k = 0; k < W; ++k) {
-                *s0 += u[k][0];
-                if (pair) *s1 += u[k][1];
-              }
-              // (the compiler joins the last reads of the three sums, and loses the address of one)
-              asm volatile("; %0 partial sums" ::"n"(W));
-            };
-            if (p.WK == 8) add_up(std::integral_constant<int, 8>{});
-            else if (p.WK == 4) add_up(std::integral_constant<int, 4>{});
-            else if (p.WK == 2) add_up(std::integral_constant<int, 2>{});
-            else
-              for (int k = 0; k < p.WK; ++k) {
-                *s0 += src[k * next];
-                if (pair) *s1 += src[k * next + 64];
-              }
+            if (pair) add_up<2>(src, p.WF * TT * 64, p.WK, sums);
+            else add_up<1>(src, p.WF * TT * 64, p.WK, sums);
+            *s0 = sums[0];
+            *s1 = sums[1];
             return;
           }
           for (int k = 0; k < p.WK; ++k) {

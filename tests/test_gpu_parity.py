@@ -350,6 +350,23 @@ def test_every_window_tile_forced(fx, tile, waves):
     assert ran >= 5 if (wk - 1) * wf * mt * nt <= 160 else ran == 0
 
 
+@pytest.mark.parametrize("waves", ["1x16", "2x8", "8x2"])
+@pytest.mark.parametrize("tile", range(4), ids=WINDOW_TILES[:4])
+def test_window_tiles_of_sixteen_waves(fx, tile, waves):
+    """The small tiles, whose partial sums are asked for eight waves at a time."""
+    B, network, torch = fx
+    B.fupr_tuning_set("window_tile", f"{tile}x{waves}")
+    try:
+        for case in FORCED_WINDOW[:2] + FORCED_WINDOW[4:5]:
+            for dtype in ("bf16", "f16", "f32"):
+                name = kernel_of(B, dtype, case)
+                if dtype != "f32":
+                    assert name.endswith("_w" + WINDOW_TILES[tile]), name
+                conv_site(fx, case, dtype)
+    finally:
+        B.fupr_tuning_set("window_tile", None)
+
+
 # Padding beyond half a window (some of it beyond the window, or beyond its shorter side only), on
 # images narrower and wider than a tile, and the largest padding that the kernel above still takes.
 PADDING_CASES = [
