@@ -174,10 +174,15 @@ __device__ __forceinline__ void add_up(const f32x4* src, int next, int WK, f32x4
 
 // A wave's tile is MT x NT tiles of 16 pixels x 16 filters.  D: steps of weights in flight per
 // wave; G: steps whose pixels are read from LDS together.  IX: every filter adds into its listed
-// channel of y (p.keep); without it p.keep is not read.
+// channel of y (p.keep); without it p.keep is not read.  `given`: the kernel's arguments, of several in a row the one
+// numbered `which`.
 template <int EL, int MODE, int MT, int NT, int D, int G, bool IX>
-__device__ __forceinline__ void window_tile(const int which) {
-  const WindowParams p = load_arguments<WindowParams>(which);
+__device__ __forceinline__ void window_tile(const WindowParams& given, const int which) {
+  // Short launches load them all at once.  Longer ones leave it to the compiler, behind one look at every line: 3 x 3 with a
+  // shortcut, 77 -> 102 channels at 57 x 38 x 6 6.60 -> 6.54 us, 86 -> 46 at 30 x 50 x 8 2.7 % less; networks are equal.
+  constexpr bool kShort = MT <= 2;
+  if constexpr (!kShort) touch_arguments<sizeof(WindowParams)>();
+  const WindowParams p = kShort ? load_arguments<WindowParams>(which) : given;
   constexpr bool F32 = EL == FUPR_F32, BF = EL == FUPR_BF16;
   constexpr uint32_t ES = F32 ? 4 : 2;       // bytes per element
   extern __shared__ uint4 lds4[];
@@ -419,7 +424,11 @@ __device__ __forceinline__ void window_tile(const int which) {
     for (int mt = 0; mt < MT; ++mt) acc[mt][t] = b4;
   }
 
+  // (twice: the loads to LDS have landed, and the compiler knows that the weights have, or it waits for them anew in every
+  // step of the first round: 3 x 3, 77 -> 102 channels at 57 x 38 x 6 6.71 -> 6.67 us, ResNet-18 of 11 images, half
+  // pruned, 148.6 -> 148.1)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70);
   __syncthreads();
 
   uint32_t origin[MT], origin2[MT], inside[MT];
@@ -683,12 +692,14 @@ __device__ __forceinline__ void window_tile(const int which) {
 }
 
 template <int EL, int MODE, int MT, int NT, int D, int G, int THREADS, int MINWAVES, bool IX>
-__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams) {
-  window_tile<EL, MODE, MT, NT, D, G, IX>(0);
+__global__ __launch_bounds__(THREADS, MINWAVES) void conv_window_kernel(const WindowParams p) {
+  window_tile<EL, MODE, MT, NT, D, G, IX>(p, 0);
 }
 
-// D: steps of weights in flight; G: steps per group of pixel reads; vgprs: registers of the 16-bit
-// window form, as the estimate below was fitted with (one-tap forms take up to 18 more, fp32 up to 15).
+// D: steps of weights in flight; G: steps per group of pixel reads; vgprs: registers as the estimate below was fitted
+// with.  (They were those of the 16-bit window form; 16 x 48, 32 x 16 and 32 x 32, which hold the shortcut while they multiply, take 4
+// - 8 more now, one-tap forms up to 18, fp32 up to 18.  With each form's own registers, in steps of 8, 6 % of plans are others
+// and no network or operator of 46 is faster or slower by more than its runs differ.)
 struct WindowTile {
   int MT, NT, D, G, threads, min_waves, vgprs;
   const char *three, *one_tap, *other, *single;
@@ -820,10 +831,10 @@ struct TwoWindowParams {
 };
 
 template <int EL, int WINDOW, int TAP>
-__global__ __launch_bounds__(kTiles[WINDOW].threads, kTiles[WINDOW].min_waves) void conv_window_two_kernel(const TwoWindowParams) {
+__global__ __launch_bounds__(kTiles[WINDOW].threads, kTiles[WINDOW].min_waves) void conv_window_two_kernel(const TwoWindowParams two) {
   constexpr WindowTile A = kTiles[WINDOW], B = kTiles[TAP];
-  if (blockIdx.y == 0) window_tile<EL, kWindow, A.MT, A.NT, A.D, A.G, false>(0);
-  else window_tile<EL, kOneTap, B.MT, B.NT, B.D, B.G, false>(1);
+  if (blockIdx.y == 0) window_tile<EL, kWindow, A.MT, A.NT, A.D, A.G, false>(two.p[0], 0);
+  else window_tile<EL, kOneTap, B.MT, B.NT, B.D, B.G, false>(two.p[1], 1);
 }
 // The tiles that it is compiled for, of the window and of the 1 x 1 convolution.
 constexpr int kTwoWindow[] = {0, 2, 4, 6, 7, 10}, kTwoTap[] = {0, 2, 6};
