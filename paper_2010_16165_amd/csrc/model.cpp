@@ -52,11 +52,11 @@ struct fupr_model {
   std::vector<size_t> buffer_elems;       // per image, per workspace buffer
   std::vector<char> pair_planned;         // per operator: the workspace lets it run together with the next one
   bool blocks = false;                    // fupr_model_fuse_blocks
-  // Blocks as one launch at a batch size: the same workspace buffers, tensors placed in them so that
+  // The launches of a batch size, and blocks as one launch: the same workspace buffers, tensors placed in them so that
   // what a block reads outlives the block.  Made at the first pass of that many images and kept.
   struct Placement {
     std::vector<Launch> launches;
-    std::vector<int> buffer;              // per tensor, as TensorInfo::buffer; -3: not needed
+    std::vector<int> buffer;              // per tensor, as TensorInfo::buffer; -3: not needed; empty: the model's own
     // per number of images of a sub-batch (up to two for each of at most four splits): the block's plan
     // per operator that starts one
     mutable std::map<int, std::shared_ptr<const std::vector<int>>> parts;
@@ -1138,7 +1138,7 @@ void find_blocks(fupr_model* m) {
 
 // Places the tensors anew in the buffers that the workspace has, for a batch of N images whose wanted
 // blocks run as one launch each; blocks for which there is no room do not.  Empty if there is no block.
-std::shared_ptr<const fupr_model::Placement> place_blocks(const fupr_model* m, int N) {
+std::shared_ptr<fupr_model::Placement> place_blocks(const fupr_model* m, int N) {
   const int n = (int)m->ops.size();
   auto out = std::make_shared<fupr_model::Placement>();
   std::vector<char> chosen(n, 0);          // operators of the block that starts there
@@ -1240,44 +1240,11 @@ std::vector<Launch> launches_of(const fupr_model* m) {
   return tuning_any() ? list_launches(m, m->schedule) : m->launches[m->schedule];
 }
 
-// The placement of a batch of N images, null if none of its blocks runs as one launch.
-std::shared_ptr<const fupr_model::Placement> blocks_on(const fupr_model* m, int N) {
-  if (!m->blocks || m->schedule != FUPR_SCHEDULE_AUTO) return nullptr;
-  std::shared_ptr<const fupr_model::Placement> p;
-  if (tuning_any()) {
-    p = place_blocks(m, N);              // (switches decide it as well)
-  } else {
-    fupr_model* const keeper = const_cast<fupr_model*>(m);
-    std::lock_guard<std::mutex> lock(keeper->placed_mutex);
-    const auto known = m->placed.find(N);
-    if (known != m->placed.end()) {
-      p = known->second;
-    } else {
-      const WithoutTuning no_switches;   // (one that another thread sets meanwhile has no place in what is kept)
-      p = place_blocks(m, N);
-      if (m->placed.size() >= 256) keeper->placed.clear();
-      keeper->placed.emplace(N, p);
-    }
-  }
-  return p->buffer.empty() ? nullptr : p;
-}
-
-// The launches of a batch and the placement that they need, null for the model's own.  Looked up once
-// for a pass: a launch is right only with the tensors where its list has them, and switches may change
-// between two looks.
-struct Scheduled {
-  std::vector<Launch> launches;
-  std::shared_ptr<const fupr_model::Placement> placed;
-};
-
 // Of a pair of 1 x 1 convolutions whose tensors are small, two launches that fill the GPU are faster than
 // one that walks it (nine images of 193 x 193, 49 x 49 pixels, 47 -> 256 -> 111 channels: 18 us in one,
 // 12 in two; a launch more costs 1.7).
-Scheduled scheduled_at(const fupr_model* m, int N) {
-  Scheduled out;
-  out.placed = blocks_on(m, N);
-  std::vector<Launch>& v = out.launches;
-  v = out.placed ? out.placed->launches : launches_of(m);
+void adapt_pairs(const fupr_model* m, int N, std::vector<Launch>* list) {
+  std::vector<Launch>& v = *list;
   for (size_t i = 0; i < v.size(); ++i) {
     const Launch l = v[i];
     if (l.count != 2 || l.block || m->ops[l.first + 1].kind != FUPR_OP_CONV) continue;
@@ -1309,6 +1276,49 @@ Scheduled scheduled_at(const fupr_model* m, int N) {
     v[i] = Launch{v[i].first, 2, kBeside};
     v.erase(v.begin() + i + 1);
   }
+}
+
+// What a batch of N images runs, with blocks as one launch; the placement's buffers are empty if there is none of these.
+std::shared_ptr<const fupr_model::Placement> plan_batch(const fupr_model* m, int N) {
+  auto p = place_blocks(m, N);
+  if (p->buffer.empty()) p->launches = launches_of(m);
+  adapt_pairs(m, N, &p->launches);
+  return p;
+}
+
+// The same, kept by the model where no switch decides it too (2 us of host time for ResNet-18 otherwise, on every
+// pass); null without fupr_model_fuse_blocks.
+std::shared_ptr<const fupr_model::Placement> blocks_on(const fupr_model* m, int N) {
+  if (!m->blocks || m->schedule != FUPR_SCHEDULE_AUTO) return nullptr;
+  if (tuning_any()) return plan_batch(m, N);
+  fupr_model* const keeper = const_cast<fupr_model*>(m);
+  std::lock_guard<std::mutex> lock(keeper->placed_mutex);
+  const auto known = m->placed.find(N);
+  if (known != m->placed.end()) return known->second;
+  const WithoutTuning no_switches;   // (one that another thread sets meanwhile has no place in what is kept)
+  const auto p = plan_batch(m, N);
+  if (m->placed.size() >= 256) keeper->placed.clear();
+  keeper->placed.emplace(N, p);
+  return p;
+}
+
+// The launches of a batch and the placement that they need, null for the model's own.  Looked up once
+// for a pass: a launch is right only with the tensors where its list has them, and switches may change
+// between two looks.
+struct Scheduled {
+  std::vector<Launch> launches;
+  std::shared_ptr<const fupr_model::Placement> placed;
+};
+
+Scheduled scheduled_at(const fupr_model* m, int N) {
+  Scheduled out;
+  if (const auto kept = blocks_on(m, N)) {
+    out.launches = kept->launches;
+    if (!kept->buffer.empty()) out.placed = kept;
+    return out;
+  }
+  out.launches = launches_of(m);
+  adapt_pairs(m, N, &out.launches);
   return out;
 }
 

@@ -800,6 +800,32 @@ def test_blocks_only_where_networks_gain_from_them():
     assert not deep
 
 
+@pytest.mark.parametrize("config", [2, 3, 4])
+def test_kept_launch_list_is_the_one_made_anew(config):
+    """The list of a batch, pairs of operators in one launch among it, is kept from the first look on; with a switch set
+    that decides nothing here it is made anew, and one that splits the pairs is neither kept nor overlooked."""
+    model, _ = synth.make_config(config)
+    m, _ = build_host_model(network.optimise(model), 1 << 20)
+    m.fuse_blocks(True)
+    look = lambda n: [(s["first_op"], s["n_ops"], s["kernel"]) for s in
+                      (m.launch_stats(n, i) for i in range(m.num_launches_at(n)))]
+    batches = (1, 2, 9, 12, 20, 64, 200)
+    kept = [look(n) for n in batches]
+    pairs = {"conv_w+conv1x1p_w", "mean_fc"}
+    if config == 2:
+        assert {k for l in kept for _, _, k in l} >= pairs
+    try:
+        B.fupr_tuning_set("res_item", "1/1/1:1x1")
+        assert [look(n) for n in batches] == kept
+        for switch in ("conv_two", "mean_fc"):
+            B.fupr_tuning_set(switch, 0)
+        assert not pairs & {k for n in batches for _, _, k in look(n)}
+    finally:
+        for switch in ("res_item", "conv_two", "mean_fc"):
+            B.fupr_tuning_set(switch, None)
+    assert [look(n) for n in batches] == kept
+
+
 def launch_list(m, batch):
     return [(s["first_op"], s["n_ops"], s["kernel"]) for s in (m.launch_stats(batch, i) for i in range(m.num_launches))]
 
