@@ -624,6 +624,8 @@ void fupr_graph_destroy(fupr_graph* g);
  *   pair_filters = 16..128                        most filters of the second convolution of a pair of
  *                                                 1 x 1 convolutions in one launch
  *   conv_two = 0                                  two convolutions of one tensor as two launches
+ *   two_tap = <index>                             force the tile of the 1 x 1 convolution among two in one launch
+ *                                                 (an index of window_tile; two launches where it is not built)
  *   mean_fc = 0                                   a global mean and the layer behind it as two launches
  *   bottleneck_fuse, basic_fuse = 0               blocks of fupr_model_fuse_blocks as several launches
  *   bottleneck_tile = <index>                     force a tile of the kernel that runs bottleneck blocks

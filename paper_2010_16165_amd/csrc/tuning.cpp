@@ -32,6 +32,7 @@ Switch g_switches[] = {
     {"window_tile", false, {0}},     // <index>x<waves on filters>x<waves on the reduction>
     {"conv_window", false, {0}},     // 0: layers skip the kernel with weights straight into registers
     {"conv_two", false, {0}},        // 0: two convolutions of one tensor are two launches
+    {"two_tap", false, {0}},         // index of the 1 x 1 convolution's tile in such a launch
     {"mean_fc", false, {0}},         // 0: a global mean and the layer behind it are two launches
     {"conv_patch", false, {0}},      // 0: 3 x 3 layers skip the patch kernel
     {"conv1x1_stream", false, {0}},  // 0: 1 x 1 layers skip the streaming kernel

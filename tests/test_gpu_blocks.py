@@ -389,17 +389,22 @@ BESIDE = [(1, 14, 14, 64, 90, 128), (2, 15, 9, 45, 20, 33), (3, 7, 7, 136, 200, 
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("tap", [None, 0, 2, "window first"])
 @pytest.mark.parametrize("tile", ["", "0x2x2", "2x1x4", "4x2x4", "6x4x1", "7x2x2", "10x4x1", "0x1x8"])
 @pytest.mark.parametrize("case", BESIDE, ids=lambda c: "-".join(map(str, c)))
-def test_projection_beside_the_first_convolution(fx, case, tile, dtype):
-    """A block's stride-2 convolution and its projection in one launch: against both references, and
-    the bits of the two launches."""
+def test_projection_beside_the_first_convolution(fx, case, tile, tap, dtype):
+    """A block's stride-2 convolution and its projection in one launch, in either order and with each tile of the
+    1 x 1 convolution: against both references, and the bits of the two launches."""
     B, torch = fx
     n, h, w, c, k1, k2 = case
     net = Net(fx, dtype, n, (16, h, w), seed=sum(case))
     t_x = net.conv(net.conv(0, 24, 1), c, 1)
-    t_p = net.conv(t_x, k2, 1, stride=2, relu=False)
-    t_1 = net.conv(t_x, k1, 3, stride=2)
+    if tap == "window first":
+        t_1 = net.conv(t_x, k1, 3, stride=2)
+        t_p = net.conv(t_x, k2, 1, stride=2, relu=False)
+    else:
+        t_p = net.conv(t_x, k2, 1, stride=2, relu=False)
+        t_1 = net.conv(t_x, k1, 3, stride=2)
     net.conv(net.conv(t_1, k2, 3, add=t_p), 24, 1)
     B.fupr_tuning_set("basic_fuse", 0)
     try:
@@ -407,12 +412,13 @@ def test_projection_beside_the_first_convolution(fx, case, tile, dtype):
         assert B._lib.fupr_model_set_table(m._h, None) in (B.FUPR_OK, B.ERR_ARG)
         m.fuse_blocks(True)
         B.fupr_tuning_set("window_tile", tile or None)
+        B.fupr_tuning_set("two_tap", tap if tap != "window first" else None)
         x = B.DeviceTensor.from_nchw(net.x, net.dt)
         outs = []
         for two in (None, 0):
             B.fupr_tuning_set("conv_two", two)
             kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
-            assert ("conv_w+conv1x1p_w" in kernels) == (two is None) or tile == "7x2x2", kernels
+            assert ("conv_w+conv1x1p_w" in kernels) == (two is None and tile != "10x4x1"), kernels
             out, ws = m.alloc(n)
             ws.fill_(255)
             m.fupr_forward(x, out, ws)
@@ -423,7 +429,36 @@ def test_projection_beside_the_first_convolution(fx, case, tile, dtype):
         net.check("window_tile", tile or None, "conv_w+conv1x1p_w", takes="conv_w+conv1x1p_w" in [
             m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))])
     finally:
-        for switch in ("basic_fuse", "window_tile", "conv_two"):
+        for switch in ("basic_fuse", "window_tile", "conv_two", "two_tap"):
+            B.fupr_tuning_set(switch, None)
+
+
+def test_sub_batches_of_launches_of_two_operators(fx):
+    """Parts of a batch run a projection beside its block's first convolution, and the mean with the layer behind it,
+    with the bits of the whole."""
+    import synth
+    from paper_2010_16165_amd import network
+    B, torch = fx
+    model = synth.make_imagenet_basic_resnet(17, "bf16", (1, 1, 1, 1), 300, widths=(16, 24, 40, 64), size=64, classes=9)
+    n = 27
+    m, _ = network.build(network.optimise(model))
+    x = B.DeviceTensor.from_nchw(synth.make_input(17, n, model["in_shape"]), B.BF16)
+    whole = None
+    try:
+        B.fupr_tuning_set("basic_fuse", 0)
+        kernels = [m.launch_stats(n, i)["kernel"] for i in range(m.num_launches_at(n))]
+        assert kernels.count("conv_w+conv1x1p_w") >= 2 and "mean_fc" in kernels, kernels
+        for parts in (1, 2, 3):
+            print("sub-batches:", parts, flush=True)
+            B.fupr_tuning_set("split", parts)
+            out, ws = m.alloc(n)
+            ws.fill_(255)
+            m.fupr_forward(x, out, ws)
+            torch.cuda.synchronize()
+            whole = out.data.clone() if whole is None else whole
+            assert torch.equal(whole, out.data)
+    finally:
+        for switch in ("basic_fuse", "split"):
             B.fupr_tuning_set(switch, None)
 
 
