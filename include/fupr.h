@@ -434,10 +434,9 @@ void fupr_model_destroy(fupr_model* m);
  * agree within the rounding of the storage type, not bit for bit.  The
  * one-kernel schedule also assumes FINITE activations: a shortcut value of
  * +-Inf turns all 16 filters of its tile at that pixel into NaN (0 x Inf), where
- * the per-operator kernels keep the other filters finite.  Networks that it runs tap
- * by tap (launch_stats: resident_network_taps) read a window's first 8 channels again
- * where they fill up a step with zero weights, so +-Inf among those is NaN, not +-Inf,
- * in the outputs of that window.
+ * the per-operator kernels keep the other filters finite.  Where channels do not fill
+ * a step up, some of a window's values are multiplied by zero weights as well, so
+ * +-Inf can be NaN, not +-Inf, in outputs whose window holds it (in no others).
  * The one-kernel schedule is taken only when input->c_stride is the minimal one
  * (C rounded up to 8) and output->c_stride is at most the last operator's padded
  * width; other strides run one kernel per operator.

@@ -367,9 +367,10 @@ __device__ __forceinline__ RowWork load_work(ConstWords entry, int wave) {
 // multiplied for all tiles that have a tap there, and at stride 1 an item reads M + 2 rows where tile by tile it
 // would read 3 M.  The 3 * CPT chunks of a row of taps are FULL steps of four chunks and REM chunks over;
 // those of two or three rows of taps share a step where they fit one (REM 2 and 1).  Lanes with nothing left
-// multiply zeros with the zero chunks that pad the weights (there is one: 9 * CPT is no multiple of 4 then): the left
-// halo, or where the lane's pixels are another tile's (REM 2) zeros in their place.  (Any pixel would do but for
-// an infinite one, 0 x Inf; ResNet-56, 128 images, 81.3 us with pixels of the window or the row below it, 81.5 so.)
+// multiply the zero chunks that pad the weights (there is one: 9 * CPT is no multiple of 4 then) with zeros, or with a
+// pixel of the same window, so that an infinite pixel stays in the windows that see it: the left halo where REM is 1 or 3; where
+// it is 2, the second row of taps, read with the third one (stride 1), or zeros in the place of the row below (stride 2).
+// (Zeros everywhere: ResNet-56, 128 images 81.2 -> 81.6 us.)
 // The filters of an item stay in registers.
 //
 // A layer is some 50 MFMAs per wave, so instructions in front of them count: what depends on the wave comes
@@ -424,7 +425,7 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
     if constexpr (REM == 1) {
       if (i % S == 0 && i < S * M) bv[FULL] = *reinterpret_cast<const uint4*>(act + at[FULL] + i * row);
     } else if constexpr (REM == 2) {
-      if (i % S == 0) bv[FULL] = *reinterpret_cast<const uint4*>(act + (i == ROWS - 1 ? last_at : at[FULL]) + i * row);
+      if (S == 1 ? i < ROWS - 1 : i % S == 0) bv[FULL] = *reinterpret_cast<const uint4*>(act + (i == ROWS - 1 ? last_at : at[FULL]) + i * row);
     } else if constexpr (REM == 3) {
       bv[FULL] = *reinterpret_cast<const uint4*>(act + at[FULL] + i * row);
     }
@@ -446,7 +447,8 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
       ax[r] = chunk(g < 3 ? r * T + C0 + g : 9 * CPT);
     } else if constexpr (REM == 2) {
       if (r == 0) ax[0] = chunk(g < 2 ? C0 + g : T + C0 + g - 2);
-      if (r == 2) ax[1] = chunk(g < 2 ? 2 * T + C0 + g : 9 * CPT + g - 2);
+      if (r == 2 && S == 1) ax[1] = chunk(g < 2 ? 9 * CPT + g : 2 * T + C0 + g - 2);
+      if (r == 2 && S == 2) ax[1] = chunk(g < 2 ? 2 * T + C0 + g : 9 * CPT + g - 2);
     } else if constexpr (REM == 1) {
       if (r == 0) ax[0] = chunk(g < 3 ? g * T + C0 : 9 * CPT);
     }
@@ -483,6 +485,7 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
     else acc[t] = bias;
   }
 
+  uint4 above = {};   // REM 2 at stride 1: what the row before read of the chunks over
   const uint32_t floor2 = (L.kind & kResRowRelu) ? 0u : 0x80008000u;
   const int out = __mul24(col, L.out_col) + (second ? L.half_out : 0) + ((g & 1) ? L.out_row : 0) +
                   ((ft * 32 + (g >> 1) * 16) ^ (FLIP ? swizzle_of(col + 1, L.swizzle >> 4) : 0)) + (L.out_org + L.out * 16);
@@ -515,7 +518,10 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
         if (tile(r) >= 0) acc[tile(r)] = mfma_16x16x32<BF>(ax[r], bv[FULL], acc[tile(r)]);
     } else if constexpr (REM == 2) {
       if (tile(0) >= 0) acc[tile(0)] = mfma_16x16x32<BF>(ax[0], bv[FULL], acc[tile(0)]);
-      if (tile(2) >= 0) {
+      if constexpr (S == 1) {
+        if (tile(2) >= 0) acc[tile(2)] = mfma_16x16x32<BF>(ax[1], above, acc[tile(2)]);
+        above = bv[FULL];
+      } else if (tile(2) >= 0) {
         const uint4 &v = bv[FULL], own = {g < 2 ? v.x : 0u, g < 2 ? v.y : 0u, g < 2 ? v.z : 0u, g < 2 ? v.w : 0u};
         acc[tile(2)] = mfma_16x16x32<BF>(ax[1], own, acc[tile(2)]);
       }

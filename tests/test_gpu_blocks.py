@@ -566,26 +566,33 @@ INFINITE = ([(8 * c, 8, 16, 1) for c in range(1, 9)] + [(8 * c, 16, 16, 1) for c
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("case", INFINITE, ids=lambda c: "-".join(map(str, c)))
 def test_row_layers_keep_infinities_to_their_window(fx, case, dtype):
-    """With positive weights an infinite pixel makes what sees it +Inf.  A lane whose weights are the zeros that fill a
-    step up has to multiply zeros, or 0 x Inf is NaN somewhere, and the mean over all pixels shows it."""
+    """With positive weights a pixel of -Inf makes -Inf of what sees it, or NaN, both 0 behind the ReLU; all else is as
+    in a float64 evaluation.  One of +Inf makes +Inf; NaN only at stride 1 with 2 or 6 chunks a tap, where zeros that fill
+    a step up meet a pixel of the same window."""
     B, torch = fx
     c, h, w, stride = case
-    net = Net(fx, dtype, 2, (c, h, w), seed=h * w + c)
-    net.rng = Positive(c)
-    net.conv(0, 32, 3, stride=stride, relu=False)     # (NaN with a sign is 0 behind a ReLU)
-    with_mean(B, net, 10)
-    m, _ = row_model(fx, net)
-    for channel in (0, c - 1):
-        for row, col in ((0, 0), (h // 2, w // 2), (h // 2 + 1, 3), (h - 1, w - 1)):
-            x = net.x.copy()
-            x[0, channel, row, col] = np.inf
-            out, ws = m.alloc(2)
-            m.fupr_forward(B.DeviceTensor.from_nchw(x, net.dt), out, ws)
-            torch.cuda.synchronize()
-            got = np.ascontiguousarray(out.to_nchw())[:, :, 0, 0]
-            assert (got[0] == np.inf).all(), (channel, row, col, got[0])
-            want = net.tensors[-1].numpy()[1, :, 0, 0]
-            assert np.abs(got[1] - want).max() <= 4 * {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] * np.abs(want).max()
+    unit = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    for relu in (True, False):
+        for channel in (0, c - 1):
+            for row, col in ((h // 2 + 1, 3), (h - 1, w - 1)):
+                net = Net(fx, dtype, 2, (c, h, w), seed=h * w + c)
+                net.rng = Positive(c)
+                net.x[0, channel, row, col] = -np.inf if relu else np.inf
+                net.tensors[0] = net.stored(torch.from_numpy(net.x).double())
+                net.conv(0, 32, 3, stride=stride, relu=relu)
+                with_mean(B, net, 10)
+                m, _ = row_model(fx, net)
+                out, ws = m.alloc(2)
+                m.fupr_forward(B.DeviceTensor.from_nchw(net.x, net.dt), out, ws)
+                torch.cuda.synchronize()
+                got = np.ascontiguousarray(out.to_nchw())[:, :, 0, 0]
+                want = net.tensors[-1].numpy()[:, :, 0, 0]
+                at = (channel, row, col, got, want)
+                if not relu:
+                    seen = np.isinf(got[0]) | np.isnan(got[0]) if stride == 1 and c // 8 % 4 == 2 else got[0] == np.inf
+                    assert seen.all() and (want[0] == np.inf).all(), at
+                    got, want = got[1:], want[1:]
+                assert np.abs(got - want).max() <= 4 * unit * np.abs(want).max(), at
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
