@@ -533,7 +533,8 @@ __device__ __forceinline__ void rows_item(const RowWork& L, char* act, int lane,
     __builtin_amdgcn_sched_barrier(0);
   }
   store(M - 2);
-  // (or the stores of all sizes end in one common part)
+  // (or the last stores of all sizes become one, with an address for each: more instructions, and the compiler has lost
+  // such an address elsewhere - add_up in conv_window.hip)
   asm volatile("; rows %0 %1 %2 %3" ::"n"(S), "n"(CPT), "n"(M), "n"(RES));
 }
 
@@ -778,7 +779,7 @@ constexpr int kRowWords = sizeof(ResRow) / 4;
 // layer's descriptor from a cold scalar cache, address arithmetic, the parameters' issue by waves that also
 // compute) and, tile by tile, LDS reads that were waited for one at a time.  Here it takes 3400.
 // What bounds it: the chain of a layer on two waves per SIMD - descriptor and addresses 700 clocks, LDS reads and MFMAs
-// 2000 (LDS busy half of the time, the matrix pipe a third), last store, barrier 500.  Without any work in the
+// 2000 (of all clocks LDS is busy in 39 %, the matrix pipe in 32 %), last store, barrier 500.  Without any work in the
 // layers ResNet-56 takes 21 us, with the parameters' staging 41 (an L2 latency per layer, hidden here).  Tried and not
 // kept: filters read row by row in front of their MFMAs instead of at once, the shortcut added last (2 % slower
 // together); the next layer's descriptor asked for ahead of the layer (1 % slower: every LDS wait then waits for it
